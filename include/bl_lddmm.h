@@ -285,8 +285,8 @@ int bl_kernel_timing_enable(bl_ctx* ctx, int32_t on);
 int bl_kernel_timing_read(bl_ctx* ctx, int32_t kclass, int64_t* launches, double* ms);
 
 /*
- * Launch shapes of the transport kernels.  A 3D transport launch runs tiles of 64 x 4 x zv
- * voxels (zv voxels per thread along z, zv in {1, 2, 4, 8}) per kernel class: zv_out[0] forward
+ * Launch shapes of the transport kernels.  A 3D transport launch runs blocks of 256 columns of
+ * zv voxels (zv voxels per thread along z, zv in {1, 2, 4, 8}) per kernel class: zv_out[0] forward
  * state step, [1] incremental state, [2] adjoint steps, [3] body force.  Every shape computes
  * bitwise the same values.  The library times the candidates on the context's own fields at
  * the first velocity set on a grid shape and keeps the fastest per shape for the process; the
@@ -303,8 +303,8 @@ int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);
  * once, then all are timed in turn three times over and each keeps its fastest round; another
  * shape must beat the default by 5%.  BL_TUNE_LOG=1 prints the times and choices to stderr.
  * Choices are kept for the process and appended to a cache file read by later processes:
- * BL_TUNE_CACHE (a path, or "off"), else $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v2.txt or
- * ~/.cache/bl_lddmm/launch_shapes_v2.txt (lines with a value a class does not accept are
+ * BL_TUNE_CACHE (a path, or "off"), else $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v3.txt or
+ * ~/.cache/bl_lddmm/launch_shapes_v3.txt (lines with a value a class does not accept are
  * skipped).  BL_LAUNCH_SHAPES="s0,...,s6" fixes all classes
  * (state, incremental, adjoint, body force, setup, iota z, iota x/y); only through it can the
  * iota x/y stages run as one fused kernel with 32 or 16 rows per block (s6 = 32 or 16; 0 = the

@@ -42,6 +42,11 @@ __device__ __forceinline__ T* batch_ptr(T* p, const Batch& b, int pair) {
   using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
   return p == nullptr ? p : reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + (int64_t)pair * b.stride);
 }
+template <class T>
+__device__ __forceinline__ T* batch_ptr_nn(T* p, const Batch& b, int pair) {
+  using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+  return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + (int64_t)pair * b.stride);
+}
 inline dim3 batch_grid(dim3 d, const Batch& b) {
   d.z *= (unsigned)b.count;
   return d;
@@ -50,6 +55,12 @@ inline dim3 batch_grid(dim3 d, const Batch& b) {
 #define BL_BATCH(bt)                                  \
   const int bpair_ = ::bl::batch_pair(bt);            \
   if (::bl::batch_gated_off(bt, bpair_)) return;
+// the same for launches of one z per problem: no division
+#define BL_BATCH_Z1(bt)               \
+  const int bpair_ = (int)blockIdx.z; \
+  if (::bl::batch_gated_off(bt, bpair_)) return;
+// (a buffer that is never null: no test)
+#define BL_AT_NN(p, bt) p = ::bl::batch_ptr_nn(p, bt, bpair_)
 #define BL_AT(p, bt) p = ::bl::batch_ptr(p, bt, bpair_)
 
 // Sum (MAX: maximum) of one double per thread of a 1D block of 256 threads, in a fixed order:
@@ -94,6 +105,23 @@ LaunchEvents* take_launch_events();
       hipLaunchKernelGGL(KERNEL, GRID, BLOCK, SHMEM, STREAM, __VA_ARGS__);                  \
   } while (0)
 
+// Quotient by a constant d as one high multiply and a shift: n / d = umulhi(n, m) >> s for
+// every n < 2^31 (d = 1: m = s = 0 and the quotient is n * one).  With s = ceil(log2 d) - 1 and m = ceil(2^(32 + s) / d) the
+// excess e = m d - 2^(32 + s) is below d <= 2^(s + 1), so n e < 2^(32 + s) and the floor is exact.
+struct FastDiv {
+  uint32_t m = 0, s = 0, one = 0;
+};
+inline FastDiv make_div(uint32_t d) {
+  FastDiv f;
+  f.one = d < 2 ? 1 : 0;
+  if (d < 2) return f;
+  uint32_t s = 0;
+  while ((uint64_t(2) << s) < d) ++s;
+  f.s = s;
+  f.m = (uint32_t)(((uint64_t(1) << (32 + s)) + d - 1) / d);
+  return f;
+}
+
 // Geometry and weights of one problem, passed by value to every kernel.
 struct Geo {
   int dim;            // 2 or 3
@@ -109,6 +137,8 @@ struct Geo {
   float half_nref;    // nref/2 (central difference scale)
   float lam_scale;    // -2/sigma^2
   float inv_nx, inv_ny, inv_nz;   // 1/n per axis (periodic index wrap)
+  int nqb;            // blocks of kTransportBlock column entries in a plane (transports)
+  FastDiv div_nqb, div_nx;
   int gamma;          // 1: incompressible flow (velocities projected divergence-free)
   int newton;         // 1: full Newton Hessian products (else Gauss-Newton)
   int nodes;          // band velocity fields: 1 (stationary) or nt + 1 (one per time node)
@@ -125,6 +155,8 @@ struct Geo {
   // several problems of this shape in one launch (default: one)
   Batch bat;
 };
+
+constexpr int kTransportBlock = 256;   // threads of a transport block
 
 // kernel classes of the launch shapes (Geo::zv)
 enum { TR_STATE = 0, TR_INC, TR_ADJ, TR_FORCE, TR_SETUP, TR_IOTA_Z, TR_IOTA_XY, TR_CLASSES };

@@ -81,6 +81,9 @@ int validate(const bl_problem* p, bl::Geo* g) {
     g->inv_nx = 1.0f / (float)n[0];
     g->inv_ny = 1.0f / (float)n[1];
     g->inv_nz = 1.0f / (float)n[2];
+    g->nqb = (n[0] * n[1] + bl::kTransportBlock - 1) / bl::kTransportBlock;
+    g->div_nqb = bl::make_div((uint32_t)g->nqb);
+    g->div_nx = bl::make_div((uint32_t)n[0]);
     g->gamma = p->gamma;
     g->newton = (p->flags & BL_NEWTON) ? 1 : 0;
     g->nodes = (p->flags & BL_NONSTATIONARY) ? p->nt + 1 : 1;
@@ -589,7 +592,7 @@ void t_collect(bl_ctx* c) {
 // Every class's candidates compute bitwise the same values -- they only change how work is
 // split over threads and blocks -- so tuning never changes a result:
 //   transports (state, incremental, adjoint, body force) and setup: voxels per thread along z
-//     (tiles of 64 x 4 x zv voxels), 1, 2, 4 or 8;
+//     (blocks of 256 column entries), 1, 2, 4 or 8;
 //   iota z stage (FP32): the z-chunk multiplier of its grid, 1, 2 or 4;
 //   iota x and y stages: two kernels (0) or one fused kernel with 32 or 16 rows per block.
 // Candidates are timed on the context's own fields right after the first setup on a problem
@@ -597,7 +600,7 @@ void t_collect(bl_ctx* c) {
 // (T0, T1, Bf, DV, X, YA with the same values, the transform buffers) are work space that every
 // operation rewrites before use.  Choices are kept per (GPU architecture, grid, band,
 // precision) for the process and in a cache file -- BL_TUNE_CACHE, else
-// $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v2.txt or ~/.cache/bl_lddmm/launch_shapes_v2.txt -- read at
+// $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v3.txt or ~/.cache/bl_lddmm/launch_shapes_v3.txt -- read at
 // the first tuning and appended to after each new choice, so later processes skip the timing.
 // BL_TUNE_CACHE=off disables the file; BL_TRANSPORT_ZV = 1, 2, 4 or 8 fixes the transports'
 // and the setup's voxels per thread and skips the timing, BL_LAUNCH_SHAPES fixes every class.
@@ -609,9 +612,9 @@ std::string tune_cache_path() {
   const char* e = std::getenv("BL_TUNE_CACHE");
   if (e && *e) return std::string(e) == "off" ? std::string() : std::string(e);
   if (const char* x = std::getenv("XDG_CACHE_HOME"))
-    if (*x) return std::string(x) + "/bl_lddmm/launch_shapes_v2.txt";
+    if (*x) return std::string(x) + "/bl_lddmm/launch_shapes_v3.txt";
   if (const char* h = std::getenv("HOME"))
-    if (*h) return std::string(h) + "/.cache/bl_lddmm/launch_shapes_v2.txt";
+    if (*h) return std::string(h) + "/.cache/bl_lddmm/launch_shapes_v3.txt";
   return std::string();
 }
 

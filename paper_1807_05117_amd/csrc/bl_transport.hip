@@ -24,11 +24,128 @@
 namespace bl {
 namespace {
 
-constexpr int BX = 64;
+// ------------------------------------------------------------------ threads and addresses
+// One thread per (x, y) column entry and ZV voxels of it along z.  A block takes kTB
+// consecutive entries of the flattened (y, x) plane, whatever nx is: every wavefront reads and
+// writes 64 consecutive floats of each plane and only a plane's last block has idle lanes
+// (tiles of whole 64-voxel x runs leave a quarter of the lanes idle at nx = 96).
+//
+// While their fields come from the caches these kernels are bound by the issue of vector
+// instructions and by the address path of the gathers, not by bandwidth: a wavefront
+// instruction takes four cycles of its SIMD, 128^3 voxels are 32 wavefront-voxels per SIMD, so
+// every instruction per voxel costs about 53 ns of a launch, and a 32-bit integer multiply
+// four times that.  So
+//   - the place of a voxel within its plane is one 32-bit byte offset per thread, shared by
+//     every field (raw buffer loads: the plane's resource and the z offset are scalars), its
+//     stencil neighbours four more; all divisions are scalar multiplications by host constants;
+//   - an interpolation tap wraps each axis with two unsigned minima and forms its four row
+//     addresses with two 24-bit multiply-adds; offsets of a whole period or more (and
+//     non-finite ones) take a general path that a wavefront enters only if a lane needs it.
+// A tap with its interpolation takes about 55 instructions per voxel; with 64 x 4 tiles, 64-bit
+// addresses and multiplied wraps it took about 190 instruction times.  Per launch, before and
+// after: state step 13.1 -> 12.1 us at 128^3, 8.2 -> 6.4 at 96^3, 26.2 -> 22.3 at 160x192x160,
+// 73 -> 61 at 256^3 (5.5 TB/s); incremental step 15.9 -> 15.4, 9.9 -> 8.3, 32.7 -> 28.8, 136 -> 135.
+constexpr int kTB = kTransportBlock;
 
-// Periodic index without branches (|i| < 2^21, so i is exact in float): the quotient from
-// i * (1/n) may be off by one near multiples of n, which the two selects correct.  No branch
-// keeps the voxels of a thread in one basic block, so their loads can all be in flight.
+// XCD-aware tile order: the hardware deals consecutive workgroups round-robin to the 8
+// XCDs, each with its own L2.  The launch is 1D with a multiple of 8 workgroups and workgroup
+// b works on tile (b % 8) * (nb / 8) + b / 8 of the plane-fastest tile order, so every XCD
+// sweeps one contiguous slab of the volume and the y / z neighbours that gathers and central
+// differences touch are mostly in its own L2.
+constexpr int kXCD = 8;
+
+// quotient by a host constant (FastDiv), exact for n < 2^31
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv& d) {
+  return (__umulhi(n, d.m) + n * d.one) >> d.s;
+}
+
+// the thread's column entry and the byte offsets of its stencil within a plane (periodic)
+struct Col {
+  int x, y;
+  uint32_t q;                 // y nx + x
+  uint32_t c, xm, xp, ym, yp; // byte offsets of the entry and its x and y neighbours
+  int zb;                     // the block's first plane / ZV
+  uint32_t plane4;            // bytes of a plane
+};
+
+__device__ __forceinline__ bool locate(const Geo& g, int zv, Col& t) {
+  const uint32_t nb = gridDim.x;            // multiple of kXCD
+  const uint32_t b = blockIdx.x;
+  const uint32_t tile = (b % kXCD) * (nb / kXCD) + b / kXCD;
+  const uint32_t zb = fast_div(tile, g.div_nqb);
+  const uint32_t q0 = (tile - zb * (uint32_t)g.nqb) * kTB;
+  if ((int)zb * zv >= g.nz) return false;
+  const uint32_t y0 = fast_div(q0, g.div_nx);
+  const uint32_t xx = q0 - y0 * (uint32_t)g.nx + threadIdx.x;
+  const uint32_t dy = fast_div(xx, g.div_nx);
+  t.zb = (int)zb;
+  t.x = (int)(xx - __umul24(dy, (uint32_t)g.nx));
+  t.y = (int)(y0 + dy);
+  t.q = q0 + threadIdx.x;
+  t.c = t.q * 4u;
+  t.plane4 = (uint32_t)g.nx * (uint32_t)g.ny * 4u;
+  const uint32_t row = (uint32_t)g.nx * 4u, wx = row - 4u, wy = ((uint32_t)g.ny - 1u) * row;
+  t.xm = t.x == 0 ? t.c + wx : t.c - 4u;
+  t.xp = t.x + 1 == g.nx ? t.c - wx : t.c + 4u;
+  t.ym = t.y == 0 ? t.c + wy : t.c - row;
+  t.yp = t.y + 1 == g.ny ? t.c - wy : t.c + row;
+  return t.q < (uint32_t)g.nx * (uint32_t)g.ny;
+}
+
+#define COLUMN                         \
+  Col t;                               \
+  if (!locate(g, ZV, t)) return;
+// plane z of the thread's voxel zz, clamped to the grid so that every load stays in bounds and
+// the ZV voxels' loads can be issued together (only the stores are guarded), and the byte
+// offsets of the plane and its periodic z neighbours; all scalar
+#define VOXEL(zz)                                                               \
+  const int zr = t.zb * ZV + (zz);                                              \
+  const int z = zr < g.nz ? zr : g.nz - 1;                                      \
+  const bool live = zr < g.nz;                                                  \
+  const uint32_t zo = (uint32_t)z * t.plane4;                                   \
+  const uint32_t zm = z == 0 ? (uint32_t)(g.nz - 1) * t.plane4 : zo - t.plane4; \
+  const uint32_t zp = z + 1 == g.nz ? 0u : zo + t.plane4;                       \
+  (void)live; (void)zo; (void)zm; (void)zp;
+
+// Fields are read through raw buffer resources: the plane's z offset is a scalar operand of the
+// load, an 8-byte load of two consecutive floats needs only 4-byte alignment, and the hardware
+// range check returns 0 for any dword past the buffer instead of faulting.
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+
+__device__ __forceinline__ Rsrc field_rsrc(const float* f, const Geo& g) {
+  const uint64_t bytes = (uint64_t)g.M * 4u;   // < 2^32: the host limits prod(n) to < 2^30
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(f), (short)0, (int)(uint32_t)bytes,
+                                           0x00020000);
+}
+__device__ __forceinline__ float ld(Rsrc rs, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff, (int)soff, 0));
+}
+__device__ __forceinline__ void st(Rsrc rs, uint32_t voff, uint32_t soff, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, (int)voff, (int)soff, 0);
+}
+// (Y, a) of the thread's voxel: plane z as a scalar base, 16 bytes per column entry (< 2^26)
+__device__ __forceinline__ float4 ld_ya(const Geo& g, const float4* YA, int z, const Col& t) {
+  const char* base = reinterpret_cast<const char*>(YA + (size_t)z * ((size_t)g.nx * g.ny));
+  return *reinterpret_cast<const float4*>(base + (uint32_t)(t.q << 4));
+}
+
+__device__ __forceinline__ void st_ya(const Geo& g, float4* YA, int z, const Col& t, float4 v) {
+  char* base = reinterpret_cast<char*>(YA + (size_t)z * ((size_t)g.nx * g.ny));
+  *reinterpret_cast<float4*>(base + (uint32_t)(t.q << 4)) = v;
+}
+
+// -------------------------------------------------------------------------- interpolation
+// Byte addresses of the four (2D: two) rows' x0 entries, the weights, and whether the x1
+// neighbour wraps to the row's start.
+struct Tap {
+  uint32_t a00, a01, a10, a11;   // (z0,y0) (z0,y1) (z1,y0) (z1,y1)
+  float wx, wy, wz;
+  bool wrapped;
+};
+
+// Periodic index of any |i| < 2^21 (i is exact in float): the quotient from i * (1/n) may be
+// off by one near multiples of n, which the two selects correct.
 __device__ __forceinline__ int wrap(int i, int n, float inv_n) {
   const int q = (int)floorf((float)i * inv_n);
   int r = i - q * n;
@@ -36,141 +153,132 @@ __device__ __forceinline__ int wrap(int i, int n, float inv_n) {
   r -= r >= n ? n : 0;
   return r;
 }
-
-// Split an offset into the lower cell index (periodic) and the fractional weight.  Offsets
-// are clamped to +-2^20 voxels and non-finite offsets are mapped to 0, so every index that
+// Lower cell index (periodic) and fractional weight of an offset.  General form: offsets are
+// clamped to +-2^20 voxels and non-finite offsets are mapped to 0, so every index that
 // reaches memory lies in [0, n).
-__device__ __forceinline__ void split(float o, int base, int n, float inv_n, int& i0, int& i1,
-                                      float& w) {
+__device__ __forceinline__ uint32_t split_any(float o, int base, int n, float inv_n, float& w) {
   if (!(fabsf(o) <= 1048576.0f)) o = 0.0f;
   const float f = floorf(o);
   w = o - f;
-  i0 = wrap(base + (int)f, n, inv_n);
-  i1 = (i0 + 1 == n) ? 0 : i0 + 1;
+  return (uint32_t)wrap(base + (int)f, n, inv_n);
+}
+// The same for |o| < n: base + floor(o) lies in [-n, 2n - 2], which two unsigned minima fold
+// into [0, n) (a negative value is a huge unsigned one, so the first minimum takes i + n, and
+// for i < n the second keeps i).
+__device__ __forceinline__ uint32_t split_near(float o, int base, int n, float& w) {
+  const float f = floorf(o);
+  w = o - f;
+  uint32_t i = (uint32_t)(base + (int)f);
+  i = min(i, i + (uint32_t)n);
+  return min(i, i - (uint32_t)n);
 }
 
-// Interpolation rows are read through a raw buffer resource: an 8-byte load of two
-// consecutive floats needs only 4-byte alignment there (global loads would be split), and the
-// hardware range check returns 0 for any dword past the buffer instead of faulting.
-typedef float f2v __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t field_rsrc(const float* f, const Geo& g) {
-  const uint64_t bytes = (uint64_t)g.M * 4u;   // < 2^32: the host limits prod(n) to < 2^30
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(f), (short)0, (int)(uint32_t)bytes,
-                                           0x00020000);
+__device__ __forceinline__ uint64_t lanes_far(float o, int n) {
+  return __builtin_amdgcn_ballot_w64(!(fabsf(o) < (float)n));   // NaN: far
 }
 
-// f[row + x0] and f[row + x1] where x1 is x0 + 1 or the periodic wrap to 0.  The wrapped
-// value comes from a second load that every lane issues; lanes that do not wrap point it past
-// the end of the buffer, where the range check returns 0 without touching memory.  No branch.
+template <int DIM>
+__device__ __forceinline__ void tap_rows(const Geo& g, uint32_t x0, uint32_t y0, uint32_t z0,
+                                         Tap& t) {
+  // nx ny < 2^23 and every index < 2^11: 24-bit multiplies are exact
+  const uint32_t nx = (uint32_t)g.nx, ny = (uint32_t)g.ny, row = nx * 4u;
+  uint32_t e = __umul24(y0, nx) + x0;
+  if (DIM == 3) e += __umul24(z0, nx * ny);
+  t.a00 = e * 4u;
+  const uint32_t dy = y0 == ny - 1u ? 0u - (ny - 1u) * row : row;
+  t.a01 = t.a00 + dy;
+  if (DIM == 3) {
+    const uint32_t pl = ny * row;
+    const uint32_t dz = z0 == (uint32_t)g.nz - 1u ? 0u - ((uint32_t)g.nz - 1u) * pl : pl;
+    t.a10 = t.a00 + dz;
+    t.a11 = t.a01 + dz;
+  } else {
+    t.a10 = t.a00;
+    t.a11 = t.a01;
+  }
+  t.wrapped = x0 == nx - 1u;
+}
+
+// the taps of a thread's ZV voxels at (x, y, z[zz]) + o[zz]
+template <int DIM, int ZV>
+__device__ __forceinline__ void make_taps(const Geo& g, const Col& t, const float (&ox)[ZV],
+                                          const float (&oy)[ZV], const float (&oz)[ZV],
+                                          Tap (&tp)[ZV]) {
+  uint64_t far = 0;   // lanes with an offset of a period or more, or a non-finite one
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    far |= lanes_far(ox[zz], g.nx) | lanes_far(oy[zz], g.ny);
+    if (DIM == 3) far |= lanes_far(oz[zz], g.nz);
+  }
+  uint32_t x0[ZV], y0[ZV], z0[ZV];
+  if (far == 0) {
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) {
+      VOXEL(zz)
+      x0[zz] = split_near(ox[zz], t.x, g.nx, tp[zz].wx);
+      y0[zz] = split_near(oy[zz], t.y, g.ny, tp[zz].wy);
+      tp[zz].wz = 0.0f;
+      z0[zz] = 0;
+      if (DIM == 3) z0[zz] = split_near(oz[zz], z, g.nz, tp[zz].wz);
+    }
+  } else {
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) {
+      VOXEL(zz)
+      x0[zz] = split_any(ox[zz], t.x, g.nx, g.inv_nx, tp[zz].wx);
+      y0[zz] = split_any(oy[zz], t.y, g.ny, g.inv_ny, tp[zz].wy);
+      tp[zz].wz = 0.0f;
+      z0[zz] = 0;
+      if (DIM == 3) z0[zz] = split_any(oz[zz], z, g.nz, g.inv_nz, tp[zz].wz);
+    }
+  }
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) tap_rows<DIM>(g, x0[zz], y0[zz], z0[zz], tp[zz]);
+}
+
+// Interpolated values of f at the ZV taps of a thread.  f[x0] and f[x0 + 1] of a row come in
+// one 8-byte load: with the addresses of a real gather (runs of consecutive floats broken
+// where the offset crosses a voxel) a wavefront's load occupies its compute unit's address path
+// for about 16 cycles whatever its width, so two 4-byte loads per row cost more (state step
+// 13.4 against 12.1 us, setup 60 against 47 us at 128^3).  Where x1 wraps to the row's start
+// its value comes from a second load, issued only by waves in which some lane wraps (one
+// wave-uniform branch after every row load of the thread is in flight) and, by lanes that do
+// not wrap, past the end of the buffer, where the range check returns 0 without touching memory.
 constexpr uint32_t kPastEnd = 0xFFFFFFFCu;   // >= the byte size of any field (< 2^32)
 
-__device__ __forceinline__ void load_pair(__amdgpu_buffer_rsrc_t rs, uint32_t row, int x0,
-                                          int x1, float& v0, float& v1) {
-  const f2v v = __builtin_bit_cast(
-      f2v, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)((row + (uint32_t)x0) * 4u), 0, 0));
-  const bool wrapped = x1 != x0 + 1;
-  const uint32_t off = wrapped ? (row + (uint32_t)x1) * 4u : kPastEnd;
-  const float w = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
-  v0 = v.x;
-  v1 = wrapped ? w : v.y;
-}
-
-// All in-volume indices are 32-bit (the host guarantees prod(n) <= 2^30).
-template <int DIM>
-struct Tap {
-  uint32_t r00, r01, r10, r11;  // row starts (z0,y0) (z0,y1) (z1,y0) (z1,y1)
-  int x0, x1;
-  float wx, wy, wz;
-};
-
-template <int DIM>
-__device__ __forceinline__ Tap<DIM> make_tap(const Geo& g, int x, int y, int z, float ox,
-                                             float oy, float oz) {
-  Tap<DIM> t;
-  int y0, y1;
-  split(ox, x, g.nx, g.inv_nx, t.x0, t.x1, t.wx);
-  split(oy, y, g.ny, g.inv_ny, y0, y1, t.wy);
-  if (DIM == 3) {
-    int z0, z1;
-    split(oz, z, g.nz, g.inv_nz, z0, z1, t.wz);
-    t.r00 = ((uint32_t)z0 * g.ny + y0) * g.nx;
-    t.r01 = ((uint32_t)z0 * g.ny + y1) * g.nx;
-    t.r10 = ((uint32_t)z1 * g.ny + y0) * g.nx;
-    t.r11 = ((uint32_t)z1 * g.ny + y1) * g.nx;
-  } else {
-    t.wz = 0.0f;
-    t.r00 = (uint32_t)y0 * g.nx;
-    t.r01 = (uint32_t)y1 * g.nx;
-    t.r10 = t.r00;
-    t.r11 = t.r01;
-  }
-  return t;
-}
-
-template <int DIM>
-__device__ __forceinline__ float apply(__amdgpu_buffer_rsrc_t f, const Tap<DIM>& t) {
-  float a0, a1, b0, b1;
-  load_pair(f, t.r00, t.x0, t.x1, a0, a1);
-  load_pair(f, t.r01, t.x0, t.x1, b0, b1);
-  const float ra = fmaf(t.wx, a1 - a0, a0);
-  const float rb = fmaf(t.wx, b1 - b0, b0);
-  const float pa = fmaf(t.wy, rb - ra, ra);
-  if (DIM == 2) return pa;
-  float c0, c1, d0, d1;
-  load_pair(f, t.r10, t.x0, t.x1, c0, c1);
-  load_pair(f, t.r11, t.x0, t.x1, d0, d1);
-  const float rc = fmaf(t.wx, c1 - c0, c0);
-  const float rd = fmaf(t.wx, d1 - d0, d0);
-  const float pb = fmaf(t.wy, rd - rc, rc);
-  return fmaf(t.wz, pb - pa, pa);
-}
-
-// apply() at the ZV taps of a thread, with the same loaded values and arithmetic, but the
-// second loads of wrapped pairs issued only by waves in which some lane wraps (one
-// wave-uniform branch after every 8-byte row load of the thread is in flight): waves away
-// from the x boundary skip them.  The taps are all formed before the call, so no load of the
-// thread waits behind the branch.
 template <int DIM, int ZV>
-__device__ __forceinline__ void gather_zv(__amdgpu_buffer_rsrc_t f, const Tap<DIM> (&t)[ZV],
+__device__ __forceinline__ void gather_zv(const Geo& g, Rsrc f, const Tap (&t)[ZV],
                                           float (&out)[ZV]) {
   constexpr int R = DIM == 3 ? 4 : 2;
   f2v v[ZV][R];
-  float w[ZV][R];
-  bool any = false;
+  uint64_t any = 0;
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    const uint32_t rows[4] = {t[zz].r00, t[zz].r01, t[zz].r10, t[zz].r11};
+    const uint32_t a[4] = {t[zz].a00, t[zz].a01, t[zz].a10, t[zz].a11};
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      v[zz][r] = __builtin_bit_cast(
-          f2v, __builtin_amdgcn_raw_buffer_load_b64(f, (int)((rows[r] + (uint32_t)t[zz].x0) * 4u),
-                                                    0, 0));
-      w[zz][r] = 0.0f;
-    }
-    any |= t[zz].x1 != t[zz].x0 + 1;
+    for (int r = 0; r < R; ++r)
+      v[zz][r] = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(f, (int)a[r], 0, 0));
+    any |= __builtin_amdgcn_ballot_w64(t[zz].wrapped);
   }
-  if (__builtin_amdgcn_ballot_w64(any) != 0) {
+  if (any != 0) {
+    const uint32_t back = ((uint32_t)g.nx - 1u) * 4u;
+    float w[ZV][R];
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
-      const uint32_t rows[4] = {t[zz].r00, t[zz].r01, t[zz].r10, t[zz].r11};
-      const bool wrapped = t[zz].x1 != t[zz].x0 + 1;
+      const uint32_t a[4] = {t[zz].a00, t[zz].a01, t[zz].a10, t[zz].a11};
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const uint32_t off = wrapped ? (rows[r] + (uint32_t)t[zz].x1) * 4u : kPastEnd;
-        w[zz][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(f, (int)off, 0, 0));
-      }
+      for (int r = 0; r < R; ++r) w[zz][r] = ld(f, t[zz].wrapped ? a[r] - back : kPastEnd, 0);
     }
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz)
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[zz][r].y = t[zz].wrapped ? w[zz][r] : v[zz][r].y;
   }
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    const bool wrapped = t[zz].x1 != t[zz].x0 + 1;
     float rr[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float lo = v[zz][r].x, hi = wrapped ? w[zz][r] : v[zz][r].y;
-      rr[r] = fmaf(t[zz].wx, hi - lo, lo);
-    }
+    for (int r = 0; r < R; ++r) rr[r] = fmaf(t[zz].wx, v[zz][r].y - v[zz][r].x, v[zz][r].x);
     const float pa = fmaf(t[zz].wy, rr[1] - rr[0], rr[0]);
     if (DIM == 2) {
       out[zz] = pa;
@@ -181,131 +289,121 @@ __device__ __forceinline__ void gather_zv(__amdgpu_buffer_rsrc_t f, const Tap<DI
   }
 }
 
-// ------------------------------------------------------------------ gather kernels (64 x 4)
-// One thread per ZV voxels along z; z is clamped to the grid so that every load stays in
-// bounds and the ZV voxels' loads can be issued together; only the stores are guarded.
-constexpr int GBY = 4;
-
-// XCD-aware tile order: the hardware deals consecutive workgroups round-robin to the 8
-// XCDs, each with its own L2.  The launch is 1D with a multiple of 8 workgroups and workgroup
-// b works on tile (b % 8) * (nb / 8) + b / 8 of the x-fastest tile order, so every XCD sweeps
-// one contiguous slab of the volume and the y / z neighbours that gathers and central
-// differences touch are mostly in its own L2.
-constexpr int kXCD = 8;
-
-struct TileIdx {
-  int bx, by, bz;
-  bool valid;
-};
-
-__device__ __forceinline__ TileIdx xcd_tile(int gx, int gy, int gz) {
-  const int nb = gridDim.x;                 // multiple of kXCD
-  const int b = blockIdx.x;
-  const int t = (b % kXCD) * (nb / kXCD) + b / kXCD;
-  TileIdx r;
-  r.bx = t % gx;
-  r.by = (t / gx) % gy;
-  r.bz = t / (gx * gy);
-  r.valid = r.bz < gz;
-  return r;
+// X offsets of the thread's voxels (dim planes at X) as taps
+template <int DIM, int ZV>
+__device__ __forceinline__ void taps_x(const Geo& g, const Col& t, const float* X, Tap (&tp)[ZV]) {
+  const size_t M = (size_t)g.M;
+  const Rsrc r0 = field_rsrc(X, g), r1 = field_rsrc(X + M, g);
+  const Rsrc r2 = field_rsrc(DIM == 3 ? X + 2 * M : X, g);
+  float ox[ZV], oy[ZV], oz[ZV];
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    ox[zz] = ld(r0, t.c, zo);
+    oy[zz] = ld(r1, t.c, zo);
+    oz[zz] = DIM == 3 ? ld(r2, t.c, zo) : 0.f;
+  }
+  make_taps<DIM, ZV>(g, t, ox, oy, oz, tp);
 }
 
-#define GATHER_XY                                                                \
-  const TileIdx tile = xcd_tile((g.nx + BX - 1) / BX, (g.ny + GBY - 1) / GBY,    \
-                                (g.nz + ZV - 1) / ZV);                           \
-  if (!tile.valid) return;                                                       \
-  const int x = tile.bx * BX + threadIdx.x;                                      \
-  const int y = tile.by * GBY + threadIdx.y;                                     \
-  if (x >= g.nx || y >= g.ny) return;
-#define GATHER_Z(zz)                                     \
-  const int zr = tile.bz * ZV + (zz);                    \
-  const int z = zr < g.nz ? zr : g.nz - 1;               \
-  const bool live = zr < g.nz;                           \
-  const uint32_t p = ((uint32_t)z * g.ny + y) * g.nx + x;
+// (Y, a) of the thread's voxels as taps and factors
+template <int DIM, int ZV>
+__device__ __forceinline__ void taps_ya(const Geo& g, const Col& t, const float4* YA,
+                                        Tap (&tp)[ZV], float (&aw)[ZV]) {
+  float ox[ZV], oy[ZV], oz[ZV];
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    const float4 o = ld_ya(g, YA, z, t);
+    ox[zz] = o.x;
+    oy[zz] = o.y;
+    oz[zz] = o.z;
+    aw[zz] = o.w;
+  }
+  make_taps<DIM, ZV>(g, t, ox, oy, oz, tp);
+}
+
 // The values of a thread's ZV voxels are computed first and stored afterwards, so no store
 // sits between the voxels' loads.  Large grids store with the streaming hint (Geo::stream_out).
 // Both forms are raw buffer stores that differ in their cache-policy immediate (bit 1: nt), so
 // the compiler cannot merge the two branches into one plain store.
-__device__ __forceinline__ void store_out(const Geo& g, float* out, uint32_t p, float v) {
-  const __amdgpu_buffer_rsrc_t rs = field_rsrc(out, g);
-  if (g.stream_out)
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, (int)(p * 4u), 0, 2);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, (int)(p * 4u), 0, 0);
-}
-#define STORE_ZV(out, val)                                 \
-  _Pragma("unroll") for (int zz = 0; zz < ZV; ++zz) {      \
-    GATHER_Z(zz)                                           \
-    if (live) store_out(g, (out), p, (val)[zz]);           \
+template <int ZV>
+__device__ __forceinline__ void store_zv(const Geo& g, const Col& t, float* out,
+                                         const float (&val)[ZV]) {
+  const Rsrc rs = field_rsrc(out, g);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    if (!live) continue;
+    const uint32_t v = __builtin_bit_cast(uint32_t, val[zz]);
+    if (g.stream_out)
+      __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)t.c, (int)zo, 2);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)t.c, (int)zo, 0);
   }
+}
 
+// ---------------------------------------------------------------------------------- setup
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_setup(Geo g, const float* __restrict__ v,
-                                                   float* __restrict__ X,
-                                                   float4* __restrict__ YA) {
-  BL_BATCH(g.bat)
-  BL_AT(v, g.bat);
-  BL_AT(X, g.bat);
-  BL_AT(YA, g.bat);
-  GATHER_XY
+__global__ __launch_bounds__(kTB) void k_setup(Geo g, const float* __restrict__ v,
+                                               float* __restrict__ X,
+                                               float4* __restrict__ YA) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(v, g.bat);
+  BL_AT_NN(X, g.bat);
+  BL_AT_NN(YA, g.bat);
+  COLUMN
   const size_t M = (size_t)g.M;
   const float s = g.dt * (float)g.nref;
   // the ZV voxels of the thread are computed first and stored afterwards (their gathers can
   // all be in flight)
-  float u[ZV][3];
-  Tap<DIM> tf[ZV], tb[ZV];
+  float u[3][ZV], nu[3][ZV];
 #pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    u[zz][0] = u[zz][1] = u[zz][2] = 0.f;
-    for (int c = 0; c < DIM; ++c) u[zz][c] = s * v[c * M + p];
-    // forward: X = -(u + Interp(u, i - u)) / 2
-    tf[zz] = make_tap<DIM>(g, x, y, z, -u[zz][0], -u[zz][1], -u[zz][2]);
-    // backward: Y = +(u + Interp(u, i + u)) / 2
-    tb[zz] = make_tap<DIM>(g, x, y, z, u[zz][0], u[zz][1], u[zz][2]);
-  }
-  float xo[ZV][3], yo[ZV][3], av[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    xo[zz][0] = xo[zz][1] = xo[zz][2] = 0.f;
-    yo[zz][0] = yo[zz][1] = yo[zz][2] = 0.f;
-  }
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    const __amdgpu_buffer_rsrc_t vc = field_rsrc(v + c * M, g);
-    float gf[ZV], gb[ZV];
-    gather_zv<DIM, ZV>(vc, tf, gf);
-    gather_zv<DIM, ZV>(vc, tb, gb);
+  for (int c = 0; c < 3; ++c) {
+    const Rsrc vc = field_rsrc(v + (c < DIM ? c : 0) * M, g);
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
-      xo[zz][c] = -0.5f * (u[zz][c] + s * gf[zz]);
-      yo[zz][c] = 0.5f * (u[zz][c] + s * gb[zz]);
+      VOXEL(zz)
+      u[c][zz] = c < DIM ? s * ld(vc, t.c, zo) : 0.f;
+      nu[c][zz] = -u[c][zz];
+    }
+  }
+  Tap tf[ZV], tb[ZV];
+  make_taps<DIM, ZV>(g, t, nu[0], nu[1], nu[2], tf);   // X = -(u + Interp(u, i - u)) / 2
+  make_taps<DIM, ZV>(g, t, u[0], u[1], u[2], tb);      // Y = +(u + Interp(u, i + u)) / 2
+  float xo[3][ZV], yo[3][ZV], av[ZV];
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) xo[2][zz] = yo[2][zz] = 0.f;
+#pragma unroll
+  for (int c = 0; c < DIM; ++c) {
+    const Rsrc vc = field_rsrc(v + c * M, g);
+    float gf[ZV], gb[ZV];
+    gather_zv<DIM, ZV>(g, vc, tf, gf);
+    gather_zv<DIM, ZV>(g, vc, tb, gb);
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) {
+      xo[c][zz] = -0.5f * (u[c][zz] + s * gf[zz]);
+      yo[c][zz] = 0.5f * (u[c][zz] + s * gb[zz]);
     }
   }
   // reaction factor of the adjoint along the backward characteristic (Heun)
-  const float* r = v + DIM * M;
-  Tap<DIM> ty[ZV];
-  float ri[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    ty[zz] = make_tap<DIM>(g, x, y, z, yo[zz][0], yo[zz][1], yo[zz][2]);
-    ri[zz] = r[p];
-  }
+  const Rsrc rr = field_rsrc(v + DIM * M, g);
+  Tap ty[ZV];
+  make_taps<DIM, ZV>(g, t, yo[0], yo[1], yo[2], ty);
   float R[ZV];
-  gather_zv<DIM, ZV>(field_rsrc(r, g), ty, R);
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz)
-    av[zz] = 1.0f + 0.5f * g.dt * (R[zz] + (1.0f + g.dt * R[zz]) * ri[zz]);
+  gather_zv<DIM, ZV>(g, rr, ty, R);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    if (live) {
-      for (int c = 0; c < DIM; ++c) X[c * M + p] = xo[zz][c];
-      YA[p] = make_float4(yo[zz][0], yo[zz][1], yo[zz][2], av[zz]);
-    }
+    VOXEL(zz)
+    const float ri = ld(rr, t.c, zo);
+    av[zz] = 1.0f + 0.5f * g.dt * (R[zz] + (1.0f + g.dt * R[zz]) * ri);
+  }
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    if (!live) continue;
+    for (int c = 0; c < DIM; ++c) st(field_rsrc(X + c * M, g), t.c, zo, xo[c][zz]);
+    st_ya(g, YA, z, t, make_float4(yo[0][zz], yo[1][zz], yo[2][zz], av[zz]));
   }
 }
 
@@ -316,17 +414,16 @@ __global__ __launch_bounds__(BX* GBY) void k_setup(Geo g, const float* __restric
 // (every step n of the time grid in one launch: n = blockIdx.y, v0 = V[n], v1 = V[n + 1] with
 // dim + 1 planes per node, X[n], YA[n])
 template <int DIM>
-__global__ __launch_bounds__(BX* GBY) void k_setup_ns(Geo g, const float* __restrict__ V,
-                                                      float* __restrict__ Xall,
-                                                      float4* __restrict__ YAall) {
-  BL_BATCH(g.bat)
-  BL_AT(V, g.bat);
-  BL_AT(Xall, g.bat);
-  BL_AT(YAall, g.bat);
+__global__ __launch_bounds__(kTB) void k_setup_ns(Geo g, const float* __restrict__ V,
+                                                  float* __restrict__ Xall,
+                                                  float4* __restrict__ YAall) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(V, g.bat);
+  BL_AT_NN(Xall, g.bat);
+  BL_AT_NN(YAall, g.bat);
   constexpr int ZV = 1;
-  GATHER_XY
-  GATHER_Z(0)
-  (void)live;
+  COLUMN
+  VOXEL(0)
   const size_t M = (size_t)g.M;
   const size_t n = blockIdx.y;
   const float* __restrict__ v0 = V + n * (DIM + 1) * M;
@@ -334,209 +431,189 @@ __global__ __launch_bounds__(BX* GBY) void k_setup_ns(Geo g, const float* __rest
   float* __restrict__ X = Xall + n * DIM * M;
   float4* __restrict__ YA = YAall + n * M;
   const float s = g.dt * (float)g.nref;
-  float u0[3] = {0.f, 0.f, 0.f}, u1[3] = {0.f, 0.f, 0.f};
+  float u0[3][1] = {{0.f}, {0.f}, {0.f}}, u1[3] = {0.f, 0.f, 0.f}, nu1[3][1];
+#pragma unroll
   for (int c = 0; c < DIM; ++c) {
-    u0[c] = s * v0[c * M + p];
-    u1[c] = s * v1[c * M + p];
+    u0[c][0] = s * ld(field_rsrc(v0 + c * M, g), t.c, zo);
+    u1[c] = s * ld(field_rsrc(v1 + c * M, g), t.c, zo);
   }
-  const Tap<DIM> tf[1] = {make_tap<DIM>(g, x, y, z, -u1[0], -u1[1], -u1[2])};
-  const Tap<DIM> tb[1] = {make_tap<DIM>(g, x, y, z, u0[0], u0[1], u0[2])};
-  float xo[3] = {0.f, 0.f, 0.f}, yo[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) nu1[c][0] = -u1[c];
+  Tap tf[1], tb[1];
+  make_taps<DIM, 1>(g, t, nu1[0], nu1[1], nu1[2], tf);
+  make_taps<DIM, 1>(g, t, u0[0], u0[1], u0[2], tb);
+  float xo[3] = {0.f, 0.f, 0.f}, yo[3][1] = {{0.f}, {0.f}, {0.f}};
 #pragma unroll
   for (int c = 0; c < DIM; ++c) {
     float gf[1], gb[1];
-    gather_zv<DIM, 1>(field_rsrc(v0 + c * M, g), tf, gf);
-    gather_zv<DIM, 1>(field_rsrc(v1 + c * M, g), tb, gb);
+    gather_zv<DIM, 1>(g, field_rsrc(v0 + c * M, g), tf, gf);
+    gather_zv<DIM, 1>(g, field_rsrc(v1 + c * M, g), tb, gb);
     xo[c] = -0.5f * (u1[c] + s * gf[0]);
-    yo[c] = 0.5f * (u0[c] + s * gb[0]);
+    yo[c][0] = 0.5f * (u0[c][0] + s * gb[0]);
   }
-  const Tap<DIM> ty[1] = {make_tap<DIM>(g, x, y, z, yo[0], yo[1], yo[2])};
-  const float ri = v0[DIM * M + p];
+  Tap ty[1];
+  make_taps<DIM, 1>(g, t, yo[0], yo[1], yo[2], ty);
+  const float ri = ld(field_rsrc(v0 + DIM * M, g), t.c, zo);
   float Rv[1];
-  gather_zv<DIM, 1>(field_rsrc(v1 + DIM * M, g), ty, Rv);
+  gather_zv<DIM, 1>(g, field_rsrc(v1 + DIM * M, g), ty, Rv);
   const float R = Rv[0];
   const float a = 1.0f + 0.5f * g.dt * (R + (1.0f + g.dt * R) * ri);
-  for (int c = 0; c < DIM; ++c) X[c * M + p] = xo[c];
-  YA[p] = make_float4(yo[0], yo[1], yo[2], a);
+  for (int c = 0; c < DIM; ++c) st(field_rsrc(X + c * M, g), t.c, zo, xo[c]);
+  st_ya(g, YA, z, t, make_float4(yo[0][0], yo[1][0], yo[2][0], a));
+}
+
+// ----------------------------------------------------------------------------- transports
+template <int DIM, int ZV>
+__global__ __launch_bounds__(kTB) void k_state_step(Geo g, const float* __restrict__ m_in,
+                                                    const float* __restrict__ X,
+                                                    float* __restrict__ m_out) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(m_in, g.bat);
+  BL_AT_NN(X, g.bat);
+  BL_AT_NN(m_out, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  taps_x<DIM, ZV>(g, t, X, tp);
+  float val[ZV];
+  gather_zv<DIM, ZV>(g, field_rsrc(m_in, g), tp, val);
+  store_zv<ZV>(g, t, m_out, val);
 }
 
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_state_step(Geo g, const float* __restrict__ m_in,
-                                                        const float* __restrict__ X,
-                                                        float* __restrict__ m_out) {
-  BL_BATCH(g.bat)
-  BL_AT(m_in, g.bat);
-  BL_AT(X, g.bat);
-  BL_AT(m_out, g.bat);
-  GATHER_XY
-  const size_t M = (size_t)g.M;
-  Tap<DIM> tp[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float ox = X[p], oy = X[M + p], oz = DIM == 3 ? X[2 * M + p] : 0.f;
-    tp[zz] = make_tap<DIM>(g, x, y, z, ox, oy, oz);
-  }
-  float val[ZV];
-  gather_zv<DIM, ZV>(field_rsrc(m_in, g), tp, val);
-  STORE_ZV(m_out, val)
-}
-
-template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_adj_step(Geo g, const float* __restrict__ lam_in,
-                                                      const float4* __restrict__ YA,
-                                                      float* __restrict__ lam_out) {
-  BL_BATCH(g.bat)
-  BL_AT(lam_in, g.bat);
-  BL_AT(YA, g.bat);
-  BL_AT(lam_out, g.bat);
-  GATHER_XY
-  Tap<DIM> tp[ZV];
-  float aw[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float4 o = YA[p];
-    tp[zz] = make_tap<DIM>(g, x, y, z, o.x, o.y, o.z);
-    aw[zz] = o.w;
-  }
-  float val[ZV];
-  gather_zv<DIM, ZV>(field_rsrc(lam_in, g), tp, val);
+__global__ __launch_bounds__(kTB) void k_adj_step(Geo g, const float* __restrict__ lam_in,
+                                                  const float4* __restrict__ YA,
+                                                  float* __restrict__ lam_out) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(lam_in, g.bat);
+  BL_AT_NN(YA, g.bat);
+  BL_AT_NN(lam_out, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  float aw[ZV], val[ZV];
+  taps_ya<DIM, ZV>(g, t, YA, tp, aw);
+  gather_zv<DIM, ZV>(g, field_rsrc(lam_in, g), tp, val);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) val[zz] = aw[zz] * val[zz];
-  STORE_ZV(lam_out, val)
+  store_zv<ZV>(g, t, lam_out, val);
 }
 
 template <int DIM>
-__global__ __launch_bounds__(BX* GBY) void k_terminal(Geo g, const float* __restrict__ mT,
-                                                      const float* __restrict__ I1,
-                                                      float* __restrict__ lam) {
-  BL_BATCH(g.bat)
-  BL_AT(mT, g.bat);
-  BL_AT(I1, g.bat);
-  BL_AT(lam, g.bat);
+__global__ __launch_bounds__(kTB) void k_terminal(Geo g, const float* __restrict__ mT,
+                                                  const float* __restrict__ I1,
+                                                  float* __restrict__ lam) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(mT, g.bat);
+  BL_AT_NN(I1, g.bat);
+  BL_AT_NN(lam, g.bat);
   constexpr int ZV = 1;
-  GATHER_XY
-  GATHER_Z(0)
-  (void)live;
-  lam[p] = g.lam_scale * (mT[p] - I1[p]);
+  COLUMN
+  VOXEL(0)
+  st(field_rsrc(lam, g), t.c, zo,
+     g.lam_scale * (ld(field_rsrc(mT, g), t.c, zo) - ld(field_rsrc(I1, g), t.c, zo)));
 }
 
 // ---------------------------------------------------------------- stencil + gather kernels
-// Central differences of f at voxel (x, y, z), scaled by N_ref / 2.
+// Central differences of the field at the thread's entry of plane zo (z neighbours zm, zp),
+// scaled by N_ref / 2.
 template <int DIM>
-__device__ __forceinline__ void grad_c(const Geo& g, const float* __restrict__ f, int x, int y,
-                                       int z, uint32_t p, float* gr) {
-  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x + 1 == g.nx ? 0 : x + 1;
-  const uint32_t row = p - x;
-  gr[0] = (f[row + xp] - f[row + xm]) * g.half_nref;
-  const uint32_t sy = g.nx;
-  const uint32_t pym = y == 0 ? p + (uint32_t)(g.ny - 1) * sy : p - sy;
-  const uint32_t pyp = y + 1 == g.ny ? p - (uint32_t)(g.ny - 1) * sy : p + sy;
-  gr[1] = (f[pyp] - f[pym]) * g.half_nref;
-  if (DIM == 3) {
-    const uint32_t sz = (uint32_t)g.nx * g.ny;
-    const uint32_t pzm = z == 0 ? p + (uint32_t)(g.nz - 1) * sz : p - sz;
-    const uint32_t pzp = z + 1 == g.nz ? p - (uint32_t)(g.nz - 1) * sz : p + sz;
-    gr[2] = (f[pzp] - f[pzm]) * g.half_nref;
-  }
+__device__ __forceinline__ void grad_c(const Geo& g, Rsrc f, const Col& t, uint32_t zo,
+                                       uint32_t zm, uint32_t zp, float* gr) {
+  gr[0] = (ld(f, t.xp, zo) - ld(f, t.xm, zo)) * g.half_nref;
+  gr[1] = (ld(f, t.yp, zo) - ld(f, t.ym, zo)) * g.half_nref;
+  if (DIM == 3) gr[2] = (ld(f, t.c, zp) - ld(f, t.c, zm)) * g.half_nref;
 }
 
-// f = -grad m . dv at voxel p (dv: dim planes)
+// dim planes of a vector field
 template <int DIM>
-__device__ __forceinline__ float source_f(const Geo& g, const float* __restrict__ m,
-                                          const float* __restrict__ dv, int x, int y, int z,
-                                          uint32_t p) {
-  float gr[3];
-  grad_c<DIM>(g, m, x, y, z, p, gr);
-  const size_t M = (size_t)g.M;
-  float s = gr[0] * dv[p];
-  s = fmaf(gr[1], dv[M + p], s);
-  if (DIM == 3) s = fmaf(gr[2], dv[2 * M + p], s);
-  return -s;
+struct Vec {
+  Rsrc c[DIM];
+};
+template <int DIM>
+__device__ __forceinline__ Vec<DIM> vec_rsrc(const float* f, const Geo& g) {
+  Vec<DIM> v;
+#pragma unroll
+  for (int c = 0; c < DIM; ++c) v.c[c] = field_rsrc(f + c * (size_t)g.M, g);
+  return v;
+}
+
+// f = -grad m . dv at the thread's ZV voxels
+template <int DIM, int ZV>
+__device__ __forceinline__ void source_f(const Geo& g, const Col& t, const float* m,
+                                         const float* dv, float (&src)[ZV]) {
+  const Rsrc rm = field_rsrc(m, g);
+  const Vec<DIM> rd = vec_rsrc<DIM>(dv, g);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    float gr[3];
+    grad_c<DIM>(g, rm, t, zo, zm, zp, gr);
+    float s = gr[0] * ld(rd.c[0], t.c, zo);
+    s = fmaf(gr[1], ld(rd.c[1], t.c, zo), s);
+    if constexpr (DIM == 3) s = fmaf(gr[2], ld(rd.c[2], t.c, zo), s);
+    src[zz] = -s;
+  }
 }
 
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_inc_init(Geo g, const float* __restrict__ m0,
-                                                      const float* __restrict__ dv,
-                                                      float* __restrict__ t0) {
-  BL_BATCH(g.bat)
-  BL_AT(m0, g.bat);
-  BL_AT(dv, g.bat);
-  BL_AT(t0, g.bat);
-  GATHER_XY
+__global__ __launch_bounds__(kTB) void k_inc_init(Geo g, const float* __restrict__ m0,
+                                                  const float* __restrict__ dv,
+                                                  float* __restrict__ t0) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(m0, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(t0, g.bat);
+  COLUMN
   float val[ZV];
+  source_f<DIM, ZV>(g, t, m0, dv, val);
 #pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    val[zz] = 0.5f * g.dt * source_f<DIM>(g, m0, dv, x, y, z, p);
-  }
-  STORE_ZV(t0, val)
+  for (int zz = 0; zz < ZV; ++zz) val[zz] = 0.5f * g.dt * val[zz];
+  store_zv<ZV>(g, t, t0, val);
 }
 
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_inc_step(Geo g, const float* __restrict__ t_in,
-                                                      const float* __restrict__ X,
-                                                      const float* __restrict__ m_next,
-                                                      const float* __restrict__ dv,
-                                                      float* __restrict__ t_out) {
-  BL_BATCH(g.bat)
-  BL_AT(t_in, g.bat);
-  BL_AT(X, g.bat);
-  BL_AT(m_next, g.bat);
-  BL_AT(dv, g.bat);
-  BL_AT(t_out, g.bat);
-  GATHER_XY
-  const size_t M = (size_t)g.M;
-  Tap<DIM> tp[ZV];
-  float src[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float ox = X[p], oy = X[M + p], oz = DIM == 3 ? X[2 * M + p] : 0.f;
-    tp[zz] = make_tap<DIM>(g, x, y, z, ox, oy, oz);
-    src[zz] = source_f<DIM>(g, m_next, dv, x, y, z, p);
-  }
-  float val[ZV];
-  gather_zv<DIM, ZV>(field_rsrc(t_in, g), tp, val);
+__global__ __launch_bounds__(kTB) void k_inc_step(Geo g, const float* __restrict__ t_in,
+                                                  const float* __restrict__ X,
+                                                  const float* __restrict__ m_next,
+                                                  const float* __restrict__ dv,
+                                                  float* __restrict__ t_out) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(t_in, g.bat);
+  BL_AT_NN(X, g.bat);
+  BL_AT_NN(m_next, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(t_out, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  float src[ZV], val[ZV];
+  taps_x<DIM, ZV>(g, t, X, tp);
+  source_f<DIM, ZV>(g, t, m_next, dv, src);
+  gather_zv<DIM, ZV>(g, field_rsrc(t_in, g), tp, val);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) val[zz] = fmaf(g.dt, src[zz], val[zz]);
-  STORE_ZV(t_out, val)
+  store_zv<ZV>(g, t, t_out, val);
 }
 
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_inc_last(Geo g, const float* __restrict__ t_in,
-                                                      const float* __restrict__ X,
-                                                      const float* __restrict__ mT,
-                                                      const float* __restrict__ dv,
-                                                      float* __restrict__ dlam) {
-  BL_BATCH(g.bat)
-  BL_AT(t_in, g.bat);
-  BL_AT(X, g.bat);
-  BL_AT(mT, g.bat);
-  BL_AT(dv, g.bat);
-  BL_AT(dlam, g.bat);
-  GATHER_XY
-  const size_t M = (size_t)g.M;
-  Tap<DIM> tp[ZV];
-  float src[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float ox = X[p], oy = X[M + p], oz = DIM == 3 ? X[2 * M + p] : 0.f;
-    tp[zz] = make_tap<DIM>(g, x, y, z, ox, oy, oz);
-    src[zz] = source_f<DIM>(g, mT, dv, x, y, z, p);
-  }
-  float val[ZV];
-  gather_zv<DIM, ZV>(field_rsrc(t_in, g), tp, val);
+__global__ __launch_bounds__(kTB) void k_inc_last(Geo g, const float* __restrict__ t_in,
+                                                  const float* __restrict__ X,
+                                                  const float* __restrict__ mT,
+                                                  const float* __restrict__ dv,
+                                                  float* __restrict__ dlam) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(t_in, g.bat);
+  BL_AT_NN(X, g.bat);
+  BL_AT_NN(mT, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(dlam, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  float src[ZV], val[ZV];
+  taps_x<DIM, ZV>(g, t, X, tp);
+  source_f<DIM, ZV>(g, t, mT, dv, src);
+  gather_zv<DIM, ZV>(g, field_rsrc(t_in, g), tp, val);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) val[zz] = g.lam_scale * fmaf(0.5f * g.dt, src[zz], val[zz]);
-  STORE_ZV(dlam, val)
+  store_zv<ZV>(g, t, dlam, val);
 }
 
 // b = sum_n w_n lambda^n grad m^n over the stored adjoint and state planes (trapezoid in
@@ -548,84 +625,78 @@ __global__ __launch_bounds__(BX* GBY) void k_inc_last(Geo g, const float* __rest
 // would, a Interp(lambda^1, i + Y), with the same arithmetic (the caller then stops the
 // backward transport at lambda^1; lambda^0 is needed by nothing but this sum).
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_body_force(Geo g, const float* __restrict__ lam,
-                                                        const float* __restrict__ m,
-                                                        float* __restrict__ b,
-                                                        const float4* __restrict__ YA) {
-  BL_BATCH(g.bat)
-  BL_AT(lam, g.bat);
-  BL_AT(m, g.bat);
-  BL_AT(b, g.bat);
+__global__ __launch_bounds__(kTB) void k_body_force(Geo g, const float* __restrict__ lam,
+                                                    const float* __restrict__ m,
+                                                    float* __restrict__ b,
+                                                    const float4* __restrict__ YA) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(lam, g.bat);
+  BL_AT_NN(m, g.bat);
+  BL_AT_NN(b, g.bat);
   BL_AT(YA, g.bat);
-  GATHER_XY
+  COLUMN
   const size_t M = (size_t)g.M;
-  const uint32_t sz = (uint32_t)g.nx * g.ny;
-  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x + 1 == g.nx ? 0 : x + 1;
-  const uint32_t sy = g.nx;
   float acc[ZV][3];
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) acc[zz][0] = acc[zz][1] = acc[zz][2] = 0.f;
-  // the run's first voxel and its lower z neighbour (periodic); the run starts below nz
-  const int z0 = tile.bz * ZV;
-  const uint32_t p0 = ((uint32_t)z0 * g.ny + y) * g.nx + x;
-  const uint32_t p0m = z0 == 0 ? p0 + (uint32_t)(g.nz - 1) * sz : p0 - sz;
-  // lambda^0 of the thread's voxels from lambda^1 (as k_adj_step)
-  float l0[ZV];
-  const bool form0 = YA != nullptr;
-  if (form0) {
-    Tap<DIM> tp[ZV];
+  // lambda^0 of the thread's voxels: from lambda^1 (as k_adj_step), or its stored plane
+  float l[ZV];
+  if (YA != nullptr) {
+    Tap tp[ZV];
     float aw[ZV];
+    taps_ya<DIM, ZV>(g, t, YA, tp, aw);
+    gather_zv<DIM, ZV>(g, field_rsrc(lam + M, g), tp, l);
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) l[zz] = aw[zz] * l[zz];
+  } else {
+    const Rsrc rl = field_rsrc(lam, g);
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
-      GATHER_Z(zz)
-      (void)live;
-      const float4 o = YA[p];
-      tp[zz] = make_tap<DIM>(g, x, y, z, o.x, o.y, o.z);
-      aw[zz] = o.w;
+      VOXEL(zz)
+      l[zz] = ld(rl, t.c, zo);
     }
-    gather_zv<DIM, ZV>(field_rsrc(lam + M, g), tp, l0);
-#pragma unroll
-    for (int zz = 0; zz < ZV; ++zz) l0[zz] = aw[zz] * l0[zz];
   }
-  // one time node: own = lambda^n from l0 (n = 0 only), else from its stored plane
-  auto node = [&](int n, bool own) {
+  for (int n = 0; n <= g.nt; ++n) {
     const float w = (n == 0 || n == g.nt) ? 0.5f * g.dt : g.dt;
-    const float* __restrict__ mn = m + n * M;
-    const float* __restrict__ ln = lam + n * M;
-    float prev = DIM == 3 ? mn[p0m] : 0.f;   // m at z - 1
-    float cur = DIM == 3 ? mn[p0] : 0.f;     // m at z
+    const Rsrc rm = field_rsrc(m + n * M, g);
+    if (n > 0) {
+      const Rsrc rl = field_rsrc(lam + n * M, g);
+#pragma unroll
+      for (int zz = 0; zz < ZV; ++zz) {
+        VOXEL(zz)
+        l[zz] = ld(rl, t.c, zo);
+      }
+    }
+    float prev = 0.f, cur = 0.f;   // m at z - 1 and z
+    if (DIM == 3) {                // the run starts below nz
+      VOXEL(0)
+      prev = ld(rm, t.c, zm);
+      cur = ld(rm, t.c, zo);
+    }
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
-      GATHER_Z(zz)
-      (void)live;
-      const uint32_t row = p - x;
-      const float gx = (mn[row + xp] - mn[row + xm]) * g.half_nref;
-      const uint32_t pym = y == 0 ? p + (uint32_t)(g.ny - 1) * sy : p - sy;
-      const uint32_t pyp = y + 1 == g.ny ? p - (uint32_t)(g.ny - 1) * sy : p + sy;
-      const float gy = (mn[pyp] - mn[pym]) * g.half_nref;
+      VOXEL(zz)
+      const float gx = (ld(rm, t.xp, zo) - ld(rm, t.xm, zo)) * g.half_nref;
+      const float gy = (ld(rm, t.yp, zo) - ld(rm, t.ym, zo)) * g.half_nref;
       float gz = 0.f;
       if (DIM == 3) {
         // voxels past nz repeat the clamped last plane and are not stored
-        const uint32_t pzp = z + 1 == g.nz ? p - (uint32_t)(g.nz - 1) * sz : p + sz;
-        const float next = mn[pzp];
+        const float next = ld(rm, t.c, zp);
         gz = (next - prev) * g.half_nref;
         prev = cur;
         cur = next;
       }
-      const float wl = w * (own ? l0[zz] : ln[p]);
+      const float wl = w * l[zz];
       acc[zz][0] = fmaf(wl, gx, acc[zz][0]);
       acc[zz][1] = fmaf(wl, gy, acc[zz][1]);
       if (DIM == 3) acc[zz][2] = fmaf(wl, gz, acc[zz][2]);
     }
-  };
-  if (form0) node(0, true);
-  else node(0, false);
-  for (int n = 1; n <= g.nt; ++n) node(n, false);
+  }
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
+    VOXEL(zz)
     if (live)
-      for (int c = 0; c < DIM; ++c) b[c * M + p] = acc[zz][c];
+      for (int c = 0; c < DIM; ++c) st(field_rsrc(b + c * M, g), t.c, zo, acc[zz][c]);
   }
 }
 
@@ -637,174 +708,166 @@ __global__ __launch_bounds__(BX* GBY) void k_body_force(Geo g, const float* __re
 //   q^n = a Interp(u^{n+1}, i + Y) + dt/2 s^n,  dlambda^n = q^n,  u^n = q^n + dt/2 s^n  (0 < n < Nt),
 //   dlambda^0 = a Interp(u^1, i + Y).
 
-// central-difference divergence of lambda dv at voxel p: sum_j (lam dv_j)(i + e_j) - (i - e_j)
-template <int DIM>
-__device__ __forceinline__ float div_lam_dv(const Geo& g, const float* __restrict__ lam,
-                                            const float* __restrict__ dv, int x, int y, int z,
-                                            uint32_t p) {
-  const size_t M = (size_t)g.M;
-  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x + 1 == g.nx ? 0 : x + 1;
-  const uint32_t row = p - x;
-  float s = lam[row + xp] * dv[row + xp] - lam[row + xm] * dv[row + xm];
-  const uint32_t sy = g.nx;
-  const uint32_t pym = y == 0 ? p + (uint32_t)(g.ny - 1) * sy : p - sy;
-  const uint32_t pyp = y + 1 == g.ny ? p - (uint32_t)(g.ny - 1) * sy : p + sy;
-  s += lam[pyp] * dv[M + pyp] - lam[pym] * dv[M + pym];
-  if (DIM == 3) {
-    const uint32_t sz = (uint32_t)g.nx * g.ny;
-    const uint32_t pzm = z == 0 ? p + (uint32_t)(g.nz - 1) * sz : p - sz;
-    const uint32_t pzp = z + 1 == g.nz ? p - (uint32_t)(g.nz - 1) * sz : p + sz;
-    s += lam[pzp] * dv[2 * M + pzp] - lam[pzm] * dv[2 * M + pzm];
+// central-difference divergence of lambda dv: sum_j (lam dv_j)(i + e_j) - (i - e_j)
+template <int DIM, int ZV>
+__device__ __forceinline__ void div_lam_dv(const Geo& g, const Col& t, const float* lam,
+                                           const float* dv, float (&out)[ZV]) {
+  const Rsrc rl = field_rsrc(lam, g);
+  const Vec<DIM> rd = vec_rsrc<DIM>(dv, g);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    float s = ld(rl, t.xp, zo) * ld(rd.c[0], t.xp, zo) - ld(rl, t.xm, zo) * ld(rd.c[0], t.xm, zo);
+    s += ld(rl, t.yp, zo) * ld(rd.c[1], t.yp, zo) - ld(rl, t.ym, zo) * ld(rd.c[1], t.ym, zo);
+    if constexpr (DIM == 3)
+      s += ld(rl, t.c, zp) * ld(rd.c[2], t.c, zp) - ld(rl, t.c, zm) * ld(rd.c[2], t.c, zm);
+    out[zz] = s * g.half_nref;
   }
-  return s * g.half_nref;
 }
 
 // incremental state step that also stores dm^{n+1} = Interp(t^n, i + X) + dt/2 f^{n+1}
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_inc_step_n(Geo g, const float* __restrict__ t_in,
-                                                        const float* __restrict__ X,
-                                                        const float* __restrict__ m_next,
-                                                        const float* __restrict__ dv,
-                                                        float* __restrict__ t_out,
-                                                        float* __restrict__ dm_out) {
-  BL_BATCH(g.bat)
-  BL_AT(t_in, g.bat);
-  BL_AT(X, g.bat);
-  BL_AT(m_next, g.bat);
-  BL_AT(dv, g.bat);
-  BL_AT(t_out, g.bat);
-  BL_AT(dm_out, g.bat);
-  GATHER_XY
-  const size_t M = (size_t)g.M;
-  float val[ZV], dmv[ZV];
+__global__ __launch_bounds__(kTB) void k_inc_step_n(Geo g, const float* __restrict__ t_in,
+                                                    const float* __restrict__ X,
+                                                    const float* __restrict__ m_next,
+                                                    const float* __restrict__ dv,
+                                                    float* __restrict__ t_out,
+                                                    float* __restrict__ dm_out) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(t_in, g.bat);
+  BL_AT_NN(X, g.bat);
+  BL_AT_NN(m_next, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(t_out, g.bat);
+  BL_AT_NN(dm_out, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  float src[ZV], val[ZV], dmv[ZV];
+  taps_x<DIM, ZV>(g, t, X, tp);
+  source_f<DIM, ZV>(g, t, m_next, dv, src);
+  gather_zv<DIM, ZV>(g, field_rsrc(t_in, g), tp, val);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float ox = X[p], oy = X[M + p], oz = DIM == 3 ? X[2 * M + p] : 0.f;
-    const float tr = apply<DIM>(field_rsrc(t_in, g), make_tap<DIM>(g, x, y, z, ox, oy, oz));
-    const float f = source_f<DIM>(g, m_next, dv, x, y, z, p);
-    val[zz] = fmaf(g.dt, f, tr);
-    dmv[zz] = fmaf(0.5f * g.dt, f, tr);
+    dmv[zz] = fmaf(0.5f * g.dt, src[zz], val[zz]);
+    val[zz] = fmaf(g.dt, src[zz], val[zz]);
   }
-  STORE_ZV(t_out, val)
-  STORE_ZV(dm_out, dmv)
+  store_zv<ZV>(g, t, t_out, val);
+  store_zv<ZV>(g, t, dm_out, dmv);
 }
 
 // last incremental state step: dm^Nt, and dlambda^Nt = u^Nt = -(2/sigma^2) dm^Nt + dt/2 s^Nt
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_inc_last_n(Geo g, const float* __restrict__ t_in,
-                                                        const float* __restrict__ X,
-                                                        const float* __restrict__ mT,
-                                                        const float* __restrict__ dv,
-                                                        const float* __restrict__ lamT,
-                                                        float* __restrict__ dm_out,
-                                                        float* __restrict__ dlam) {
-  BL_BATCH(g.bat)
-  BL_AT(t_in, g.bat);
-  BL_AT(X, g.bat);
-  BL_AT(mT, g.bat);
-  BL_AT(dv, g.bat);
-  BL_AT(lamT, g.bat);
-  BL_AT(dm_out, g.bat);
-  BL_AT(dlam, g.bat);
-  GATHER_XY
-  const size_t M = (size_t)g.M;
-  float dmv[ZV], val[ZV];
+__global__ __launch_bounds__(kTB) void k_inc_last_n(Geo g, const float* __restrict__ t_in,
+                                                    const float* __restrict__ X,
+                                                    const float* __restrict__ mT,
+                                                    const float* __restrict__ dv,
+                                                    const float* __restrict__ lamT,
+                                                    float* __restrict__ dm_out,
+                                                    float* __restrict__ dlam) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(t_in, g.bat);
+  BL_AT_NN(X, g.bat);
+  BL_AT_NN(mT, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(lamT, g.bat);
+  BL_AT_NN(dm_out, g.bat);
+  BL_AT_NN(dlam, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  float src[ZV], dmv[ZV], val[ZV];
+  taps_x<DIM, ZV>(g, t, X, tp);
+  source_f<DIM, ZV>(g, t, mT, dv, src);
+  div_lam_dv<DIM, ZV>(g, t, lamT, dv, val);
+  gather_zv<DIM, ZV>(g, field_rsrc(t_in, g), tp, dmv);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float ox = X[p], oy = X[M + p], oz = DIM == 3 ? X[2 * M + p] : 0.f;
-    const float tr = apply<DIM>(field_rsrc(t_in, g), make_tap<DIM>(g, x, y, z, ox, oy, oz));
-    const float dm = fmaf(0.5f * g.dt, source_f<DIM>(g, mT, dv, x, y, z, p), tr);
-    dmv[zz] = dm;
-    val[zz] = fmaf(0.5f * g.dt, div_lam_dv<DIM>(g, lamT, dv, x, y, z, p), g.lam_scale * dm);
+    dmv[zz] = fmaf(0.5f * g.dt, src[zz], dmv[zz]);
+    val[zz] = fmaf(0.5f * g.dt, val[zz], g.lam_scale * dmv[zz]);
   }
-  STORE_ZV(dm_out, dmv)
-  STORE_ZV(dlam, val)
+  store_zv<ZV>(g, t, dm_out, dmv);
+  store_zv<ZV>(g, t, dlam, val);
 }
 
 // one incremental adjoint step of the Newton product: q = a Interp(u^{n+1}, i + Y) (+ dt/2 s^n
 // when own); dlambda^n = q; with u_out, u^n = q + dt/2 s^n
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_adj_step_n(Geo g, const float* __restrict__ u_in,
-                                                        const float4* __restrict__ YA,
-                                                        const float* __restrict__ lam_n,
-                                                        const float* __restrict__ dv, int own,
-                                                        float* __restrict__ dlam,
-                                                        float* __restrict__ u_out) {
-  BL_BATCH(g.bat)
-  BL_AT(u_in, g.bat);
-  BL_AT(YA, g.bat);
-  BL_AT(lam_n, g.bat);
-  BL_AT(dv, g.bat);
-  BL_AT(dlam, g.bat);
+__global__ __launch_bounds__(kTB) void k_adj_step_n(Geo g, const float* __restrict__ u_in,
+                                                    const float4* __restrict__ YA,
+                                                    const float* __restrict__ lam_n,
+                                                    const float* __restrict__ dv, int own,
+                                                    float* __restrict__ dlam,
+                                                    float* __restrict__ u_out) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(u_in, g.bat);
+  BL_AT_NN(YA, g.bat);
+  BL_AT_NN(lam_n, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(dlam, g.bat);
   BL_AT(u_out, g.bat);
-  GATHER_XY
-  float qv[ZV], uv[ZV];
+  COLUMN
+  Tap tp[ZV];
+  float aw[ZV], hs[ZV], qv[ZV], uv[ZV];
+  taps_ya<DIM, ZV>(g, t, YA, tp, aw);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) hs[zz] = 0.f;
+  if (own) {
+    div_lam_dv<DIM, ZV>(g, t, lam_n, dv, hs);
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) hs[zz] = 0.5f * g.dt * hs[zz];
+  }
+  gather_zv<DIM, ZV>(g, field_rsrc(u_in, g), tp, qv);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
-    const float4 o = YA[p];
-    const float tr = o.w * apply<DIM>(field_rsrc(u_in, g), make_tap<DIM>(g, x, y, z, o.x, o.y, o.z));
-    const float hs = own ? 0.5f * g.dt * div_lam_dv<DIM>(g, lam_n, dv, x, y, z, p) : 0.f;
-    qv[zz] = tr + hs;
-    uv[zz] = qv[zz] + hs;
+    qv[zz] = aw[zz] * qv[zz] + hs[zz];
+    uv[zz] = qv[zz] + hs[zz];
   }
-  STORE_ZV(dlam, qv)
-  if (u_out) { STORE_ZV(u_out, uv) }
+  store_zv<ZV>(g, t, dlam, qv);
+  if (u_out) store_zv<ZV>(g, t, u_out, uv);
 }
 
 // Newton body force: sum_n w_n (dlambda^n grad m^n + lambda^n grad dm^n); the node loop is
 // outside the thread's z run and the z differences of m^n and dm^n come from sliding windows,
 // as in k_body_force
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_body_force_n(Geo g, const float* __restrict__ dlam,
-                                                          const float* __restrict__ m,
-                                                          const float* __restrict__ lam,
-                                                          const float* __restrict__ dm,
-                                                          float* __restrict__ b) {
-  BL_BATCH(g.bat)
-  BL_AT(dlam, g.bat);
-  BL_AT(m, g.bat);
-  BL_AT(lam, g.bat);
-  BL_AT(dm, g.bat);
-  BL_AT(b, g.bat);
-  GATHER_XY
+__global__ __launch_bounds__(kTB) void k_body_force_n(Geo g, const float* __restrict__ dlam,
+                                                      const float* __restrict__ m,
+                                                      const float* __restrict__ lam,
+                                                      const float* __restrict__ dm,
+                                                      float* __restrict__ b) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(dlam, g.bat);
+  BL_AT_NN(m, g.bat);
+  BL_AT_NN(lam, g.bat);
+  BL_AT_NN(dm, g.bat);
+  BL_AT_NN(b, g.bat);
+  COLUMN
   const size_t M = (size_t)g.M;
-  const uint32_t sz = (uint32_t)g.nx * g.ny;
-  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x + 1 == g.nx ? 0 : x + 1;
-  const uint32_t sy = g.nx;
   float acc[ZV][3];
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) acc[zz][0] = acc[zz][1] = acc[zz][2] = 0.f;
-  const int z0 = tile.bz * ZV;
-  const uint32_t p0 = ((uint32_t)z0 * g.ny + y) * g.nx + x;
-  const uint32_t p0m = z0 == 0 ? p0 + (uint32_t)(g.nz - 1) * sz : p0 - sz;
   for (int n = 0; n <= g.nt; ++n) {
     const float w = (n == 0 || n == g.nt) ? 0.5f * g.dt : g.dt;
-    const float* __restrict__ mn = m + n * M;
-    const float* __restrict__ dn = dm + n * M;
-    float mprev = DIM == 3 ? mn[p0m] : 0.f, mcur = DIM == 3 ? mn[p0] : 0.f;
-    float dprev = DIM == 3 ? dn[p0m] : 0.f, dcur = DIM == 3 ? dn[p0] : 0.f;
+    const Rsrc rm = field_rsrc(m + n * M, g), rd = field_rsrc(dm + n * M, g);
+    const Rsrc rq = field_rsrc(dlam + n * M, g), rl = field_rsrc(lam + n * M, g);
+    float mprev = 0.f, mcur = 0.f, dprev = 0.f, dcur = 0.f;
+    if (DIM == 3) {
+      VOXEL(0)
+      mprev = ld(rm, t.c, zm);
+      mcur = ld(rm, t.c, zo);
+      dprev = ld(rd, t.c, zm);
+      dcur = ld(rd, t.c, zo);
+    }
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
-      GATHER_Z(zz)
-      (void)live;
-      const uint32_t row = p - x;
-      const uint32_t pym = y == 0 ? p + (uint32_t)(g.ny - 1) * sy : p - sy;
-      const uint32_t pyp = y + 1 == g.ny ? p - (uint32_t)(g.ny - 1) * sy : p + sy;
+      VOXEL(zz)
       float gr[3], gd[3];
-      gr[0] = (mn[row + xp] - mn[row + xm]) * g.half_nref;
-      gr[1] = (mn[pyp] - mn[pym]) * g.half_nref;
-      gd[0] = (dn[row + xp] - dn[row + xm]) * g.half_nref;
-      gd[1] = (dn[pyp] - dn[pym]) * g.half_nref;
+      gr[0] = (ld(rm, t.xp, zo) - ld(rm, t.xm, zo)) * g.half_nref;
+      gr[1] = (ld(rm, t.yp, zo) - ld(rm, t.ym, zo)) * g.half_nref;
+      gd[0] = (ld(rd, t.xp, zo) - ld(rd, t.xm, zo)) * g.half_nref;
+      gd[1] = (ld(rd, t.yp, zo) - ld(rd, t.ym, zo)) * g.half_nref;
       gr[2] = gd[2] = 0.f;
       if (DIM == 3) {
-        const uint32_t pzp = z + 1 == g.nz ? p - (uint32_t)(g.nz - 1) * sz : p + sz;
-        const float mnext = mn[pzp], dnext = dn[pzp];
+        const float mnext = ld(rm, t.c, zp), dnext = ld(rd, t.c, zp);
         gr[2] = (mnext - mprev) * g.half_nref;
         gd[2] = (dnext - dprev) * g.half_nref;
         mprev = mcur;
@@ -812,71 +875,67 @@ __global__ __launch_bounds__(BX* GBY) void k_body_force_n(Geo g, const float* __
         dprev = dcur;
         dcur = dnext;
       }
-      const float wl = w * dlam[n * M + p];
-      const float wa = w * lam[n * M + p];
+      const float wl = w * ld(rq, t.c, zo);
+      const float wa = w * ld(rl, t.c, zo);
 #pragma unroll
       for (int c = 0; c < DIM; ++c) acc[zz][c] = fmaf(wa, gd[c], fmaf(wl, gr[c], acc[zz][c]));
     }
   }
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
+    VOXEL(zz)
     if (live)
-      for (int c = 0; c < DIM; ++c) b[c * M + p] = acc[zz][c];
+      for (int c = 0; c < DIM; ++c) st(field_rsrc(b + c * M, g), t.c, zo, acc[zz][c]);
   }
 }
 
 // b^n = lambda^n grad m^n at the time node n = blockIdx.y (a non-stationary gradient or
 // product has one body force per node, not a time integral); all nodes in one launch
 template <int DIM, int ZV>
-__global__ __launch_bounds__(BX* GBY) void k_body_node(Geo g, const float* __restrict__ lam,
-                                                       const float* __restrict__ m,
-                                                       float* __restrict__ b,
-                                                       const float4* __restrict__ YA0) {
-  BL_BATCH(g.bat)
-  BL_AT(lam, g.bat);
-  BL_AT(m, g.bat);
-  BL_AT(b, g.bat);
+__global__ __launch_bounds__(kTB) void k_body_node(Geo g, const float* __restrict__ lam,
+                                                   const float* __restrict__ m,
+                                                   float* __restrict__ b,
+                                                   const float4* __restrict__ YA0) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(lam, g.bat);
+  BL_AT_NN(m, g.bat);
+  BL_AT_NN(b, g.bat);
   BL_AT(YA0, g.bat);
-  GATHER_XY
+  COLUMN
   const size_t M = (size_t)g.M;
   // with YA0 (the first step's (Y, a)), the blocks of node 0 form lambda^0 = a Interp(lambda^1,
   // i + Y) as the adjoint step would, with the same arithmetic, instead of reading it
-  const bool form0 = YA0 != nullptr && blockIdx.y == 0;
-  float l0[ZV];
-  if (form0) {
-    Tap<DIM> tp[ZV];
+  float l[ZV];
+  if (YA0 != nullptr && blockIdx.y == 0) {
+    Tap tp[ZV];
     float aw[ZV];
+    taps_ya<DIM, ZV>(g, t, YA0, tp, aw);
+    gather_zv<DIM, ZV>(g, field_rsrc(lam + M, g), tp, l);
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) l[zz] = aw[zz] * l[zz];
+  } else {
+    const Rsrc rl = field_rsrc(lam + blockIdx.y * M, g);
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
-      GATHER_Z(zz)
-      (void)live;
-      const float4 o = YA0[p];
-      tp[zz] = make_tap<DIM>(g, x, y, z, o.x, o.y, o.z);
-      aw[zz] = o.w;
+      VOXEL(zz)
+      l[zz] = ld(rl, t.c, zo);
     }
-    gather_zv<DIM, ZV>(field_rsrc(lam + M, g), tp, l0);
-#pragma unroll
-    for (int zz = 0; zz < ZV; ++zz) l0[zz] = aw[zz] * l0[zz];
   }
-  lam += blockIdx.y * M;
-  m += blockIdx.y * M;
+  const Rsrc rm = field_rsrc(m + blockIdx.y * M, g);
   b += blockIdx.y * (size_t)DIM * M;
   float acc[ZV][3];
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
-    (void)live;
+    VOXEL(zz)
     float gr[3];
-    grad_c<DIM>(g, m, x, y, z, p, gr);
-    const float l = form0 ? l0[zz] : lam[p];
-    for (int c = 0; c < DIM; ++c) acc[zz][c] = l * gr[c];
+    grad_c<DIM>(g, rm, t, zo, zm, zp, gr);
+    for (int c = 0; c < DIM; ++c) acc[zz][c] = l[zz] * gr[c];
   }
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
-    GATHER_Z(zz)
+    VOXEL(zz)
     if (live)
-      for (int c = 0; c < DIM; ++c) b[c * M + p] = acc[zz][c];
+      for (int c = 0; c < DIM; ++c) st(field_rsrc(b + c * M, g), t.c, zo, acc[zz][c]);
   }
 }
 
@@ -887,10 +946,10 @@ __global__ __launch_bounds__(256) void k_energy_partial(int64_t n, const float* 
                                                         double* __restrict__ partial,
                                                         float* __restrict__ lam, float lam_scale,
                                                         Batch bt) {
-  BL_BATCH(bt)
-  BL_AT(a, bt);
-  BL_AT(b, bt);
-  BL_AT(partial, bt);
+  BL_BATCH_Z1(bt)
+  BL_AT_NN(a, bt);
+  BL_AT_NN(b, bt);
+  BL_AT_NN(partial, bt);
   BL_AT(lam, bt);
   // the thread's elements i, i + stride, ... in that order; kEU of them per round with all of
   // the round's loads issued before its stores (a loop that loads and stores one element per
@@ -934,8 +993,7 @@ __global__ __launch_bounds__(256) void k_unpack4(int64_t n, int comp,
 }
 
 inline dim3 gather_grid(const Geo& g, int zv) {
-  const long long nb = (long long)((g.nx + BX - 1) / BX) * ((g.ny + GBY - 1) / GBY) *
-                       ((g.nz + zv - 1) / zv);
+  const long long nb = (long long)g.nqb * ((g.nz + zv - 1) / zv);
   return dim3((unsigned)((nb + kXCD - 1) / kXCD * kXCD));
 }
 }  // namespace
@@ -948,25 +1006,25 @@ inline dim3 gather_grid(const Geo& g, int zv) {
     if (g.dim == 3) {                                                                           \
       const int zv_ = g.zv[CLS];                                                                \
       if (zv_ == 8)                                                                             \
-        BL_LAUNCH((KERNEL<3, 8>), GRID_N(8, NY), dim3(BX, GBY), 0, s, __VA_ARGS__);    \
+        BL_LAUNCH((KERNEL<3, 8>), GRID_N(8, NY), dim3(kTB), 0, s, __VA_ARGS__);    \
       else if (zv_ == 4)                                                                        \
-        BL_LAUNCH((KERNEL<3, 4>), GRID_N(4, NY), dim3(BX, GBY), 0, s, __VA_ARGS__);    \
+        BL_LAUNCH((KERNEL<3, 4>), GRID_N(4, NY), dim3(kTB), 0, s, __VA_ARGS__);    \
       else if (zv_ == 2)                                                                        \
-        BL_LAUNCH((KERNEL<3, 2>), GRID_N(2, NY), dim3(BX, GBY), 0, s, __VA_ARGS__);    \
+        BL_LAUNCH((KERNEL<3, 2>), GRID_N(2, NY), dim3(kTB), 0, s, __VA_ARGS__);    \
       else                                                                                      \
-        BL_LAUNCH((KERNEL<3, 1>), GRID_N(1, NY), dim3(BX, GBY), 0, s, __VA_ARGS__);    \
+        BL_LAUNCH((KERNEL<3, 1>), GRID_N(1, NY), dim3(kTB), 0, s, __VA_ARGS__);    \
     } else {                                                                                    \
-      BL_LAUNCH((KERNEL<2, 1>), GRID_N(1, NY), dim3(BX, GBY), 0, s, __VA_ARGS__);     \
+      BL_LAUNCH((KERNEL<2, 1>), GRID_N(1, NY), dim3(kTB), 0, s, __VA_ARGS__);     \
     }                                                                                           \
   } while (0)
 #define DISPATCH_GATHER(KERNEL, CLS, ...) DISPATCH_GATHER_N(KERNEL, CLS, 1, __VA_ARGS__)
 #define DISPATCH_ONE(KERNEL, ...)                                                          \
   do {                                                                                     \
     if (g.dim == 3)                                                                        \
-      hipLaunchKernelGGL(KERNEL<3>, batch_grid(gather_grid(g, 1), g.bat), dim3(BX, GBY), 0, s, \
+      hipLaunchKernelGGL(KERNEL<3>, batch_grid(gather_grid(g, 1), g.bat), dim3(kTB), 0, s, \
                          __VA_ARGS__);                                                     \
     else                                                                                   \
-      hipLaunchKernelGGL(KERNEL<2>, batch_grid(gather_grid(g, 1), g.bat), dim3(BX, GBY), 0, s, \
+      hipLaunchKernelGGL(KERNEL<2>, batch_grid(gather_grid(g, 1), g.bat), dim3(kTB), 0, s, \
                          __VA_ARGS__);                                                     \
   } while (0)
 void setup(const Geo& g, const float* v, float* X, float4* YA, hipStream_t s) {
@@ -975,9 +1033,9 @@ void setup(const Geo& g, const float* v, float* X, float4* YA, hipStream_t s) {
 void setup_ns(const Geo& g, const float* V, float* X, float4* YA, int steps, hipStream_t s) {
   const dim3 grid = batch_grid(dim3(gather_grid(g, 1).x, (unsigned)steps), g.bat);
   if (g.dim == 3)
-    hipLaunchKernelGGL(k_setup_ns<3>, grid, dim3(BX, GBY), 0, s, g, V, X, YA);
+    hipLaunchKernelGGL(k_setup_ns<3>, grid, dim3(kTB), 0, s, g, V, X, YA);
   else
-    hipLaunchKernelGGL(k_setup_ns<2>, grid, dim3(BX, GBY), 0, s, g, V, X, YA);
+    hipLaunchKernelGGL(k_setup_ns<2>, grid, dim3(kTB), 0, s, g, V, X, YA);
 }
 void body_nodes(const Geo& g, const float* lam, const float* m, float* b, int nodes,
                 hipStream_t s, const float4* YA0) {
