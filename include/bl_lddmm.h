@@ -279,7 +279,9 @@ int bl_lddmm_device_count(void);
  * 3 = z stage of iota of the direction in a Gauss-Newton product, 4 = z stage of pi of the
  * product's body force, 5 = body-force pass, 6 = departure-point setup.
  * Classes 3-5 are timed in Gauss-Newton products and gradients of the stationary state
- * equation only.  Errors: BL_E_INVALID for a NULL argument or a class outside [0, 6].
+ * equation only.  While enabled, every time step is a launch of its own; otherwise grids whose
+ * tiles are resident at once may run all steps of a transport in one launch, with bitwise the
+ * same values.  Errors: BL_E_INVALID for a NULL argument or a class outside [0, 6].
  */
 int bl_kernel_timing_enable(bl_ctx* ctx, int32_t on);
 int bl_kernel_timing_read(bl_ctx* ctx, int32_t kclass, int64_t* launches, double* ms);
@@ -291,7 +293,8 @@ int bl_kernel_timing_read(bl_ctx* ctx, int32_t kclass, int64_t* launches, double
  * bitwise the same values.  The library times the candidates on the context's own fields at
  * the first velocity set on a grid shape and keeps the fastest per shape for the process; the
  * environment variable BL_TRANSPORT_ZV = 1, 2, 4 or 8 forces one shape for all classes, and 0
- * keeps the built-in defaults without timing.  Reads the shapes in use (all 1 in 2D, and the
+ * keeps the built-in defaults without timing.  While it is set, every time step stays in a
+ * launch of its own.  Reads the shapes in use (all 1 in 2D, and the
  * defaults before the first velocity).  Errors: BL_E_INVALID for NULL arguments.
  */
 int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);

@@ -15,6 +15,8 @@
 
 #include <vector>
 
+#include <memory>
+
 #include "bl_host.h"
 
 namespace bl {
@@ -126,6 +128,7 @@ class Cohort {
   bool prepared_ = false;
   hipEvent_t done_ = nullptr;
   bool in_flight_ = false;
+  std::unique_ptr<host::Operation> op_;   // the step in flight, for the process's other contexts
 };
 
 }  // namespace batch

@@ -213,6 +213,7 @@ void Cohort::release() {
   for (hipGraphExec_t& e : exec_)
     if (e) (void)hipGraphExecDestroy(e);
   exec_.clear();
+  op_.reset();
   for (bl_ctx* c : ctx_) destroy_ctx(c);   // does not own the arena, stream or host scalars
   ctx_.clear();
   for (double* h : hscal_) (void)hipHostFree(h);
@@ -370,7 +371,9 @@ void Cohort::enqueue_step(int k_pcg) {
 
 void Cohort::launch(int k_pcg) {
   k_pcg = std::max(0, std::min(k_pcg, kMaxPcgPerStep));
-  HIP_TRY(hipGraphLaunch(graph(k_pcg), stream_));
+  hipGraphExec_t step = graph(k_pcg);
+  op_.reset(new Operation(ctx_[0]));
+  HIP_TRY(hipGraphLaunch(step, stream_));
   HIP_TRY(hipEventRecord(done_, stream_));
   in_flight_ = true;
 }
@@ -379,6 +382,7 @@ void Cohort::wait() {
   if (!in_flight_) return;
   HIP_TRY(hipEventSynchronize(done_));
   in_flight_ = false;
+  op_.reset();
 }
 
 bool Cohort::poll() {
@@ -387,6 +391,7 @@ bool Cohort::poll() {
   if (e == hipErrorNotReady) return false;
   if (e != hipSuccess) throw DeviceError{e, "hipEventQuery (cohort step)"};
   in_flight_ = false;
+  op_.reset();
   return true;
 }
 

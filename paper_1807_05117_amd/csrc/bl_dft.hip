@@ -483,8 +483,10 @@ __global__ __launch_bounds__(256) void k_band_prep(Geo g, const float2* __restri
                                                    const double* __restrict__ Lhat64,
                                                    double* __restrict__ reg_partial,
                                                    double reg_weight, int reg_accumulate,
-                                                   size_t nstride) {
+                                                   size_t nstride, uint32_t* __restrict__ zero,
+                                                   int nzero) {
   BL_BATCH(g.bat)
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < nzero; i += gridDim.x * 256) zero[i] = 0u;
   BL_AT(raw, g.bat);
   BL_AT(out, g.bat);
   BL_AT(Lhat64, g.bat);
@@ -553,8 +555,10 @@ __global__ __launch_bounds__(256) void k_band_finalize(Geo g,
                                                        const float2* __restrict__ dotp,
                                                        double* __restrict__ dot_part,
                                                        double* __restrict__ sq_part,
-                                                       double* __restrict__ max_part) {
+                                                       double* __restrict__ max_part, Done done) {
   BL_BATCH(g.bat)
+  if (done.word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    __hip_atomic_store(done.word, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   BL_AT(vproj, g.bat);
   BL_AT(Lhat, g.bat);
   BL_AT(P, g.bat);
@@ -756,19 +760,20 @@ void pi_yx(const Geo& g, const DftPlan& p, int C, float2* P, hipStream_t s) {
 }
 
 void band_prep(const Geo& g, const float2* raw, float2* out, int with_div, const double* Lhat64,
-               double* reg_partial, hipStream_t s, double reg_weight, int reg_accumulate) {
+               double* reg_partial, hipStream_t s, double reg_weight, int reg_accumulate,
+               uint32_t* zero, int nzero) {
   // the regulariser sum needs the fixed kRedBlocks grid; the plain projection one thread per
   // band entry
   const int blocks = reg_partial ? kRedBlocks : (int)((g.B + 255) / 256);
   if (g.dim == 3)
     hipLaunchKernelGGL(k_band_prep<3>, batch_grid(dim3(blocks), g.bat), dim3(256), 0, s, g, raw, out, with_div,
-                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0);
+                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0, zero, nzero);
   else if (g.dim == 2)
     hipLaunchKernelGGL(k_band_prep<2>, batch_grid(dim3(blocks), g.bat), dim3(256), 0, s, g, raw, out, with_div,
-                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0);
+                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0, zero, nzero);
   else
     hipLaunchKernelGGL(k_band_prep<1>, batch_grid(dim3(blocks), g.bat), dim3(256), 0, s, g, raw, out, with_div,
-                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0);
+                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0, zero, nzero);
 }
 
 void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, size_t stride,
@@ -776,10 +781,10 @@ void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, si
   const dim3 grid((unsigned)((g.B + 255) / 256), (unsigned)nodes);
   if (g.dim == 3)
     hipLaunchKernelGGL(k_band_prep<3>, grid, dim3(256), 0, s, g, raw, out, 0, nullptr, nullptr,
-                       1.0, 0, stride);
+                       1.0, 0, stride, nullptr, 0);
   else
     hipLaunchKernelGGL(k_band_prep<2>, grid, dim3(256), 0, s, g, raw, out, 0, nullptr, nullptr,
-                       1.0, 0, stride);
+                       1.0, 0, stride, nullptr, 0);
 }
 
 int finalize_blocks(const Geo& g) { return (int)std::min<int64_t>(kRedBlocks, (g.B + 255) / 256); }
@@ -788,14 +793,14 @@ namespace {
 void finalize_launch(const Geo& g, int C, const float2* vproj, size_t vstride, const float* Lhat,
                      const float2* P, size_t pstride, float scale, float2* out, size_t ostride,
                      int nodes, int* nonfinite, hipStream_t s, int leray, const float2* dotp,
-                     double* dot_part, double* sq_part, double* max_part) {
+                     double* dot_part, double* sq_part, double* max_part, Done done) {
   const dim3 blocks((unsigned)finalize_blocks(g), (unsigned)nodes);
   const int on = (leray && g.gamma && C == g.dim) ? 1 : 0;
 #define BF_LAUNCH(D, CC)                                                                        \
   hipLaunchKernelGGL((k_band_finalize<D, CC>), batch_grid(blocks, g.bat), dim3(256), 0, s, g,     \
                      vproj, Lhat, P,                                                            \
                      scale, out, nonfinite, on, vstride, pstride, ostride, dotp, dot_part,     \
-                     sq_part, max_part)
+                     sq_part, max_part, done)
   if (g.dim == 3) {
     switch (C) {
       case 1: BF_LAUNCH(3, 1); break;
@@ -818,17 +823,17 @@ void finalize_launch(const Geo& g, int C, const float2* vproj, size_t vstride, c
 void band_finalize(const Geo& g, int C, const float2* vproj, const float* Lhat,
                    const float2* P, float scale, float2* out, int* nonfinite, hipStream_t s,
                    int leray, const float2* dotp, double* dot_part, double* sq_part,
-                   double* max_part) {
+                   double* max_part, Done done) {
   finalize_launch(g, C, vproj, 0, Lhat, P, 0, scale, out, 0, 1, nonfinite, s, leray, dotp,
-                  dot_part, sq_part, max_part);
+                  dot_part, sq_part, max_part, done);
 }
 
 void band_finalize_nodes(const Geo& g, int C, const float2* vproj, size_t vstride,
                          const float* Lhat, const float2* P, size_t pstride, float scale,
                          float2* out, size_t ostride, int nodes, int* nonfinite, hipStream_t s,
-                         int leray) {
+                         int leray, Done done) {
   finalize_launch(g, C, vproj, vstride, Lhat, P, pstride, scale, out, ostride, nodes, nonfinite, s,
-                  leray, nullptr, nullptr, nullptr, nullptr);
+                  leray, nullptr, nullptr, nullptr, nullptr, done);
 }
 
 }  // namespace bl

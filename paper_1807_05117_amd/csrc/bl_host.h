@@ -2,6 +2,7 @@
 // registration problem, validation, transfers and the Gauss-Newton-Krylov driver.
 #pragma once
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -34,7 +35,7 @@ struct NonFinite {
 enum { RED_REG = 0, RED_DATA, RED_A, RED_B, RED_C, RED_SLOTS };
 // slots of the device scalars (bl_ctx::scal) and of their host-mapped mirror (bl_ctx::hscal)
 enum {
-  S_REG = 0, S_DATA, S_GG, S_GINF, S_PHP, S_SLOPE, S_RR, S_RZ0, S_RZ1, S_SQD, S_FLAG, S_SLOTS
+  S_REG = 0, S_DATA, S_GG, S_GINF, S_PHP, S_SLOPE, S_RR, S_RZ0, S_RZ1, S_SQD, S_FLAG, S_DONE, S_SLOTS
 };
 
 int fail(int code, const std::string& msg);
@@ -111,8 +112,23 @@ struct bl_ctx {
   bool own_hscal = true;
   int* flag = nullptr;
   double* hflag_dummy = nullptr;
+  // whole sweeps in one launch: tiles (run = 0: steps are launched one by one), the words of the
+  // forward and of the backward sweep, and whether each is zero for its next launch
+  bl::SweepPlan sweep;
+  uint32_t* sweep_sync = nullptr;   // 2 * kSweepWords
+  bool sweep_clean[2] = {false, false};
+  bool sweeps_allowed = false;      // inside an Operation that is not captured
+  bool sweep_now = false;           // decided with each evaluation's or product's first launch
+  // operations issued on this context and known to have ended (others are complete when the
+  // device has stored their number to hscal[S_DONE]), when and by which thread the last one was
+  // called, and its stream: read by the other contexts of the device (may_sweep)
+  std::atomic<uint64_t> op_issued{0}, op_ended{0}, op_thread{0};
+  std::atomic<int64_t> op_time{0};
+  std::atomic<void*> op_stream{nullptr};
+  bl::Done op_done;                 // where the last kernel of an enqueued operation reports
   // transport launch shapes chosen for this grid shape (Geo::zv)
   bool tuned = false;
+  bool shapes_fixed = false;   // by BL_LAUNCH_SHAPES or BL_TRANSPORT_ZV: the step launches run
   // state of the last velocity
   bool have_v = false;
   bool have_lambda = false;   // L holds the adjoint lambda^n of the current velocity
@@ -136,6 +152,9 @@ struct bl_ctx {
 namespace bl {
 namespace host {
 
+// device bytes of the sweeps' synchronisation words (forward and backward)
+constexpr size_t kSweepBytes = 2 * (size_t)kSweepWords * sizeof(uint32_t);
+
 // Device bytes of a context (transport fields, solver vectors, mixed-precision tables).
 size_t ctx_bytes(const Geo& g, bool transport, bool solver, bool mixed);
 // A context on the current device.  With arena != nullptr the caller provides (and keeps
@@ -147,6 +166,20 @@ bl_ctx* create_ctx(const bl_problem* prob, const Geo& g, bool transport, bool so
                    void* arena = nullptr, size_t arena_bytes = 0, hipStream_t stream = nullptr,
                    double* host_scalars = nullptr, bool host_mirror = true);
 void destroy_ctx(bl_ctx* c);
+// An operation on a context from its construction to its destruction, or, where `enqueued` was
+// called, until its last kernel reports.  Sweeps are used inside operations only.
+struct Operation {
+  bl_ctx* c;
+  uint64_t id;
+  bool ended_by_device = false;
+  explicit Operation(bl_ctx* c);
+  ~Operation();
+  // the caller leaves without waiting: report() before the operation's launches lets its last
+  // kernel report its end through c->op_done; enqueued() after them (publish: by a launch of
+  // its own, where the last kernel does not)
+  void report();
+  void enqueued(bool publish);
+};
 // owns a context until the end of a scope
 struct CtxHolder {
   bl_ctx* c = nullptr;

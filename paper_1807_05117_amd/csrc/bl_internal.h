@@ -214,9 +214,10 @@ void pi_z_mixed(const Geo& g, const DftPlan& p, const float* f, int C, float2* G
 // with_div: out[dim] = spectral divergence.
 // reg_partial (may be null): kRedBlocks partial sums of reg_weight * sum_c Lhat |out_c|^2,
 // added to the partials already there when reg_accumulate (one velocity per time node).
+// zero (may be null): nzero words set to zero by the same launch (a sweep's synchronisation words)
 void band_prep(const Geo& g, const float2* raw, float2* out, int with_div, const double* Lhat64,
                double* reg_partial, hipStream_t s, double reg_weight = 1.0,
-               int reg_accumulate = 0);
+               int reg_accumulate = 0, uint32_t* zero = nullptr, int nzero = 0);
 // the plain projection (no divergence, no regulariser sum) of `nodes` band vectors spaced
 // `stride` complex entries apart, in one launch
 void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, size_t stride,
@@ -227,10 +228,15 @@ void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, si
 // Re sum conj(dotp) out over all C components (each thread sums its band index's components in
 // order, then its block in the fixed order of block_reduce_256); with sq_part and max_part not
 // NULL likewise the partials of sum |out|^2 and of max |out|.
+// Given `done`, the launch also reports itself there (done.word = done.value, host memory).
+struct Done {
+  uint64_t* word = nullptr;
+  uint64_t value = 0;
+};
 void band_finalize(const Geo& g, int C, const float2* vproj, const float* Lhat,
                    const float2* P, float scale, float2* out, int* nonfinite, hipStream_t s,
                    int leray = 0, const float2* dotp = nullptr, double* dot_part = nullptr,
-                   double* sq_part = nullptr, double* max_part = nullptr);
+                   double* sq_part = nullptr, double* max_part = nullptr, Done done = {});
 // blocks of a band_finalize launch (at most kRedBlocks)
 int finalize_blocks(const Geo& g);
 // band_finalize of `nodes` vectors in one launch: node n reads vproj + n vstride and
@@ -238,7 +244,7 @@ int finalize_blocks(const Geo& g);
 void band_finalize_nodes(const Geo& g, int C, const float2* vproj, size_t vstride,
                          const float* Lhat, const float2* P, size_t pstride, float scale,
                          float2* out, size_t ostride, int nodes, int* nonfinite, hipStream_t s,
-                         int leray = 0);
+                         int leray = 0, Done done = {});
 
 // ---- transports (bl_transport.hip)
 // X: dim planes of forward offsets; YA = (Y, a) backward offsets and reaction factor
@@ -283,6 +289,42 @@ void body_force_n(const Geo& g, const float* dlam, const float* m, const float* 
                   const float* dm, float* b, hipStream_t s);
 // one component of packed float4 voxels into a plane
 void unpack4(const Geo& g, int comp, const float4* in, float* plane, hipStream_t s);
+
+// ---- whole sweeps in one launch (bl_sweep.hip), stationary velocity, single problem
+enum { SWEEP_STATE = 0, SWEEP_INC, SWEEP_ADJ };
+constexpr int kSweepTiles = 256;                    // most tiles of a sweep
+constexpr int kSweepWords = 320 + kSweepTiles * 16; // synchronisation words of a sweep, zero before it
+// tiles of a sweep: ty rows of x by tz = gz * run planes, one workgroup each
+struct SweepPlan {
+  int run = 0;          // planes per thread; 0: the grid has no plan
+  int ty = 0, tz = 0, gz = 0, nty = 0, ntz = 0, tiles = 0, threads = 0;
+  int pitch = 0;        // floats of a row in LDS
+  int box_floats = 0;   // LDS floats of a tile's rows and those its taps reach
+  FastDiv div_nx, div_ty, div_ty2, div_nty, div_n4;   // by nx, ty, ty + 2, nty, 16-byte entries per row
+};
+struct SweepArgs {
+  const float* X = nullptr;      // forward offsets (state, incremental)
+  const float4* YA = nullptr;    // backward offsets and reaction factor (adjoint)
+  float* planes = nullptr;       // nt + 1 planes of the transported field
+  const float* m = nullptr;      // nt + 1 planes of the state (incremental, adjoint)
+  const float* dv = nullptr;     // dim planes (incremental)
+  float* b = nullptr;            // dim planes: body force (adjoint)
+  int keep0 = 0;                 // adjoint: lambda^0 is stored too
+  uint32_t* sync = nullptr;      // kSweepWords words, zero
+  int* nonfinite = nullptr;      // set if a wait was given up (never in a working run)
+};
+// run = 0 where the grid's tiles cannot all be resident (one per compute unit) or do not fit
+SweepPlan sweep_plan(const Geo& g, int compute_units);
+// m^{n+1} = Interp(m^n, i + X) for n = 0..nt-1 (as nt times state_step)
+void sweep_state(const Geo& g, const SweepPlan& p, const float* X, float* m, uint32_t* sync,
+                 int* nonfinite, hipStream_t s);
+// t^0..t^{nt-1} into the planes t (as inc_init, inc_step) and inc_last's value into plane nt
+void sweep_inc(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
+               float* t, uint32_t* sync, int* nonfinite, hipStream_t s);
+// lam[nt] transported down to lam[1] (keep0: lam[0]) and the body force b (as adj_step and
+// body_force)
+void sweep_adj(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, float* lam,
+               float* b, int keep0, uint32_t* sync, int* nonfinite, hipStream_t s);
 
 // ---- deformation state equation (bl_deform.hip)
 // Band fields are full centred bands of g (B entries per component); product-grid planes have
@@ -372,6 +414,8 @@ void reduce_final2(const double* pa, double* outa, double* hosta, const double* 
 // y = alpha x + y
 void axpy(float2* y, const float2* x, double alpha, int64_t n, hipStream_t s,
           const Batch& bt = Batch{});
+// done.word = done.value (host-mapped destination)
+void publish_done(Done done, hipStream_t s);
 // host_flag[0] = flag[0] (host-mapped destination)
 void publish_flag(const int* flag, double* host_flag, hipStream_t s);
 // y = 0; y = x (kernels, so that a captured graph holds no memset or copy node)

@@ -19,6 +19,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include <sys/stat.h>
@@ -157,7 +158,7 @@ int nzp_of(const bl::Geo& g) { return round_up(g.nz, 128); }
 
 struct Offsets {
   size_t I1, m, X, YA, V, DV, T0, T1, L, Bf, DM, DL, U, braw, bv, bd, bout, P, Lhat, Lhat64, tw_x, tw_xT,
-      tw_y, tw_yT, tw_zT, wi, wp, bufA, bufB, red, scal, flag, solver;
+      tw_y, tw_yT, tw_zT, wi, wp, bufA, bufB, red, scal, flag, sweep, solver;
   // deformation state equation
   size_t IG, GP, UG, VP, DVP, DUG, GW, KG, GACC, DUb, US, ACC, KAP, RHO, ASUM, KSUM, PH, ptw_x,
       ptw_xT, ptw_y, ptw_yT, ptw_zT, pbufA, pbufB;
@@ -179,6 +180,9 @@ bl::Geo product_geo(const bl::Geo& g) {
   p.stream_out = 0;   // no transport runs on the product grid
   return p;
 }
+
+// stationary state-equation contexts may run whole sweeps in one launch
+bool sweeps_possible(const bl::Geo& g) { return !g.deform && g.nodes == 1; }
 
 Offsets plan_layout(const bl::Geo& g, bool transport, bool solver, bool mixed) {
   Layout L;
@@ -263,6 +267,7 @@ Offsets plan_layout(const bl::Geo& g, bool transport, bool solver, bool mixed) {
   o.red = L.take((size_t)RED_SLOTS * bl::kRedBlocks * sizeof(double));
   o.scal = L.take(64 * sizeof(double));
   o.flag = L.take(256);
+  if (transport && sweeps_possible(g)) o.sweep = L.take(kSweepBytes);
   o.solver = solver ? L.take(bb * vb * 8) : 0;
   o.total = L.total;
   return o;
@@ -350,8 +355,81 @@ double* alloc_host_scalars() {
   return h;
 }
 
+// ------------------------------------------------------------------ operations and sweeps
+// A sweep's workgroups wait for each other and want the whole device (bl_sweep.hip): beside
+// another stream's kernels they become resident late or not at all, and what is then finished
+// through tickets is several times slower than the step launches (two threads' gradients at
+// 128^3: 1,500 per second through tickets, 3,000 as steps).  So an operation uses sweeps only if
+// no context of another stream of this process has work in flight on the device, or had some
+// called by another thread within the last millisecond (two threads that call in turn would
+// otherwise both find the device free now and then).  This is a matter of speed alone: the
+// results are the same, and sweeps that meet other work all the same end without it.
+std::mutex g_live_mu;
+std::vector<bl_ctx*> g_live;   // transport contexts of the process
+constexpr int64_t kQuietNs = 1000000;
+
+int64_t now_ns() {
+  return std::chrono::duration_cast<std::chrono::nanoseconds>(
+             std::chrono::steady_clock::now().time_since_epoch()).count();
+}
+uint64_t thread_key() { return (uint64_t)std::hash<std::thread::id>()(std::this_thread::get_id()); }
+
+uint64_t ops_done(const bl_ctx* c) {
+  uint64_t d = c->op_ended.load(std::memory_order_relaxed);
+  if (c->hscal)
+    d = std::max(d, __atomic_load_n(reinterpret_cast<const uint64_t*>(c->hscal + S_DONE), __ATOMIC_RELAXED));
+  return d;
+}
+
+bool may_sweep(const bl_ctx* c, int64_t now, uint64_t me) {
+  std::lock_guard<std::mutex> lk(g_live_mu);
+  for (const bl_ctx* o : g_live) {
+    if (o == c || o->device != c->device || o->op_issued.load(std::memory_order_relaxed) == 0) continue;
+    if (o->op_stream.load(std::memory_order_relaxed) == (void*)c->stream) continue;
+    if (ops_done(o) < o->op_issued.load(std::memory_order_relaxed)) return false;
+    if (o->op_thread.load(std::memory_order_relaxed) != me &&
+        now - o->op_time.load(std::memory_order_relaxed) < kQuietNs)
+      return false;
+  }
+  return true;
+}
+
+Operation::Operation(bl_ctx* ctx) : c(ctx), id(ctx->op_issued.load(std::memory_order_relaxed) + 1) {
+  const int64_t now = now_ns();
+  const uint64_t me = thread_key();
+  c->op_stream.store((void*)c->stream, std::memory_order_relaxed);
+  c->op_thread.store(me, std::memory_order_relaxed);
+  c->op_time.store(now, std::memory_order_relaxed);
+  c->op_issued.store(id, std::memory_order_relaxed);
+  // what a caller captures runs later, beside work that is not known now: steps
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (c->devptr && hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+  c->sweeps_allowed = cap == hipStreamCaptureStatusNone;
+}
+
+void Operation::report() {
+  if (c->sweeps_allowed && c->hdev) c->op_done = {reinterpret_cast<uint64_t*>(c->hdev + S_DONE), id};
+}
+
+void Operation::enqueued(bool publish) {
+  if (!c->op_done.word) return;   // captured, or no host-mapped word: taken to have ended
+  if (publish) bl::publish_done(c->op_done, c->stream);
+  ended_by_device = true;
+}
+
+Operation::~Operation() {
+  c->op_done = {};
+  c->sweeps_allowed = c->sweep_now = false;
+  c->op_time.store(now_ns(), std::memory_order_relaxed);
+  if (!ended_by_device) c->op_ended.store(id, std::memory_order_relaxed);
+}
+
 void destroy_ctx(bl_ctx* c) {
   if (!c) return;
+  {
+    std::lock_guard<std::mutex> lk(g_live_mu);
+    g_live.erase(std::remove(g_live.begin(), g_live.end(), c), g_live.end());
+  }
   // best-effort teardown: errors here have nowhere to go
   (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
@@ -446,6 +524,12 @@ bl_ctx* create_ctx(const bl_problem* prob, const bl::Geo& g, bool transport, boo
     c->red = reinterpret_cast<double*>(a + o.red);
     c->scal = reinterpret_cast<double*>(a + o.scal);
     c->flag = reinterpret_cast<int*>(a + o.flag);
+    if (transport && sweeps_possible(g)) {
+      c->sweep_sync = reinterpret_cast<uint32_t*>(a + o.sweep);
+      int cus = 0;
+      HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+      c->sweep = bl::sweep_plan(g, cus);
+    }
     if (solver) {
       float2* s = C2(o.solver);
       const size_t nb = (size_t)g.nodes * g.dim * g.B;
@@ -513,6 +597,10 @@ bl_ctx* create_ctx(const bl_problem* prob, const bl::Geo& g, bool transport, boo
     HIP_TRY(hipMemsetAsync(c->flag, 0, 256, c->stream));
     if (c->DM) HIP_TRY(hipMemsetAsync(c->DM, 0, plane_bytes(g), c->stream));   // dm^0 = 0
     HIP_TRY(hipStreamSynchronize(c->stream));
+    if (transport) {
+      std::lock_guard<std::mutex> lk(g_live_mu);
+      g_live.push_back(c);
+    }
   } catch (...) {
     destroy_ctx(c);
     throw;
@@ -710,6 +798,7 @@ void choose_launch_shapes(bl_ctx* c) {
   // BL_LAUNCH_SHAPES = "s0,...,s6" fixes every class (tests of the shapes' equivalence);
   // an invalid list keeps the defaults
   if (const char* all = std::getenv("BL_LAUNCH_SHAPES")) {
+    c->shapes_fixed = true;
     int v[bl::TR_CLASSES], n = 0, off = 0;
     const char* q = all;
     while (n < bl::TR_CLASSES && std::sscanf(q, "%d%n", &v[n], &off) == 1) {
@@ -723,6 +812,7 @@ void choose_launch_shapes(bl_ctx* c) {
   }
   const char* env = std::getenv("BL_TRANSPORT_ZV");
   if (env && *env) {
+    c->shapes_fixed = true;
     const int v = std::atoi(env);
     if (v == 1 || v == 2 || v == 4 || v == 8)
       for (int k = 0; k <= bl::TR_SETUP; ++k) g.zv[k] = v;
@@ -1067,6 +1157,33 @@ double* publish(bl_ctx* c, int slot) {
   return (c->g.bat.count > 1 || !c->hdev) ? nullptr : c->hdev + slot;
 }
 
+// Whole sweeps in one launch: single problems with a plan.  A batched launch (one tile per
+// compute unit is one problem's), a fixed launch shape (it names the step launches) and
+// per-kernel timing (it times them) take the steps one by one; both give the same values.
+bool use_sweeps(const bl_ctx* c) {
+  return c->sweep_now && c->sweep.run > 0 && c->g.bat.count == 1 && c->g.bat.gate == nullptr && !c->timing &&
+         !c->shapes_fixed;
+}
+
+// the zeroed words of the forward (0) or backward (1) sweep
+uint32_t* sweep_words(bl_ctx* c, int which) {
+  uint32_t* w = c->sweep_sync + (size_t)which * bl::kSweepWords;
+  if (!c->sweep_clean[which])
+    bl::zero_band(reinterpret_cast<float2*>(w), bl::kSweepWords / 2, c->stream);
+  c->sweep_clean[which] = false;
+  return w;
+}
+
+// band_prep of a stationary velocity or direction; zeroes the sweeps' words in the same launch
+void prep_and_clean(bl_ctx* c, const float2* raw, float2* out, int with_div, const double* Lhat64,
+                    double* red_reg) {
+  c->sweep_now = c->sweeps_allowed && c->sweep.run > 0 && may_sweep(c, now_ns(), thread_key());
+  const bool z = use_sweeps(c);
+  bl::band_prep(c->g, raw, out, with_div, Lhat64, red_reg, c->stream, 1.0, 0,
+                z ? c->sweep_sync : nullptr, z ? 2 * bl::kSweepWords : 0);
+  if (z) c->sweep_clean[0] = c->sweep_clean[1] = true;
+}
+
 // setup + forward state + energy sums at the raw band vector `vraw` (stationary state
 // equation), enqueued only: the regulariser and data sums land in scal[S_REG], scal[S_DATA]
 void enqueue_set_velocity(bl_ctx* c, const float2* vraw) {
@@ -1074,13 +1191,16 @@ void enqueue_set_velocity(bl_ctx* c, const float2* vraw) {
   hipStream_t s = c->stream;
   double* red_reg = c->red + RED_REG * bl::kRedBlocks;
   double* red_data = c->red + RED_DATA * bl::kRedBlocks;
-  bl::band_prep(g, vraw, c->bv, 1, c->Lhat64, red_reg, s);
+  prep_and_clean(c, vraw, c->bv, 1, c->Lhat64, red_reg);
   bl::iota(g, c->plan, c->bv, g.dim + 1, c->V, s);
   timed(c, 6, [&] { bl::setup(g, c->V, c->X, c->YA, s); });
   if (!c->tuned) choose_launch_shapes(c);
   const size_t M = (size_t)g.M;
-  for (int n = 0; n < g.nt; ++n)
-    timed(c, 0, [&] { bl::state_step(g, c->m + n * M, c->X, c->m + (n + 1) * M, s); });
+  if (use_sweeps(c))
+    bl::sweep_state(g, c->sweep, c->X, c->m, sweep_words(c, 0), c->flag, s);
+  else
+    for (int n = 0; n < g.nt; ++n)
+      timed(c, 0, [&] { bl::state_step(g, c->m + n * M, c->X, c->m + (n + 1) * M, s); });
   // the energy's data term and, in the same pass, the terminal adjoint lambda^Nt into L[nt]
   bl::energy_partial(g, c->m + g.nt * M, c->I1, red_data, s, c->L + g.nt * M);
   c->lamT_valid = true;
@@ -1153,6 +1273,10 @@ void backward_and_body_force(bl_ctx* c) {
   const bl::Geo& g = c->g;
   hipStream_t s = c->stream;
   const size_t M = (size_t)g.M;
+  if (use_sweeps(c)) {
+    bl::sweep_adj(g, c->sweep, c->YA, c->m, c->L, c->Bf, g.newton, sweep_words(c, 1), c->flag, s);
+    return;
+  }
   const bool form0 = body_forms_lambda0(g);
   for (int n = g.nt - 1; n >= (form0 ? 1 : 0); --n)
     timed(c, 2, [&] { bl::adj_step(g, c->L + (n + 1) * M, c->YA, c->L + n * M, s); });
@@ -1217,7 +1341,7 @@ void op_hessvec_newton(bl_ctx* c, const float2* draw, float2* hout, double* dot_
   bl::body_force_n(g, c->DL, c->m, c->L, c->DM, c->Bf, s);
   bl::pi_half(g, c->plan, c->Bf, g.dim, c->P, s);
   bl::band_finalize(g, g.dim, c->bd, c->Lhat, c->P, (float)(1.0 / (double)g.M), hout, c->flag, s,
-                    1, draw, dot_part);
+                    1, draw, dot_part, nullptr, nullptr, c->op_done);
   check_launch("hessvec (Newton)");
 }
 
@@ -1238,23 +1362,28 @@ bool op_hessvec(bl_ctx* c, const float2* draw, float2* hout, double* dot_part) {
   const bl::Geo& g = c->g;
   hipStream_t s = c->stream;
   const size_t M = (size_t)g.M;
-  bl::band_prep(g, draw, c->bd, 0, nullptr, nullptr, s);
+  prep_and_clean(c, draw, c->bd, 0, nullptr, nullptr);
   bl::iota_xy(g, c->plan, c->bd, g.dim, s);
   timed(c, 3, [&] { bl::iota_z(g, c->plan, g.dim, c->DV, s); });
-  bl::inc_init(g, c->m, c->DV, c->T0, s);
-  float* tin = c->T0;
-  float* tout = c->T1;
-  for (int n = 0; n + 1 < g.nt; ++n) {
-    timed(c, 1, [&] { bl::inc_step(g, tin, c->X, c->m + (n + 1) * M, c->DV, tout, s); });
-    std::swap(tin, tout);
+  if (use_sweeps(c)) {
+    // t^n into the planes that the backward sweep overwrites
+    bl::sweep_inc(g, c->sweep, c->X, c->m, c->DV, c->L, sweep_words(c, 0), c->flag, s);
+  } else {
+    bl::inc_init(g, c->m, c->DV, c->T0, s);
+    float* tin = c->T0;
+    float* tout = c->T1;
+    for (int n = 0; n + 1 < g.nt; ++n) {
+      timed(c, 1, [&] { bl::inc_step(g, tin, c->X, c->m + (n + 1) * M, c->DV, tout, s); });
+      std::swap(tin, tout);
+    }
+    bl::inc_last(g, tin, c->X, c->m + g.nt * M, c->DV, c->L + g.nt * M, s);
   }
-  bl::inc_last(g, tin, c->X, c->m + g.nt * M, c->DV, c->L + g.nt * M, s);
   c->lamT_valid = false;   // L[nt] holds the incremental terminal adjoint now
   backward_and_body_force(c);
   timed(c, 4, [&] { bl::pi_z(g, c->plan, c->Bf, g.dim, s); });
   bl::pi_yx(g, c->plan, g.dim, c->P, s);
   bl::band_finalize(g, g.dim, c->bd, c->Lhat, c->P, (float)(1.0 / (double)g.M), hout, c->flag, s,
-                    1, draw, dot_part);
+                    1, draw, dot_part, nullptr, nullptr, c->op_done);
   check_launch("hessvec");
   return dot_part != nullptr;
 }
@@ -1643,6 +1772,7 @@ int bl_lddmm_ctx_set_velocity(bl_ctx* c, const float* v_hat, double* energy, flo
   if (!c || !v_hat) return fail(BL_E_INVALID, "NULL pointer argument");
   return guarded([&]() {
     HIP_TRY(hipSetDevice(c->device));
+    Operation op(c);
     load_band(c, v_hat, c->braw, c->g.nodes * c->g.dim);
     if (g_hat && !c->g.deform && c->g.nodes == 1) {
       op_energy_gradient(c, c->braw, c->bout,
@@ -1669,8 +1799,11 @@ int bl_lddmm_ctx_hessvec(bl_ctx* c, const float* dv_hat, float* hv_hat) {
   if (!c->have_v) return fail(BL_E_INVALID, "no velocity set on this context");
   return guarded([&]() {
     HIP_TRY(hipSetDevice(c->device));
+    Operation op(c);
     if (c->devptr) {
+      op.report();
       op_hessvec(c, reinterpret_cast<const float2*>(dv_hat), reinterpret_cast<float2*>(hv_hat));
+      op.enqueued(c->g.deform || c->g.nodes > 1);
       return BL_OK;
     }
     load_band(c, dv_hat, c->braw, c->g.nodes * c->g.dim);
@@ -1728,6 +1861,7 @@ int bl_lddmm_gradient(const bl_problem* prob, const float* I0, const float* I1,
   if (!I0 || !I1 || !v_hat || !g_hat) return fail(BL_E_INVALID, "NULL pointer argument");
   return guarded([&]() {
     CachedCtx h(prob, g, false);
+    Operation op(h.c);
     load_images(h.c, I0, I1);
     load_band(h.c, v_hat, h.c->braw, g.nodes * g.dim);
     if (!g.deform && g.nodes == 1) {
@@ -1753,6 +1887,7 @@ int bl_lddmm_hessvec(const bl_problem* prob, const float* I0, const float* I1,
   if (!I0 || !I1 || !v_hat || !dv_hat || !hv_hat) return fail(BL_E_INVALID, "NULL pointer argument");
   return guarded([&]() {
     CachedCtx h(prob, g, false);
+    Operation op(h.c);
     load_images(h.c, I0, I1);
     load_band(h.c, v_hat, h.c->braw, g.nodes * g.dim);
     op_set_velocity(h.c, h.c->braw);
@@ -1772,6 +1907,7 @@ int bl_lddmm_warp(const bl_problem* prob, const float* I0, const float* v_hat, f
   if (!I0 || !v_hat || !warped) return fail(BL_E_INVALID, "NULL pointer argument");
   return guarded([&]() {
     CachedCtx h(prob, g, false);
+    Operation op(h.c);
     load_images(h.c, I0, nullptr);
     load_band(h.c, v_hat, h.c->braw, g.nodes * g.dim);
     op_set_velocity(h.c, h.c->braw);
@@ -1796,6 +1932,7 @@ int bl_lddmm_register(const bl_problem* prob, const bl_solver_opts* opts, const 
     bl_stats local;
     std::memset(&local, 0, sizeof(local));
     CachedCtx h(prob, g, true);
+    Operation op(h.c);
     load_images(h.c, I0, I1);
     load_band(h.c, v_hat, h.c->sv, g.nodes * g.dim);
     solve(h.c, o, &local);

@@ -21,7 +21,7 @@ using namespace bl::host;
 constexpr size_t kScratchBytes = size_t(512) << 20;   // 512 MiB per device
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kSweepBytes];
 
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -51,7 +51,8 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
   if (g.deform || g.nodes > 1)
     return fail(BL_E_UNSUPPORTED, "the allocation-free product serves the stationary "
                                   "state-equation model (no BL_NONSTATIONARY, BL_DEFORMATION)");
-  const size_t need = ctx_bytes(g, true, false, prob->precision == BL_MIXED);
+  // the sweeps' words have their own room beside the limit
+  const size_t need = ctx_bytes(g, true, false, prob->precision == BL_MIXED) - kSweepBytes;
   if (need > kScratchBytes)
     return fail(BL_E_NOMEM, "problem needs " + std::to_string(need) + " bytes of scratch; the "
                             "allocation-free product is limited to " +
@@ -64,8 +65,9 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     const bool devptr = (prob->flags & BL_DEVICE_PTRS) != 0;
     hipStream_t s = devptr ? (hipStream_t)prob->stream : nullptr;
     CtxHolder h;
-    h.c = create_ctx(prob, g, true, false, arena, kScratchBytes, s, nullptr, false);
+    h.c = create_ctx(prob, g, true, false, arena, kScratchBytes + kSweepBytes, s, nullptr, false);
     bl_ctx* c = h.c;
+    Operation op(c);
     apply_known_launch_shapes(c);
     load_images(c, I0, I1);
     load_band(c, v_hat, c->braw, g.dim);

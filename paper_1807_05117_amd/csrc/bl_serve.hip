@@ -140,6 +140,7 @@ void run_request(bl_server* srv, Slot& slot, int slot_index, Request* r) {
         }
       }
     } guard{slot};
+    Operation op(c);
     load_images(c, r->I0.data(), r->I1.data());
     load_band(c, r->v.data(), c->sv, r->g.nodes * r->g.dim);
     std::memset(&r->stats, 0, sizeof(r->stats));
