@@ -276,6 +276,19 @@ __device__ __forceinline__ void gather_zv(const Geo& g, Rsrc f, const Tap (&t)[Z
   }
 }
 
+// d-linear interpolation from the eight (four) corner values, as the step launches form it
+template <int DIM>
+__device__ __forceinline__ float blend(const float (&v)[8], float wx, float wy, float wz) {
+  const float ra = fmaf(wx, v[1] - v[0], v[0]);
+  const float rb = fmaf(wx, v[3] - v[2], v[2]);
+  if constexpr (DIM == 2) return fmaf(wz, rb - ra, ra);
+  const float pa = fmaf(wy, rb - ra, ra);
+  const float rc = fmaf(wx, v[5] - v[4], v[4]);
+  const float rd = fmaf(wx, v[7] - v[6], v[6]);
+  const float pb = fmaf(wy, rd - rc, rc);
+  return fmaf(wz, pb - pa, pa);
+}
+
 // X offsets of the thread's voxels (dim planes at X) as taps
 template <int DIM, int ZV>
 __device__ __forceinline__ void taps_x(const Geo& g, const Col& t, const float* X, Tap (&tp)[ZV]) {
@@ -328,6 +341,110 @@ __device__ __forceinline__ void store_zv(const Geo& g, const Col& t, float* out,
     else
       __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)t.c, (int)zo, 0);
   }
+}
+
+// ---------------------------------------------------------------------------------- setup
+// Departure offsets X, Y and the reaction factor a at the thread's ZV voxels, with the gathers
+// from global memory; v: dim planes of the velocity, then r.
+template <int DIM, int ZV>
+__device__ __forceinline__ void setup_voxels(const Geo& g, const Col& t, const float* __restrict__ v,
+                                             float* __restrict__ X, float4* __restrict__ YA) {
+  const size_t M = (size_t)g.M;
+  const float s = g.dt * (float)g.nref;
+  // the ZV voxels of the thread are computed first and stored afterwards (their gathers can
+  // all be in flight)
+  float u[3][ZV], nu[3][ZV];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const Rsrc vc = field_rsrc(v + (c < DIM ? c : 0) * M, g);
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) {
+      VOXEL(zz)
+      u[c][zz] = c < DIM ? s * ld(vc, t.c, zo) : 0.f;
+      nu[c][zz] = -u[c][zz];
+    }
+  }
+  Tap tf[ZV], tb[ZV];
+  make_taps<DIM, ZV>(g, t, nu[0], nu[1], nu[2], tf);   // X = -(u + Interp(u, i - u)) / 2
+  make_taps<DIM, ZV>(g, t, u[0], u[1], u[2], tb);      // Y = +(u + Interp(u, i + u)) / 2
+  float xo[3][ZV], yo[3][ZV], av[ZV];
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) xo[2][zz] = yo[2][zz] = 0.f;
+#pragma unroll
+  for (int c = 0; c < DIM; ++c) {
+    const Rsrc vc = field_rsrc(v + c * M, g);
+    float gf[ZV], gb[ZV];
+    gather_zv<DIM, ZV>(g, vc, tf, gf);
+    gather_zv<DIM, ZV>(g, vc, tb, gb);
+#pragma unroll
+    for (int zz = 0; zz < ZV; ++zz) {
+      xo[c][zz] = -0.5f * (u[c][zz] + s * gf[zz]);
+      yo[c][zz] = 0.5f * (u[c][zz] + s * gb[zz]);
+    }
+  }
+  // reaction factor of the adjoint along the backward characteristic (Heun)
+  const Rsrc rr = field_rsrc(v + DIM * M, g);
+  Tap ty[ZV];
+  make_taps<DIM, ZV>(g, t, yo[0], yo[1], yo[2], ty);
+  float R[ZV];
+  gather_zv<DIM, ZV>(g, rr, ty, R);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    const float ri = ld(rr, t.c, zo);
+    av[zz] = 1.0f + 0.5f * g.dt * (R[zz] + (1.0f + g.dt * R[zz]) * ri);
+  }
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    if (!live) continue;
+    for (int c = 0; c < DIM; ++c) st(field_rsrc(X + c * M, g), t.c, zo, xo[c][zz]);
+    st_ya(g, YA, z, t, make_float4(yo[0][zz], yo[1][zz], yo[2][zz], av[zz]));
+  }
+}
+
+// Non-stationary step t_n -> t_{n+1}: the Heun characteristics take the velocity at both
+// ends of the step: X = -(u1 + Interp(u0, i - u1)) / 2 (end point i at t_{n+1}),
+// Y = +(u0 + Interp(u1, i + u0)) / 2 (start point i at t_n), R = Interp(r1, i + Y),
+// a = 1 + dt/2 [R + (1 + dt R) r0].  With v0 = v1 these are the stationary formulas.
+// (v1 follows v0, dim + 1 planes per node)
+template <int DIM>
+__device__ __forceinline__ void setup_voxel_ns(const Geo& g, const Col& t, const float* __restrict__ v0,
+                                               float* __restrict__ X, float4* __restrict__ YA) {
+  constexpr int ZV = 1;
+  VOXEL(0)
+  const size_t M = (size_t)g.M;
+  const float* __restrict__ v1 = v0 + (DIM + 1) * M;
+  const float s = g.dt * (float)g.nref;
+  float u0[3][1] = {{0.f}, {0.f}, {0.f}}, u1[3] = {0.f, 0.f, 0.f}, nu1[3][1];
+#pragma unroll
+  for (int c = 0; c < DIM; ++c) {
+    u0[c][0] = s * ld(field_rsrc(v0 + c * M, g), t.c, zo);
+    u1[c] = s * ld(field_rsrc(v1 + c * M, g), t.c, zo);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) nu1[c][0] = -u1[c];
+  Tap tf[1], tb[1];
+  make_taps<DIM, 1>(g, t, nu1[0], nu1[1], nu1[2], tf);
+  make_taps<DIM, 1>(g, t, u0[0], u0[1], u0[2], tb);
+  float xo[3] = {0.f, 0.f, 0.f}, yo[3][1] = {{0.f}, {0.f}, {0.f}};
+#pragma unroll
+  for (int c = 0; c < DIM; ++c) {
+    float gf[1], gb[1];
+    gather_zv<DIM, 1>(g, field_rsrc(v0 + c * M, g), tf, gf);
+    gather_zv<DIM, 1>(g, field_rsrc(v1 + c * M, g), tb, gb);
+    xo[c] = -0.5f * (u1[c] + s * gf[0]);
+    yo[c][0] = 0.5f * (u0[c][0] + s * gb[0]);
+  }
+  Tap ty[1];
+  make_taps<DIM, 1>(g, t, yo[0], yo[1], yo[2], ty);
+  const float ri = ld(field_rsrc(v0 + DIM * M, g), t.c, zo);
+  float Rv[1];
+  gather_zv<DIM, 1>(g, field_rsrc(v1 + DIM * M, g), ty, Rv);
+  const float R = Rv[0];
+  const float a = 1.0f + 0.5f * g.dt * (R + (1.0f + g.dt * R) * ri);
+  for (int c = 0; c < DIM; ++c) st(field_rsrc(X + c * M, g), t.c, zo, xo[c]);
+  st_ya(g, YA, z, t, make_float4(yo[0][0], yo[1][0], yo[2][0], a));
 }
 
 // ------------------------------------------------------------------------------- stencils

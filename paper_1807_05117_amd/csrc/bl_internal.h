@@ -290,6 +290,15 @@ void body_force_n(const Geo& g, const float* dlam, const float* m, const float* 
 // one component of packed float4 voxels into a plane
 void unpack4(const Geo& g, int comp, const float4* in, float* plane, hipStream_t s);
 
+// ---- setup of 3D grids from LDS (bl_box.hip): tiles of sw x 8 x 4 voxels, one
+// workgroup each
+struct BoxPlan {
+  int sw = 0, ntx = 0, nty = 0, tiles = 0;
+  FastDiv div_ntx, div_nty, div_sw;
+};
+void setup_box(const Geo& g, const float* v, float* X, float4* YA, hipStream_t s);
+void setup_box_ns(const Geo& g, const float* V, float* X, float4* YA, int steps, hipStream_t s);
+
 // ---- whole sweeps in one launch (bl_sweep.hip), stationary velocity, single problem
 enum { SWEEP_STATE = 0, SWEEP_INC, SWEEP_ADJ };
 constexpr int kSweepTiles = 256;                    // most tiles of a sweep

@@ -101,7 +101,12 @@ int validate(const bl_problem* p, bl::Geo* g) {
     g->zv[bl::TR_INC] = d3 ? 2 : 1;
     g->zv[bl::TR_ADJ] = d3 ? 2 : 1;
     g->zv[bl::TR_FORCE] = d3 ? 2 : 1;
-    g->zv[bl::TR_SETUP] = 1;
+    // the setup's neighbourhoods in LDS (4) take tiles of 64 x 8 x 4 voxels; fewer than two per
+    // compute unit are slower than gathers from global memory (64^3: 12.8 against 9.8 us; 96^3,
+    // 576 tiles: 19.6 against 22.9)
+    const int64_t tiles = (int64_t)((n[0] + 63) / 64) * ((n[1] + 7) / 8) * ((n[2] + 3) / 4) *
+                          ((p->flags & BL_NONSTATIONARY) ? p->nt : 1);
+    g->zv[bl::TR_SETUP] = d3 && tiles >= 512 ? 4 : 1;
     g->zv[bl::TR_IOTA_Z] = 1;
     g->zv[bl::TR_IOTA_XY] = 0;
     g->zv[bl::TR_CLASSES] = 0;
@@ -688,7 +693,7 @@ void t_collect(bl_ctx* c) {
 // (T0, T1, Bf, DV, X, YA with the same values, the transform buffers) are work space that every
 // operation rewrites before use.  Choices are kept per (GPU architecture, grid, band,
 // precision) for the process and in a cache file -- BL_TUNE_CACHE, else
-// $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v3.txt or ~/.cache/bl_lddmm/launch_shapes_v3.txt -- read at
+// $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v4.txt or ~/.cache/bl_lddmm/launch_shapes_v3.txt -- read at
 // the first tuning and appended to after each new choice, so later processes skip the timing.
 // BL_TUNE_CACHE=off disables the file; BL_TRANSPORT_ZV = 1, 2, 4 or 8 fixes the transports'
 // and the setup's voxels per thread and skips the timing, BL_LAUNCH_SHAPES fixes every class.
@@ -700,9 +705,9 @@ std::string tune_cache_path() {
   const char* e = std::getenv("BL_TUNE_CACHE");
   if (e && *e) return std::string(e) == "off" ? std::string() : std::string(e);
   if (const char* x = std::getenv("XDG_CACHE_HOME"))
-    if (*x) return std::string(x) + "/bl_lddmm/launch_shapes_v3.txt";
+    if (*x) return std::string(x) + "/bl_lddmm/launch_shapes_v4.txt";
   if (const char* h = std::getenv("HOME"))
-    if (*h) return std::string(h) + "/.cache/bl_lddmm/launch_shapes_v3.txt";
+    if (*h) return std::string(h) + "/.cache/bl_lddmm/launch_shapes_v4.txt";
   return std::string();
 }
 
@@ -846,9 +851,9 @@ void choose_launch_shapes(bl_ctx* c) {
   };
   auto candidates = [&](int cls) -> std::vector<int> {
     switch (cls) {
-      // (a non-stationary velocity has per-step offsets from its own setup kernel: the
+      // (a non-stationary velocity has per-step offsets from a launch of its own: the
       // stationary setup is not timed on its fields)
-      case bl::TR_SETUP: return g.nodes > 1 ? std::vector<int>{} : std::vector<int>{1, 2, 4};
+      case bl::TR_SETUP: return g.nodes > 1 ? std::vector<int>{} : std::vector<int>{1, 4};
       case bl::TR_IOTA_Z: return c->plan.mixed ? std::vector<int>{} : std::vector<int>{1, 2, 4};
       // the fused iota x/y kernel times faster alone than the two stages (15.0 against
       // 17.4 us per launch at 128^3) but runs slower inside products and registrations (25 us

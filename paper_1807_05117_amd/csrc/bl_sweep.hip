@@ -146,19 +146,6 @@ __device__ __forceinline__ float load_factor(const Geo& g, const Rows<DIM>& rw, 
   return ld(ya_rsrc(a, g), (t.c + rw.at(z)) * 4u + 12u, 0);
 }
 
-// d-linear interpolation from the eight (four) corner values, as the step launches form it
-template <int DIM>
-__device__ __forceinline__ float blend(const float (&v)[8], float wx, float wy, float wz) {
-  const float ra = fmaf(wx, v[1] - v[0], v[0]);
-  const float rb = fmaf(wx, v[3] - v[2], v[2]);
-  if constexpr (DIM == 2) return fmaf(wz, rb - ra, ra);
-  const float pa = fmaf(wy, rb - ra, ra);
-  const float rc = fmaf(wx, v[5] - v[4], v[4]);
-  const float rd = fmaf(wx, v[7] - v[6], v[6]);
-  const float pb = fmaf(wy, rd - rc, rc);
-  return fmaf(wz, pb - pa, pa);
-}
-
 // The state's plane of the tile with one row around it in every direction, in LDS: rows of
 // `pitch` floats in the order of the tile's rows, filled by direct loads to LDS.
 struct Stencil {

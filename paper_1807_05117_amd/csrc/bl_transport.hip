@@ -34,66 +34,11 @@ __global__ __launch_bounds__(kTB) void k_setup(Geo g, const float* __restrict__ 
   BL_AT_NN(X, g.bat);
   BL_AT_NN(YA, g.bat);
   COLUMN
-  const size_t M = (size_t)g.M;
-  const float s = g.dt * (float)g.nref;
-  // the ZV voxels of the thread are computed first and stored afterwards (their gathers can
-  // all be in flight)
-  float u[3][ZV], nu[3][ZV];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const Rsrc vc = field_rsrc(v + (c < DIM ? c : 0) * M, g);
-#pragma unroll
-    for (int zz = 0; zz < ZV; ++zz) {
-      VOXEL(zz)
-      u[c][zz] = c < DIM ? s * ld(vc, t.c, zo) : 0.f;
-      nu[c][zz] = -u[c][zz];
-    }
-  }
-  Tap tf[ZV], tb[ZV];
-  make_taps<DIM, ZV>(g, t, nu[0], nu[1], nu[2], tf);   // X = -(u + Interp(u, i - u)) / 2
-  make_taps<DIM, ZV>(g, t, u[0], u[1], u[2], tb);      // Y = +(u + Interp(u, i + u)) / 2
-  float xo[3][ZV], yo[3][ZV], av[ZV];
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) xo[2][zz] = yo[2][zz] = 0.f;
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    const Rsrc vc = field_rsrc(v + c * M, g);
-    float gf[ZV], gb[ZV];
-    gather_zv<DIM, ZV>(g, vc, tf, gf);
-    gather_zv<DIM, ZV>(g, vc, tb, gb);
-#pragma unroll
-    for (int zz = 0; zz < ZV; ++zz) {
-      xo[c][zz] = -0.5f * (u[c][zz] + s * gf[zz]);
-      yo[c][zz] = 0.5f * (u[c][zz] + s * gb[zz]);
-    }
-  }
-  // reaction factor of the adjoint along the backward characteristic (Heun)
-  const Rsrc rr = field_rsrc(v + DIM * M, g);
-  Tap ty[ZV];
-  make_taps<DIM, ZV>(g, t, yo[0], yo[1], yo[2], ty);
-  float R[ZV];
-  gather_zv<DIM, ZV>(g, rr, ty, R);
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    VOXEL(zz)
-    const float ri = ld(rr, t.c, zo);
-    av[zz] = 1.0f + 0.5f * g.dt * (R[zz] + (1.0f + g.dt * R[zz]) * ri);
-  }
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    VOXEL(zz)
-    if (!live) continue;
-    for (int c = 0; c < DIM; ++c) st(field_rsrc(X + c * M, g), t.c, zo, xo[c][zz]);
-    st_ya(g, YA, z, t, make_float4(yo[0][zz], yo[1][zz], yo[2][zz], av[zz]));
-  }
+  setup_voxels<DIM, ZV>(g, t, v, X, YA);
 }
 
-// Non-stationary step t_n -> t_{n+1}: the Heun characteristics take the velocity at both
-// ends of the step: X = -(u1 + Interp(u0, i - u1)) / 2 (end point i at t_{n+1}),
-// Y = +(u0 + Interp(u1, i + u0)) / 2 (start point i at t_n), R = Interp(r1, i + Y),
-// a = 1 + dt/2 [R + (1 + dt R) r0].  With v0 = v1 these are the stationary formulas.
-// (every step n of the time grid in one launch: n = blockIdx.y, v0 = V[n], v1 = V[n + 1] with
-// dim + 1 planes per node, X[n], YA[n])
+// every step n of a non-stationary velocity's time grid in one launch: n = blockIdx.y, the
+// velocities V[n] and V[n + 1] (dim + 1 planes per node), X[n], YA[n]
 template <int DIM>
 __global__ __launch_bounds__(kTB) void k_setup_ns(Geo g, const float* __restrict__ V,
                                                   float* __restrict__ Xall,
@@ -104,43 +49,8 @@ __global__ __launch_bounds__(kTB) void k_setup_ns(Geo g, const float* __restrict
   BL_AT_NN(YAall, g.bat);
   constexpr int ZV = 1;
   COLUMN
-  VOXEL(0)
-  const size_t M = (size_t)g.M;
-  const size_t n = blockIdx.y;
-  const float* __restrict__ v0 = V + n * (DIM + 1) * M;
-  const float* __restrict__ v1 = v0 + (DIM + 1) * M;
-  float* __restrict__ X = Xall + n * DIM * M;
-  float4* __restrict__ YA = YAall + n * M;
-  const float s = g.dt * (float)g.nref;
-  float u0[3][1] = {{0.f}, {0.f}, {0.f}}, u1[3] = {0.f, 0.f, 0.f}, nu1[3][1];
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    u0[c][0] = s * ld(field_rsrc(v0 + c * M, g), t.c, zo);
-    u1[c] = s * ld(field_rsrc(v1 + c * M, g), t.c, zo);
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) nu1[c][0] = -u1[c];
-  Tap tf[1], tb[1];
-  make_taps<DIM, 1>(g, t, nu1[0], nu1[1], nu1[2], tf);
-  make_taps<DIM, 1>(g, t, u0[0], u0[1], u0[2], tb);
-  float xo[3] = {0.f, 0.f, 0.f}, yo[3][1] = {{0.f}, {0.f}, {0.f}};
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    float gf[1], gb[1];
-    gather_zv<DIM, 1>(g, field_rsrc(v0 + c * M, g), tf, gf);
-    gather_zv<DIM, 1>(g, field_rsrc(v1 + c * M, g), tb, gb);
-    xo[c] = -0.5f * (u1[c] + s * gf[0]);
-    yo[c][0] = 0.5f * (u0[c][0] + s * gb[0]);
-  }
-  Tap ty[1];
-  make_taps<DIM, 1>(g, t, yo[0], yo[1], yo[2], ty);
-  const float ri = ld(field_rsrc(v0 + DIM * M, g), t.c, zo);
-  float Rv[1];
-  gather_zv<DIM, 1>(g, field_rsrc(v1 + DIM * M, g), ty, Rv);
-  const float R = Rv[0];
-  const float a = 1.0f + 0.5f * g.dt * (R + (1.0f + g.dt * R) * ri);
-  for (int c = 0; c < DIM; ++c) st(field_rsrc(X + c * M, g), t.c, zo, xo[c]);
-  st_ya(g, YA, z, t, make_float4(yo[0][0], yo[1][0], yo[2][0], a));
+  const size_t M = (size_t)g.M, n = blockIdx.y;
+  setup_voxel_ns<DIM>(g, t, V + n * (DIM + 1) * M, Xall + n * DIM * M, YAall + n * M);
 }
 
 // ----------------------------------------------------------------------------- transports
@@ -607,11 +517,19 @@ inline dim3 gather_grid(const Geo& g, int zv) {
                          __VA_ARGS__);                                                     \
   } while (0)
 void setup(const Geo& g, const float* v, float* X, float4* YA, hipStream_t s) {
-  DISPATCH_GATHER(k_setup, TR_SETUP, g, v, X, YA);
+  if (g.dim == 3 && g.zv[TR_SETUP] >= 4) return setup_box(g, v, X, YA, s);
+  if (g.dim == 3 && g.zv[TR_SETUP] == 2)
+    BL_LAUNCH((k_setup<3, 2>), GRID_N(2, 1), dim3(kTB), 0, s, g, v, X, YA);
+  else if (g.dim == 3)
+    BL_LAUNCH((k_setup<3, 1>), GRID_N(1, 1), dim3(kTB), 0, s, g, v, X, YA);
+  else
+    BL_LAUNCH((k_setup<2, 1>), GRID_N(1, 1), dim3(kTB), 0, s, g, v, X, YA);
 }
 void setup_ns(const Geo& g, const float* V, float* X, float4* YA, int steps, hipStream_t s) {
   const dim3 grid = batch_grid(dim3(gather_grid(g, 1).x, (unsigned)steps), g.bat);
-  if (g.dim == 3)
+  if (g.dim == 3 && g.zv[TR_SETUP] >= 4)
+    setup_box_ns(g, V, X, YA, steps, s);
+  else if (g.dim == 3)
     hipLaunchKernelGGL(k_setup_ns<3>, grid, dim3(kTB), 0, s, g, V, X, YA);
   else
     hipLaunchKernelGGL(k_setup_ns<2>, grid, dim3(kTB), 0, s, g, V, X, YA);
