@@ -309,10 +309,9 @@ int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);
  * Choices are kept for the process and appended to a cache file read by later processes:
  * BL_TUNE_CACHE (a path, or "off"), else $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v4.txt or
  * ~/.cache/bl_lddmm/launch_shapes_v4.txt (lines with a value a class does not accept are
- * skipped).  BL_LAUNCH_SHAPES="s0,...,s6" fixes all classes
- * (state, incremental, adjoint, body force, setup, iota z, iota x/y); only through it can the
- * iota x/y stages run as one fused kernel with 32 or 16 rows per block (s6 = 32 or 16; 0 = the
- * two separate stages, the default), which times faster alone but runs slower in products.
+ * skipped).  BL_LAUNCH_SHAPES="s0,...,s6" fixes all classes (state, incremental, adjoint, body
+ * force, setup, iota z, iota x/y); the last one (0, 16 or 32) has no effect: the x and y stages
+ * of iota are one launch.
  * bl_lddmm_tune_reload forgets the choices of this process and reads the cache file again.
  */
 void bl_lddmm_tune_reload(void);

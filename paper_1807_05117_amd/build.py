@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libbl_lddmm.so")
 
-SOURCES = ["bl_dft.hip", "bl_transport.hip", "bl_sweep.hip", "bl_box.hip", "bl_reduce.hip", "bl_mixed.hip", "bl_deform.hip",
+SOURCES = ["bl_dft.hip", "bl_dft_mfma.hip", "bl_transport.hip", "bl_sweep.hip", "bl_box.hip", "bl_reduce.hip", "bl_mixed.hip", "bl_deform.hip",
            "bl_deform_fused.hip", "bl_lddmm.hip", "bl_batch.hip", "bl_serve.hip",
            "bl_noalloc.hip"]
 

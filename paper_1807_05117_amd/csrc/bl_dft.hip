@@ -13,10 +13,9 @@
 //          y stage  H[c][h][ky][x]  = sum_y G conj Ty[ky][y]
 //          x stage  P[c][h][ky][kx] = sum_x H conj Tx[kx][x]
 // and the kz < 0 half of pi is completed by Hermitian symmetry in band_finalize.
-// The z stages touch every voxel and carry the bulk of the bytes; they keep one (y, x)
-// column of the half spectrum in registers and stream the z planes, so every wavefront
-// reads or writes whole contiguous rows.  Twiddles are FP32 values of exactly reduced
-// angles computed on the host in FP64.
+// Twiddles are FP32 values of exactly reduced angles computed on the host in FP64.  The stages
+// run on the matrix cores (bl_dft_mfma.hip); the x and y stages here serve bands with more than
+// 128 ky (iota) or kx (pi), whose intermediate does not fit a wavefront's registers there.
 #include "bl_internal.h"
 
 namespace bl {
@@ -106,220 +105,7 @@ __global__ __launch_bounds__(64) void k_iota_y(Geo g, const float2* __restrict__
     if (y0 + u < g.ny) dst[(size_t)u * g.nx] = acc[u];
 }
 
-// Fused x and y stages: one block per (c*kzh + h, tile of kFX columns, chunk of kFY rows).
-// The band plane is staged in LDS (every lane of a wavefront reads the same entry), the x
-// stage writes the block's columns of F1 for every ky to LDS, and the y stage forms the block's
-// rows of F2 from them; F1 never goes through memory.  Each output is accumulated in exactly
-// the order of k_iota_x / k_iota_y (two alternating partial sums over kx in chunks of kU; one
-// sum over ky in chunks of kU, rows past ky against zero twiddle rows), so the results are
-// bitwise those of the two separate stages.  A launch shape: the autotuner times it (16 or 32
-// rows per block) against the two separate stages when the band plane and the block's F1
-// tile fit kFusedLds bytes; every choice computes the same values.
-constexpr int kFX = 64;
-constexpr size_t kFusedLds = 64 * 1024;
-
-template <int kFY>
-__global__ __launch_bounds__(256) void k_iota_xy(Geo g, const float2* __restrict__ band,
-                                                 const float2* __restrict__ tw_x,
-                                                 const float2* __restrict__ tw_y, int nyp,
-                                                 float2* __restrict__ F2) {
-  BL_BATCH(g.bat)
-  BL_AT(band, g.bat);
-  BL_AT(F2, g.bat);
-  extern __shared__ float2 lds_xy[];
-  const int KX = g.kx, KY = g.ky;
-  float2* S = lds_xy;                    // [KY][KX] band plane
-  float2* T = S + (size_t)KY * KX;       // [KY][kFX] x-stage outputs of the block's columns
-  const int ch = batch_bz(g.bat, bpair_);
-  const int c = ch / g.kzh, h = ch - c * g.kzh;
-  const float2* plane = band + (size_t)(c * g.kz + g.kz0 + h) * KY * KX;
-  for (int i = threadIdx.x; i < KY * KX; i += 256) S[i] = plane[i];
-  __syncthreads();
-  const int xl = threadIdx.x & (kFX - 1);
-  const int wq = wave_uniform(threadIdx.x >> 6);   // 4 wavefronts
-  const int x = blockIdx.x * kFX + xl;
-  const int xc = x < g.nx ? x : g.nx - 1;          // clamped column: loads stay in bounds
-  // x stage: T[jy][xl] for jy = wq + 4 r, kNJ rows of a thread per pass sharing each twiddle
-  // load (one round of kU loads per chunk for all of them)
-  constexpr int kNJ = 8;
-  for (int jb = wq; jb < KY; jb += 4 * kNJ) {
-    float2 a0[kNJ], a1[kNJ];
-#pragma unroll
-    for (int r = 0; r < kNJ; ++r) a0[r] = a1[r] = make_float2(0.f, 0.f);
-    for (int j0 = 0; j0 < KX; j0 += kU) {
-      float2 t[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) t[u] = tw_x[(size_t)(j0 + u) * g.nx + xc];
-#pragma unroll
-      for (int r = 0; r < kNJ; ++r) {
-        const float2* row = S + (size_t)min(jb + 4 * r, KY - 1) * KX;
-#pragma unroll
-        for (int u = 0; u < kU; u += 2) {
-          cmac(a0[r], row[min(j0 + u, KX - 1)], t[u]);
-          cmac(a1[r], row[min(j0 + u + 1, KX - 1)], t[u + 1]);
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kNJ; ++r) {
-      const int jy = jb + 4 * r;
-      if (jy < KY) T[jy * kFX + xl] = make_float2(a0[r].x + a1[r].x, a0[r].y + a1[r].y);
-    }
-  }
-  __syncthreads();
-  // y stage: rows y0 + wq + 4 v (v < kFY / 4) of the block's chunk, together per ky term
-  constexpr int NV = kFY / 4;
-  const int y0 = blockIdx.y * kFY + wq;
-  float2 acc[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) acc[v] = make_float2(0.f, 0.f);
-  for (int j0 = 0; j0 < KY; j0 += kU) {
-    float2 f[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) f[u] = T[min(j0 + u, KY - 1) * kFX + xl];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const float2* tw = tw_y + (size_t)(j0 + u) * nyp + y0;   // zero past ny and ky
-#pragma unroll
-      for (int v = 0; v < NV; ++v) cmac(acc[v], f[u], tw[4 * v]);
-    }
-  }
-  if (x < g.nx) {
-    float2* dst = F2 + (size_t)ch * g.ny * g.nx + x;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int y = y0 + 4 * v;
-      if (y < g.ny) dst[(size_t)y * g.nx] = acc[v];
-    }
-  }
-}
-
-// z stage (real output): one thread per (column q, chunk of z, component); the half-spectrum
-// column is held in registers.  Planes z and nz - z share their twiddles up to conjugation,
-// so one pass over z <= nz/2 forms A = sum_h f.x t.x and B = sum_h f.y t.y and writes A - B
-// to plane z and A + B to plane nz - z.  The block's twiddle rows are staged once in LDS;
-// every lane of a wavefront reads the same entry (a broadcast), 16 bytes at a time.
-template <int KZH>
-__global__ __launch_bounds__(256) void k_iota_z(Geo g, const float2* __restrict__ F2,
-                                                const float2* __restrict__ tw_zT,
-                                                float* __restrict__ out, int zchunk) {
-  BL_BATCH(g.bat)
-  BL_AT(F2, g.bat);
-  BL_AT(out, g.bat);
-  extern __shared__ float4 tws4[];   // zchunk rows of KZH (even) or 2 (KZH == 1) float2
-  constexpr int RW = KZH == 1 ? 2 : KZH;   // row width in float2
-  float2* tws = reinterpret_cast<float2*>(tws4);
-  const int nq = g.nx * g.ny;
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  const int c = batch_bz(g.bat, bpair_);
-  const int zmax = g.nz / 2;
-  const int z0 = blockIdx.y * zchunk;
-  for (int i = threadIdx.x; i < zchunk * RW; i += 256) {
-    const int r = i / RW, h = i - r * RW;
-    tws[i] = h < KZH ? tw_zT[(size_t)min(z0 + r, zmax) * kZP + h] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  if (q >= nq) return;
-  float2 f[RW];
-  const float2* src = F2 + (size_t)c * g.kzh * nq + q;
-#pragma unroll
-  for (int h = 0; h < RW; ++h) {
-    const int hc = h < g.kzh ? h : g.kzh - 1;   // clamped, always in bounds
-    float2 v = src[(size_t)hc * nq];
-    const float sc = h >= g.kzh ? 0.f : (h > 0 ? 2.f : 1.f);
-    f[h] = make_float2(sc * v.x, sc * v.y);
-  }
-  const int z1 = min(zmax + 1, z0 + zchunk);
-  float* dst = out + (size_t)c * g.M + q;
-  for (int z = z0; z < z1; ++z) {
-    const float4* t4 = tws4 + (size_t)(z - z0) * (RW / 2);
-    float a = 0.f, b = 0.f;
-#pragma unroll
-    for (int h2 = 0; h2 < RW / 2; ++h2) {
-      const float4 t = t4[h2];
-      a = fmaf(f[2 * h2].x, t.x, a);
-      b = fmaf(f[2 * h2].y, t.y, b);
-      a = fmaf(f[2 * h2 + 1].x, t.z, a);
-      b = fmaf(f[2 * h2 + 1].y, t.w, b);
-    }
-    dst[(size_t)z * nq] = a - b;
-    const int zm = g.nz - z;
-    if (z > 0 && zm != z) dst[(size_t)zm * nq] = a + b;
-  }
-}
-
 // ------------------------------------------------------------------------------ pi stages
-// z stage: block of 64 columns x kNW wavefronts; in every round of kZU kNW planes wavefront
-// w sums the planes w + u kNW (u < kZU) with wave-uniform twiddle rows -- kZU loads in
-// flight per wavefront -- then the kNW partial sums are added in LDS in a fixed order.
-constexpr int kNW = 8;
-constexpr int kZU = 16;
-
-template <int KZH>
-// (up to 16 stored kz planes: at least 6 wavefronts per SIMD, i.e. three blocks of 8 per compute
-// unit; unbounded, the compiler used 83 registers, two blocks fit and a 128^3 call took 15.3
-// instead of 12.7 us)
-__global__ __launch_bounds__(64 * kNW, KZH <= 16 ? 6 : 1) void k_pi_z(Geo g, const float* __restrict__ f,
-                                                   const float2* __restrict__ tw_zT,
-                                                   float2* __restrict__ G) {
-  BL_BATCH(g.bat)
-  BL_AT(f, g.bat);
-  BL_AT(G, g.bat);
-  constexpr int CH = (KZH % 8 == 0) ? 8 : ((KZH % 4 == 0) ? 4 : 1);
-  __shared__ float2 sh[kNW - 1][CH][64];
-  const int nq = g.nx * g.ny;
-  const int tx = threadIdx.x;
-  const int w = wave_uniform(threadIdx.y);
-  const int q = blockIdx.x * 64 + tx;
-  const int c = blockIdx.y;
-  const int qc = q < nq ? q : nq - 1;   // clamped column: loads stay in bounds
-  float2 acc[KZH];
-#pragma unroll
-  for (int h = 0; h < KZH; ++h) acc[h] = make_float2(0.f, 0.f);
-  const float* src = f + (size_t)c * g.M + qc;
-  for (int zb = 0; zb < g.nz; zb += kZU * kNW) {
-    float v[kZU];
-#pragma unroll
-    for (int u = 0; u < kZU; ++u) v[u] = src[(size_t)min(zb + w + u * kNW, g.nz - 1) * nq];
-#pragma unroll
-    for (int u = 0; u < kZU; ++u) {
-      const float2* t = tw_zT + (size_t)(zb + w + u * kNW) * kZP;   // zero rows past nz
-#pragma unroll
-      for (int h = 0; h < KZH; ++h) {
-        acc[h].x = fmaf(v[u], t[h].x, acc[h].x);
-        acc[h].y = fmaf(-v[u], t[h].y, acc[h].y);
-      }
-    }
-  }
-#pragma unroll
-  for (int h0 = 0; h0 < KZH; h0 += CH) {
-    if (w > 0) {
-#pragma unroll
-      for (int hh = 0; hh < CH; ++hh) sh[w - 1][hh][tx] = acc[h0 + hh];
-    }
-    __syncthreads();
-    if (w == 0) {
-#pragma unroll
-      for (int hh = 0; hh < CH; ++hh) {
-        float2 s = acc[h0 + hh];
-#pragma unroll
-        for (int o = 0; o < kNW - 1; ++o) {
-          s.x += sh[o][hh][tx].x;
-          s.y += sh[o][hh][tx].y;
-        }
-        acc[h0 + hh] = s;
-      }
-    }
-    __syncthreads();
-  }
-  if (w == 0 && q < nq) {
-    float2* dst = G + (size_t)c * g.kzh * nq + q;
-#pragma unroll
-    for (int h = 0; h < KZH; ++h)
-      if (h < g.kzh) dst[(size_t)h * nq] = acc[h];
-  }
-}
-
 // y stage: block of 64 x-columns x kYS wavefronts for one group of kJG ky outputs; wavefront
 // s sums a contiguous 1/kYS of the y planes in chunks of kUY, the partial sums are added in
 // LDS in a fixed order.
@@ -657,66 +443,10 @@ __global__ __launch_bounds__(256) void k_band_finalize(Geo g,
   }
 }
 
-template <int KZH>
-void launch_z_pair(const Geo& g, const DftPlan& p, const float2* F2, float* out, int C,
-                   const float* f, float2* G, hipStream_t s, bool inverse) {
-  const int nq = g.nx * g.ny;
-  if (inverse) {
-    // split z into chunks so that a launch has enough blocks to fill the chip
-    // (z, nz - z) pairs: z = 0 .. nz/2, in chunks of at most 64 (LDS: 64 twiddle rows)
-    // split further until the launch has enough blocks to fill the chip
-    const int npair = g.nz / 2 + 1;
-    const int qblocks = (nq + 255) / 256;
-    int nchunk = (npair + 63) / 64;
-    while (qblocks * nchunk * C < 768 && nchunk * 8 < npair) nchunk *= 2;
-    // launch shape: more z chunks per column (each output's arithmetic is unchanged)
-    for (int m = g.zv[TR_IOTA_Z]; m > 1 && nchunk * 4 <= npair; m /= 2) nchunk *= 2;
-    const int zchunk = (npair + nchunk - 1) / nchunk;
-    nchunk = (npair + zchunk - 1) / zchunk;
-    const size_t lds = (size_t)zchunk * (KZH == 1 ? 2 : KZH) * sizeof(float2);
-    BL_LAUNCH(k_iota_z<KZH>, batch_grid(dim3(qblocks, nchunk, C), g.bat), dim3(256), lds, s, g,
-              F2, p.tw_zT, out, zchunk);
-  } else {
-    BL_LAUNCH(k_pi_z<KZH>, batch_grid(dim3((nq + 63) / 64, C), g.bat), dim3(64, kNW), 0, s, g,
-              f, p.tw_zT, G);
-  }
-}
-
-void z_stage(const Geo& g, const DftPlan& p, const float2* F2, float* out, int C,
-             const float* f, float2* G, hipStream_t s, bool inverse) {
-  const int k = g.kzh;
-  if (k <= 1) launch_z_pair<1>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 4) launch_z_pair<4>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 8) launch_z_pair<8>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 12) launch_z_pair<12>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 16) launch_z_pair<16>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 20) launch_z_pair<20>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 24) launch_z_pair<24>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 32) launch_z_pair<32>(g, p, F2, out, C, f, G, s, inverse);
-  else if (k <= 48) launch_z_pair<48>(g, p, F2, out, C, f, G, s, inverse);
-  else launch_z_pair<64>(g, p, F2, out, C, f, G, s, inverse);
-}
-
 }  // namespace
 
 void iota_xy(const Geo& g, const DftPlan& p, const float2* band, int C, hipStream_t s) {
-  const size_t lds = ((size_t)g.ky * g.kx + (size_t)g.ky * kFX) * sizeof(float2);
-  // launch shape 16 or 32: the fused stage with that many rows per block; 0: the two stages
-  // (nyp is a multiple of 32: the rows of every block are in the table)
-  if (g.zv[TR_IOTA_XY] != 0 && lds <= kFusedLds) {
-    const dim3 b(256);
-    if (g.zv[TR_IOTA_XY] == 16)
-      hipLaunchKernelGGL(k_iota_xy<16>,
-                         batch_grid(dim3((g.nx + kFX - 1) / kFX, (g.ny + 15) / 16, C * g.kzh),
-                                    g.bat),
-                         b, lds, s, g, band, p.tw_x, p.tw_y, p.nyp, p.bufB);
-    else
-      hipLaunchKernelGGL(k_iota_xy<32>,
-                         batch_grid(dim3((g.nx + kFX - 1) / kFX, (g.ny + 31) / 32, C * g.kzh),
-                                    g.bat),
-                         b, lds, s, g, band, p.tw_x, p.tw_y, p.nyp, p.bufB);
-    return;
-  }
+  if (iota_xy_mfma(g, p, band, C, p.bufB, s)) return;
   const int xb = (g.nx + 63) / 64;
   hipLaunchKernelGGL(k_iota_x, batch_grid(dim3(xb, g.ky, C * g.kzh), g.bat), dim3(64), 0, s, g,
                      band, p.tw_x, p.bufA);
@@ -728,7 +458,7 @@ void iota_z(const Geo& g, const DftPlan& p, int C, float* out, hipStream_t s) {
   if (p.mixed)
     iota_z_mixed(g, p, p.bufB, C, out, s);
   else
-    z_stage(g, p, p.bufB, out, C, nullptr, nullptr, s, true);
+    iota_z_mfma(g, p, p.bufB, out, C, s);
 }
 
 void iota(const Geo& g, const DftPlan& p, const float2* band, int C, float* out, hipStream_t s) {
@@ -745,10 +475,11 @@ void pi_z(const Geo& g, const DftPlan& p, const float* grid, int C, hipStream_t 
   if (p.mixed)
     pi_z_mixed(g, p, grid, C, p.bufA, s);
   else
-    z_stage(g, p, nullptr, nullptr, C, grid, p.bufA, s, false);
+    pi_z_mfma(g, p, grid, C, p.bufA, s);
 }
 
 void pi_yx(const Geo& g, const DftPlan& p, int C, float2* P, hipStream_t s) {
+  if (pi_yx_mfma(g, p, p.bufA, C, P, s)) return;
   const int xb = (g.nx + 63) / 64;
   const int yseg = ((g.ny + kYS - 1) / kYS + kUY - 1) / kUY * kUY;
   hipLaunchKernelGGL(k_pi_y, batch_grid(dim3(xb, p.kyp / kJG, C * g.kzh), g.bat), dim3(64, kYS),

