@@ -263,13 +263,16 @@ __device__ __forceinline__ void leray(const float* q, float2* o) {
   }
 }
 
+// The velocities of `nodes` time nodes (istride and ostride entries apart): a loop in the thread
+// where the regulariser is summed (weights w, at the first and last node wend), else one node per
+// blockIdx.y.
 template <int DIM>
 __global__ __launch_bounds__(256) void k_band_prep(Geo g, const float2* __restrict__ raw,
                                                    float2* __restrict__ out, int with_div,
                                                    const double* __restrict__ Lhat64,
-                                                   double* __restrict__ reg_partial,
-                                                   double reg_weight, int reg_accumulate,
-                                                   size_t nstride, uint32_t* __restrict__ zero,
+                                                   double* __restrict__ reg_partial, double w,
+                                                   double wend, int nodes, size_t istride,
+                                                   size_t ostride, uint32_t* __restrict__ zero,
                                                    int nzero) {
   BL_BATCH(g.bat)
   for (int i = blockIdx.x * 256 + threadIdx.x; i < nzero; i += gridDim.x * 256) zero[i] = 0u;
@@ -279,50 +282,53 @@ __global__ __launch_bounds__(256) void k_band_prep(Geo g, const float2* __restri
   BL_AT(reg_partial, g.bat);
   double acc = 0.0;
   const int B = (int)g.B;
-  raw += blockIdx.y * nstride;   // node blockIdx.y (nodes > 1 only without the regulariser sum)
-  out += blockIdx.y * nstride;
+  const int n0 = reg_partial ? 0 : (int)blockIdx.y, n1 = reg_partial ? nodes : n0 + 1;
   for (int b = blockIdx.x * 256 + threadIdx.x; b < B; b += gridDim.x * 256) {
     int jx, jy, jz;
     band_index(g, b, jx, jy, jz);
     const bool up = unpaired(g, jx, jy, jz);
     const int mb = up ? b : mirror(g, jx, jy, jz);
-    float2 a[DIM], m[DIM], o[DIM];
-#pragma unroll
-    for (int c = 0; c < DIM; ++c) {
-      a[c] = raw[c * B + b];
-      m[c] = raw[c * B + mb];
-    }
     float q[DIM];
     div_symbol<DIM>(g, jx, jy, jz, q);
-#pragma unroll
-    for (int c = 0; c < DIM; ++c)
-      o[c] = up ? make_float2(0.f, 0.f)
-                : make_float2(0.5f * (a[c].x + m[c].x), 0.5f * (a[c].y - m[c].y));
-    if (g.gamma) leray<DIM>(q, o);
-#pragma unroll
-    for (int c = 0; c < DIM; ++c) out[c * B + b] = o[c];
-    if (reg_partial) {
-      const double l = Lhat64[b];
-#pragma unroll
-      for (int c = 0; c < DIM; ++c) acc += l * ((double)o[c].x * o[c].x + (double)o[c].y * o[c].y);
-    }
-    if (with_div) {
-      // r~ = sum_c 2 pi i (k_c / l_c) v~_c with l_c = n_c / N_ref
-      float2 d = make_float2(0.f, 0.f);
+    const double l = reg_partial ? Lhat64[b] : 0.0;
+#pragma unroll 2
+    for (int n = n0; n < n1; ++n) {
+      const float2* __restrict__ in = raw + n * istride;
+      float2* __restrict__ to = out + n * ostride;
+      float2 a[DIM], m[DIM], o[DIM];
 #pragma unroll
       for (int c = 0; c < DIM; ++c) {
-        d.x = fmaf(-q[c], o[c].y, d.x);
-        d.y = fmaf(q[c], o[c].x, d.y);
+        a[c] = in[c * B + b];
+        m[c] = in[c * B + mb];
       }
-      out[DIM * B + b] = d;
+#pragma unroll
+      for (int c = 0; c < DIM; ++c)
+        o[c] = up ? make_float2(0.f, 0.f)
+                  : make_float2(0.5f * (a[c].x + m[c].x), 0.5f * (a[c].y - m[c].y));
+      if (g.gamma) leray<DIM>(q, o);
+#pragma unroll
+      for (int c = 0; c < DIM; ++c) to[c * B + b] = o[c];
+      if (reg_partial) {
+        double e = 0.0;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) e += l * ((double)o[c].x * o[c].x + (double)o[c].y * o[c].y);
+        acc += (n == 0 || n + 1 == nodes ? wend : w) * e;
+      }
+      if (with_div) {
+        // r~ = sum_c 2 pi i (k_c / l_c) v~_c with l_c = n_c / N_ref
+        float2 d = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+          d.x = fmaf(-q[c], o[c].y, d.x);
+          d.y = fmaf(q[c], o[c].x, d.y);
+        }
+        to[DIM * B + b] = d;
+      }
     }
   }
   if (reg_partial) {
     const double tot = block_reduce_256<false>(acc);
-    if (threadIdx.x == 0) {
-      const double v = reg_weight == 1.0 ? tot : reg_weight * tot;
-      reg_partial[blockIdx.x] = reg_accumulate ? reg_partial[blockIdx.x] + v : v;
-    }
+    if (threadIdx.x == 0) reg_partial[blockIdx.x] = tot;
   }
 }
 
@@ -490,32 +496,32 @@ void pi_yx(const Geo& g, const DftPlan& p, int C, float2* P, hipStream_t s) {
                      s, g, rows, xseg, p.bufB, p.tw_xT, P);
 }
 
-void band_prep(const Geo& g, const float2* raw, float2* out, int with_div, const double* Lhat64,
-               double* reg_partial, hipStream_t s, double reg_weight, int reg_accumulate,
-               uint32_t* zero, int nzero) {
+namespace {
+void prep_launch(const Geo& g, const float2* raw, float2* out, int with_div, const double* Lhat64,
+                 double* reg_partial, double w, double wend, int nodes, size_t istride, size_t ostride,
+                 hipStream_t s, uint32_t* zero, int nzero) {
   // the regulariser sum needs the fixed kRedBlocks grid; the plain projection one thread per
-  // band entry
-  const int blocks = reg_partial ? kRedBlocks : (int)((g.B + 255) / 256);
-  if (g.dim == 3)
-    hipLaunchKernelGGL(k_band_prep<3>, batch_grid(dim3(blocks), g.bat), dim3(256), 0, s, g, raw, out, with_div,
-                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0, zero, nzero);
-  else if (g.dim == 2)
-    hipLaunchKernelGGL(k_band_prep<2>, batch_grid(dim3(blocks), g.bat), dim3(256), 0, s, g, raw, out, with_div,
-                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0, zero, nzero);
-  else
-    hipLaunchKernelGGL(k_band_prep<1>, batch_grid(dim3(blocks), g.bat), dim3(256), 0, s, g, raw, out, with_div,
-                       Lhat64, reg_partial, reg_weight, reg_accumulate, (size_t)0, zero, nzero);
+  // band entry and node
+  const dim3 grid = reg_partial ? dim3(kRedBlocks) : dim3((unsigned)((g.B + 255) / 256), (unsigned)nodes);
+#define BP_LAUNCH(D)                                                                                \
+  hipLaunchKernelGGL(k_band_prep<D>, batch_grid(grid, g.bat), dim3(256), 0, s, g, raw, out, with_div, \
+                     Lhat64, reg_partial, w, wend, nodes, istride, ostride, zero, nzero)
+  if (g.dim == 3) BP_LAUNCH(3);
+  else if (g.dim == 2) BP_LAUNCH(2);
+  else BP_LAUNCH(1);
+#undef BP_LAUNCH
+}
+}  // namespace
+
+void band_prep(const Geo& g, const float2* raw, float2* out, int with_div, const double* Lhat64,
+               double* reg_partial, hipStream_t s, uint32_t* zero, int nzero) {
+  prep_launch(g, raw, out, with_div, Lhat64, reg_partial, 1.0, 1.0, 1, 0, 0, s, zero, nzero);
 }
 
-void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, size_t stride,
-                     hipStream_t s) {
-  const dim3 grid((unsigned)((g.B + 255) / 256), (unsigned)nodes);
-  if (g.dim == 3)
-    hipLaunchKernelGGL(k_band_prep<3>, grid, dim3(256), 0, s, g, raw, out, 0, nullptr, nullptr,
-                       1.0, 0, stride, nullptr, 0);
-  else
-    hipLaunchKernelGGL(k_band_prep<2>, grid, dim3(256), 0, s, g, raw, out, 0, nullptr, nullptr,
-                       1.0, 0, stride, nullptr, 0);
+void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, size_t istride,
+                     size_t ostride, hipStream_t s, int with_div, const double* Lhat64,
+                     double* reg_partial, double w, double wend) {
+  prep_launch(g, raw, out, with_div, Lhat64, reg_partial, w, wend, nodes, istride, ostride, s, nullptr, 0);
 }
 
 int finalize_blocks(const Geo& g) { return (int)std::min<int64_t>(kRedBlocks, (g.B + 255) / 256); }

@@ -219,16 +219,15 @@ void pi_z_mixed(const Geo& g, const DftPlan& p, const float* f, int C, float2* G
 // ---- band kernels (bl_dft.hip)
 // out[c] = projection of raw[c] (c < dim): Hermitian, and divergence-free when g.gamma = 1;
 // with_div: out[dim] = spectral divergence.
-// reg_partial (may be null): kRedBlocks partial sums of reg_weight * sum_c Lhat |out_c|^2,
-// added to the partials already there when reg_accumulate (one velocity per time node).
+// reg_partial (may be null): kRedBlocks partial sums of sum_c Lhat |out_c|^2.
 // zero (may be null): nzero words set to zero by the same launch (a sweep's synchronisation words)
 void band_prep(const Geo& g, const float2* raw, float2* out, int with_div, const double* Lhat64,
-               double* reg_partial, hipStream_t s, double reg_weight = 1.0,
-               int reg_accumulate = 0, uint32_t* zero = nullptr, int nzero = 0);
-// the plain projection (no divergence, no regulariser sum) of `nodes` band vectors spaced
-// `stride` complex entries apart, in one launch
-void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, size_t stride,
-                     hipStream_t s);
+               double* reg_partial, hipStream_t s, uint32_t* zero = nullptr, int nzero = 0);
+// the same for `nodes` band vectors in one launch, istride and ostride complex entries apart; the
+// regulariser is the weighted sum (w, at the first and the last node wend)
+void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, size_t istride,
+                     size_t ostride, hipStream_t s, int with_div = 0, const double* Lhat64 = nullptr,
+                     double* reg_partial = nullptr, double w = 0.0, double wend = 0.0);
 // out[c][k] = Lhat(k) vproj[c][k] + scale * P (Hermitian-completed), zero on unpaired planes;
 // leray (C == dim): then projected divergence-free per index k.
 // With dot_part not NULL (one node), also the finalize_blocks(g) block partials of

@@ -927,11 +927,8 @@ void op_set_velocity_ns(bl_ctx* c, const float2* vraw) {
   const int d = g.dim;
   double* red_reg = c->red + RED_REG * bl::kRedBlocks;
   double* red_data = c->red + RED_DATA * bl::kRedBlocks;
-  for (int n = 0; n <= g.nt; ++n) {
-    const double w = (n == 0 || n == g.nt) ? 0.5 / g.nt : 1.0 / g.nt;
-    bl::band_prep(g, vraw + (size_t)n * d * B, c->bv + (size_t)n * (d + 1) * B, 1, c->Lhat64,
-                  red_reg, s, w, n > 0);
-  }
+  bl::band_prep_nodes(g, vraw, c->bv, g.nt + 1, d * B, (d + 1) * B, s, 1, c->Lhat64, red_reg,
+                      1.0 / g.nt, 0.5 / g.nt);
   // (v^n, r^n) of every node in one transform: V[n][c]
   bl::iota(g, c->plan, c->bv, (g.nt + 1) * (d + 1), c->V, s);
   // every step's offsets in one launch, then the state steps
@@ -992,7 +989,7 @@ void op_hessvec_ns(bl_ctx* c, const float2* draw, float2* hout) {
   hipStream_t s = c->stream;
   const size_t M = (size_t)g.M, B = (size_t)g.B;
   const int d = g.dim;
-  bl::band_prep_nodes(g, draw, c->bd, g.nt + 1, (size_t)d * B, s);
+  bl::band_prep_nodes(g, draw, c->bd, g.nt + 1, (size_t)d * B, (size_t)d * B, s);
   // every node's dv^n in one transform: DV[n][c]
   bl::iota(g, c->plan, c->bd, (g.nt + 1) * d, c->DV, s);
   bl::inc_init(g, c->m, c->DV, c->T0, s);
@@ -1181,7 +1178,7 @@ void prep_and_clean(bl_ctx* c, const float2* raw, float2* out, int with_div, con
                     double* red_reg) {
   c->sweep_now = c->sweeps_allowed && c->sweep.run > 0 && may_sweep(c, now_ns(), thread_key());
   const bool z = use_sweeps(c);
-  bl::band_prep(c->g, raw, out, with_div, Lhat64, red_reg, c->stream, 1.0, 0,
+  bl::band_prep(c->g, raw, out, with_div, Lhat64, red_reg, c->stream,
                 z ? c->sweep_sync : nullptr, z ? 2 * bl::kSweepWords : 0);
   if (z) c->sweep_clean[0] = c->sweep_clean[1] = true;
 }
