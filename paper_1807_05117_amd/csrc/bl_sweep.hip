@@ -523,7 +523,7 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
       load_m(1);
       stores_done();
       __syncthreads();
-      publish(1u);
+      if (!bail) publish(1u);   // (an abandoned tile has stored nothing)
       source<DIM, R>(g, st, dv, src);
     } else {
       const Rsrc in = field_rsrc(a.planes + (size_t)plane_in<KIND>(g, 0) * M, g);

@@ -81,6 +81,19 @@ def test_offsets_past_the_box(gpu_lib, n, k, disp):
     assert _same(got, ref)
 
 
+def test_first_sweeps_of_a_shape_past_the_box(gpu_lib):
+    """the first launches of a kernel start their workgroups late: a tile that abandons the sweep at
+    once must not show progress to tiles that have not noticed"""
+    for i, n in enumerate([(130, 50, 37), (127, 49, 40), (90, 77, 30), (60, 100, 41), (34, 120, 80)]):
+        prob, I0, I1, vs, dv = _inputs(n, (8, 8, 8), 3, 60.0, i)
+        ctx = B.Ctx(bl_problem(prob), I0, I1)
+        got = _results(ctx, prob, vs, dv)
+        ctx.bl_kernel_timing_enable(True)
+        ref = _results(ctx, prob, vs, dv)
+        ctx.close()
+        assert _same(got, ref), n
+
+
 @pytest.mark.parametrize("newton", [False, True])
 @pytest.mark.parametrize("mixed", [False, True])
 def test_models(gpu_lib, newton, mixed):
