@@ -471,6 +471,17 @@ __device__ __forceinline__ Vec<DIM> vec_rsrc(const float* f, const Geo& g) {
   return v;
 }
 
+// central-difference divergence of lambda dv, unscaled: sum_j (lam dv_j)(i + e_j) - (i - e_j);
+// lz: lambda at z - 1 and z + 1, dz: dv_z there
+template <int DIM>
+__device__ __forceinline__ float div_lam_dv(float lxm, float lxp, float lym, float lyp, float lzm, float lzp,
+                                            const float (&d)[6]) {
+  float s = lxp * d[1] - lxm * d[0];
+  s += lyp * d[3] - lym * d[2];
+  if constexpr (DIM == 3) s += lzp * d[5] - lzm * d[4];
+  return s;
+}
+
 // f = -grad m . dv at the thread's ZV voxels
 template <int DIM, int ZV>
 __device__ __forceinline__ void source_f(const Geo& g, const Col& t, const float* m,
@@ -497,13 +508,12 @@ __device__ __forceinline__ void source_f(const Geo& g, const Col& t, const float
 // once, plus one plane above and below, and the ZV voxels' loads of a node are in flight
 // together.  With YA given, lambda^0 is not read: it is formed here as the last adjoint step
 // would, a Interp(lambda^1, i + Y), with the same arithmetic (the caller then stops the
-// backward transport at lambda^1; lambda^0 is needed by nothing but this sum).
+// backward transport at lambda^1; lambda^0 is needed by nothing but this sum).  The sum starts at
+// what acc holds.
 template <int DIM, int ZV>
 __device__ __forceinline__ void body_sum(const Geo& g, const Col& t, const float* lam, const float* m,
                                          const float4* YA, float (&acc)[ZV][3]) {
   const size_t M = (size_t)g.M;
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) acc[zz][0] = acc[zz][1] = acc[zz][2] = 0.f;
   for (int n = g.nt; n >= 0; --n) {   // in the order of the backward sweep (bl_sweep.hip)
     const float w = (n == 0 || n == g.nt) ? 0.5f * g.dt : g.dt;
     const Rsrc rm = field_rsrc(m + n * M, g);

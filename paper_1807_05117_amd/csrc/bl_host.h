@@ -71,8 +71,7 @@ struct bl_ctx {
   // full Newton products only
   float* DM = nullptr;     // (nt + 1) planes: dm^n (dm^0 = 0)
   float* DL = nullptr;     // (nt + 1) planes: dlambda^n
-  float* U0 = nullptr;     // u ping-pong of the incremental adjoint
-  float* U1 = nullptr;
+  float* U = nullptr;      // with T0 and T1, where the Newton body force starts
   float* mfinal = nullptr;  // m(1): the warped source
   // deformation state equation only (image grid)
   float4* IG = nullptr;    // (I0, central-difference gradient of I0)

@@ -272,27 +272,28 @@ void terminal(const Geo& g, const float* mT, const float* I1, float* lam, hipStr
 void adj_step(const Geo& g, const float* lam_in, const float4* YA, float* lam_out,
               hipStream_t s);
 // b_c = sum_n w_n lam^n d_c m^n over nt + 1 stored planes of lam and m; with YA, lam^0 is
-// formed from lam^1 as a Interp(lam^1, i + Y) instead of read (the plane lam^0 is not used)
+// formed from lam^1 as a Interp(lam^1, i + Y) instead of read (the plane lam^0 is not used); the sum starts at b0 where given (dim planes)
+struct BodyStart {
+  float* c[3] = {nullptr, nullptr, nullptr};
+};
 void body_force(const Geo& g, const float* lam, const float* m, float* b, hipStream_t s,
-                const float4* YA = nullptr);
+                const float4* YA = nullptr, BodyStart b0 = {});
 void inc_init(const Geo& g, const float* m0, const float* dv, float* t0, hipStream_t s);
 void inc_step(const Geo& g, const float* t_in, const float* X, const float* m_next,
               const float* dv, float* t_out, hipStream_t s);
 void inc_last(const Geo& g, const float* t_in, const float* X, const float* mT,
               const float* dv, float* dlam, hipStream_t s);
-// full Newton product (the incremental adjoint with its source div(lambda dv), lambda grad dm
-// in the body force): incremental state steps that also store dm^{n+1}; the last one also
-// forms dlambda^Nt = -(2/sigma^2) dm^Nt + dt/2 div(lambda^Nt dv)
+// full Newton product: incremental state step that also stores dm^{n+1} (t_out null: the last)
 void inc_step_n(const Geo& g, const float* t_in, const float* X, const float* m_next,
                 const float* dv, float* t_out, float* dm_out, hipStream_t s);
-void inc_last_n(const Geo& g, const float* t_in, const float* X, const float* mT,
-                const float* dv, const float* lamT, float* dm_out, float* dlam, hipStream_t s);
-// q = a Interp(u_in, i + Y) (+ dt/2 div(lam_n dv) when own); dlam = q; u_out = q + dt/2 div(..)
-void adj_step_n(const Geo& g, const float* u_in, const float4* YA, const float* lam_n,
-                const float* dv, int own, float* dlam, float* u_out, hipStream_t s);
-// b = sum_n w_n (dlam^n grad m^n + lam^n grad dm^n)
-void body_force_n(const Geo& g, const float* dlam, const float* m, const float* lam,
-                  const float* dm, float* b, hipStream_t s);
+// hs^n = dt/2 div(lam^n dv) for 0 < n < nt, hs^nt = u^nt = -(2/sigma^2) dm^nt + dt/2 div(lam^nt dv)
+// and b2 = sum_n w_n lam^n grad dm^n, from nt + 1 planes of lam and dm
+void newton_terms(const Geo& g, const float* lam, const float* dm, const float* dv, float* hs,
+                  const BodyStart& b2, hipStream_t s);
+// q = a Interp(u_in, i + Y) + hs, in place of hs; u_out = q + hs (u_out null: without hs)
+void adj_step_n(const Geo& g, const float* u_in, const float4* YA, float* hs, float* u_out,
+                hipStream_t s);
+
 // one component of packed float4 voxels into a plane
 void unpack4(const Geo& g, int comp, const float4* in, float* plane, hipStream_t s);
 
@@ -306,7 +307,7 @@ void setup_box(const Geo& g, const float* v, float* X, float4* YA, hipStream_t s
 void setup_box_ns(const Geo& g, const float* V, float* X, float4* YA, int steps, hipStream_t s);
 
 // ---- whole sweeps in one launch (bl_sweep.hip), stationary velocity, single problem
-enum { SWEEP_STATE = 0, SWEEP_INC, SWEEP_ADJ };
+enum { SWEEP_STATE = 0, SWEEP_INC, SWEEP_ADJ, SWEEP_INC_N, SWEEP_ADJ_N };   // _N: full Newton product
 constexpr int kSweepTiles = 256;                    // most tiles of a sweep
 constexpr int kSweepWords = 320 + kSweepTiles * 16; // synchronisation words of a sweep, zero before it
 // tiles of a sweep: ty rows of x by tz = gz * run planes, one workgroup each
@@ -325,6 +326,10 @@ struct SweepArgs {
   const float* dv = nullptr;     // dim planes (incremental)
   float* b = nullptr;            // dim planes: body force (adjoint)
   int keep0 = 0;                 // adjoint: lambda^0 is stored too
+  float* dm = nullptr;           // nt + 1 planes (Newton incremental)
+  const float* hs = nullptr;     // nt + 1 planes: hs^n and, in plane nt, u^nt (Newton adjoint)
+  BodyStart b2;                  // dim planes: where b starts (Newton adjoint)
+  float* acc = nullptr;          // dim planes to work in (Newton adjoint)
   uint32_t* sync = nullptr;      // kSweepWords words, zero
   int* nonfinite = nullptr;      // set if a wait was given up (never in a working run)
 };
@@ -340,6 +345,14 @@ void sweep_inc(const Geo& g, const SweepPlan& p, const float* X, const float* m,
 // body_force)
 void sweep_adj(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, float* lam,
                float* b, int keep0, uint32_t* sync, int* nonfinite, hipStream_t s);
+
+// the Newton product's: t^0..t^{nt-1} into the planes t and dm^1..dm^nt into dm; and, with the
+// terms of newton_terms, u^{nt-1}..u^1 into the planes u and the body force b
+void sweep_inc_n(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
+                 float* t, float* dm, uint32_t* sync, int* nonfinite, hipStream_t s);
+void sweep_adj_n(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, const float* hs,
+                 const BodyStart& b2, float* acc, float* u, float* b, uint32_t* sync, int* nonfinite,
+                 hipStream_t s);
 
 // ---- deformation state equation (bl_deform.hip)
 // Band fields are full centred bands of g (B entries per component); product-grid planes have

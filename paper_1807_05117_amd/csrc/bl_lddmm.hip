@@ -242,10 +242,10 @@ Offsets plan_layout(const bl::Geo& g, bool transport, bool solver, bool mixed) {
     o.T1 = L.take(pb);
     o.L = L.take(pb * (g.nt + 1));
     o.Bf = L.take(pb * d * g.nodes);
-    if (g.newton) {   // dm^n, dlambda^n (Nt + 1 planes each) and the u ping-pong
+    if (g.newton) {   // dm^n (then u^n), hs^n and a plane of b2
       o.DM = L.take(pb * (g.nt + 1));
       o.DL = L.take(pb * (g.nt + 1));
-      o.U = L.take(pb * 2);
+      o.U = L.take(pb);
     }
   } else {
     o.V = L.take(pb * 4);
@@ -507,7 +507,7 @@ bl_ctx* create_ctx(const bl_problem* prob, const bl::Geo& g, bool transport, boo
       c->DV = F(o.DV);
       c->T0 = F(o.T0); c->T1 = F(o.T1); c->L = F(o.L); c->Bf = F(o.Bf);
       if (g.newton) {
-        c->DM = F(o.DM); c->DL = F(o.DL); c->U0 = F(o.U); c->U1 = F(o.U) + g.M;
+        c->DM = F(o.DM); c->DL = F(o.DL); c->U = F(o.U);
       }
     }
     if (!g.deform || !transport) c->V = F(o.V);
@@ -1317,27 +1317,37 @@ void op_hessvec_newton(bl_ctx* c, const float2* draw, float2* hout, double* dot_
     for (int n = g.nt - 1; n >= 0; --n) bl::adj_step(g, c->L + (n + 1) * M, c->YA, c->L + n * M, s);
     c->have_lambda = true;
   }
-  bl::band_prep(g, draw, c->bd, 0, nullptr, nullptr, s);
+  prep_and_clean(c, draw, c->bd, 0, nullptr, nullptr);
   bl::iota(g, c->plan, c->bd, g.dim, c->DV, s);
-  bl::inc_init(g, c->m, c->DV, c->T0, s);
-  float* tin = c->T0;
-  float* tout = c->T1;
-  for (int n = 0; n + 1 < g.nt; ++n) {
-    bl::inc_step_n(g, tin, c->X, c->m + (n + 1) * M, c->DV, tout, c->DM + (n + 1) * M, s);
-    std::swap(tin, tout);
+  // t^n lies in planes that the terms overwrite, or by turns in T0 and T1; then the terms hs^n (u^Nt
+  // in the last plane) take DL, u^n the planes of dm^n, and b starts at b2
+  const bool sweep = use_sweeps(c);
+  if (sweep) {
+    bl::sweep_inc_n(g, c->sweep, c->X, c->m, c->DV, c->DL, c->DM, sweep_words(c, 0), c->flag, s);
+  } else {
+    bl::inc_init(g, c->m, c->DV, c->T0, s);
+    float* tin = c->T0;
+    float* tout = c->T1;
+    for (int n = 0; n < g.nt; ++n) {
+      bl::inc_step_n(g, tin, c->X, c->m + (n + 1) * M, c->DV, n + 1 < g.nt ? tout : nullptr,
+                     c->DM + (n + 1) * M, s);
+      std::swap(tin, tout);
+    }
   }
-  bl::inc_last_n(g, tin, c->X, c->m + g.nt * M, c->DV, c->L + g.nt * M, c->DM + g.nt * M,
-                 c->DL + g.nt * M, s);
-  const float* uin = c->DL + g.nt * M;   // u^Nt = dlambda^Nt
-  float* ua = c->U0;
-  float* ub = c->U1;
-  for (int n = g.nt - 1; n >= 1; --n) {
-    bl::adj_step_n(g, uin, c->YA, c->L + n * M, c->DV, 1, c->DL + n * M, ua, s);
-    uin = ua;
-    std::swap(ua, ub);
+  const bl::BodyStart b2{{c->T0, c->T1, c->U}};
+  bl::newton_terms(g, c->L, c->DM, c->DV, c->DL, b2, s);
+  if (sweep) {
+    bl::sweep_adj_n(g, c->sweep, c->YA, c->m, c->DL, b2, c->DV, c->DM, c->Bf, sweep_words(c, 1),
+                    c->flag, s);
+  } else {
+    const float* uin = c->DL + g.nt * M;
+    for (int n = g.nt - 1; n >= 0; --n) {
+      float* u = n > 0 ? c->DM + n * M : nullptr;
+      bl::adj_step_n(g, uin, c->YA, c->DL + n * M, u, s);
+      uin = u;
+    }
+    bl::body_force(g, c->DL, c->m, c->Bf, s, nullptr, b2);
   }
-  bl::adj_step_n(g, uin, c->YA, c->L, c->DV, 0, c->DL, nullptr, s);
-  bl::body_force_n(g, c->DL, c->m, c->L, c->DM, c->Bf, s);
   bl::pi_half(g, c->plan, c->Bf, g.dim, c->P, s);
   bl::band_finalize(g, g.dim, c->bd, c->Lhat, c->P, (float)(1.0 / (double)g.M), hout, c->flag, s,
                     1, draw, dot_part, nullptr, nullptr, c->op_done);

@@ -115,6 +115,9 @@ __device__ __forceinline__ int fresh(int v) {
 }
 __device__ __forceinline__ int clampz(int z, int rz) { return z < rz ? z : rz - 1; }
 
+constexpr bool is_inc(int kind) { return kind == SWEEP_INC || kind == SWEEP_INC_N; }
+constexpr bool is_adj(int kind) { return kind == SWEEP_ADJ || kind == SWEEP_ADJ_N; }
+
 // offsets along x, y, z of voxel (t, z)
 typedef float f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ Rsrc ya_rsrc(const SweepArgs& a, const Geo& g) {   // 16 M < 2^32 here
@@ -125,7 +128,7 @@ template <int KIND, int DIM>
 __device__ __forceinline__ void load_offsets(const Geo& g, const Rows<DIM>& rw, const SweepArgs& a,
                                              const Lane& t, int z, float& ox, float& oy, float& oz) {
   const uint32_t off = t.c + rw.at(z);
-  if constexpr (KIND == SWEEP_ADJ) {
+  if constexpr (is_adj(KIND)) {
     const f4 o = __builtin_bit_cast(
         f4, __builtin_amdgcn_raw_buffer_load_b128(ya_rsrc(a, g), (int)(off * 4u), 0, 0));
     ox = o.x;
@@ -226,13 +229,21 @@ __device__ __forceinline__ void store_b(const Geo& g, const Rows<DIM>& rw, const
 
 // step s of a sweep: the plane it reads and the plane it writes
 template <int KIND>
-__device__ __forceinline__ int plane_in(const Geo& g, int s) { return KIND == SWEEP_ADJ ? g.nt - s : s; }
+__device__ __forceinline__ int plane_in(const Geo& g, int s) { return is_adj(KIND) ? g.nt - s : s; }
 template <int KIND>
-__device__ __forceinline__ int plane_out(const Geo& g, int s) { return KIND == SWEEP_ADJ ? g.nt - s - 1 : s + 1; }
+__device__ __forceinline__ int plane_out(const Geo& g, int s) { return is_adj(KIND) ? g.nt - s - 1 : s + 1; }
 
-// the step's value from the interpolated one
+// the plane that step s reads
+template <int KIND>
+__device__ __forceinline__ const float* input(const Geo& g, const SweepArgs& a, int s) {
+  const float* f = KIND == SWEEP_ADJ_N && s == 0 ? a.hs : a.planes;   // u^nt lies with hs
+  return f + (size_t)plane_in<KIND>(g, s) * (size_t)g.M;
+}
+// the step's value from the interpolated one (src: of the Newton adjoint hs, and q is returned)
 template <int KIND>
 __device__ __forceinline__ float finish(const Geo& g, int s, float v, float src, float fac) {
+  if constexpr (KIND == SWEEP_INC_N) return fmaf(g.dt, src, v);
+  if constexpr (KIND == SWEEP_ADJ_N) return fmaf(fac, v, src);
   if constexpr (KIND == SWEEP_INC)
     return s + 1 < g.nt ? fmaf(g.dt, src, v) : g.lam_scale * fmaf(0.5f * g.dt, src, v);
   if constexpr (KIND == SWEEP_ADJ) return fac * v;
@@ -249,7 +260,7 @@ __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, in
   const uint32_t nthr = blockDim.x, nq = ((uint32_t)(g.nx * g.ny) + nthr - 1u) / nthr;
   constexpr int kRuns = DIM == 3 ? 4 : 1;   // ZV planes at a time
   const uint32_t chunks = nq * (uint32_t)((g.nz + ZV * kRuns - 1) / (ZV * kRuns));
-  const uint32_t stages = (uint32_t)g.nt + (KIND == SWEEP_STATE ? 0u : 1u);
+  const uint32_t stages = (uint32_t)g.nt + (KIND == SWEEP_STATE || KIND == SWEEP_ADJ_N ? 0u : 1u);
   for (;;) {
     __syncthreads();
     if (threadIdx.x == 0) sh[0] = (int)add_flag(a.sync + SY_TICKET);
@@ -271,12 +282,12 @@ __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, in
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     Col t;
     const bool column = place(g, (chunk - zb * nq) * nthr, zb * kRuns, t);
-    const int s = KIND == SWEEP_INC ? (int)stage - 1 : (int)stage;   // incremental: -1 is t^0
+    const int s = is_inc(KIND) ? (int)stage - 1 : (int)stage;   // incremental: -1 is t^0
 #pragma unroll 1
     for (int k2 = 0; k2 < kRuns; ++k2, ++t.zb) {
       const bool on = column && t.zb * ZV < g.nz;
       if (on && KIND == SWEEP_ADJ && s == g.nt) {
-        float acc[ZV][3];
+        float acc[ZV][3] = {};
         body_sum<DIM, ZV>(g, t, a.planes, a.m, nullptr, acc);
 #pragma unroll
         for (int zz = 0; zz < ZV; ++zz) {
@@ -287,22 +298,47 @@ __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, in
       } else if (on) {
         float val[ZV], src[ZV] = {}, fac[ZV] = {};
         Tap tp[ZV];
-        if constexpr (KIND == SWEEP_ADJ) taps_ya<DIM, ZV>(g, t, a.YA, tp, fac);
+        if constexpr (is_adj(KIND)) taps_ya<DIM, ZV>(g, t, a.YA, tp, fac);
         else taps_x<DIM, ZV>(g, t, a.X, tp);
-        if constexpr (KIND == SWEEP_INC) source_f<DIM, ZV>(g, t, a.m + (size_t)(s + 1) * M, a.dv, src);
+        if constexpr (is_inc(KIND)) source_f<DIM, ZV>(g, t, a.m + (size_t)(s + 1) * M, a.dv, src);
         if (s < 0) {
 #pragma unroll
           for (int zz = 0; zz < ZV; ++zz) val[zz] = 0.5f * g.dt * src[zz];
         } else {
-          gather_zv<DIM, ZV>(g, field_rsrc(a.planes + (size_t)plane_in<KIND>(g, s) * M, g), tp, val);
+          const int n = plane_out<KIND>(g, s);
+          gather_zv<DIM, ZV>(g, field_rsrc(input<KIND>(g, a, s), g), tp, val);
 #pragma unroll
-          for (int zz = 0; zz < ZV; ++zz) val[zz] = finish<KIND>(g, s, val[zz], src[zz], fac[zz]);
+          for (int zz = 0; zz < ZV; ++zz) {
+            VOXEL(zz)
+            if constexpr (KIND == SWEEP_INC_N) {
+              if (live) st(field_rsrc(a.dm + (size_t)n * M, g), t.c, zo, fmaf(0.5f * g.dt, src[zz], val[zz]));
+            }
+            if constexpr (KIND == SWEEP_ADJ_N) src[zz] = n > 0 ? ld(field_rsrc(a.hs + (size_t)n * M, g), t.c, zo) : 0.f;
+            val[zz] = finish<KIND>(g, s, val[zz], src[zz], fac[zz]);
+            if constexpr (KIND == SWEEP_ADJ_N) {   // b so far, in acc (others may still read b2)
+              const float wn = n == 0 ? 0.5f * g.dt : g.dt;
+              const float first = s == 0 ? 0.5f * g.dt * ld(field_rsrc(input<KIND>(g, a, 0), g), t.c, zo) : 0.f;
+              float gr[3], g0[3];
+              grad_c<DIM>(g, field_rsrc(a.m + (size_t)n * M, g), t, zo, zm, zp, gr);
+              if (s == 0) grad_c<DIM>(g, field_rsrc(a.m + (size_t)g.nt * M, g), t, zo, zm, zp, g0);
+              for (int c = 0; c < DIM; ++c) {
+                float b = ld(field_rsrc(s == 0 ? a.b2.c[c] : a.acc + c * M, g), t.c, zo);
+                if (s == 0) b = fmaf(first, g0[c], b);
+                b = fmaf(wn * val[zz], gr[c], b);
+                if (live) st_dev(field_rsrc((n == 0 ? a.b : a.acc) + c * M, g), t.c + zo, b);
+              }
+              val[zz] += src[zz];
+            }
+          }
         }
-        const Rsrc out = field_rsrc(a.planes + (size_t)(s < 0 ? 0 : plane_out<KIND>(g, s)) * M, g);
+        const int n = s < 0 ? 0 : plane_out<KIND>(g, s);
+        if (KIND == SWEEP_INC_N ? n < g.nt : KIND == SWEEP_ADJ_N ? n > 0 : true) {
+          const Rsrc out = field_rsrc(a.planes + (size_t)n * M, g);
 #pragma unroll
-        for (int zz = 0; zz < ZV; ++zz) {
-          VOXEL(zz)
-          if (live) st_dev(out, t.c + zo, val[zz]);
+          for (int zz = 0; zz < ZV; ++zz) {
+            VOXEL(zz)
+            if (live) st_dev(out, t.c + zo, val[zz]);
+          }
         }
       }
     }
@@ -423,8 +459,8 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
       atomicMax(&sh[3], zhi);
     }
     __syncthreads();
-    if constexpr (KIND == SWEEP_INC) load_m(0);
-    if constexpr (KIND == SWEEP_ADJ) load_m(g.nt);
+    if constexpr (is_inc(KIND)) load_m(0);
+    if constexpr (is_adj(KIND)) load_m(g.nt);
     // the box: the tile's own rows and every row its taps reach
     ylo = DIM == 2 || fully ? 0 : min(sh[0], y0);
     yhi = DIM == 2 ? 0 : fully ? rw.ry : max(sh[1] + 1, y0 + ey - 1);
@@ -504,13 +540,23 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
         if (r < run) st_dev(out, t.c + rw.at(z + r), v[r]);
     };
 
-    float val[R], fx[R] = {}, fy[R] = {}, fz[R] = {}, dv[KIND == SWEEP_INC ? DIM : 1][R] = {};
+    float val[R], fx[R] = {}, fy[R] = {}, fz[R] = {}, dv[is_inc(KIND) ? DIM : 1][R] = {};
     float src[R] = {}, fac[R] = {};
-    if constexpr (KIND == SWEEP_ADJ) {
+    if constexpr (KIND == SWEEP_ADJ_N) {
+      auto start = [&](int c, float (&f)[R]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          f[r] = ld(field_rsrc(a.b2.c[c], g), t.c + rw.at(clampz(t.z0 + r, rw.rz)), 0);
+      };
+      start(0, fx);
+      start(1, fy);
+      if constexpr (DIM == 3) start(2, fz);
+    }
+    if constexpr (is_adj(KIND)) {
 #pragma unroll
       for (int r = 0; r < R; ++r) fac[r] = load_factor<DIM>(g, rw, a, t, clampz(t.z0 + r, rw.rz));
     }
-    if constexpr (KIND == SWEEP_INC) {
+    if constexpr (is_inc(KIND)) {
       load_dv<DIM, R>(g, rw, t, a.dv, dv);
       stores_done();
       __syncthreads();
@@ -526,13 +572,13 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
       if (!bail) publish(1u);   // (an abandoned tile has stored nothing)
       source<DIM, R>(g, st, dv, src);
     } else {
-      const Rsrc in = field_rsrc(a.planes + (size_t)plane_in<KIND>(g, 0) * M, g);
+      const Rsrc in = field_rsrc(input<KIND>(g, a, 0), g);
 #pragma unroll
       for (int r = 0; r < R; ++r) val[r] = ld(in, t.c + rw.at(clampz(t.z0 + r, rw.rz)), 0);
       put(val);
-      if constexpr (KIND == SWEEP_ADJ) stores_done();
+      if constexpr (is_adj(KIND)) stores_done();
       __syncthreads();
-      if constexpr (KIND == SWEEP_ADJ) add_node<DIM, R>(g, st, g.nt, val, fx, fy, fz);
+      if constexpr (is_adj(KIND)) add_node<DIM, R>(g, st, g.nt, val, fx, fy, fz);
     }
     // an entry of the other tiles' rows: where it comes from, and floats of the box | tile << 16
     auto entry = [&](uint32_t e, uint32_t& from, uint32_t& to) {
@@ -544,10 +590,10 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
     };
 
     for (int s = 0; s < g.nt && !bail; ++s) {
-      const Rsrc in = field_rsrc(a.planes + (size_t)plane_in<KIND>(g, s) * M, g);
+      const Rsrc in = field_rsrc(input<KIND>(g, a, s), g);
       // progress the other tiles must show: this step's input plane (the first one of the state
       // and adjoint sweeps is there before the launch)
-      const uint32_t need = (uint32_t)s + (KIND == SWEEP_INC ? 1u : 0u);
+      const uint32_t need = (uint32_t)s + (is_inc(KIND) ? 1u : 0u);
       bool out_of_time = false;
       auto wait = [&](uint32_t ta, uint32_t tb) {
         if (need == 0) return;
@@ -601,10 +647,16 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
       }
       const int n = plane_out<KIND>(g, s);
       // the plane of the next stencils: the last ones that used the buffer are done
-      if constexpr (KIND == SWEEP_INC) {
+      if constexpr (is_inc(KIND)) {
         if (s + 2 <= g.nt) load_m(s + 2);
       }
-      if constexpr (KIND == SWEEP_ADJ) load_m(n);
+      if constexpr (is_adj(KIND)) load_m(n);
+      if constexpr (KIND == SWEEP_ADJ_N) {
+        const Rsrc rh = field_rsrc(a.hs + (size_t)n * M, g);
+        const int z = fresh(t.z0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) src[r] = n > 0 ? ld(rh, t.c + rw.at(clampz(z + r, rw.rz)), 0) : 0.f;
+      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const uint32_t pair = (uint32_t)fresh((int)ad[r / 2]);
@@ -624,27 +676,38 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
           v[2] = q2[0];
           v[3] = q2[1];
         }
-        val[r] = finish<KIND>(g, s, blend<DIM>(v, wx[r], wy[r], wz[r]), src[r], fac[r]);
+        const float at = blend<DIM>(v, wx[r], wy[r], wz[r]);
+        if constexpr (KIND == SWEEP_INC_N) {
+          const uint32_t o = t.c + rw.at(fresh(t.z0) + r);
+          if (r < run) ::bl::st(field_rsrc(a.dm + (size_t)n * M, g), o, 0, fmaf(0.5f * g.dt, src[r], at));
+        }
+        val[r] = finish<KIND>(g, s, at, src[r], fac[r]);
         // few voxels' corners at a time: more would not fit the registers
         if (R > 4 && (KIND == SWEEP_STATE ? (r & 1) : true)) __builtin_amdgcn_sched_barrier(0);
       }
       const bool more = s + 1 < g.nt;
-      if (KIND != SWEEP_ADJ || n > 0 || a.keep0) store(n, val);
-      if (more || KIND == SWEEP_ADJ) {
+      if constexpr (KIND == SWEEP_ADJ_N) {   // q^n meets grad m^n, u^n = q^n + hs^n goes on
+#pragma unroll
+        for (int r = 0; r < R; ++r) src[r] += val[r];
+        if (n > 0) store(n, src);
+      } else if (KIND == SWEEP_INC_N ? more : KIND != SWEEP_ADJ || n > 0 || a.keep0) {
+        store(n, val);
+      }
+      if (more || is_adj(KIND)) {
         __syncthreads();   // every gather of this step is done
-        if (more) put(val);
+        if (more) put(KIND == SWEEP_ADJ_N ? src : val);
         stores_done();
         __syncthreads();
-        if (more) publish((uint32_t)s + (KIND == SWEEP_INC ? 2u : 1u));
+        if (more) publish((uint32_t)s + (is_inc(KIND) ? 2u : 1u));
       }
-      if constexpr (KIND == SWEEP_INC) {
+      if constexpr (is_inc(KIND)) {
         if (more) source<DIM, R>(g, st, dv, src);
       }
-      if constexpr (KIND == SWEEP_ADJ) add_node<DIM, R>(g, st, n, val, fx, fy, fz);
+      if constexpr (is_adj(KIND)) add_node<DIM, R>(g, st, n, val, fx, fy, fz);
     }
     if (bail) {   // the same for every thread of the block
       run_tickets<KIND, DIM>(g, a, sh);
-    } else if constexpr (KIND == SWEEP_ADJ) {
+    } else if constexpr (is_adj(KIND)) {
       store_b<DIM, R>(g, rw, t, a.b, fx, fy, fz);
     }
   }
@@ -770,6 +833,34 @@ void sweep_adj(const Geo& g, const SweepPlan& p, const float4* YA, const float* 
   a.sync = sync;
   a.nonfinite = nonfinite;
   launch_kind<SWEEP_ADJ>(g, p, a, s);
+}
+
+void sweep_inc_n(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
+                 float* t, float* dm, uint32_t* sync, int* nonfinite, hipStream_t s) {
+  SweepArgs a{};
+  a.X = X;
+  a.planes = t;
+  a.m = m;
+  a.dv = dv;
+  a.dm = dm;
+  a.sync = sync;
+  a.nonfinite = nonfinite;
+  launch_kind<SWEEP_INC_N>(g, p, a, s);
+}
+void sweep_adj_n(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, const float* hs,
+                 const BodyStart& b2, float* acc, float* u, float* b, uint32_t* sync, int* nonfinite,
+                 hipStream_t s) {
+  SweepArgs a{};
+  a.YA = YA;
+  a.planes = u;
+  a.m = m;
+  a.hs = hs;
+  a.b2 = b2;
+  a.acc = acc;
+  a.b = b;
+  a.sync = sync;
+  a.nonfinite = nonfinite;
+  launch_kind<SWEEP_ADJ_N>(g, p, a, s);
 }
 
 }  // namespace bl

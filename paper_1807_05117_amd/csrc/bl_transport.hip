@@ -171,7 +171,7 @@ template <int DIM, int ZV>
 __global__ __launch_bounds__(kTB) void k_body_force(Geo g, const float* __restrict__ lam,
                                                     const float* __restrict__ m,
                                                     float* __restrict__ b,
-                                                    const float4* __restrict__ YA) {
+                                                    const float4* __restrict__ YA, BodyStart b0) {
   BL_BATCH_Z1(g.bat)
   BL_AT_NN(lam, g.bat);
   BL_AT_NN(m, g.bat);
@@ -180,6 +180,12 @@ __global__ __launch_bounds__(kTB) void k_body_force(Geo g, const float* __restri
   COLUMN
   const size_t M = (size_t)g.M;
   float acc[ZV][3];
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    for (int c = 0; c < 3; ++c)
+      acc[zz][c] = c < DIM && b0.c[c] ? ld(field_rsrc(batch_ptr_nn(b0.c[c], g.bat, bpair_), g), t.c, zo) : 0.f;
+  }
   body_sum<DIM, ZV>(g, t, lam, m, YA, acc);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
@@ -196,25 +202,15 @@ __global__ __launch_bounds__(kTB) void k_body_force(Geo g, const float* __restri
 //   q^Nt = -(2/sigma^2) dm^Nt,  dlambda^Nt = u^Nt = q^Nt + dt/2 s^Nt,
 //   q^n = a Interp(u^{n+1}, i + Y) + dt/2 s^n,  dlambda^n = q^n,  u^n = q^n + dt/2 s^n  (0 < n < Nt),
 //   dlambda^0 = a Interp(u^1, i + Y).
+// One pass over all time nodes (k_newton_terms) forms what does not depend on the adjoint: dt/2 s^n
+// and the body force's second term.  The adjoint steps then read one field more than the
+// Gauss-Newton ones, and both they and the incremental state run as sweeps where those do
+// (bl_sweep.hip).  At 128^3 with ten steps (us): incremental state 92 (184 as steps), terms 92,
+// adjoint with the body force 105.  Steps that formed s^n themselves took 182 and a body force of
+// both terms 100; as steps it is 148 + 54 now.
 
-// central-difference divergence of lambda dv: sum_j (lam dv_j)(i + e_j) - (i - e_j)
-template <int DIM, int ZV>
-__device__ __forceinline__ void div_lam_dv(const Geo& g, const Col& t, const float* lam,
-                                           const float* dv, float (&out)[ZV]) {
-  const Rsrc rl = field_rsrc(lam, g);
-  const Vec<DIM> rd = vec_rsrc<DIM>(dv, g);
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    VOXEL(zz)
-    float s = ld(rl, t.xp, zo) * ld(rd.c[0], t.xp, zo) - ld(rl, t.xm, zo) * ld(rd.c[0], t.xm, zo);
-    s += ld(rl, t.yp, zo) * ld(rd.c[1], t.yp, zo) - ld(rl, t.ym, zo) * ld(rd.c[1], t.ym, zo);
-    if constexpr (DIM == 3)
-      s += ld(rl, t.c, zp) * ld(rd.c[2], t.c, zp) - ld(rl, t.c, zm) * ld(rd.c[2], t.c, zm);
-    out[zz] = s * g.half_nref;
-  }
-}
-
-// incremental state step that also stores dm^{n+1} = Interp(t^n, i + X) + dt/2 f^{n+1}
+// incremental state step that also stores dm^{n+1} = Interp(t^n, i + X) + dt/2 f^{n+1} (t_out
+// null: the last step)
 template <int DIM, int ZV>
 __global__ __launch_bounds__(kTB) void k_inc_step_n(Geo g, const float* __restrict__ t_in,
                                                     const float* __restrict__ X,
@@ -227,7 +223,7 @@ __global__ __launch_bounds__(kTB) void k_inc_step_n(Geo g, const float* __restri
   BL_AT_NN(X, g.bat);
   BL_AT_NN(m_next, g.bat);
   BL_AT_NN(dv, g.bat);
-  BL_AT_NN(t_out, g.bat);
+  BL_AT(t_out, g.bat);
   BL_AT_NN(dm_out, g.bat);
   COLUMN
   Tap tp[ZV];
@@ -240,142 +236,124 @@ __global__ __launch_bounds__(kTB) void k_inc_step_n(Geo g, const float* __restri
     dmv[zz] = fmaf(0.5f * g.dt, src[zz], val[zz]);
     val[zz] = fmaf(g.dt, src[zz], val[zz]);
   }
-  store_zv<ZV>(g, t, t_out, val);
+  if (t_out) store_zv<ZV>(g, t, t_out, val);
   store_zv<ZV>(g, t, dm_out, dmv);
 }
 
-// last incremental state step: dm^Nt, and dlambda^Nt = u^Nt = -(2/sigma^2) dm^Nt + dt/2 s^Nt
+// hs^n = dt/2 s^n for 0 < n < Nt, u^Nt in plane Nt of hs, and b2 = sum_n w_n lambda^n grad dm^n
+// (dm^0 = 0); the nodes in turn, dv around the voxels in registers, z neighbours from sliding
+// windows as in body_sum
 template <int DIM, int ZV>
-__global__ __launch_bounds__(kTB) void k_inc_last_n(Geo g, const float* __restrict__ t_in,
-                                                    const float* __restrict__ X,
-                                                    const float* __restrict__ mT,
-                                                    const float* __restrict__ dv,
-                                                    const float* __restrict__ lamT,
-                                                    float* __restrict__ dm_out,
-                                                    float* __restrict__ dlam) {
-  BL_BATCH_Z1(g.bat)
-  BL_AT_NN(t_in, g.bat);
-  BL_AT_NN(X, g.bat);
-  BL_AT_NN(mT, g.bat);
-  BL_AT_NN(dv, g.bat);
-  BL_AT_NN(lamT, g.bat);
-  BL_AT_NN(dm_out, g.bat);
-  BL_AT_NN(dlam, g.bat);
-  COLUMN
-  Tap tp[ZV];
-  float src[ZV], dmv[ZV], val[ZV];
-  taps_x<DIM, ZV>(g, t, X, tp);
-  source_f<DIM, ZV>(g, t, mT, dv, src);
-  div_lam_dv<DIM, ZV>(g, t, lamT, dv, val);
-  gather_zv<DIM, ZV>(g, field_rsrc(t_in, g), tp, dmv);
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    dmv[zz] = fmaf(0.5f * g.dt, src[zz], dmv[zz]);
-    val[zz] = fmaf(0.5f * g.dt, val[zz], g.lam_scale * dmv[zz]);
-  }
-  store_zv<ZV>(g, t, dm_out, dmv);
-  store_zv<ZV>(g, t, dlam, val);
-}
-
-// one incremental adjoint step of the Newton product: q = a Interp(u^{n+1}, i + Y) (+ dt/2 s^n
-// when own); dlambda^n = q; with u_out, u^n = q + dt/2 s^n
-template <int DIM, int ZV>
-__global__ __launch_bounds__(kTB) void k_adj_step_n(Geo g, const float* __restrict__ u_in,
-                                                    const float4* __restrict__ YA,
-                                                    const float* __restrict__ lam_n,
-                                                    const float* __restrict__ dv, int own,
-                                                    float* __restrict__ dlam,
-                                                    float* __restrict__ u_out) {
-  BL_BATCH_Z1(g.bat)
-  BL_AT_NN(u_in, g.bat);
-  BL_AT_NN(YA, g.bat);
-  BL_AT_NN(lam_n, g.bat);
-  BL_AT_NN(dv, g.bat);
-  BL_AT_NN(dlam, g.bat);
-  BL_AT(u_out, g.bat);
-  COLUMN
-  Tap tp[ZV];
-  float aw[ZV], hs[ZV], qv[ZV], uv[ZV];
-  taps_ya<DIM, ZV>(g, t, YA, tp, aw);
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) hs[zz] = 0.f;
-  if (own) {
-    div_lam_dv<DIM, ZV>(g, t, lam_n, dv, hs);
-#pragma unroll
-    for (int zz = 0; zz < ZV; ++zz) hs[zz] = 0.5f * g.dt * hs[zz];
-  }
-  gather_zv<DIM, ZV>(g, field_rsrc(u_in, g), tp, qv);
-#pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) {
-    qv[zz] = aw[zz] * qv[zz] + hs[zz];
-    uv[zz] = qv[zz] + hs[zz];
-  }
-  store_zv<ZV>(g, t, dlam, qv);
-  if (u_out) store_zv<ZV>(g, t, u_out, uv);
-}
-
-// Newton body force: sum_n w_n (dlambda^n grad m^n + lambda^n grad dm^n); the node loop is
-// outside the thread's z run and the z differences of m^n and dm^n come from sliding windows,
-// as in k_body_force
-template <int DIM, int ZV>
-__global__ __launch_bounds__(kTB) void k_body_force_n(Geo g, const float* __restrict__ dlam,
-                                                      const float* __restrict__ m,
-                                                      const float* __restrict__ lam,
+__global__ __launch_bounds__(kTB) void k_newton_terms(Geo g, const float* __restrict__ lam,
                                                       const float* __restrict__ dm,
-                                                      float* __restrict__ b) {
+                                                      const float* __restrict__ dv,
+                                                      float* __restrict__ hs, float* __restrict__ bx,
+                                                      float* __restrict__ by, float* __restrict__ bz) {
   BL_BATCH_Z1(g.bat)
-  BL_AT_NN(dlam, g.bat);
-  BL_AT_NN(m, g.bat);
   BL_AT_NN(lam, g.bat);
   BL_AT_NN(dm, g.bat);
-  BL_AT_NN(b, g.bat);
+  BL_AT_NN(dv, g.bat);
+  BL_AT_NN(hs, g.bat);
+  BL_AT_NN(bx, g.bat);
+  BL_AT_NN(by, g.bat);
+  BL_AT_NN(bz, g.bat);
   COLUMN
   const size_t M = (size_t)g.M;
-  float acc[ZV][3];
+  const Vec<DIM> rd = vec_rsrc<DIM>(dv, g);
+  float d[ZV][6], acc[ZV][3];
 #pragma unroll
-  for (int zz = 0; zz < ZV; ++zz) acc[zz][0] = acc[zz][1] = acc[zz][2] = 0.f;
-  for (int n = 0; n <= g.nt; ++n) {
-    const float w = (n == 0 || n == g.nt) ? 0.5f * g.dt : g.dt;
-    const Rsrc rm = field_rsrc(m + n * M, g), rd = field_rsrc(dm + n * M, g);
-    const Rsrc rq = field_rsrc(dlam + n * M, g), rl = field_rsrc(lam + n * M, g);
-    float mprev = 0.f, mcur = 0.f, dprev = 0.f, dcur = 0.f;
-    if (DIM == 3) {
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    d[zz][0] = ld(rd.c[0], t.xm, zo);
+    d[zz][1] = ld(rd.c[0], t.xp, zo);
+    d[zz][2] = ld(rd.c[1], t.ym, zo);
+    d[zz][3] = ld(rd.c[1], t.yp, zo);
+    d[zz][4] = d[zz][5] = 0.f;
+    if constexpr (DIM == 3) {
+      d[zz][4] = ld(rd.c[2], t.c, zm);
+      d[zz][5] = ld(rd.c[2], t.c, zp);
+    }
+    acc[zz][0] = acc[zz][1] = acc[zz][2] = 0.f;
+  }
+  for (int n = g.nt; n >= 1; --n) {
+    const float w = n == g.nt ? 0.5f * g.dt : g.dt;
+    const Rsrc rl = field_rsrc(lam + n * M, g), rm = field_rsrc(dm + n * M, g);
+    const Rsrc out = field_rsrc(hs + n * M, g);
+    float lprev = 0.f, lcur = 0.f, prev = 0.f, cur = 0.f;
+    {
       VOXEL(0)
-      mprev = ld(rm, t.c, zm);
-      mcur = ld(rm, t.c, zo);
-      dprev = ld(rd, t.c, zm);
-      dcur = ld(rd, t.c, zo);
+      lcur = ld(rl, t.c, zo);
+      cur = ld(rm, t.c, zo);
+      if (DIM == 3) {
+        lprev = ld(rl, t.c, zm);
+        prev = ld(rm, t.c, zm);
+      }
     }
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz) {
       VOXEL(zz)
-      float gr[3], gd[3];
-      gr[0] = (ld(rm, t.xp, zo) - ld(rm, t.xm, zo)) * g.half_nref;
-      gr[1] = (ld(rm, t.yp, zo) - ld(rm, t.ym, zo)) * g.half_nref;
-      gd[0] = (ld(rd, t.xp, zo) - ld(rd, t.xm, zo)) * g.half_nref;
-      gd[1] = (ld(rd, t.yp, zo) - ld(rd, t.ym, zo)) * g.half_nref;
-      gr[2] = gd[2] = 0.f;
+      float lnext = 0.f, next = 0.f;
       if (DIM == 3) {
-        const float mnext = ld(rm, t.c, zp), dnext = ld(rd, t.c, zp);
-        gr[2] = (mnext - mprev) * g.half_nref;
-        gd[2] = (dnext - dprev) * g.half_nref;
-        mprev = mcur;
-        mcur = mnext;
-        dprev = dcur;
-        dcur = dnext;
+        lnext = ld(rl, t.c, zp);
+        next = ld(rm, t.c, zp);
       }
-      const float wl = w * ld(rq, t.c, zo);
-      const float wa = w * ld(rl, t.c, zo);
-#pragma unroll
-      for (int c = 0; c < DIM; ++c) acc[zz][c] = fmaf(wa, gd[c], fmaf(wl, gr[c], acc[zz][c]));
+      const float gx = (ld(rm, t.xp, zo) - ld(rm, t.xm, zo)) * g.half_nref;
+      const float gy = (ld(rm, t.yp, zo) - ld(rm, t.ym, zo)) * g.half_nref;
+      const float wl = w * lcur;
+      acc[zz][0] = fmaf(wl, gx, acc[zz][0]);
+      acc[zz][1] = fmaf(wl, gy, acc[zz][1]);
+      if (DIM == 3) acc[zz][2] = fmaf(wl, (next - prev) * g.half_nref, acc[zz][2]);
+      const float s = div_lam_dv<DIM>(ld(rl, t.xm, zo), ld(rl, t.xp, zo), ld(rl, t.ym, zo),
+                                      ld(rl, t.yp, zo), lprev, lnext, d[zz]) * g.half_nref;
+      const float h = 0.5f * g.dt * s;
+      // (2D: one voxel per thread, so cur is its own)
+      if (live) st(out, t.c, zo, n == g.nt ? g.lam_scale * cur + h : h);
+      lprev = lcur;
+      lcur = lnext;
+      prev = cur;
+      cur = next;
     }
   }
+  const Rsrc r0 = field_rsrc(bx, g), r1 = field_rsrc(by, g), r2 = field_rsrc(bz, g);
 #pragma unroll
   for (int zz = 0; zz < ZV; ++zz) {
     VOXEL(zz)
-    if (live)
-      for (int c = 0; c < DIM; ++c) st(field_rsrc(b + c * M, g), t.c, zo, acc[zz][c]);
+    if (!live) continue;
+    st(r0, t.c, zo, acc[zz][0]);
+    st(r1, t.c, zo, acc[zz][1]);
+    if (DIM == 3) st(r2, t.c, zo, acc[zz][2]);
   }
+}
+
+// one incremental adjoint step of the Newton product: q^n = a Interp(u^{n+1}, i + Y) + hs^n in
+// place of hs^n, u^n = q^n + hs^n (u_out null: the last step, without hs)
+template <int DIM, int ZV>
+__global__ __launch_bounds__(kTB) void k_adj_step_n(Geo g, const float* __restrict__ u_in,
+                                                    const float4* __restrict__ YA,
+                                                    float* __restrict__ hs, float* __restrict__ u_out) {
+  BL_BATCH_Z1(g.bat)
+  BL_AT_NN(u_in, g.bat);
+  BL_AT_NN(YA, g.bat);
+  BL_AT_NN(hs, g.bat);
+  BL_AT(u_out, g.bat);
+  COLUMN
+  Tap tp[ZV];
+  float aw[ZV], h[ZV], q[ZV], u[ZV];
+  taps_ya<DIM, ZV>(g, t, YA, tp, aw);
+  const Rsrc rh = field_rsrc(hs, g);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    VOXEL(zz)
+    h[zz] = u_out ? ld(rh, t.c, zo) : 0.f;
+  }
+  gather_zv<DIM, ZV>(g, field_rsrc(u_in, g), tp, q);
+#pragma unroll
+  for (int zz = 0; zz < ZV; ++zz) {
+    q[zz] = fmaf(aw[zz], q[zz], h[zz]);
+    u[zz] = q[zz] + h[zz];
+  }
+  store_zv<ZV>(g, t, hs, q);
+  if (u_out) store_zv<ZV>(g, t, u_out, u);
 }
 
 // b^n = lambda^n grad m^n at the time node n = blockIdx.y (a non-stationary gradient or
@@ -549,8 +527,8 @@ void adj_step(const Geo& g, const float* lam_in, const float4* YA, float* lam_ou
   DISPATCH_GATHER(k_adj_step, TR_ADJ, g, lam_in, YA, lam_out);
 }
 void body_force(const Geo& g, const float* lam, const float* m, float* b, hipStream_t s,
-                const float4* YA) {
-  DISPATCH_GATHER(k_body_force, TR_FORCE, g, lam, m, b, YA);
+                const float4* YA, BodyStart b0) {
+  DISPATCH_GATHER(k_body_force, TR_FORCE, g, lam, m, b, YA, b0);
 }
 void inc_init(const Geo& g, const float* m0, const float* dv, float* t0, hipStream_t s) {
   DISPATCH_GATHER(k_inc_init, TR_INC, g, m0, dv, t0);
@@ -567,17 +545,13 @@ void inc_step_n(const Geo& g, const float* t_in, const float* X, const float* m_
                 const float* dv, float* t_out, float* dm_out, hipStream_t s) {
   DISPATCH_GATHER(k_inc_step_n, TR_INC, g, t_in, X, m_next, dv, t_out, dm_out);
 }
-void inc_last_n(const Geo& g, const float* t_in, const float* X, const float* mT,
-                const float* dv, const float* lamT, float* dm_out, float* dlam, hipStream_t s) {
-  DISPATCH_GATHER(k_inc_last_n, TR_INC, g, t_in, X, mT, dv, lamT, dm_out, dlam);
+void newton_terms(const Geo& g, const float* lam, const float* dm, const float* dv, float* hs,
+                  const BodyStart& b2, hipStream_t s) {
+  DISPATCH_GATHER(k_newton_terms, TR_FORCE, g, lam, dm, dv, hs, b2.c[0], b2.c[1], b2.c[2]);
 }
-void adj_step_n(const Geo& g, const float* u_in, const float4* YA, const float* lam_n,
-                const float* dv, int own, float* dlam, float* u_out, hipStream_t s) {
-  DISPATCH_GATHER(k_adj_step_n, TR_ADJ, g, u_in, YA, lam_n, dv, own, dlam, u_out);
-}
-void body_force_n(const Geo& g, const float* dlam, const float* m, const float* lam,
-                  const float* dm, float* b, hipStream_t s) {
-  DISPATCH_GATHER(k_body_force_n, TR_FORCE, g, dlam, m, lam, dm, b);
+void adj_step_n(const Geo& g, const float* u_in, const float4* YA, float* hs, float* u_out,
+                hipStream_t s) {
+  DISPATCH_GATHER(k_adj_step_n, TR_ADJ, g, u_in, YA, hs, u_out);
 }
 void energy_partial(const Geo& g, const float* mT, const float* I1, double* partial,
                     hipStream_t s, float* lam) {

@@ -156,3 +156,21 @@ def test_graph_replays(gpu_lib):
             s.synchronize()
             assert torch.isfinite(torch.view_as_real(eager)).all()
         ctx.close()
+
+
+@pytest.mark.parametrize("n,k", [((128, 128, 128), (16, 16, 16)), ((33, 21, 13), (8, 8, 4)),
+                                 ((130, 50, 37), (8, 8, 8)), ((8, 8, 8), (4, 4, 4)), ((96, 40), (8, 8)),
+                                 ((300, 200), (16, 16))])
+@pytest.mark.parametrize("nt,disp", [(4, 3.0), (1, 1.0), (3, 60.0)])
+def test_newton_products(gpu_lib, n, k, nt, disp):
+    """the Newton product's sweeps (at 60 voxels finished by tickets) against its steps"""
+    prob, I0, I1, vs, dv = _inputs(n, k, nt, disp)
+    ctx = B.Ctx(bl_problem(prob, newton=True), I0, I1)
+    got = _results(ctx, prob, vs, dv)
+    ctx.bl_kernel_timing_enable(True)
+    ref = _results(ctx, prob, vs, dv)
+    ctx.bl_kernel_timing_enable(False)
+    again = _results(ctx, prob, vs, dv)
+    ctx.close()
+    assert _same(got, ref)
+    assert _same(again, ref)
