@@ -2,16 +2,15 @@
 //
 // One Runge-Kutta stage (or one stage of the transposed sweep) is three launches instead of a
 // chain of separate transform, product and band kernels:
-//   1. xy:  band (kz >= 0 half) -> F2[c][h][y][x]: the x and y contractions of iota for one
-//           (component, h) plane and a chunk of x, the band plane staged in LDS.  In the
-//           derivative form the components are the spectral derivatives d~_j U_i (c = i dim + j)
-//           formed on the fly from the state U.
+//   1. xy:  band (kz >= 0 half) -> F2[c][h][y][x]: the x and y contractions of iota
+//           (bl_dft_mfma.hip).  In the derivative form the components are the spectral derivatives
+//           d~_j U_i (c = i dim + j) formed on the fly from the state U.
 //   2. col: per (y, x) column of the product grid: the z contraction of iota, the pointwise
 //           products (and their side outputs), and the z contraction of pi, the column's z
 //           values exchanged through LDS; two lanes per column split the kz spectrum.
-//   3. yx:  G[c][h][y][x] -> the band: the x and y contractions of pi for one (component, h)
-//           plane and a chunk of kx, the G plane staged in LDS (the transposed sweep stages
-//           its three derivative planes together), followed by the band-side update of the
+//   3. yx:  G[c][h][y][x] -> the band: the x and y contractions of pi for 16 ky by 32 kx of one
+//           (component, h) plane (the transposed sweep takes its three derivative planes
+//           together), followed by the band-side update of the
 //           stage (forward) or of the transposed sweep (backward) at kz = h and at the
 //           conjugate-mirror index -k.  On the kz = 0 plane the entry k is owned by the half
 //           ky > 0 or (ky = 0, kx >= 0); its owner writes k and -k, so the result is exactly
@@ -20,31 +19,16 @@
 // These kernels are bound by memory latency at ~1.5 waves per SIMD, so every global load a
 // phase needs is issued before its first wait: no load sits behind a condition (a guarded load
 // compiles to a branch and a wait) and no runtime loop alternates loads and LDS stores.
-#include "bl_internal.h"
+#include <algorithm>
 
-#include <mutex>
+#include "bl_mfma.h"
 
 namespace bl {
 namespace {
 
 constexpr int kColW = 32;     // columns per column-kernel block (two lanes each)
 constexpr int kColWaves = 8;  // waves per column-kernel block
-constexpr int kXC = 16;       // x outputs per iota xy block
-constexpr int kKC = 4;        // kx outputs per pi yx block
 
-__device__ __forceinline__ void cmac(float2& acc, float2 a, float2 b) {
-  acc.x = fmaf(a.x, b.x, acc.x);
-  acc.x = fmaf(-a.y, b.y, acc.x);
-  acc.y = fmaf(a.x, b.y, acc.y);
-  acc.y = fmaf(a.y, b.x, acc.y);
-}
-// acc += a * conj(b)
-__device__ __forceinline__ void cmac_conj(float2& acc, float2 a, float2 b) {
-  acc.x = fmaf(a.x, b.x, acc.x);
-  acc.x = fmaf(a.y, b.y, acc.x);
-  acc.y = fmaf(a.y, b.x, acc.y);
-  acc.y = fmaf(-a.x, b.y, acc.y);
-}
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // q = 2 pi k / l of band index j on axis a (l from the image grid)
@@ -76,122 +60,6 @@ struct Stager {
     }
   }
 };
-
-// ---------------------------------------------------------------------------- 1. iota xy
-// block (c * kzh + h, x chunk); F2[c][h][y][x] = sum_ky sum_kx S[ky][kx] Tx[kx][x] Ty[ky][y]
-// with S the band plane kz = h of component c (deriv: i q_j U_i for c = i dim + j).  The band
-// plane and the twiddles the block needs are staged in LDS first (all loads in flight at once).
-__global__ __launch_bounds__(256) void k_fx_iota_xy(Geo g, Geo gp, const float2* __restrict__ in,
-                                                    int deriv, const float2* __restrict__ tw_x,
-                                                    const float2* __restrict__ tw_y, int nyp,
-                                                    float2* __restrict__ F2) {
-  extern __shared__ float2 lds[];
-  const int KX = g.kx, KY = g.ky, PX = gp.nx, PY = gp.ny;
-  const int SX = KX + 1;                // padded row: rows fall in different LDS banks
-  float2* S = lds;                      // [KY][SX]
-  float2* T = S + (size_t)KY * SX;      // [KY][kXC]
-  float2* Txc = T + (size_t)KY * kXC;   // [KX][kXC]
-  float2* Ty = Txc + (size_t)KX * kXC;  // [KY][PY]
-  const int ch = blockIdx.x;
-  const int c = ch / g.kzh, h = ch - c * g.kzh;
-  const int x0 = blockIdx.y * kXC;
-  const int jz = g.kz0 + h;
-  const int d = g.dim;
-  const int ci = deriv ? c / d : c;
-  const int cj = deriv ? c - ci * d : 0;
-  const float2* plane = in + ((size_t)ci * g.kz + jz) * KY * KX;
-  // the band plane and both twiddle tables, all loads of a round in flight together (one round
-  // up to a 32 x 32 band and 48 y values)
-  const int nS = KY * KX, nX = KX * kXC, nY = KY * PY;
-  const int rounds = max(max((nS + 1023) / 1024, (nX + 511) / 512), (nY + 1535) / 1536);
-  for (int r = 0; r < rounds; ++r) {
-    Stager<256, 4> sS;
-    Stager<256, 2> sX;
-    Stager<256, 6> sY;
-    sS.load(nS, r * 1024, [&](int o) { return plane[o]; });
-    sX.load(nX, r * 512, [&](int o) {
-      const int jx = o / kXC, xl = o - jx * kXC;
-      return tw_x[(size_t)jx * PX + min(x0 + xl, PX - 1)];
-    });
-    sY.load(nY, r * 1536, [&](int o) {
-      const int jy = o / PY, y = o - jy * PY;
-      return tw_y[(size_t)jy * nyp + y];
-    });
-    sS.store(nS, r * 1024, [&](int o, float2 v) {
-      const int jy = o / KX, jx = o - jy * KX;
-      if (deriv) {
-        const float q = cj == 0 ? qaxis(g, 0, jx) : (cj == 1 ? qaxis(g, 1, jy) : qaxis(g, 2, jz));
-        v = make_float2(-q * v.y, q * v.x);
-      }
-      S[jy * SX + jx] = v;
-    });
-    sX.store(nX, r * 512, [&](int o, float2 v) { Txc[o] = v; });
-    sY.store(nY, r * 1536, [&](int o, float2 v) { Ty[o] = v; });
-  }
-  __syncthreads();
-  // Both passes give a thread several outputs of one column xl (256 is a multiple of kXC) and
-  // compute them together: the operand they share is read once per term, and their chains of
-  // dependent LDS reads run side by side.  Each output keeps its own two alternating partial
-  // sums, as a single-output loop would.
-  const int xl = threadIdx.x % kXC;
-  // x: T[jy][xl] = sum_jx S[jy][jx] Tx[jx][x0 + xl], two rows per thread and round
-  const int nT = KY * kXC;
-  for (int ob = 0; ob < nT; ob += 512) {
-    const int o0 = ob + threadIdx.x, o1 = o0 + 256;
-    const int jy0 = min(o0, nT - 1) / kXC, jy1 = min(o1, nT - 1) / kXC;
-    float2 a0 = make_float2(0.f, 0.f), b0 = a0, a1 = a0, b1 = a0;
-    int jx = 0;
-#pragma unroll 4
-    for (; jx + 1 < KX; jx += 2) {
-      const float2 t0 = Txc[jx * kXC + xl], t1 = Txc[(jx + 1) * kXC + xl];
-      cmac(a0, S[jy0 * SX + jx], t0);
-      cmac(b0, S[jy0 * SX + jx + 1], t1);
-      cmac(a1, S[jy1 * SX + jx], t0);
-      cmac(b1, S[jy1 * SX + jx + 1], t1);
-    }
-    if (jx < KX) {
-      const float2 t0 = Txc[jx * kXC + xl];
-      cmac(a0, S[jy0 * SX + jx], t0);
-      cmac(a1, S[jy1 * SX + jx], t0);
-    }
-    if (o0 < nT) T[o0] = make_float2(a0.x + b0.x, a0.y + b0.y);
-    if (o1 < nT) T[o1] = make_float2(a1.x + b1.x, a1.y + b1.y);
-  }
-  __syncthreads();
-  // y: F2[y][x0 + xl] = sum_jy T[jy][xl] Ty[jy][y], three rows per thread and round
-  float2* dst = F2 + (size_t)ch * PY * PX;
-  const int nF = PY * kXC;
-  const bool xin = x0 + xl < PX;
-  for (int ob = 0; ob < nF; ob += 768) {
-    int yr[3];
-#pragma unroll
-    for (int u = 0; u < 3; ++u) yr[u] = min(ob + (int)threadIdx.x + 256 * u, nF - 1) / kXC;
-    float2 a[3], b[3];
-#pragma unroll
-    for (int u = 0; u < 3; ++u) a[u] = b[u] = make_float2(0.f, 0.f);
-    int jy = 0;
-#pragma unroll 2
-    for (; jy + 1 < KY; jy += 2) {
-      const float2 t0 = T[jy * kXC + xl], t1 = T[(jy + 1) * kXC + xl];
-#pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        cmac(a[u], t0, Ty[jy * PY + yr[u]]);
-        cmac(b[u], t1, Ty[(jy + 1) * PY + yr[u]]);
-      }
-    }
-    if (jy < KY) {
-      const float2 t0 = T[jy * kXC + xl];
-#pragma unroll
-      for (int u = 0; u < 3; ++u) cmac(a[u], t0, Ty[jy * PY + yr[u]]);
-    }
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      const int o = ob + (int)threadIdx.x + 256 * u;
-      if (xin && o < nF)
-        dst[(size_t)yr[u] * PX + x0 + xl] = make_float2(a[u].x + b[u].x, a[u].y + b[u].y);
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------- 2. columns
 // Block (32 columns, component), eight waves: lane l of a wave serves column l mod 32 and the
@@ -425,101 +293,6 @@ __global__ __launch_bounds__(64 * kColWaves) void k_fx_col_bwd(Geo gp, const flo
 }
 
 // ------------------------------------------------------------------------------ 3. pi yx
-// LDS layout of a yx block: the G plane, the x-stage result, R, and the block's twiddles
-struct YxLds {
-  float2 *Pl, *T, *Rs, *Tx, *Ty;
-};
-__device__ __forceinline__ YxLds yx_lds(const Geo& g, const Geo& gp, float2* base) {
-  YxLds L;
-  L.Pl = base;                                // [PY][PX + 1] (padded rows)
-  L.T = L.Pl + (size_t)gp.ny * (gp.nx + 1);   // [PY][kKC]
-  L.Rs = L.T + (size_t)gp.ny * kKC;           // [KY][kKC]
-  L.Tx = L.Rs + (size_t)g.ky * kKC;           // [PX][kKC]: Tx[jx][x] of the block's kx chunk
-  L.Ty = L.Tx + (size_t)gp.nx * kKC;          // [PY][KY]
-  return L;
-}
-// the block's twiddles into LDS (once per block); one round of loads in flight together up to
-// 64 x values and 48 x 32 (y, ky) pairs
-__device__ __forceinline__ void yx_twiddles(const Geo& g, const Geo& gp,
-                                            const float2* __restrict__ tw_xT,
-                                            const float2* __restrict__ tw_yT, int kyp, int k0,
-                                            const YxLds& L) {
-  const int KX = g.kx, KY = g.ky, PX = gp.nx, PY = gp.ny;
-  const int nX = PX * kKC, nY = PY * KY;
-  const int rounds = max((nX + 255) / 256, (nY + 1535) / 1536);
-  for (int r = 0; r < rounds; ++r) {
-    Stager<256, 1> sx;
-    Stager<256, 6> sy;
-    sx.load(nX, r * 256, [&](int o) {
-      const int x = o / kKC, kl = o - x * kKC;
-      return tw_xT[(size_t)x * KX + min(k0 + kl, KX - 1)];
-    });
-    sy.load(nY, r * 1536, [&](int o) {
-      const int y = o / KY, jy = o - y * KY;
-      return tw_yT[(size_t)y * kyp + jy];
-    });
-    sx.store(nX, r * 256, [&](int o, float2 v) { L.Tx[o] = v; });
-    sy.store(nY, r * 1536, [&](int o, float2 v) { L.Ty[o] = v; });
-  }
-}
-
-// R[jy][kl] = sum_y sum_x G[y][x] conj Tx[jx][x] conj Ty[jy][y] for the block's kx chunk, the
-// G plane (c, h) staged in LDS; R for (jy, jx = k0 + kl) lands in L.Rs.  Starts and ends with a
-// block barrier.
-__device__ __forceinline__ void pi_yx_passes(const Geo& g, const Geo& gp, const YxLds& L);
-
-// a G plane held in registers, kPlaneRegs entries per thread (entry o = threadIdx.x + 256 u)
-constexpr int kPlaneRegs = 24;
-__device__ __forceinline__ void plane_to_regs(const float2* __restrict__ Gp, int n, float2* R) {
-#pragma unroll
-  for (int u = 0; u < kPlaneRegs; ++u) {
-    const int o = threadIdx.x + 256 * u;
-    R[u] = o < n ? Gp[o] : make_float2(0.f, 0.f);
-  }
-}
-__device__ __forceinline__ void regs_to_lds(const float2* R, int PX, int n, float2* Pl) {
-#pragma unroll
-  for (int u = 0; u < kPlaneRegs; ++u) {
-    const int o = threadIdx.x + 256 * u;
-    if (o < n) {
-      const int y = o / PX;
-      Pl[y * (PX + 1) + (o - y * PX)] = R[u];
-    }
-  }
-}
-
-// the x and y contractions of the plane staged in L.Pl (a block barrier first and last)
-__device__ __forceinline__ void pi_yx_passes(const Geo& g, const Geo& gp, const YxLds& L) {
-  const int KY = g.ky, PX = gp.nx, PY = gp.ny, SP = PX + 1;
-  __syncthreads();
-  for (int o = threadIdx.x; o < PY * kKC; o += 256) {
-    const int y = o / kKC, kl = o - y * kKC;
-    float2 a = make_float2(0.f, 0.f), b = a;
-    int x = 0;
-#pragma unroll 4
-    for (; x + 1 < PX; x += 2) {
-      cmac_conj(a, L.Pl[y * SP + x], L.Tx[x * kKC + kl]);
-      cmac_conj(b, L.Pl[y * SP + x + 1], L.Tx[(x + 1) * kKC + kl]);
-    }
-    if (x < PX) cmac_conj(a, L.Pl[y * SP + x], L.Tx[x * kKC + kl]);
-    L.T[o] = make_float2(a.x + b.x, a.y + b.y);
-  }
-  __syncthreads();
-  for (int o = threadIdx.x; o < KY * kKC; o += 256) {
-    const int jy = o / kKC, kl = o - jy * kKC;
-    float2 a = make_float2(0.f, 0.f), b = a;
-    int y = 0;
-#pragma unroll 4
-    for (; y + 1 < PY; y += 2) {
-      cmac_conj(a, L.T[y * kKC + kl], L.Ty[y * KY + jy]);
-      cmac_conj(b, L.T[(y + 1) * kKC + kl], L.Ty[(y + 1) * KY + jy]);
-    }
-    if (y < PY) cmac_conj(a, L.T[y * kKC + kl], L.Ty[y * KY + jy]);
-    L.Rs[o] = make_float2(a.x + b.x, a.y + b.y);
-  }
-  __syncthreads();
-}
-
 // the band entries a thread of a yx block writes: entry k = (jx, jy, kz0 + h) with value R and,
 // where its mirror is written by the same thread, the mirror -k with conj(R).  Unpaired entries
 // (jx = 0 or jy = 0) are written as zero by their own k; the unpaired plane jz = 0 by h = 0.
@@ -606,62 +379,6 @@ __device__ __forceinline__ void stage_zero(const Geo& g, int i, int b, float2* _
   wout[o] = make_float2(0.f, 0.f);
 }
 
-// block (i * kzh + h, kx chunk); NO = output entries (jy, kl) per thread.  The G plane, the
-// twiddles and the band values of the thread's entries are all loaded before the first barrier.
-template <int NO>
-__global__ __launch_bounds__(256) void k_fx_pi_yx_stage(Geo g, Geo gp, const float2* __restrict__ G,
-                                                        const float2* __restrict__ tw_xT,
-                                                        const float2* __restrict__ tw_yT, int kyp,
-                                                        float scaleP,
-                                                        const float2* __restrict__ src,
-                                                        const float2* __restrict__ un,
-                                                        float2* __restrict__ acc, int st,
-                                                        float2* __restrict__ wout) {
-  extern __shared__ float2 lds[];
-  const int KY = g.ky, PX = gp.nx, PY = gp.ny;
-  const YxLds L = yx_lds(g, gp, lds);
-  const float2* Rs = L.Rs;
-  const int ih = blockIdx.x;
-  const int i = ih / g.kzh, h = ih - i * g.kzh;
-  const int k0 = blockIdx.y * kKC;
-  const int np = PY * PX;
-  float2 R[kPlaneRegs];
-  plane_to_regs(G + (size_t)ih * np, np, R);
-  Target t[NO];
-  StageIn in[NO][2];
-#pragma unroll
-  for (int u = 0; u < NO; ++u) {
-    const int o = threadIdx.x + 256 * u;
-    const int jy = o / kKC, kl = o - jy * kKC;
-    const int jx = k0 + kl;
-    t[u] = target(g, h, min(jx, g.kx - 1), min(jy, KY - 1));
-    if (o >= KY * kKC || jx >= g.kx) t[u].b = -1;   // no entry for this slot
-    in[u][0] = stage_load(g, i, t[u].zero ? -1 : t[u].b, src, un, acc);
-    in[u][1] = stage_load(g, i, t[u].bm, src, un, acc);
-  }
-  yx_twiddles(g, gp, tw_xT, tw_yT, kyp, k0, L);
-  regs_to_lds(R, PX, np, L.Pl);
-  pi_yx_passes(g, gp, L);
-#pragma unroll
-  for (int u = 0; u < NO; ++u) {
-    const int o = threadIdx.x + 256 * u;
-    const Target& tu = t[u];
-    if (tu.b < 0) continue;
-    if (tu.zero) {
-      stage_zero(g, i, tu.b, acc, st, wout);
-      if (tu.bz >= 0) stage_zero(g, i, tu.bz, acc, st, wout);
-      continue;
-    }
-    float2 r = Rs[o];
-    if (tu.real) r.y = 0.f;
-    stage_entry(g, i, tu.b, r, scaleP, in[u][0], acc, st, wout);
-    if (tu.bm >= 0) stage_entry(g, i, tu.bm, make_float2(r.x, -r.y), scaleP, in[u][1], acc, st, wout);
-  }
-  if (h == 0 && blockIdx.y == 0) {   // the unpaired plane kz = -K/2
-    for (int o = threadIdx.x; o < g.ky * g.kx; o += 256) stage_zero(g, i, o, acc, st, wout);
-  }
-}
-
 // the band values a transposed-sweep update of component i at band index b reads (b < 0: a
 // harmless in-bounds load of entry 0, not used)
 struct AdjIn {
@@ -705,172 +422,198 @@ __device__ __forceinline__ void adj_entry(const Geo& g, int i, int b, float2 A, 
   Ksum[o] = make_float2(ks.x + kp.x, ks.y + kp.y);
 }
 
-// Transposed-sweep yx block (i * kzh + h, kx chunk); NO = output entries (jy, kl) per thread.
-// A = i scaleP sum_j q_j R_j with R_j = Y(X(G_j)) and q_j the derivative symbol of axis j.  q_x
-// depends on kx only and q_z is constant in the block, so both commute with the y contraction:
-//   A = i scaleP [Y(q_x X(G_0) + q_z X(G_2)) + q_y Y(X(G_1))].
-// The three G planes are staged in LDS together; one x pass forms T02 = q_x X(G_0) + q_z X(G_2)
-// and T1 = X(G_1), one y pass both y sums.  All global loads (planes, twiddles, the band entries
-// the thread updates) are issued before the first barrier.
-constexpr int kAdjRegs = 9;   // plane entries per thread and round (one round for 48 x 48)
-
-__host__ __device__ __forceinline__ size_t adj_plane_stride(const Geo& gp) {
-  return (size_t)gp.ny * (gp.nx + 1);
-}
-
-template <int NO>
-__global__ __launch_bounds__(256) void k_fx_pi_yx_adj(Geo g, Geo gp, const float2* __restrict__ G,
-                                                      const float2* __restrict__ tw_xT,
-                                                      const float2* __restrict__ tw_yT, int kyp,
-                                                      float scaleP, float2* __restrict__ rho,
-                                                      float2* __restrict__ Asum,
-                                                      float2* __restrict__ Ksum,
-                                                      float2* __restrict__ kap, int st, int more) {
-  extern __shared__ float2 lds[];
-  const int KX = g.kx, KY = g.ky, PX = gp.nx, PY = gp.ny, SP = PX + 1;
-  const size_t PS = adj_plane_stride(gp);
-  float2* Pl = lds;                      // [3][PY][SP]
-  float2* T02 = Pl + 3 * PS;             // [PY][kKC]
-  float2* T1 = T02 + (size_t)PY * kKC;   // [PY][kKC]
-  float2* Tx = T1 + (size_t)PY * kKC;    // [PX][kKC]
-  float2* Ty = Tx + (size_t)PX * kKC;    // [PY][KY]
-  const int ih = blockIdx.x;
-  const int i = ih / g.kzh, h = ih - i * g.kzh;
-  const int k0 = blockIdx.y * kKC;
-  const int jz = g.kz0 + h;
-  const int np = PY * PX;
-  const float2* Gp[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) Gp[j] = G + ((size_t)(3 * i + j) * g.kzh + h) * np;
-  // the band entries this thread updates, loaded first
-  Target t[NO];
-  AdjIn in[NO][3];
-#pragma unroll
-  for (int u = 0; u < NO; ++u) {
-    const int o = threadIdx.x + 256 * u;
-    const int jy = o / kKC, kl = o - jy * kKC;
-    const int jx = k0 + kl;
-    t[u] = target(g, h, min(jx, KX - 1), min(jy, KY - 1));
-    if (o >= KY * kKC || jx >= KX) t[u].b = -1;   // no entry for this slot
-    in[u][0] = adj_load(g, i, t[u].b, rho, Asum, Ksum);
-    in[u][1] = adj_load(g, i, t[u].bm, rho, Asum, Ksum);
-    in[u][2] = adj_load(g, i, t[u].bz, rho, Asum, Ksum);
+// A block takes 16 ky by 32 kx of one (component i, kz = h) plane: R = sum_y sum_x G conj Tx conj
+// Ty on the matrix cores (as k_pi_yx, bl_dft_mfma.hip), then the update of its band entries, one per
+// thread, whose operands are loaded first.  Wavefront (x tile, part):
+//   forward sweep: part of 3 of the terms y, R is the sum of all;
+//   transposed sweep: derivative plane j, and R = q_x R_0 + q_y R_1 + q_z R_2, A = i scaleP R.
+// At a 48^3 product grid (96 blocks) a launch takes 7.8 and 10.1 us; with the planes and
+// twiddles staged in LDS for the vector units it took 8.1 and 13.0.
+constexpr int kKY = 16, kKX = 32;      // entries of a block
+constexpr int kYxTiles = 3;            // x tiles at a time
+constexpr int kYxWaves = 3 * kYxTiles;
+struct YxArgs {
+  float scaleP;
+  int st, more;
+  const float2 *src, *un;              // forward
+  float2 *acc, *wout;
+  float2 *rho, *Asum, *Ksum, *kap;     // transposed
+};
+template <bool ADJ>
+__global__ __launch_bounds__(64 * kYxWaves) void k_fx_pi_yx(Geo g, Geo gp, const float2* __restrict__ G,
+                                                            const float2* __restrict__ tw_x,
+                                                            const float2* __restrict__ tw_yT, int kyp,
+                                                            int nyp, int ntx, YxArgs a) {
+  __shared__ float part[kYxWaves][2][8][65];
+  const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4, w = wave_of(threadIdx.x);
+  const int KX = g.kx, KY = g.ky, PX = gp.nx, PY = gp.ny;
+  const int ih = blockIdx.x, i = ih / g.kzh, h = ih - i * g.kzh;
+  const int kyt = (int)blockIdx.y / ((KX + kKX - 1) / kKX), ky0 = kyt * kKY;
+  const int kx0 = ((int)blockIdx.y - kyt * ((KX + kKX - 1) / kKX)) * kKX;
+  // this thread's entry and what its update reads
+  const int e = (int)threadIdx.x, el = e & (kKX - 1), ey = e / kKX;
+  const int jx = kx0 + el, jy = ky0 + ey;
+  const bool entry = ey < kKY && jx < KX && jy < KY;
+  Target t = target(g, h, min(jx, KX - 1), min(jy, KY - 1));
+  if (!entry) t.b = -1;
+  StageIn sin[2];
+  AdjIn ain[3];
+  if constexpr (ADJ) {
+    ain[0] = adj_load(g, i, t.b, a.rho, a.Asum, a.Ksum);
+    ain[1] = adj_load(g, i, t.bm, a.rho, a.Asum, a.Ksum);
+    ain[2] = adj_load(g, i, t.bz, a.rho, a.Asum, a.Ksum);
+  } else {
+    sin[0] = stage_load(g, i, t.zero ? -1 : t.b, a.src, a.un, a.acc);
+    sin[1] = stage_load(g, i, t.bm, a.src, a.un, a.acc);
   }
-  // the three planes, kAdjRegs entries of each per thread and round, then the twiddles
-  const int rounds = (np + 256 * kAdjRegs - 1) / (256 * kAdjRegs);
-  for (int r = 0; r < rounds; ++r) {
-    const int base = r * 256 * kAdjRegs;
-    Stager<256, kAdjRegs> sp[3];
+  const int p = w / ntx, xt = w - p * ntx;   // part, x tile
+  if (p < 3) {
+    const size_t plane = ADJ ? (size_t)(3 * i + p) * g.kzh + h : (size_t)ih;
+    const Rsrc rg = rsrc(G + plane * PY * PX, (uint32_t)PY * (uint32_t)PX * 8u);
+    const Rsrc ry = rsrc(tw_yT, (uint32_t)nyp * (uint32_t)kyp * 8u);
+    const Rsrc rx = rsrc(tw_x, (uint32_t)KX * (uint32_t)PX * 8u);
+    f4 pre[2], pim[2];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) sp[j].load(np, base, [&](int o) { return Gp[j][o]; });
-    if (r == 0) yx_twiddles(g, gp, tw_xT, tw_yT, kyp, k0, YxLds{nullptr, nullptr, nullptr, Tx, Ty});
+    for (int v = 0; v < 2; ++v) pre[v] = pim[v] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int x0 = xt * 16; x0 < PX; x0 += 16 * ntx) {
+      f4 tx[2][2];   // twiddles of the terms x = x0 + 4 q + n
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
-      sp[j].store(np, base, [&](int o, float2 v) {
-        const int y = o / PX;
-        Pl[j * PS + y * SP + (o - y * PX)] = v;
-      });
+      for (int v = 0; v < 2; ++v) {
+        const int kx = kx0 + 16 * v + m;
+        const uint32_t off = kx < KX ? ((uint32_t)kx * (uint32_t)PX + (uint32_t)(x0 + 4 * q)) * 8u : kPast;
+        tx[v][0] = ld4(rx, off);
+        tx[v][1] = ld4(rx, off == kPast ? kPast : off + 16u);
+      }
+      f4 cr[2], ci[2], sr[2], si[2];
+#pragma unroll
+      for (int v = 0; v < 2; ++v) cr[v] = ci[v] = sr[v] = si[v] = f4{0.f, 0.f, 0.f, 0.f};
+      const uint32_t xoff = (uint32_t)(x0 + m) * 8u;
+      const bool on = x0 + m < PX;
+      constexpr int U = ADJ ? 4 : 3;
+      const int first = ADJ ? 0 : 4 * p, step = ADJ ? 4 : 12;
+      for (int y0 = first; y0 <= PY / 2; y0 += step * U) {
+        f2 s[U], d[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t y = (uint32_t)(y0 + step * u + q), ym = (uint32_t)PY - y;
+          const bool one = on && (int)y <= PY / 2, two = one && y > 0 && y != ym;
+          const f2 v0 = ld2(rg, one ? y * (uint32_t)PX * 8u + xoff : kPast);
+          const f2 v1 = ld2(rg, two ? ym * (uint32_t)PX * 8u + xoff : kPast);
+          b[u] = ld2(ry, (y * (uint32_t)kyp + (uint32_t)(ky0 + m)) * 8u);
+          s[u] = v0 + v1;
+          d[u] = v0 - v1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          cr[u & 1] = mfma(s[u].x, b[u].x, cr[u & 1]);
+          ci[u & 1] = mfma(s[u].y, b[u].x, ci[u & 1]);
+          sr[u & 1] = mfma(d[u].y, b[u].y, sr[u & 1]);
+          si[u & 1] = mfma(d[u].x, b[u].y, si[u & 1]);
+        }
+      }
+      const f4 hr = (cr[0] + cr[1]) + (sr[0] + sr[1]), hi = (ci[0] + ci[1]) - (si[0] + si[1]);
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const f4 t0 = tx[v][0], t1 = tx[v][1];
+        f4 pa[2], pb[2], pc[2], pd[2];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) pa[n] = pb[n] = pc[n] = pd[n] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          const float tr = n < 2 ? t0[2 * n] : t1[2 * n - 4], ti = n < 2 ? t0[2 * n + 1] : t1[2 * n - 3];
+          pa[n & 1] = mfma(tr, hr[n], pa[n & 1]);
+          pb[n & 1] = mfma(tr, hi[n], pb[n & 1]);
+          pc[n & 1] = mfma(ti, hi[n], pc[n & 1]);
+          pd[n & 1] = mfma(ti, hr[n], pd[n & 1]);
+        }
+        pre[v] += (pa[0] + pa[1]) + (pc[0] + pc[1]);
+        pim[v] += (pb[0] + pb[1]) - (pd[0] + pd[1]);
+      }
+    }
+    // row 4 q + n of tile v is kx = kx0 + 16 v + 4 q + n, column m is ky = ky0 + m (65: the
+    // entries of a wavefront's readers lie in different banks)
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        part[w][v][2 * n][lane] = pre[v][n];
+        part[w][v][2 * n + 1][lane] = pim[v][n];
+      }
   }
   __syncthreads();
-  // x pass: (y, kl) outputs, the three planes' sums together
-  const float qz = qaxis(g, 2, jz);
-  for (int o = threadIdx.x; o < PY * kKC; o += 256) {
-    const int y = o / kKC, kl = o - y * kKC;
-    const float qx = qaxis(g, 0, min(k0 + kl, KX - 1));
-    float2 a0 = make_float2(0.f, 0.f), a1 = a0, a2 = a0;
-    const float2* r0 = Pl + y * SP;
-    const float2* r1 = r0 + PS;
-    const float2* r2 = r1 + PS;
-#pragma unroll 4
-    for (int x = 0; x < PX; ++x) {
-      const float2 tw = Tx[x * kKC + kl];
-      cmac_conj(a0, r0[x], tw);
-      cmac_conj(a1, r1[x], tw);
-      cmac_conj(a2, r2[x], tw);
+  if (entry) {
+    const int v = el >> 4, n = el & 3, l = (el >> 2 & 3) * 16 + ey;
+    float2 r = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      float2 s = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int o = 0; o < kYxTiles; ++o)
+        if (o < ntx) {
+          s.x += part[j * ntx + o][v][2 * n][l];
+          s.y += part[j * ntx + o][v][2 * n + 1][l];
+        }
+      const float qj = !ADJ ? 1.f : j == 0 ? qaxis(g, 0, jx) : j == 1 ? qaxis(g, 1, jy) : qaxis(g, 2, g.kz0 + h);
+      r.x = fmaf(qj, s.x, r.x);
+      r.y = fmaf(qj, s.y, r.y);
     }
-    T02[o] = make_float2(fmaf(qx, a0.x, qz * a2.x), fmaf(qx, a0.y, qz * a2.y));
-    T1[o] = a1;
-  }
-  __syncthreads();
-  // y pass: A for the thread's outputs
-  float2 A[NO];
-#pragma unroll
-  for (int u = 0; u < NO; ++u) {
-    A[u] = make_float2(0.f, 0.f);
-    const int o = threadIdx.x + 256 * u;
-    if (o >= KY * kKC) continue;
-    const int jy = o / kKC, kl = o - jy * kKC;
-    float2 s02 = make_float2(0.f, 0.f), s1 = s02;
-#pragma unroll 4
-    for (int y = 0; y < PY; ++y) {
-      const float2 tw = Ty[y * KY + jy];
-      cmac_conj(s02, T02[y * kKC + kl], tw);
-      cmac_conj(s1, T1[y * kKC + kl], tw);
-    }
-    const float qy = qaxis(g, 1, jy);
-    const float2 R = make_float2(fmaf(qy, s1.x, s02.x), fmaf(qy, s1.y, s02.y));
-    A[u] = make_float2(-scaleP * R.y, scaleP * R.x);
-  }
-#pragma unroll
-  for (int u = 0; u < NO; ++u) {
-    const Target& tu = t[u];
-    if (tu.b < 0) continue;
-    float2 a = tu.zero ? make_float2(0.f, 0.f) : A[u];
-    if (tu.real) a.y = 0.f;
-    adj_entry(g, i, tu.b, a, st, more, in[u][0], rho, Asum, Ksum, kap);
-    if (tu.bm >= 0)
-      adj_entry(g, i, tu.bm, make_float2(a.x, -a.y), st, more, in[u][1], rho, Asum, Ksum, kap);
-    if (tu.bz >= 0)
-      adj_entry(g, i, tu.bz, make_float2(0.f, 0.f), st, more, in[u][2], rho, Asum, Ksum, kap);
-  }
-  if (h == 0 && blockIdx.y == 0) {   // the unpaired plane kz = -K/2: A = 0 there
-    const int n = KY * KX;
-    for (int base = 0; base < n; base += 1024) {
-      AdjIn zin[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        zin[u] = adj_load(g, i, min(base + (int)threadIdx.x + 256 * u, n - 1), rho, Asum, Ksum);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int o = base + (int)threadIdx.x + 256 * u;
-        if (o < n) adj_entry(g, i, o, make_float2(0.f, 0.f), st, more, zin[u], rho, Asum, Ksum, kap);
+    if constexpr (ADJ) {
+      float2 A = t.zero ? make_float2(0.f, 0.f) : make_float2(-a.scaleP * r.y, a.scaleP * r.x);
+      if (t.real) A.y = 0.f;
+      if (t.b >= 0) {
+        adj_entry(g, i, t.b, A, a.st, a.more, ain[0], a.rho, a.Asum, a.Ksum, a.kap);
+        if (t.bm >= 0)
+          adj_entry(g, i, t.bm, make_float2(A.x, -A.y), a.st, a.more, ain[1], a.rho, a.Asum, a.Ksum, a.kap);
+        if (t.bz >= 0)
+          adj_entry(g, i, t.bz, make_float2(0.f, 0.f), a.st, a.more, ain[2], a.rho, a.Asum, a.Ksum, a.kap);
+      }
+    } else if (t.b >= 0) {
+      if (t.zero) {
+        stage_zero(g, i, t.b, a.acc, a.st, a.wout);
+        if (t.bz >= 0) stage_zero(g, i, t.bz, a.acc, a.st, a.wout);
+      } else {
+        if (t.real) r.y = 0.f;
+        stage_entry(g, i, t.b, r, a.scaleP, sin[0], a.acc, a.st, a.wout);
+        if (t.bm >= 0)
+          stage_entry(g, i, t.bm, make_float2(r.x, -r.y), a.scaleP, sin[1], a.acc, a.st, a.wout);
       }
     }
   }
+  if (h == 0 && blockIdx.y == 0) {   // the unpaired plane kz = -K/2 (A = 0 there)
+    for (int o = threadIdx.x; o < KY * KX; o += (int)blockDim.x) {
+      if constexpr (ADJ)
+        adj_entry(g, i, o, make_float2(0.f, 0.f), a.st, a.more, adj_load(g, i, o, a.rho, a.Asum, a.Ksum),
+                  a.rho, a.Asum, a.Ksum, a.kap);
+      else
+        stage_zero(g, i, o, a.acc, a.st, a.wout);
+    }
+  }
+}
+
+template <bool ADJ>
+void launch_yx(const Geo& g, const Geo& gp, const DftPlan& pl, const float2* G, const YxArgs& a,
+               hipStream_t s) {
+  const int ntx = std::min((gp.nx + 15) / 16, kYxTiles);
+  const int waves = std::max(3 * ntx, kKY * kKX / 64);   // at least a thread per entry
+  const dim3 grid(g.dim * g.kzh, ((g.ky + kKY - 1) / kKY) * ((g.kx + kKX - 1) / kKX));
+  hipLaunchKernelGGL(k_fx_pi_yx<ADJ>, grid, dim3(64 * waves), 0, s, g, gp, G, pl.tw_x, pl.tw_yT, pl.kyp,
+                     pl.nyp, ntx, a);
 }
 
 int nzs_of(int pz) { return pz <= 16 ? 2 : pz <= 32 ? 4 : 6; }
 int kzh_of(int kzh) { return kzh <= 8 ? 8 : 16; }
 
-size_t lds_xy(const Geo& g, const Geo& gp) {
-  return ((size_t)g.ky * (g.kx + 1) + (size_t)g.ky * kXC + (size_t)g.kx * kXC + (size_t)g.ky * gp.ny) *
-         sizeof(float2);
-}
-size_t lds_yx_adj(const Geo& g, const Geo& gp) {
-  return (3 * adj_plane_stride(gp) + 2 * (size_t)gp.ny * kKC + (size_t)gp.nx * kKC +
-          (size_t)gp.ny * g.ky) *
-         sizeof(float2);
-}
-size_t lds_yx(const Geo& g, const Geo& gp) {
-  return ((size_t)gp.ny * (gp.nx + 1) + (size_t)gp.ny * kKC + (size_t)g.ky * kKC + (size_t)gp.nx * kKC +
-          (size_t)gp.ny * g.ky) *
-         sizeof(float2);
-}
-
 }  // namespace
 
 bool fused_ok(const Geo& g, const Geo& gp) {
-  return g.dim == 3 && gp.nz <= 48 && g.kzh <= 16 && g.kzh >= 2 && g.ky * kKC <= 4 * 256 &&
-         gp.nx * gp.ny <= 256 * kPlaneRegs &&
-         lds_xy(g, gp) <= 64 * 1024 && lds_yx(g, gp) <= 64 * 1024 &&
-         lds_yx_adj(g, gp) <= 160 * 1024;
+  return g.dim == 3 && gp.nz <= 48 && g.kzh <= 16 && g.kzh >= 2 && g.ky <= 128 && gp.nx * gp.ny <= 6144;
 }
 
 void fx_iota_xy(const Geo& g, const Geo& gp, const DftPlan& pl, const float2* in, int deriv,
                 float2* F2, hipStream_t s) {
-  const int C = deriv ? g.dim * g.dim : g.dim;
-  hipLaunchKernelGGL(k_fx_iota_xy, dim3(C * g.kzh, (gp.nx + kXC - 1) / kXC), dim3(256), lds_xy(g, gp),
-                     s, g, gp, in, deriv, pl.tw_x, pl.tw_y, pl.nyp, F2);
+  // (fused_ok: ky is below the bound of these)
+  if (deriv) iota_xy_deriv_mfma(g, gp, pl, in, F2, s);
+  else iota_xy_mfma(gp, pl, in, g.dim, F2, s);
 }
 
 #define COL_LAUNCH(KERNEL, NZS, KZH, ...)                                                 \
@@ -911,41 +654,31 @@ void fx_col_bwd(const Geo& gp, const DftPlan& pl, const float2* F2, const float*
   NZS_DISPATCH(k_fx_col_bwd, gp, F2, VP, DUG, GACC, first, pl.tw_zT, G);
 }
 
-// output entries per thread of a yx block: ky * kKC <= 4 * 256 (fused_ok)
-#define NO_DISPATCH(KERNEL, LDS, ...)                                                       \
-  do {                                                                                      \
-    const dim3 grid_(g.dim * g.kzh, (g.kx + kKC - 1) / kKC);                                \
-    const size_t lds_ = (LDS);                                                              \
-    switch ((g.ky * kKC + 255) / 256) {                                                     \
-      case 1: hipLaunchKernelGGL(KERNEL<1>, grid_, dim3(256), lds_, s, __VA_ARGS__); break; \
-      case 2: hipLaunchKernelGGL(KERNEL<2>, grid_, dim3(256), lds_, s, __VA_ARGS__); break; \
-      case 3: hipLaunchKernelGGL(KERNEL<3>, grid_, dim3(256), lds_, s, __VA_ARGS__); break; \
-      default: hipLaunchKernelGGL(KERNEL<4>, grid_, dim3(256), lds_, s, __VA_ARGS__); break; \
-    }                                                                                       \
-  } while (0)
-
 void fx_pi_yx_stage(const Geo& g, const Geo& gp, const DftPlan& pl, const float2* G, float scaleP,
                     const float2* src, const float2* un, float2* acc, int st, float2* wout,
                     hipStream_t s) {
-  NO_DISPATCH(k_fx_pi_yx_stage, lds_yx(g, gp), g, gp, G, pl.tw_xT, pl.tw_yT, pl.kyp, scaleP,
-              src, un, acc, st, wout);
+  YxArgs a{};
+  a.scaleP = scaleP;
+  a.st = st;
+  a.src = src;
+  a.un = un;
+  a.acc = acc;
+  a.wout = wout;
+  launch_yx<false>(g, gp, pl, G, a, s);
 }
 
 void fx_pi_yx_adj(const Geo& g, const Geo& gp, const DftPlan& pl, const float2* G, float scaleP,
                   float2* rho, float2* Asum, float2* Ksum, float2* kap, int st, int more,
                   hipStream_t s) {
-  // the three staged planes take up to 160 KiB of LDS (fused_ok): allow the launches that size
-  static std::once_flag once;
-  std::call_once(once, [] {
-    const int cap = 160 * 1024;
-    (void)hipFuncSetAttribute((const void*)k_fx_pi_yx_adj<1>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    (void)hipFuncSetAttribute((const void*)k_fx_pi_yx_adj<2>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    (void)hipFuncSetAttribute((const void*)k_fx_pi_yx_adj<3>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    (void)hipFuncSetAttribute((const void*)k_fx_pi_yx_adj<4>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    (void)hipGetLastError();   // an attribute the runtime does not need leaves no error behind
-  });
-  NO_DISPATCH(k_fx_pi_yx_adj, lds_yx_adj(g, gp), g, gp, G, pl.tw_xT, pl.tw_yT, pl.kyp, scaleP,
-              rho, Asum, Ksum, kap, st, more);
+  YxArgs a{};
+  a.scaleP = scaleP;
+  a.st = st;
+  a.more = more;
+  a.rho = rho;
+  a.Asum = Asum;
+  a.Ksum = Ksum;
+  a.kap = kap;
+  launch_yx<true>(g, gp, pl, G, a, s);
 }
 
 }  // namespace bl

@@ -18,45 +18,11 @@
 // white noise by 1.2 to 1.8e-7 (1.2 to 2.0e-7) over ten shapes up to 256 points and 64 terms an axis.
 // The z stages are bound by their fields (256^3: 201 MB at 3.4 to 3.7 TB/s).  pi y and x has one
 // workgroup per (component, kz, 16 ky) and does not fill the device at 128^3 (96 of them).
-//
-// Lane l of a wavefront: m = l & 15, q = l >> 4.  An instruction takes A[row m][term q] and
-// B[term q][column m] from lane l and adds to D[row 4 q + i][column m], i = 0..3, in lane l.
-// The terms of a contraction may be taken in any order as long as A and B agree, so each lane
-// loads runs of consecutive terms.  Terms, rows and columns past an axis read 0 (addresses past
-// the end of a buffer resource) or meet a 0 on the other side.
-#include "bl_internal.h"
+#include "bl_mfma.h"
 
 namespace bl {
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-constexpr uint32_t kPast = 0xFFFFFFF0u;   // past every buffer (all smaller than this)
-
-__device__ __forceinline__ Rsrc rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ f4 ld4(Rsrc r, uint32_t off) {
-  return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
-__device__ __forceinline__ f2 ld2(Rsrc r, uint32_t off) {
-  return __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-}
-typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void st1(Rsrc r, uint32_t off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)off, 0, 0);
-}
-__device__ __forceinline__ void st2(Rsrc r, uint32_t off, f2 v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, (int)off, 0, 0);
-}
-__device__ __forceinline__ void st4(Rsrc r, uint32_t off, f4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, (int)off, 0, 0);
-}
-__device__ __forceinline__ f4 mfma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 // Consecutive workgroups go to the 8 XCDs in turn, each with an L2 of its own; so that neighbours,
 // which share cache lines where rows are not aligned, meet in one L2, workgroup b takes unit
 // (b % 8) (n / 8) + b / 8 of n (a multiple of 8; the last ones may have no unit).
@@ -65,15 +31,18 @@ __device__ __forceinline__ unsigned unit_of() {
   return (blockIdx.x % kXcd) * (gridDim.x / kXcd) + blockIdx.x / kXcd;
 }
 inline unsigned units(int64_t n) { return (unsigned)((n + kXcd - 1) / kXcd * kXcd); }
-__device__ __forceinline__ int wave_of(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
 
 // ---------------------------------------------------------------------- iota, x and y stages
 // A block takes 16 columns x of one (component, kz) plane and a run of y tiles: its wavefronts
 // share the x stage (F1[ky][x] for all ky, through LDS), then each forms y tiles of 16 rows.
-// KYM: tiles of 16 ky.
+// KYM: tiles of 16 ky.  DERIV: component c = i dim + j is the derivative of band field i along
+// axis j, i q_j band_i with q_j = 2 pi k_j ratio_j.
 constexpr int kIW = 4;   // wavefronts of a block
-template <int KYM>
-__global__ __launch_bounds__(64 * kIW) void k_iota_xy(Geo g, const float2* __restrict__ band,
+struct Ratios {
+  float r[3];
+};
+template <int KYM, bool DERIV>
+__global__ __launch_bounds__(64 * kIW) void k_iota_xy(Geo g, Ratios ratio, const float2* __restrict__ band,
                                                       const float2* __restrict__ tw_x,
                                                       const float2* __restrict__ tw_yT, int kyp, int nyp,
                                                       int nxt, int nyr, int yrun, int nch,
@@ -89,7 +58,8 @@ __global__ __launch_bounds__(64 * kIW) void k_iota_xy(Geo g, const float2* __res
   const int c = ch / g.kzh, h = ch - c * g.kzh;
   const int x = xt * 16 + m, xc = min(x, g.nx - 1);
   const size_t plane = (size_t)g.ky * g.kx;
-  const Rsrc rb = rsrc(band + (size_t)(c * g.kz + g.kz0 + h) * plane, (uint32_t)plane * 8u);
+  const int ci = DERIV ? c / g.dim : c, axis = c - ci * g.dim;
+  const Rsrc rb = rsrc(band + (size_t)(ci * g.kz + g.kz0 + h) * plane, (uint32_t)plane * 8u);
   const Rsrc rx = rsrc(tw_x, (uint32_t)g.kx * (uint32_t)g.nx * 8u);
   for (int t = w; t < KYM; t += kIW) {
     const int row = t * 16 + m;
@@ -103,6 +73,13 @@ __global__ __launch_bounds__(64 * kIW) void k_iota_xy(Geo g, const float2* __res
       for (int u = 0; u < 4; ++u) {
         const uint32_t k = (uint32_t)(k0 + 8 * u + 2 * q);
         a[u] = ld4(rb, row < g.ky && (int)k < g.kx ? ((uint32_t)row * (uint32_t)g.kx + k) * 8u : kPast);
+        if constexpr (DERIV) {
+          const float two_pi = 6.283185307179586f;
+          const int k0i = axis == 0 ? (int)k - g.kx / 2 : axis == 1 ? row - g.ky / 2 : h;
+          const int k1i = axis == 0 ? k0i + 1 : k0i;
+          const float q0 = two_pi * (float)k0i * ratio.r[axis], q1 = two_pi * (float)k1i * ratio.r[axis];
+          a[u] = f4{-q0 * a[u].y, q0 * a[u].x, -q1 * a[u].w, q1 * a[u].z};
+        }
         b[u][0] = ld2(rx, (k * (uint32_t)g.nx + (uint32_t)xc) * 8u);
         b[u][1] = ld2(rx, ((k + 1u) * (uint32_t)g.nx + (uint32_t)xc) * 8u);
       }
@@ -484,7 +461,9 @@ void pi_z_mfma(const Geo& g, const DftPlan& p, const float* f, int C, float2* G,
   }
 }
 
-bool iota_xy_mfma(const Geo& g, const DftPlan& p, const float2* band, int C, float2* F2, hipStream_t s) {
+namespace {
+bool launch_iota_xy(const Geo& g, const DftPlan& p, const float2* band, int C, float2* F2, bool deriv,
+                    const Ratios& r, hipStream_t s) {
   if (g.ky > 128) return false;
   const unsigned xt = (unsigned)((g.nx + 15) / 16);
   // y tiles over blocks until the launch fills the device (each repeats the x stage)
@@ -494,9 +473,14 @@ bool iota_xy_mfma(const Geo& g, const DftPlan& p, const float2* band, int C, flo
   const int yrun = (tiles + n - 1) / n * 16 * kIW;
   const int nyr = (rows + yrun - 1) / yrun, nch = C * g.kzh;
   const dim3 grid = batch_grid(dim3(units((int64_t)xt * nyr * nch)), g.bat);
-#define XY(K)                                                                                        \
-  hipLaunchKernelGGL(k_iota_xy<K>, grid, dim3(64 * kIW), 0, s, g, band, p.tw_x, p.tw_yT, p.kyp, p.nyp, \
-                     (int)xt, nyr, yrun, nch, F2)
+#define XY_D(K, D)                                                                               \
+  hipLaunchKernelGGL((k_iota_xy<K, D>), grid, dim3(64 * kIW), 0, s, g, r, band, p.tw_x, p.tw_yT, p.kyp, \
+                     p.nyp, (int)xt, nyr, yrun, nch, F2)
+#define XY(K)              \
+  do {                     \
+    if (deriv) XY_D(K, true); \
+    else XY_D(K, false);   \
+  } while (0)
   switch ((g.ky + 15) / 16) {
     case 1: XY(1); break;
     case 2: XY(2); break;
@@ -507,7 +491,18 @@ bool iota_xy_mfma(const Geo& g, const DftPlan& p, const float2* band, int C, flo
     default: XY(8); break;
   }
 #undef XY
+#undef XY_D
   return true;
+}
+}  // namespace
+
+bool iota_xy_mfma(const Geo& g, const DftPlan& p, const float2* band, int C, float2* F2, hipStream_t s) {
+  return launch_iota_xy(g, p, band, C, F2, false, Ratios{}, s);
+}
+bool iota_xy_deriv_mfma(const Geo& g, const Geo& gp, const DftPlan& p, const float2* band, float2* F2,
+                        hipStream_t s) {
+  const Ratios r{{(float)g.nref / (float)g.nx, (float)g.nref / (float)g.ny, (float)g.nref / (float)g.nz}};
+  return launch_iota_xy(gp, p, band, g.dim * g.dim, F2, true, r, s);
 }
 
 bool pi_yx_mfma(const Geo& g, const DftPlan& p, const float2* G, int C, float2* P, hipStream_t s) {

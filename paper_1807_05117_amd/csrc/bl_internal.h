@@ -195,6 +195,10 @@ constexpr int kRedBlocks = 512;   // partial sums per deterministic FP64 reducti
 void iota_z_mfma(const Geo& g, const DftPlan& p, const float2* F2, float* out, int C, hipStream_t s);
 void pi_z_mfma(const Geo& g, const DftPlan& p, const float* f, int C, float2* G, hipStream_t s);
 bool iota_xy_mfma(const Geo& g, const DftPlan& p, const float2* band, int C, float2* F2, hipStream_t s);
+// the derivatives along every axis of dim band fields (i q_j band_i as component i dim + j), with
+// the symbols of g on the grid gp
+bool iota_xy_deriv_mfma(const Geo& g, const Geo& gp, const DftPlan& p, const float2* band, float2* F2,
+                        hipStream_t s);
 bool pi_yx_mfma(const Geo& g, const DftPlan& p, const float2* G, int C, float2* P, hipStream_t s);
 
 // ---- transforms (bl_dft.hip)
@@ -394,7 +398,7 @@ void def_rho1(const Geo& g, const float* m1, const float* I1, const float4* GP, 
 void def_drho1(const Geo& g, const float* DU, const float4* GP, float* Bf, hipStream_t s);
 
 // fused stage kernels of the deformation method (bl_deform_fused.hip), 3D product grids with
-// pz <= 64 whose tiles fit the LDS budget (fused_ok); F2 and G are work buffers of
+// pz <= 48 and px py <= 6144 (fused_ok); F2 and G are work buffers of
 // dim^2 * kzh * py * px complex entries (the product plan's bufA / bufB)
 bool fused_ok(const Geo& g, const Geo& gp);
 // F2[c][h][y][x] from the kz >= 0 half of `in` (dim fields; deriv: the dim^2 fields i q_j in_i)
