@@ -348,6 +348,7 @@ void Cohort::enqueue_step(int k_pcg) {
   bl::add_scaled_dev(c->stry, c->sv, c->sdelta, &ctl0->eps, nb, s, b);
   b = use(&ctl0->g_eval);
   enqueue_set_velocity(c, c->stry);
+  enqueue_energy(c, false);
   hipLaunchKernelGGL(k_ctl_armijo, one, lanes, 0, s, scal0, st, cap_);
 
   // accepted: v = projected trial, gradient and its norms

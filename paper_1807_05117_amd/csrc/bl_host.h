@@ -194,6 +194,7 @@ void store_plane(bl_ctx* c, const float* src, float* dst, size_t nplanes);
 void solve(bl_ctx* c, const bl_solver_opts& o, bl_stats* st);
 // operator sequences on a context (enqueued on c->stream; launches follow c->g.bat)
 void enqueue_set_velocity(bl_ctx* c, const float2* vraw);   // stationary state equation only
+void enqueue_energy(bl_ctx* c, bool with_flag);              // the energy's sums after it
 void op_set_velocity(bl_ctx* c, const float2* vraw);        // enqueue, synchronise, read E
 void finish_set_velocity(bl_ctx* c);   // E from the published sums (after a sync)
 // gradient into gout; with sq_part / max_part not NULL, also the finalize_blocks partials of

@@ -920,7 +920,7 @@ void choose_launch_shapes(bl_ctx* c) {
 // Per node: projection (and divergence) of the band fields with the trapezoid-weighted
 // regulariser; iota of every node's velocity and divergence in one launch sequence; per step
 // t_n -> t_{n+1}: the step's offsets from both ends, and the state step.
-void op_set_velocity_ns(bl_ctx* c, const float2* vraw) {
+void enqueue_set_velocity_ns(bl_ctx* c, const float2* vraw) {
   const bl::Geo& g = c->g;
   hipStream_t s = c->stream;
   const size_t M = (size_t)g.M, B = (size_t)g.B;
@@ -936,18 +936,9 @@ void op_set_velocity_ns(bl_ctx* c, const float2* vraw) {
   if (!c->tuned) choose_launch_shapes(c);
   for (int n = 0; n < g.nt; ++n)
     bl::state_step(g, c->m + n * M, c->X + (size_t)n * d * M, c->m + (n + 1) * M, s);
-  bl::energy_partial(g, c->m + g.nt * M, c->I1, red_data, s);
-  bl::reduce_final2(red_reg, c->scal + S_REG, c->hdev + S_REG, red_data, c->scal + S_DATA,
-                    c->hdev + S_DATA, bl::kRedBlocks, s);
+  bl::energy_partial(g, c->m + g.nt * M, c->I1, red_data, s, c->L + g.nt * M);
+  c->lamT_valid = true;
   check_launch("set_velocity (non-stationary)");
-  sync(c);
-  c->reg = c->hscal[S_REG];
-  c->data_sum = c->hscal[S_DATA];
-  const double sig = c->prob.sigma;
-  c->E = 0.5 * c->reg + c->data_sum / (sig * sig * (double)g.M);
-  c->have_v = true;
-  c->have_lambda = false;
-  if (!std::isfinite(c->E)) throw NonFinite{"energy"};
 }
 
 // adjoint from L[nt] down to L[1] with the per-step (Y, a): lambda^0 is read by nothing but
@@ -977,7 +968,7 @@ void per_node_outputs(bl_ctx* c, const float2* vproj, size_t vstride, float2* ou
 void op_gradient_ns(bl_ctx* c, float2* gout) {
   const bl::Geo& g = c->g;
   const size_t M = (size_t)g.M;
-  bl::terminal(g, c->m + g.nt * M, c->I1, c->L + g.nt * M, c->stream);
+  if (!c->lamT_valid) bl::terminal(g, c->m + g.nt * M, c->I1, c->L + g.nt * M, c->stream);
   backward_ns(c);
   c->have_lambda = true;
   per_node_outputs(c, c->bv, (size_t)(g.dim + 1) * g.B, gout);
@@ -1183,8 +1174,8 @@ void prep_and_clean(bl_ctx* c, const float2* raw, float2* out, int with_div, con
   if (z) c->sweep_clean[0] = c->sweep_clean[1] = true;
 }
 
-// setup + forward state + energy sums at the raw band vector `vraw` (stationary state
-// equation), enqueued only: the regulariser and data sums land in scal[S_REG], scal[S_DATA]
+// setup + forward state + the energy's partial sums at the raw band vector `vraw` (stationary
+// state equation), enqueued only; enqueue_energy adds them up
 void enqueue_set_velocity(bl_ctx* c, const float2* vraw) {
   const bl::Geo& g = c->g;
   hipStream_t s = c->stream;
@@ -1203,9 +1194,17 @@ void enqueue_set_velocity(bl_ctx* c, const float2* vraw) {
   // the energy's data term and, in the same pass, the terminal adjoint lambda^Nt into L[nt]
   bl::energy_partial(g, c->m + g.nt * M, c->I1, red_data, s, c->L + g.nt * M);
   c->lamT_valid = true;
-  bl::reduce_final2(red_reg, c->scal + S_REG, publish(c, S_REG), red_data, c->scal + S_DATA,
-                    publish(c, S_DATA), bl::kRedBlocks, s, false, nullptr, nullptr, g.bat);
   check_launch("set_velocity");
+}
+
+// the energy's sums of an enqueued velocity into scal[S_REG], scal[S_DATA]; with_flag: the
+// non-finite flag of the band outputs is published by the same launch
+void enqueue_energy(bl_ctx* c, bool with_flag) {
+  const bl::Geo& g = c->g;
+  bl::reduce_final2(c->red + RED_REG * bl::kRedBlocks, c->scal + S_REG, publish(c, S_REG),
+                    c->red + RED_DATA * bl::kRedBlocks, c->scal + S_DATA, publish(c, S_DATA), bl::kRedBlocks,
+                    c->stream, false, with_flag ? c->flag : nullptr,
+                    with_flag ? c->hdev + S_FLAG : nullptr, g.bat);
 }
 
 // setup + forward state + energy at the raw band vector `vraw` (device, dim components)
@@ -1215,11 +1214,9 @@ void op_set_velocity(bl_ctx* c, const float2* vraw) {
     op_set_velocity_def(c, vraw);
     return;
   }
-  if (c->g.nodes > 1) {
-    op_set_velocity_ns(c, vraw);
-    return;
-  }
-  enqueue_set_velocity(c, vraw);
+  if (c->g.nodes > 1) enqueue_set_velocity_ns(c, vraw);
+  else enqueue_set_velocity(c, vraw);
+  enqueue_energy(c, false);
   sync(c);
   finish_set_velocity(c);
 }
@@ -1237,18 +1234,20 @@ void finish_set_velocity(bl_ctx* c) {
 }
 
 // Energy and gradient at the raw band vector `vraw` into gout with one host synchronisation
-// (stationary state equation): the energy sums and the non-finite flag of the band outputs
+// (state equation): the energy sums and the non-finite flag of the band outputs
 // are published to host-mapped memory and read together; `after` enqueues the caller's
 // copies of the results before that synchronisation.
 template <class After>
-void op_energy_gradient(bl_ctx* c, const float2* vraw, float2* gout, After&& after) {
-  enqueue_set_velocity(c, vraw);
+void op_energy_gradient(bl_ctx* c, const float2* vraw, float2* gout, double* energy, After&& after) {
+  if (c->g.nodes > 1) enqueue_set_velocity_ns(c, vraw);
+  else enqueue_set_velocity(c, vraw);
   op_gradient(c, gout);
-  bl::publish_flag(c->flag, c->hdev + S_FLAG, c->stream);
+  enqueue_energy(c, true);
   after();
   check_launch("energy and gradient");
   sync(c);
   finish_set_velocity(c);
+  if (energy) *energy = c->E;
   c->have_lambda = true;   // L holds this velocity's adjoint (the full Newton product reuses it)
   if (c->hscal[S_FLAG] != 0.0) {
     HIP_TRY(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
@@ -1485,6 +1484,36 @@ void load_band(bl_ctx* c, const float* src, float2* dst, int ncomp) {
 void store_band(bl_ctx* c, const float2* src, float* dst, int ncomp) {
   HIP_TRY(hipMemcpyAsync(dst, src, band_bytes(c->g) * ncomp,
                          c->devptr ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream));
+}
+// a caller's band vector as the kernels read or write it: device vectors in place (8-byte aligned
+// ones), others through the context's staging (`staged` is stored afterwards)
+const float2* band_in(bl_ctx* c, const float* src, int ncomp) {
+  if (c->devptr && (reinterpret_cast<uintptr_t>(src) & 7) == 0) return reinterpret_cast<const float2*>(src);
+  load_band(c, src, c->braw, ncomp);
+  return c->braw;
+}
+float2* band_out(bl_ctx* c, float* dst, bool* staged) {
+  *staged = !(c->devptr && (reinterpret_cast<uintptr_t>(dst) & 7) == 0);
+  return *staged ? c->bout : reinterpret_cast<float2*>(dst);
+}
+// energy and gradient of a caller's velocity into the caller's variables (energy may be null)
+void velocity_and_gradient(bl_ctx* c, const float* v_hat, double* energy, float* g_hat) {
+  const int ncomp = c->g.nodes * c->g.dim;
+  const float2* v = band_in(c, v_hat, ncomp);
+  bool staged;
+  float2* out = band_out(c, g_hat, &staged);
+  auto store = [&]() {
+    if (staged) store_band(c, out, g_hat, ncomp);
+  };
+  if (!c->g.deform) {
+    op_energy_gradient(c, v, out, energy, store);
+    return;
+  }
+  op_set_velocity(c, v);
+  if (energy) *energy = c->E;
+  op_gradient(c, out);
+  store();
+  check_flag(c, "gradient");
 }
 void store_plane(bl_ctx* c, const float* src, float* dst, size_t nplanes) {
   HIP_TRY(hipMemcpyAsync(dst, src, plane_bytes(c->g) * nplanes,
@@ -1782,20 +1811,11 @@ int bl_lddmm_ctx_set_velocity(bl_ctx* c, const float* v_hat, double* energy, flo
   return guarded([&]() {
     HIP_TRY(hipSetDevice(c->device));
     Operation op(c);
-    load_band(c, v_hat, c->braw, c->g.nodes * c->g.dim);
-    if (g_hat && !c->g.deform && c->g.nodes == 1) {
-      op_energy_gradient(c, c->braw, c->bout,
-                         [&]() { store_band(c, c->bout, g_hat, c->g.dim); });
-      if (energy) *energy = c->E;
-      t_collect(c);
-      return BL_OK;
-    }
-    op_set_velocity(c, c->braw);
-    if (energy) *energy = c->E;
     if (g_hat) {
-      op_gradient(c, c->bout);
-      store_band(c, c->bout, g_hat, c->g.nodes * c->g.dim);
-      check_flag(c, "gradient");
+      velocity_and_gradient(c, v_hat, energy, g_hat);
+    } else {
+      op_set_velocity(c, band_in(c, v_hat, c->g.nodes * c->g.dim));
+      if (energy) *energy = c->E;
     }
     t_collect(c);
     return BL_OK;
@@ -1872,17 +1892,7 @@ int bl_lddmm_gradient(const bl_problem* prob, const float* I0, const float* I1,
     CachedCtx h(prob, g, false);
     Operation op(h.c);
     load_images(h.c, I0, I1);
-    load_band(h.c, v_hat, h.c->braw, g.nodes * g.dim);
-    if (!g.deform && g.nodes == 1) {
-      op_energy_gradient(h.c, h.c->braw, h.c->bout,
-                         [&]() { store_band(h.c, h.c->bout, g_hat, g.dim); });
-    } else {
-      op_set_velocity(h.c, h.c->braw);
-      op_gradient(h.c, h.c->bout);
-      store_band(h.c, h.c->bout, g_hat, g.nodes * g.dim);
-      check_flag(h.c, "gradient");
-    }
-    if (energy) *energy = h.c->E;
+    velocity_and_gradient(h.c, v_hat, energy, g_hat);
     h.ok = true;
     return BL_OK;
   });
@@ -1898,11 +1908,11 @@ int bl_lddmm_hessvec(const bl_problem* prob, const float* I0, const float* I1,
     CachedCtx h(prob, g, false);
     Operation op(h.c);
     load_images(h.c, I0, I1);
-    load_band(h.c, v_hat, h.c->braw, g.nodes * g.dim);
-    op_set_velocity(h.c, h.c->braw);
-    load_band(h.c, dv_hat, h.c->braw, g.nodes * g.dim);
-    op_hessvec(h.c, h.c->braw, h.c->bout);
-    store_band(h.c, h.c->bout, hv_hat, g.nodes * g.dim);
+    op_set_velocity(h.c, band_in(h.c, v_hat, g.nodes * g.dim));
+    bool staged;
+    float2* out = band_out(h.c, hv_hat, &staged);
+    op_hessvec(h.c, band_in(h.c, dv_hat, g.nodes * g.dim), out);
+    if (staged) store_band(h.c, out, hv_hat, g.nodes * g.dim);
     check_flag(h.c, "Hessian-vector product");
     h.ok = true;
     return BL_OK;
@@ -1918,8 +1928,7 @@ int bl_lddmm_warp(const bl_problem* prob, const float* I0, const float* v_hat, f
     CachedCtx h(prob, g, false);
     Operation op(h.c);
     load_images(h.c, I0, nullptr);
-    load_band(h.c, v_hat, h.c->braw, g.nodes * g.dim);
-    op_set_velocity(h.c, h.c->braw);
+    op_set_velocity(h.c, band_in(h.c, v_hat, g.nodes * g.dim));
     store_plane(h.c, h.c->mfinal, warped, 1);
     sync(h.c);
     h.ok = true;
