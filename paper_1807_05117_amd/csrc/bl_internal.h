@@ -181,8 +181,8 @@ struct DftPlan {
                             // the widest transform (4, or every node of a non-stationary field)
   float2* bufB = nullptr;
   // split hi/lo BF16 twiddle matrices of the mixed-precision z stages (FP32 mode: unused)
-  unsigned short* wi_bf16 = nullptr;   // [2][nzp32][mixed_kp]    iota: (hi, lo)
-  unsigned short* wp_bf16 = nullptr;   // [2][32 mixed_jt][nzp16] pi:   (hi, lo)
+  unsigned short* wi_bf16 = nullptr;   // 2 nzp32 mixed_kp     iota: (hi, lo)
+  unsigned short* wp_bf16 = nullptr;   // 64 mixed_jt nzp16    pi:   (hi, lo)
   int nzp32 = 0, nzp16 = 0;
   int mixed = 0;
 };

@@ -323,32 +323,36 @@ void split_bf16(double t, unsigned short& hi, unsigned short& lo) {
 //   Wi[z][2h] = s_h cos(2 pi h z / nz), Wi[z][2h+1] = -s_h sin(..), s_0 = 1, s_h = 2, rows
 //   z < round_up(nz, 32), columns < mixed_kp;  Wp[2h][z] = cos(..), Wp[2h+1][z] = -sin(..),
 //   rows < 32 mixed_jt, columns z < round_up(nz, 16).  Each as a hi table followed by a lo
-//   table; entries outside h < kzh, z < nz are zero.
+//   table; entries outside h < kzh, z < nz are zero.  A table is made of fragments of 32 rows
+//   by 16 columns, [row tile][column tile] in Wi and [column tile][row tile] in Wp; lane l of
+//   the 64 holds row l % 32, columns 8 (l / 32) .. + 7.
 void mixed_tables(const bl::Geo& g, std::vector<unsigned short>& wi,
                   std::vector<unsigned short>& wp) {
   const double two_pi = 6.283185307179586476925286766559;
   const int kp = bl::mixed_kp(g), zi = round_up(g.nz, 32);
-  const int jr = 32 * bl::mixed_jt(g), zp = round_up(g.nz, 16);
+  const int jt = bl::mixed_jt(g), zp = round_up(g.nz, 16);
   wi.assign((size_t)2 * zi * kp, 0);
-  wp.assign((size_t)2 * jr * zp, 0);
+  wp.assign((size_t)2 * 32 * jt * zp, 0);
+  const auto in_fragment = [](int row, int col) {
+    return (size_t)(row % 32 + 32 * (col % 16 / 8)) * 8 + col % 8;
+  };
   for (int z = 0; z < g.nz; ++z)
     for (int h = 0; h < g.kzh; ++h) {
       long long r = ((long long)h * z) % g.nz;
       const double ang = two_pi * (double)r / (double)g.nz;
       const double cs = std::cos(ang), sn = std::sin(ang), sh = h == 0 ? 1.0 : 2.0;
-      unsigned short hi, lo;
-      split_bf16(sh * cs, hi, lo);
-      wi[(size_t)z * kp + 2 * h] = hi;
-      wi[(size_t)zi * kp + (size_t)z * kp + 2 * h] = lo;
-      split_bf16(-sh * sn, hi, lo);
-      wi[(size_t)z * kp + 2 * h + 1] = hi;
-      wi[(size_t)zi * kp + (size_t)z * kp + 2 * h + 1] = lo;
-      split_bf16(cs, hi, lo);
-      wp[(size_t)(2 * h) * zp + z] = hi;
-      wp[(size_t)jr * zp + (size_t)(2 * h) * zp + z] = lo;
-      split_bf16(-sn, hi, lo);
-      wp[(size_t)(2 * h + 1) * zp + z] = hi;
-      wp[(size_t)jr * zp + (size_t)(2 * h + 1) * zp + z] = lo;
+      for (int im = 0; im < 2; ++im) {
+        const int k = 2 * h + im;
+        const size_t ai = ((size_t)(z / 32) * (kp / 16) + k / 16) * 512 + in_fragment(z, k);
+        const size_t ap = ((size_t)(z / 16) * jt + k / 32) * 512 + in_fragment(k, z);
+        unsigned short hi, lo;
+        split_bf16(im ? -sh * sn : sh * cs, hi, lo);
+        wi[ai] = hi;
+        wi[(size_t)zi * kp + ai] = lo;
+        split_bf16(im ? -sn : cs, hi, lo);
+        wp[ap] = hi;
+        wp[(size_t)32 * jt * zp + ap] = lo;
+      }
     }
 }
 

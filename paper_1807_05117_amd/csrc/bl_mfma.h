@@ -23,6 +23,9 @@ __device__ __forceinline__ Rsrc rsrc(const void* p, uint32_t bytes) {
 __device__ __forceinline__ f4 ld4(Rsrc r, uint32_t off) {
   return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
+__device__ __forceinline__ float ld1(Rsrc r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
 __device__ __forceinline__ f2 ld2(Rsrc r, uint32_t off) {
   return __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }

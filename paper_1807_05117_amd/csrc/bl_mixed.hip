@@ -15,26 +15,29 @@
 // Matrix-core operand layout (32x32x16, wave64): lane l holds A[i = l % 32][k = 8 (l / 32) + e]
 // and B[k = 8 (l / 32) + e][j = l % 32] for e = 0..7; the accumulator register r of lane l
 // holds D[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32].
-#include "bl_internal.h"
+//
+// Twiddle operands lie in the tables fragment by fragment, as a wavefront loads them: 64 lanes of
+// 8 consecutive values, 1 KB in one piece.  In rows of the matrices the same loads touched 32 to
+// 64 cache lines each, more cache traffic than the fields.  A lane's NT columns are consecutive,
+// so that it loads and stores 4 NT bytes at a time and a wavefront uses an operand NT times
+// (NT = 2 while the operands and sums of two columns leave registers for a second wavefront).
+// Bound by the grid's planes.  Three components, before and now: 160x192x160 (band 40x48x40)
+// iota 27.9 -> 16.7 us, pi 30.7 -> 19.8; 256^3 (band 64^3) 99.6 -> 50.6 and 97.2 -> 60.8 (5.0
+// and 4.1 TB/s); 128^3 11.1 -> 9.5 and 13.1 -> 10.4; 64^3 5.5 -> 4.5 and 6.2 -> 5.9; 96^3 with
+// band 96^3 (NT = 1) 11.5 -> 9.0 and 14.5 -> 11.6.
+#include "bl_mfma.h"
 
 namespace bl {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// FP32 -> BF16 bits, round to nearest even (finite inputs)
-__device__ __forceinline__ unsigned short bf16_rne(float x) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  return (unsigned short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-__device__ __forceinline__ float bf16_to_f32(unsigned short h) {
-  return __builtin_bit_cast(float, (uint32_t)h << 16);
-}
-__device__ __forceinline__ void split_bf16(float x, unsigned short& hi, unsigned short& lo) {
-  hi = bf16_rne(x);
-  lo = bf16_rne(x - bf16_to_f32(hi));
+// round to nearest even
+__device__ __forceinline__ void split2(f2 x, bf16x2& hi, bf16x2& lo) {
+  hi = __builtin_convertvector(x, bf16x2);
+  lo = __builtin_convertvector(x - __builtin_convertvector(hi, f2), bf16x2);
 }
 
 __device__ __forceinline__ f32x16 mfma3(bf16x8 ahi, bf16x8 alo, bf16x8 bhi, bf16x8 blo,
@@ -45,170 +48,211 @@ __device__ __forceinline__ f32x16 mfma3(bf16x8 ahi, bf16x8 alo, bf16x8 bhi, bf16
   return acc;
 }
 
-// iota z stage.  One wavefront per (component, 32 columns); the B operand (the half spectrum
-// of its 32 columns) stays in registers while the wavefront walks all 32-plane z tiles.
-// Wi is [2][nzp32][KP] BF16 (hi table then lo table), KP = 16 * KS.
-template <int KS>
+// the fragment of a lane: hi at f, lo at f + half
+__device__ __forceinline__ void frag(const bf16x8* W, size_t half, size_t f, bf16x8& hi, bf16x8& lo) {
+  hi = W[f];
+  lo = W[half + f];
+}
+
+// iota z stage.  A wavefront holds the half spectrum of 32 NT columns in registers (the B
+// operands) and forms z tiles of 32 planes; the next tile's twiddles are loaded meanwhile.
+// Wi: KS fragments for each z tile.
+template <int KS, int NT>
 __global__ __launch_bounds__(256) void k_iota_z_mfma(Geo g, const float2* __restrict__ F2,
-                                                     const unsigned short* __restrict__ Wi,
-                                                     int nzp32, float* __restrict__ out,
-                                                     int nqt) {
+                                                     const bf16x8* __restrict__ Wi, int tiles,
+                                                     float* __restrict__ out, int qblocks,
+                                                     int run) {
   BL_BATCH(g.bat)
   BL_AT(F2, g.bat);
   BL_AT(out, g.bat);
-  constexpr int KP = 16 * KS;
-  const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int nq = g.nx * g.ny;
-  const int c = blockIdx.y;
-  if (wave >= nqt) return;
-  const int q0 = wave * 32;
-  const int col = lane & 31, kq = lane >> 5;
-  const int q = q0 + col;
-  const int qc = q < nq ? q : nq - 1;
+  const int lane = threadIdx.x & 63, m = lane & 31, kq = lane >> 5;
+  const uint32_t nq = (uint32_t)g.nx * (uint32_t)g.ny;
+  const int c = blockIdx.y, chunk = (int)blockIdx.x / qblocks;
+  const uint32_t unit = blockIdx.x - chunk * qblocks;
+  const uint32_t col0 = (unit * 4u + (uint32_t)wave_of(threadIdx.x)) * (32u * NT);
+  const uint32_t col = col0 + NT * (uint32_t)m;
+  if (col0 >= nq) return;
+  const Rsrc rf = rsrc(F2 + (size_t)c * g.kzh * nq, (uint32_t)g.kzh * nq * 8u);
+  const Rsrc ro = rsrc(out + (size_t)c * g.M, (uint32_t)g.M * 4u);
   // B operand: k = 16 s + 8 kq + e  ->  h = 8 s + 4 kq + e/2, (Re, Im) by e parity
-  bf16x8 bhi[KS], blo[KS];
-  const float2* src = F2 + (size_t)c * g.kzh * nq + qc;
+  bf16x8 bhi[NT][KS], blo[NT][KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
-    u16x8 hv, lv;
+    bf16x2 hi[NT][4], lo[NT][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int h = 8 * s + 4 * kq + i;
-      const int hcl = h < g.kzh ? h : g.kzh - 1;
-      float2 v = src[(size_t)hcl * nq];
-      if (h >= g.kzh || q >= nq) v = make_float2(0.f, 0.f);
-      unsigned short a, b;
-      split_bf16(v.x, a, b);
-      hv[2 * i] = a;
-      lv[2 * i] = b;
-      split_bf16(v.y, a, b);
-      hv[2 * i + 1] = a;
-      lv[2 * i + 1] = b;
+      const uint32_t off = h < g.kzh ? ((uint32_t)h * nq + col) * 8u : kPast;
+      if constexpr (NT == 2) {
+        const f4 v = ld4(rf, off);
+        split2(f2{v.x, v.y}, hi[0][i], lo[0][i]);
+        split2(f2{v.z, v.w}, hi[1][i], lo[1][i]);
+      } else {
+        split2(ld2(rf, off), hi[0][i], lo[0][i]);
+      }
     }
-    bhi[s] = __builtin_bit_cast(bf16x8, hv);
-    blo[s] = __builtin_bit_cast(bf16x8, lv);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        bhi[j][s][e] = hi[j][e / 2][e & 1];
+        blo[j][s][e] = lo[j][e / 2][e & 1];
+      }
   }
-  const u16x8* Whi = reinterpret_cast<const u16x8*>(Wi);
-  const u16x8* Wlo = reinterpret_cast<const u16x8*>(Wi + (size_t)nzp32 * KP);
-  float* dst = out + (size_t)c * g.M + qc;
-  // z tiles four at a time: the A operands of the four tiles are loaded before any product
-  for (int zt0 = 0; zt0 * 32 < g.nz; zt0 += 4) {
-    bf16x8 ahi[4][KS], alo[4][KS];
+  const size_t half = (size_t)tiles * KS * 64;
+  const int t1 = min(tiles, (chunk + 1) * run);
+  bf16x8 nhi[KS], nlo[KS];
+  auto load = [&](int zt) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      // A row of this lane; rows past the table (tiles beyond nz) reuse row 0, never stored
-      const int zrow = (zt0 + u) * 32 < g.nz ? (zt0 + u) * 32 + col : col;
+    for (int s = 0; s < KS; ++s) frag(Wi, half, ((size_t)zt * KS + s) * 64 + lane, nhi[s], nlo[s]);
+  };
+  int zt = chunk * run;
+  if (zt < t1) load(zt);
+  for (; zt < t1; ++zt) {
+    bf16x8 ahi[KS], alo[KS];
+    f32x16 acc[NT];
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const size_t ai = ((size_t)zrow * KP + 16 * s + 8 * kq) / 8;
-        ahi[u][s] = __builtin_bit_cast(bf16x8, Whi[ai]);
-        alo[u][s] = __builtin_bit_cast(bf16x8, Wlo[ai]);
+    for (int s = 0; s < KS; ++s) ahi[s] = nhi[s], alo[s] = nlo[s];
+    if (zt + 1 < t1) load(zt + 1);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[j] = mfma3(ahi[s], alo[s], bhi[j][s], blo[j][s], acc[j]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int z = zt * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
+      const uint32_t o = ((uint32_t)z * nq + col) * 4u;
+      if (z >= g.nz) continue;
+      if constexpr (NT == 2) {
+        if (col + 2 <= nq) {
+          st2(ro, o, f2{acc[0][r], acc[1][r]});
+          continue;
+        }
       }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int zt = zt0 + u;
-      if (zt * 32 >= g.nz) break;
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) acc = mfma3(ahi[u][s], alo[u][s], bhi[s], blo[s], acc);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int z = zt * 32 + 8 * (r >> 2) + 4 * kq + (r & 3);
-        if (z < g.nz && q < nq) dst[(size_t)z * nq] = acc[r];
-      }
+      if (col < nq) st1(ro, o, acc[0][r]);
     }
   }
 }
 
-// pi z stage.  One block of four wavefronts per (component, 32 columns); wavefront w takes
-// the 16-plane steps w, w + 4, ... two at a time (16 loads in flight), splitting its B operand
-// on the fly, for JT 32-row tiles of (Re, Im) outputs; the four partial accumulators are
-// added in LDS in a fixed order.  Wp is [2][32 JT][nzp16] BF16 (hi table then lo table).
-template <int JT>
+// pi z stage.  The four wavefronts of a block share 32 NT columns; wavefront w takes the
+// 16-plane steps w, w + 4, ... two at a time, for JT 32-row tiles of (Re, Im) outputs; the
+// four sums are added in LDS in a fixed order.  Wp: JT fragments for each step.
+template <int JT, int NT>
 __global__ __launch_bounds__(256) void k_pi_z_mfma(Geo g, const float* __restrict__ f,
-                                                   const unsigned short* __restrict__ Wp,
-                                                   int nzp16, float2* __restrict__ G) {
+                                                   const bf16x8* __restrict__ Wp, int steps,
+                                                   float2* __restrict__ G) {
   BL_BATCH(g.bat)
   BL_AT(f, g.bat);
   BL_AT(G, g.bat);
-  __shared__ float red[3][JT][16][64];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nq = g.nx * g.ny;
+  __shared__ float red[4][NT][16][64];
+  const int lane = threadIdx.x & 63, m = lane & 31, kq = lane >> 5, w = wave_of(threadIdx.x);
+  const uint32_t nq = (uint32_t)g.nx * (uint32_t)g.ny;
   const int c = blockIdx.y;
-  const int q0 = blockIdx.x * 32;
-  const int col = lane & 31, kq = lane >> 5;
-  const int q = q0 + col;
-  const int qc = q < nq ? q : nq - 1;
-  f32x16 acc[JT];
+  const uint32_t col = blockIdx.x * (32u * NT) + NT * (uint32_t)m;
+  const Rsrc rf = rsrc(f + (size_t)c * g.M, (uint32_t)g.M * 4u);
+  const Rsrc ro = rsrc(G + (size_t)c * g.kzh * nq, (uint32_t)g.kzh * nq * 8u);
+  const size_t half = (size_t)steps * JT * 64;
+  f32x16 acc[NT][JT];
 #pragma unroll
-  for (int t = 0; t < JT; ++t)
+  for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-  const float* src = f + (size_t)c * g.M + qc;
-  const u16x8* Whi = reinterpret_cast<const u16x8*>(Wp);
-  const u16x8* Wlo = reinterpret_cast<const u16x8*>(Wp + (size_t)32 * JT * nzp16);
-  const int nsteps = (g.nz + 15) / 16;
-  for (int s0 = w; s0 < nsteps; s0 += 8) {
-    float v[2][8];
+    for (int t = 0; t < JT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
+  for (int s0 = w; s0 < steps; s0 += 8) {
+    float v[2][NT][8];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int z = 16 * (s0 + 4 * u) + 8 * kq + e;
-        v[u][e] = src[(size_t)(z < g.nz ? z : g.nz - 1) * nq];
-        if (z >= g.nz || q >= nq) v[u][e] = 0.f;
+        const uint32_t o = z < g.nz ? ((uint32_t)z * nq + col) * 4u : kPast;
+        if constexpr (NT == 2) {
+          const f2 x = ld2(rf, o);
+          v[u][0][e] = x.x;
+          v[u][1][e] = x.y;
+        } else {
+          v[u][0][e] = ld1(rf, o);
+        }
       }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int z0 = 16 * (s0 + 4 * u);
-      if (z0 >= g.nz) break;
-      u16x8 hv, lv;
+      if (s0 + 4 * u >= steps) break;   // the same for the wavefront
+      bf16x8 bhi[NT], blo[NT];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        unsigned short a, b;
-        split_bf16(v[u][e], a, b);
-        hv[e] = a;
-        lv[e] = b;
-      }
-      const bf16x8 bhi = __builtin_bit_cast(bf16x8, hv);
-      const bf16x8 blo = __builtin_bit_cast(bf16x8, lv);
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          bf16x2 hi, lo;
+          split2(f2{v[u][j][e], v[u][j][e + 1]}, hi, lo);
+          bhi[j][e] = hi.x, bhi[j][e + 1] = hi.y;
+          blo[j][e] = lo.x, blo[j][e + 1] = lo.y;
+        }
 #pragma unroll
       for (int t = 0; t < JT; ++t) {
-        const size_t ai = ((size_t)(32 * t + col) * nzp16 + z0 + 8 * kq) / 8;
-        acc[t] = mfma3(__builtin_bit_cast(bf16x8, Whi[ai]), __builtin_bit_cast(bf16x8, Wlo[ai]),
-                       bhi, blo, acc[t]);
+        bf16x8 ahi, alo;
+        frag(Wp, half, ((size_t)(s0 + 4 * u) * JT + t) * 64 + lane, ahi, alo);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j][t] = mfma3(ahi, alo, bhi[j], blo[j], acc[j][t]);
       }
     }
   }
-  if (w > 0) {
 #pragma unroll
-    for (int t = 0; t < JT; ++t)
+  for (int t = 0; t < JT; ++t) {
+    if (t > 0) __syncthreads();
 #pragma unroll
-      for (int r = 0; r < 16; ++r) red[w - 1][t][r][lane] = acc[t][r];
-  }
-  __syncthreads();
-  if (w != 0) return;
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-  for (int t = 0; t < JT; ++t)
+      for (int r = 0; r < 16; ++r) red[w][j][r][lane] = acc[j][t][r];
+    __syncthreads();
+    // wavefront w adds the registers 4 w .. 4 w + 3: rows 32 t + 8 w + 4 kq + 0..3, which are
+    // the (Re, Im) pairs of two h
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      acc[t][r] = ((acc[t][r] + red[0][t][r][lane]) + red[1][t][r][lane]) + red[2][t][r][lane];
-  // rows j = 8 (r / 4) + 4 kq + r % 4: registers (r, r + 1) with r % 4 in {0, 2} hold the
-  // (Re, Im) pair of h = j / 2
-  float2* dst = G + (size_t)c * g.kzh * nq + qc;
+    for (int i = 0; i < 2; ++i) {
+      const int h = 16 * t + 4 * w + 2 * kq + i;
+      f2 sum[NT];
 #pragma unroll
-  for (int t = 0; t < JT; ++t)
+      for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int j = 32 * t + 8 * (r >> 2) + 4 * kq + (r & 3);
-      const int h = j >> 1;
-      if (h < g.kzh && q < nq) dst[(size_t)h * nq] = make_float2(acc[t][r], acc[t][r + 1]);
+        for (int e = 0; e < 2; ++e) {
+          const int r = 4 * w + 2 * i + e;
+          sum[j][e] = ((red[0][j][r][lane] + red[1][j][r][lane]) + red[2][j][r][lane]) +
+                      red[3][j][r][lane];
+        }
+      const uint32_t o = ((uint32_t)h * nq + col) * 8u;
+      if (h >= g.kzh) continue;
+      if constexpr (NT == 2) {
+        if (col + 2 <= nq) {
+          st4(ro, o, f4{sum[0].x, sum[0].y, sum[1].x, sum[1].y});
+          continue;
+        }
+      }
+      if (col < nq) st2(ro, o, sum[0]);
     }
+  }
+}
+
+template <int KS, int NT>
+void launch_iota(const Geo& g, const DftPlan& p, const float2* F2, int C, float* out,
+                 hipStream_t s) {
+  const int64_t nq = (int64_t)g.nx * g.ny;
+  const int qb = (int)((nq + 128 * NT - 1) / (128 * NT)), tiles = p.nzp32 / 32;
+  // z tiles over blocks until the launch fills the device
+  int n = 1;
+  while ((int64_t)qb * C * n < 1024 && 2 * n <= tiles) n *= 2;
+  const int run = (tiles + n - 1) / n;
+  BL_LAUNCH((k_iota_z_mfma<KS, NT>), batch_grid(dim3((unsigned)(qb * ((tiles + run - 1) / run)), C), g.bat),
+            dim3(256), 0, s, g, F2, reinterpret_cast<const bf16x8*>(p.wi_bf16), tiles, out, qb, run);
+}
+template <int JT, int NT>
+void launch_pi(const Geo& g, const DftPlan& p, const float* f, int C, float2* G, hipStream_t s) {
+  const int64_t nq = (int64_t)g.nx * g.ny;
+  BL_LAUNCH((k_pi_z_mfma<JT, NT>), batch_grid(dim3((unsigned)((nq + 32 * NT - 1) / (32 * NT)), C), g.bat),
+            dim3(256), 0, s, g, f, reinterpret_cast<const bf16x8*>(p.wp_bf16), p.nzp16 / 16, G);
 }
 
 }  // namespace
@@ -218,42 +262,24 @@ int mixed_jt(const Geo& g) { return (2 * g.kzh + 31) / 32; }
 
 void iota_z_mixed(const Geo& g, const DftPlan& p, const float2* F2, int C, float* out,
                   hipStream_t s) {
-  const int nq = g.nx * g.ny;
-  const int nqt = (nq + 31) / 32;
-  const dim3 grid = batch_grid(dim3((nqt + 3) / 4, C), g.bat);
-  const int ks = mixed_kp(g) / 16;
-#define L_IOTA(K)                                                                             \
-  BL_LAUNCH(k_iota_z_mfma<K>, grid, dim3(256), 0, s, g, F2, p.wi_bf16, p.nzp32, out,          \
-                     nqt)
-  switch (ks) {
-    case 1: L_IOTA(1); break;
-    case 2: L_IOTA(2); break;
-    case 3: L_IOTA(3); break;
-    case 4: L_IOTA(4); break;
-    case 5: L_IOTA(5); break;
-    case 6: L_IOTA(6); break;
-    case 7: L_IOTA(7); break;
-    default: L_IOTA(8); break;
+  switch (mixed_kp(g) / 16) {
+    case 1: launch_iota<1, 2>(g, p, F2, C, out, s); break;
+    case 2: launch_iota<2, 2>(g, p, F2, C, out, s); break;
+    case 3: launch_iota<3, 2>(g, p, F2, C, out, s); break;
+    case 4: launch_iota<4, 2>(g, p, F2, C, out, s); break;
+    case 5: launch_iota<5, 1>(g, p, F2, C, out, s); break;
+    case 6: launch_iota<6, 1>(g, p, F2, C, out, s); break;
+    case 7: launch_iota<7, 1>(g, p, F2, C, out, s); break;
+    default: launch_iota<8, 1>(g, p, F2, C, out, s); break;
   }
-#undef L_IOTA
 }
 
 void pi_z_mixed(const Geo& g, const DftPlan& p, const float* f, int C, float2* G, hipStream_t s) {
-  const int nq = g.nx * g.ny;
-  const dim3 grid = batch_grid(dim3((nq + 31) / 32, C), g.bat);
   switch (mixed_jt(g)) {
-    case 1:
-      BL_LAUNCH(k_pi_z_mfma<1>, grid, dim3(256), 0, s, g, f, p.wp_bf16, p.nzp16, G);
-      break;
-    case 2:
-      BL_LAUNCH(k_pi_z_mfma<2>, grid, dim3(256), 0, s, g, f, p.wp_bf16, p.nzp16, G);
-      break;
-    case 3:
-      BL_LAUNCH(k_pi_z_mfma<3>, grid, dim3(256), 0, s, g, f, p.wp_bf16, p.nzp16, G);
-      break;
-    default:
-      BL_LAUNCH(k_pi_z_mfma<4>, grid, dim3(256), 0, s, g, f, p.wp_bf16, p.nzp16, G);
-      break;
+    case 1: launch_pi<1, 2>(g, p, f, C, G, s); break;
+    case 2: launch_pi<2, 2>(g, p, f, C, G, s); break;
+    case 3: launch_pi<3, 1>(g, p, f, C, G, s); break;
+    default: launch_pi<4, 1>(g, p, f, C, G, s); break;
   }
 }
 
