@@ -311,13 +311,9 @@ void Cohort::enqueue_step(int k_pcg) {
 
   // PCG start: delta = 0, r = -g, z = K r with <r, r> and <r, z>, p = z
   b = use(&ctl0->g_pstart);
-  bl::zero_band(c->sdelta, nb, s, b);
-  bl::zero_band(c->sr, nb, s, b);
-  bl::axpy(c->sr, c->sg, -1.0, nb, s, b);
-  bl::precond_dots(c->g, c->sr, c->Lhat, c->sz, pa, pb, s);
+  bl::pcg_start(c->g, c->sg, c->Lhat, c->sdelta, c->sr, c->sz, c->sp, pa, pb, s);
   bl::reduce_final2(pa, c->scal + S_RR, nullptr, pb, c->scal + S_RZ0, nullptr, bl::kRedBlocks, s,
                     false, nullptr, nullptr, b);
-  bl::copy_band(c->sp, c->sz, nb, s, b);
 
   // PCG iterations
   for (int j = 0; j < k_pcg; ++j) {

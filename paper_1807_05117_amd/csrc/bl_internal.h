@@ -443,9 +443,6 @@ void reduce_final2(const double* pa, double* outa, double* hosta, const double* 
                    double* hostb, int n, hipStream_t s, bool max_b = false,
                    const int* flag = nullptr, double* host_flag = nullptr,
                    const Batch& bt = Batch{});
-// y = alpha x + y
-void axpy(float2* y, const float2* x, double alpha, int64_t n, hipStream_t s,
-          const Batch& bt = Batch{});
 // done.word = done.value (host-mapped destination)
 void publish_done(Done done, hipStream_t s);
 // y = 0; y = x (kernels, so that a captured graph holds no memset or copy node)
@@ -466,9 +463,15 @@ void pcg_step(const Geo& g, const float2* p, const float2* Hp, const double* rz,
 // y = x + (num[0] / den[0]) y with device scalars
 void xpby_dev(float2* y, const float2* x, const double* num, const double* den, int64_t n,
               hipStream_t s, const Batch& bt = Batch{});
-// z = r / Lhat (per component); also kRedBlocks partials of <r, r> (p0) and <r, z> (p1)
-void precond_dots(const Geo& g, const float2* r, const float* Lhat, float2* z, double* p0,
-                  double* p1, hipStream_t s);
+// p = z + (rz_next / rz) p after summing kRedBlocks partials each: rr_next (also to host-mapped
+// rr_host) of p0, rz_next of p1, the same values as reduce_final2; rz and rz_next differ
+void pcg_direction(float2* p, const float2* z, const double* p0, const double* p1,
+                   const double* rz, double* rr_next, double* rr_host, double* rz_next, int64_t n,
+                   hipStream_t s);
+// delta = 0, r = -grad, z = r / Lhat (per component), p = z; also kRedBlocks partials of <r, r>
+// (p0) and <r, z> (p1)
+void pcg_start(const Geo& g, const float2* grad, const float* Lhat, float2* delta, float2* r,
+               float2* z, float2* p, double* p0, double* p1, hipStream_t s);
 // y = x + eps d
 void add_scaled(float2* y, const float2* x, const float2* d, double eps, int64_t n,
                 hipStream_t s);

@@ -1453,15 +1453,6 @@ void grad_stats(bl_ctx* c, const float2* gvec, double* gg, double* ginf, bool ha
   *ginf = c->hscal[S_GINF];
 }
 
-// enqueue z = r / Lhat with <r, r> -> slot S_RR (also published) and <r, z> -> slot rz_slot
-void enqueue_precond(bl_ctx* c, int rz_slot) {
-  double* pa = c->red + RED_A * bl::kRedBlocks;
-  double* pb = c->red + RED_B * bl::kRedBlocks;
-  bl::precond_dots(c->g, c->sr, c->Lhat, c->sz, pa, pb, c->stream);
-  bl::reduce_final2(pa, c->scal + S_RR, c->hdev + S_RR, pb, c->scal + rz_slot, nullptr,
-                    bl::kRedBlocks, c->stream);
-}
-
 double dev_sqdiff(bl_ctx* c, const float* a, const float* b) {
   double* part = c->red + RED_A * bl::kRedBlocks;
   bl::sqdiff_partial(a, b, c->g.M, part, c->stream);
@@ -1576,12 +1567,9 @@ void solve(bl_ctx* c, const bl_solver_opts& o, bl_stats* st) {
     const double thr = eta * gn;
     const double thr2 = thr * thr;
     // PCG on H delta = -g with preconditioner K = 1/Lhat, delta_0 = 0
-    HIP_TRY(hipMemsetAsync(c->sdelta, 0, nb * sizeof(float2), s));
-    HIP_TRY(hipMemsetAsync(c->sr, 0, nb * sizeof(float2), s));
-    bl::axpy(c->sr, c->sg, -1.0, nb, s);  // r = -g
     int rz_cur = S_RZ0, rz_next = S_RZ1;
-    enqueue_precond(c, rz_cur);
-    HIP_TRY(hipMemcpyAsync(c->sp, c->sz, nb * sizeof(float2), hipMemcpyDeviceToDevice, s));
+    bl::pcg_start(g, c->sg, c->Lhat, c->sdelta, c->sr, c->sz, c->sp, pa, pb, s);
+    bl::reduce_final(pb, bl::kRedBlocks, c->scal + rz_cur, s);
     int iters = 0;
     for (int j = 0; j < o.max_pcg; ++j) {
       // the partials of <p, Hp> come with the product's last kernel where it can form them
@@ -1593,8 +1581,10 @@ void solve(bl_ctx* c, const bl_solver_opts& o, bl_stats* st) {
       bl::pcg_step(g, c->sp, c->sHp, c->scal + rz_cur, pc,
                    fused ? bl::finalize_blocks(g) : bl::kRedBlocks, c->scal + S_PHP,
                    c->hdev + S_PHP, c->sdelta, c->sr, c->Lhat, c->sz, pa, pb, s);
-      bl::reduce_final2(pa, c->scal + S_RR, c->hdev + S_RR, pb, c->scal + rz_next, nullptr,
-                        bl::kRedBlocks, s);
+      // <r, r> and <r, z> from their partials, and the next direction p = z + beta p (of no use, and
+      // not read, if this step turns out to be the last)
+      bl::pcg_direction(c->sp, c->sz, pa, pb, c->scal + rz_cur, c->scal + S_RR, c->hdev + S_RR,
+                        c->scal + rz_next, nb, s);
       check_launch("pcg");
       sync(c);
       const double pHp = c->hscal[S_PHP];
@@ -1607,7 +1597,6 @@ void solve(bl_ctx* c, const bl_solver_opts& o, bl_stats* st) {
       // |r| <= eta |g|, compared as squares (the same FP64 operations as the batched engine's
       // device-side test, so both take the same decisions)
       if (std::max(c->hscal[S_RR], 0.0) <= thr2) break;
-      bl::xpby_dev(c->sp, c->sz, c->scal + rz_next, c->scal + rz_cur, nb, s);  // p = z + beta p
       std::swap(rz_cur, rz_next);
     }
     check_launch("pcg");

@@ -188,6 +188,42 @@ __global__ __launch_bounds__(256) void k_xpby_dev(float2* __restrict__ y, const 
   }
 }
 
+// The same for one problem, with the final sums before it: every block sums the partials p1 of
+// <r', z'> in the order of the final reduction pass, block 0 stores that and block 1 the sum of the
+// partials p0 of <r', r'>.  Bound by launch latency: a launch fewer for each PCG step, and the next
+// direction stands when the host has read <r', r'>.  With k_pcg_start, a registration at 128^3 (29
+// products) 8.27 -> 8.04 ms.
+__global__ __launch_bounds__(256) void k_pcg_direction(float2* __restrict__ p,
+                                                       const float2* __restrict__ z,
+                                                       const double* __restrict__ p0,
+                                                       const double* __restrict__ p1,
+                                                       const double* __restrict__ rz,
+                                                       double* __restrict__ rr_next,
+                                                       double* __restrict__ rr_host,
+                                                       double* __restrict__ rz_next, int64_t n) {
+  if (blockIdx.x == 1) {
+    reduce_block<false>(p0, kRedBlocks, rr_next, rr_host, nullptr, nullptr);
+    __syncthreads();
+  }
+  __shared__ double s_rz;
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < kRedBlocks; i += 256) acc += p1[i];
+  const double t = block_reduce_256<false>(acc);
+  if (threadIdx.x == 0) {
+    s_rz = t;
+    if (blockIdx.x == 0) rz_next[0] = t;
+  }
+  __syncthreads();
+  const double beta = s_rz / rz[0];
+  GRID_STRIDE(i, n) {
+    const float2 a = z[i];
+    float2 b = p[i];
+    b.x = (float)fma(beta, (double)b.x, (double)a.x);
+    b.y = (float)fma(beta, (double)b.y, (double)a.y);
+    p[i] = b;
+  }
+}
+
 __global__ __launch_bounds__(256) void k_dot_partial(const float2* __restrict__ a,
                                                      const float2* __restrict__ b, int64_t n,
                                                      double* __restrict__ partial, Batch bt) {
@@ -231,20 +267,6 @@ __global__ __launch_bounds__(256) void k_maxabs_partial(const float2* __restrict
   block_max_store(acc, partial);
 }
 
-__global__ __launch_bounds__(256) void k_axpy(float2* __restrict__ y, const float2* __restrict__ x,
-                                              double alpha, int64_t n, Batch bt) {
-  BL_BATCH(bt)
-  BL_AT(y, bt);
-  BL_AT(x, bt);
-  GRID_STRIDE(i, n) {
-    const float2 a = x[i];
-    float2 b = y[i];
-    b.x = (float)fma(alpha, (double)a.x, (double)b.x);
-    b.y = (float)fma(alpha, (double)a.y, (double)b.y);
-    y[i] = b;
-  }
-}
-
 __global__ __launch_bounds__(256) void k_xpby(float2* __restrict__ y, const float2* __restrict__ x,
                                               double beta, int64_t n) {
   GRID_STRIDE(i, n) {
@@ -271,25 +293,37 @@ __global__ __launch_bounds__(256) void k_add_scaled(float2* __restrict__ y,
   }
 }
 
-__global__ __launch_bounds__(256) void k_precond_dots(Geo g, const float2* __restrict__ r,
-                                                      const float* __restrict__ Lhat,
-                                                      float2* __restrict__ z,
-                                                      double* __restrict__ p0,
-                                                      double* __restrict__ p1) {
+// Start of PCG on H delta = -grad in one launch: delta = 0, r = -grad, z = r / Lhat, p = z and the
+// block partials of <r, r> (p0) and <r, z> (p1).  Bound by launch and memory latency: five
+// launches of 2 to 4 us before (two fills, an axpy, the product with the preconditioner, a copy).
+__global__ __launch_bounds__(256) void k_pcg_start(Geo g, const float2* __restrict__ grad,
+                                                   const float* __restrict__ Lhat,
+                                                   float2* __restrict__ delta,
+                                                   float2* __restrict__ r, float2* __restrict__ z,
+                                                   float2* __restrict__ p, double* __restrict__ p0,
+                                                   double* __restrict__ p1) {
   BL_BATCH(g.bat)
-  BL_AT(r, g.bat);
+  BL_AT(grad, g.bat);
   BL_AT(Lhat, g.bat);
+  BL_AT(delta, g.bat);
+  BL_AT(r, g.bat);
   BL_AT(z, g.bat);
+  BL_AT(p, g.bat);
   BL_AT(p0, g.bat);
   BL_AT(p1, g.bat);
   const int64_t n = (int64_t)g.nodes * g.dim * g.B;
   double rr = 0.0, rz = 0.0;
   GRID_STRIDE(i, n) {
     const int64_t b = i % g.B;
-    const float2 x = r[i];
+    const float2 gi = grad[i];
+    // 0 - grad, so that a zero stays +0
+    const float2 x = make_float2(0.f - gi.x, 0.f - gi.y);
     const float inv = 1.0f / Lhat[b];
     const float2 w = make_float2(x.x * inv, x.y * inv);
+    delta[i] = make_float2(0.f, 0.f);
+    r[i] = x;
     z[i] = w;
+    p[i] = w;
     if (g.nodes > 1) {
       const double wt = node_weight(g, i);
       rr = fma(wt * (double)x.x, (double)x.x, rr);
@@ -412,10 +446,6 @@ void maxabs_partial(const float2* a, int64_t n, double* partial, hipStream_t s, 
   hipLaunchKernelGGL(k_maxabs_partial, batch_grid(dim3(kRedBlocks), bt), dim3(256), 0, s, a, n,
                      partial, bt);
 }
-void axpy(float2* y, const float2* x, double alpha, int64_t n, hipStream_t s, const Batch& bt) {
-  hipLaunchKernelGGL(k_axpy, batch_grid(dim3(blocks_for(n)), bt), dim3(256), 0, s, y, x, alpha, n,
-                     bt);
-}
 void publish_done(Done done, hipStream_t s) {
   hipLaunchKernelGGL(k_publish_done, dim3(1), dim3(1), 0, s, done);
 }
@@ -437,10 +467,16 @@ void add_scaled(float2* y, const float2* x, const float2* d, double eps, int64_t
                 hipStream_t s) {
   hipLaunchKernelGGL(k_add_scaled, dim3(blocks_for(n)), dim3(256), 0, s, y, x, d, eps, n, Batch{});
 }
-void precond_dots(const Geo& g, const float2* r, const float* Lhat, float2* z, double* p0,
-                  double* p1, hipStream_t s) {
-  hipLaunchKernelGGL(k_precond_dots, batch_grid(dim3(kRedBlocks), g.bat), dim3(256), 0, s, g, r,
-                     Lhat, z, p0, p1);
+void pcg_start(const Geo& g, const float2* grad, const float* Lhat, float2* delta, float2* r,
+               float2* z, float2* p, double* p0, double* p1, hipStream_t s) {
+  hipLaunchKernelGGL(k_pcg_start, batch_grid(dim3(kRedBlocks), g.bat), dim3(256), 0, s, g, grad,
+                     Lhat, delta, r, z, p, p0, p1);
+}
+void pcg_direction(float2* p, const float2* z, const double* p0, const double* p1,
+                   const double* rz, double* rr_next, double* rr_host, double* rz_next, int64_t n,
+                   hipStream_t s) {
+  hipLaunchKernelGGL(k_pcg_direction, dim3(kRedBlocks), dim3(256), 0, s, p, z, p0, p1, rz, rr_next,
+                     rr_host, rz_next, n);
 }
 void sqdiff_partial(const float* a, const float* b, int64_t n, double* partial, hipStream_t s,
                     const Batch& bt) {
