@@ -1250,14 +1250,15 @@ void op_energy_gradient(bl_ctx* c, const float2* vraw, float2* gout, double* ene
   after();
   check_launch("energy and gradient");
   sync(c);
+  const bool nonfinite = c->hscal[S_FLAG] != 0.0;
+  if (nonfinite) {   // cleared whatever is thrown: the flag is this call's alone
+    HIP_TRY(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
+    sync(c);
+  }
   finish_set_velocity(c);
   if (energy) *energy = c->E;
   c->have_lambda = true;   // L holds this velocity's adjoint (the full Newton product reuses it)
-  if (c->hscal[S_FLAG] != 0.0) {
-    HIP_TRY(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
-    sync(c);
-    throw NonFinite{"gradient"};
-  }
+  if (nonfinite) throw NonFinite{"gradient"};
 }
 
 // backward transport of L[nt] down to L[0], then the body force b = sum_n w_n L[n] grad m^n
