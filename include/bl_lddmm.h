@@ -300,6 +300,23 @@ int bl_kernel_timing_read(bl_ctx* ctx, int32_t kclass, int64_t* launches, double
 int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);
 
 /*
+ * Sweeps: on grids whose tiles are resident on the device at once, a stationary state-equation
+ * context may run all time steps of a transport in one launch, with the values of the step
+ * launches.  A sweep abandons itself, and finishes more slowly, where offsets of several voxels
+ * per step leave the neighbourhood that a tile holds, or where a tile has waited too long for others
+ * (other work holds the device).
+ *   ctx_sweeps       out[0] tiles of the context's plan (0: its steps are launched one by one),
+ *                    out[1], [2] forward (state, incremental) and backward (adjoint) sweeps
+ *                    launched, out[3], [4] of these abandoned for their offsets and out[5], [6] for a
+ *                    wait, as far as it is known by now
+ *   ctx_sweep_wait   how long a tile waits before it abandons the sweep, 0 <= microseconds <= 1e6
+ *                    (default 50; 0: it never waits).  No value changes a result.
+ * Errors: BL_E_INVALID for a NULL argument or a wait outside its range.
+ */
+int bl_lddmm_ctx_sweeps(bl_ctx* ctx, int64_t out[7]);
+int bl_lddmm_ctx_sweep_wait(bl_ctx* ctx, double microseconds);
+
+/*
  * The autotuner: besides the transports' zv, it chooses the setup kernel's form (1, 2: gathers
  * from global memory, one or two voxels per thread; 4, 8: neighbourhoods in LDS) and the
  * z-chunking of the FP32 iota z stage, all bitwise-invariant, by timing at the first velocity of

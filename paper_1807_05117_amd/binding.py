@@ -128,6 +128,8 @@ def load():
         "bl_kernel_timing_enable": (C.c_int, [_P, C.c_int32]),
         "bl_kernel_timing_read": (C.c_int, [_P, C.c_int32, C.POINTER(C.c_int64), C.POINTER(C.c_double)]),
         "bl_lddmm_ctx_launch_shapes": (C.c_int, [_P, C.POINTER(C.c_int32)]),
+        "bl_lddmm_ctx_sweeps": (C.c_int, [_P, C.POINTER(C.c_int64)]),
+        "bl_lddmm_ctx_sweep_wait": (C.c_int, [_P, C.c_double]),
         "bl_server_create": (C.c_int, [C.c_uint64, C.c_int32, C.POINTER(C.c_void_p)]),
         "bl_server_create_batched": (C.c_int, [C.c_uint64, C.c_int32, C.POINTER(C.c_void_p)]),
         "bl_server_submit": (C.c_int, [_P, PP, C.POINTER(SolverOpts), _P, _P, _P,
@@ -407,6 +409,16 @@ class Ctx:
         out = (C.c_int32 * 4)()
         _check(self.lib.bl_lddmm_ctx_launch_shapes(self.h, out))
         return tuple(out)
+
+    def bl_lddmm_ctx_sweeps(self):
+        """(tiles of the plan or 0, forward and backward sweeps launched, those abandoned for their
+        offsets, those abandoned for a wait)"""
+        out = (C.c_int64 * 7)()
+        _check(self.lib.bl_lddmm_ctx_sweeps(self.h, out))
+        return tuple(out)
+
+    def bl_lddmm_ctx_sweep_wait(self, microseconds):
+        _check(self.lib.bl_lddmm_ctx_sweep_wait(self.h, float(microseconds)))
 
 
 # ----------------------------------------------------------------------------- serving

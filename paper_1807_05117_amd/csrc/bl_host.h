@@ -35,7 +35,9 @@ struct NonFinite {
 enum { RED_REG = 0, RED_DATA, RED_A, RED_B, RED_C, RED_SLOTS };
 // slots of the device scalars (bl_ctx::scal) and of their host-mapped mirror (bl_ctx::hscal)
 enum {
-  S_REG = 0, S_DATA, S_GG, S_GINF, S_PHP, S_SLOPE, S_RR, S_RZ0, S_RZ1, S_SQD, S_FLAG, S_DONE, S_SLOTS
+  S_REG = 0, S_DATA, S_GG, S_GINF, S_PHP, S_SLOPE, S_RR, S_RZ0, S_RZ1, S_SQD, S_FLAG, S_DONE,
+  S_SWEEP,   // [direction][SR_WORDS] words: what abandoned sweeps report
+  S_SLOTS = S_SWEEP + 4
 };
 
 int fail(int code, const std::string& msg);
@@ -116,6 +118,17 @@ struct bl_ctx {
   bl::SweepPlan sweep;
   uint32_t* sweep_sync = nullptr;   // 2 * kSweepWords
   bool sweep_clean[2] = {false, false};
+  // per direction: sweeps launched, the times at which any of them abandoned itself (the last known
+  // ones) and how many did
+  struct SweepSeen {
+    int64_t launched = 0;
+    uint64_t time[bl::SR_WORDS] = {};
+    int64_t count[bl::SR_WORDS] = {};
+  } sweep_seen[2];
+  // where they report: [direction][SR_WORDS] at hscal[S_SWEEP], or device memory where there is no
+  // host-mapped one (device address)
+  uint64_t* sweep_report = nullptr;
+  uint32_t sweep_wait = bl::kSweepWait;
   bool sweeps_allowed = false;      // inside an Operation that is not captured
   bool sweep_now = false;           // decided with each evaluation's or product's first launch
   // operations issued on this context and known to have ended (others are complete when the

@@ -322,6 +322,17 @@ struct SweepPlan {
   int box_floats = 0;   // LDS floats of a tile's rows and those its taps reach
   FastDiv div_nx, div_ty, div_ty2, div_nty, div_n4;   // by nx, ty, ty + 2, nty, 16-byte entries per row
 };
+// what the host gives a sweep beside its fields
+constexpr uint32_t kSweepWait = 5000;   // 50 us of the 100 MHz realtime counter
+struct SweepRun {
+  uint32_t* sync = nullptr;      // kSweepWords words, zero
+  int* nonfinite = nullptr;      // set if a wait was given up (never in a working run)
+  // SR_WORDS words: a sweep that abandons itself stores the time to one of them
+  uint64_t* report = nullptr;
+  uint32_t wait = kSweepWait;    // realtime ticks that a tile waits for others (0: not once)
+};
+// a tile's offsets left its box; a tile waited too long
+enum { SR_LEFT = 0, SR_LATE, SR_WORDS };
 struct SweepArgs {
   const float* X = nullptr;      // forward offsets (state, incremental)
   const float4* YA = nullptr;    // backward offsets and reaction factor (adjoint)
@@ -334,29 +345,27 @@ struct SweepArgs {
   const float* hs = nullptr;     // nt + 1 planes: hs^n and, in plane nt, u^nt (Newton adjoint)
   BodyStart b2;                  // dim planes: where b starts (Newton adjoint)
   float* acc = nullptr;          // dim planes to work in (Newton adjoint)
-  uint32_t* sync = nullptr;      // kSweepWords words, zero
-  int* nonfinite = nullptr;      // set if a wait was given up (never in a working run)
+  SweepRun run;
 };
 // run = 0 where the grid's tiles cannot all be resident (one per compute unit) or do not fit
 SweepPlan sweep_plan(const Geo& g, int compute_units);
 // m^{n+1} = Interp(m^n, i + X) for n = 0..nt-1 (as nt times state_step)
-void sweep_state(const Geo& g, const SweepPlan& p, const float* X, float* m, uint32_t* sync,
-                 int* nonfinite, hipStream_t s);
+void sweep_state(const Geo& g, const SweepPlan& p, const float* X, float* m, const SweepRun& r,
+                 hipStream_t s);
 // t^0..t^{nt-1} into the planes t (as inc_init, inc_step) and inc_last's value into plane nt
 void sweep_inc(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
-               float* t, uint32_t* sync, int* nonfinite, hipStream_t s);
+               float* t, const SweepRun& r, hipStream_t s);
 // lam[nt] transported down to lam[1] (keep0: lam[0]) and the body force b (as adj_step and
 // body_force)
 void sweep_adj(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, float* lam,
-               float* b, int keep0, uint32_t* sync, int* nonfinite, hipStream_t s);
+               float* b, int keep0, const SweepRun& r, hipStream_t s);
 
 // the Newton product's: t^0..t^{nt-1} into the planes t and dm^1..dm^nt into dm; and, with the
 // terms of newton_terms, u^{nt-1}..u^1 into the planes u and the body force b
 void sweep_inc_n(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
-                 float* t, float* dm, uint32_t* sync, int* nonfinite, hipStream_t s);
+                 float* t, float* dm, const SweepRun& r, hipStream_t s);
 void sweep_adj_n(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, const float* hs,
-                 const BodyStart& b2, float* acc, float* u, float* b, uint32_t* sync, int* nonfinite,
-                 hipStream_t s);
+                 const BodyStart& b2, float* acc, float* u, float* b, const SweepRun& r, hipStream_t s);
 
 // ---- deformation state equation (bl_deform.hip)
 // Band fields are full centred bands of g (B entries per component); product-grid planes have

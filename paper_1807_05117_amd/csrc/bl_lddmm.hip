@@ -556,6 +556,9 @@ bl_ctx* create_ctx(const bl_problem* prob, const bl::Geo& g, bool transport, boo
       c->hscal = alloc_host_scalars();
     }
     if (c->hscal) HIP_TRY(hipHostGetDevicePointer((void**)&c->hdev, c->hscal, 0));
+    // a slot's scalars may have served another context
+    for (int i = 0; c->hscal && i < 2 * bl::SR_WORDS; ++i) c->hscal[S_SWEEP + i] = 0.0;
+    c->sweep_report = reinterpret_cast<uint64_t*>(c->hdev ? (char*)(c->hdev + S_SWEEP) : (char*)(c->flag + 16));
     // host tables: twiddles of exactly reduced angles, the symbol of L
     std::vector<float2> tw;
     auto upload = [&](float2* dst) {
@@ -1159,13 +1162,31 @@ bool use_sweeps(const bl_ctx* c) {
          !c->shapes_fixed;
 }
 
-// the zeroed words of the forward (0) or backward (1) sweep
-uint32_t* sweep_words(bl_ctx* c, int which) {
-  uint32_t* w = c->sweep_sync + (size_t)which * bl::kSweepWords;
-  if (!c->sweep_clean[which])
-    bl::zero_band(reinterpret_cast<float2*>(w), bl::kSweepWords / 2, c->stream);
-  c->sweep_clean[which] = false;
-  return w;
+// the next forward (0) or backward (1) sweep, with its zeroed words
+bl::SweepRun next_sweep(bl_ctx* c, int dir) {
+  bl::SweepRun r;
+  r.sync = c->sweep_sync + (size_t)dir * bl::kSweepWords;
+  if (!c->sweep_clean[dir])
+    bl::zero_band(reinterpret_cast<float2*>(r.sync), bl::kSweepWords / 2, c->stream);
+  c->sweep_clean[dir] = false;
+  r.nonfinite = c->flag;
+  r.report = c->sweep_report + dir * bl::SR_WORDS;
+  r.wait = c->sweep_wait;
+  c->sweep_seen[dir].launched += 1;
+  return r;
+}
+
+// what sweeps have reported to host memory so far
+void read_sweep_reports(bl_ctx* c) {
+  if (!c->hscal) return;
+  const uint64_t* w = reinterpret_cast<const uint64_t*>(c->hscal + S_SWEEP);
+  for (int dir = 0; dir < 2; ++dir)
+    for (int k = 0; k < bl::SR_WORDS; ++k) {
+      const uint64_t t = __atomic_load_n(w + dir * bl::SR_WORDS + k, __ATOMIC_RELAXED);
+      if (t == c->sweep_seen[dir].time[k]) continue;
+      c->sweep_seen[dir].time[k] = t;
+      c->sweep_seen[dir].count[k] += 1;
+    }
 }
 
 // band_prep of a stationary velocity or direction; zeroes the sweeps' words in the same launch
@@ -1191,7 +1212,7 @@ void enqueue_set_velocity(bl_ctx* c, const float2* vraw) {
   if (!c->tuned) choose_launch_shapes(c);
   const size_t M = (size_t)g.M;
   if (use_sweeps(c))
-    bl::sweep_state(g, c->sweep, c->X, c->m, sweep_words(c, 0), c->flag, s);
+    bl::sweep_state(g, c->sweep, c->X, c->m, next_sweep(c, 0), s);
   else
     for (int n = 0; n < g.nt; ++n)
       timed(c, 0, [&] { bl::state_step(g, c->m + n * M, c->X, c->m + (n + 1) * M, s); });
@@ -1277,7 +1298,7 @@ void backward_and_body_force(bl_ctx* c) {
   hipStream_t s = c->stream;
   const size_t M = (size_t)g.M;
   if (use_sweeps(c)) {
-    bl::sweep_adj(g, c->sweep, c->YA, c->m, c->L, c->Bf, g.newton, sweep_words(c, 1), c->flag, s);
+    bl::sweep_adj(g, c->sweep, c->YA, c->m, c->L, c->Bf, g.newton, next_sweep(c, 1), s);
     return;
   }
   const bool form0 = body_forms_lambda0(g);
@@ -1327,7 +1348,7 @@ void op_hessvec_newton(bl_ctx* c, const float2* draw, float2* hout, double* dot_
   // in the last plane) take DL, u^n the planes of dm^n, and b starts at b2
   const bool sweep = use_sweeps(c);
   if (sweep) {
-    bl::sweep_inc_n(g, c->sweep, c->X, c->m, c->DV, c->DL, c->DM, sweep_words(c, 0), c->flag, s);
+    bl::sweep_inc_n(g, c->sweep, c->X, c->m, c->DV, c->DL, c->DM, next_sweep(c, 0), s);
   } else {
     bl::inc_init(g, c->m, c->DV, c->T0, s);
     float* tin = c->T0;
@@ -1341,8 +1362,7 @@ void op_hessvec_newton(bl_ctx* c, const float2* draw, float2* hout, double* dot_
   const bl::BodyStart b2{{c->T0, c->T1, c->U}};
   bl::newton_terms(g, c->L, c->DM, c->DV, c->DL, b2, s);
   if (sweep) {
-    bl::sweep_adj_n(g, c->sweep, c->YA, c->m, c->DL, b2, c->DV, c->DM, c->Bf, sweep_words(c, 1),
-                    c->flag, s);
+    bl::sweep_adj_n(g, c->sweep, c->YA, c->m, c->DL, b2, c->DV, c->DM, c->Bf, next_sweep(c, 1), s);
   } else {
     const float* uin = c->DL + g.nt * M;
     for (int n = g.nt - 1; n >= 0; --n) {
@@ -1380,7 +1400,7 @@ bool op_hessvec(bl_ctx* c, const float2* draw, float2* hout, double* dot_part) {
   timed(c, 3, [&] { bl::iota_z(g, c->plan, g.dim, c->DV, s); });
   if (use_sweeps(c)) {
     // t^n into the planes that the backward sweep overwrites
-    bl::sweep_inc(g, c->sweep, c->X, c->m, c->DV, c->L, sweep_words(c, 0), c->flag, s);
+    bl::sweep_inc(g, c->sweep, c->X, c->m, c->DV, c->L, next_sweep(c, 0), s);
   } else {
     bl::inc_init(g, c->m, c->DV, c->T0, s);
     float* tin = c->T0;
@@ -2009,6 +2029,28 @@ int bl_lddmm_ctx_launch_shapes(bl_ctx* c, int32_t zv_out[4]) {
   t_err.clear();
   if (!c || !zv_out) return fail(BL_E_INVALID, "NULL pointer argument");
   for (int k = 0; k < 4; ++k) zv_out[k] = c->g.dim == 3 ? c->g.zv[k] : 1;
+  return BL_OK;
+}
+
+int bl_lddmm_ctx_sweeps(bl_ctx* c, int64_t out[7]) {
+  t_err.clear();
+  if (!c || !out) return fail(BL_E_INVALID, "NULL pointer argument");
+  read_sweep_reports(c);
+  out[0] = c->sweep.run > 0 ? c->sweep.tiles : 0;
+  for (int dir = 0; dir < 2; ++dir) {
+    out[1 + dir] = c->sweep_seen[dir].launched;
+    out[3 + dir] = c->sweep_seen[dir].count[bl::SR_LEFT];
+    out[5 + dir] = c->sweep_seen[dir].count[bl::SR_LATE];
+  }
+  return BL_OK;
+}
+
+int bl_lddmm_ctx_sweep_wait(bl_ctx* c, double microseconds) {
+  t_err.clear();
+  if (!c) return fail(BL_E_INVALID, "NULL context");
+  if (!(microseconds >= 0.0 && microseconds <= 1e6))
+    return fail(BL_E_INVALID, "the wait must lie in [0, 1e6] microseconds");
+  c->sweep_wait = (uint32_t)(microseconds * 100.0);   // ticks of 10 ns
   return BL_OK;
 }
 

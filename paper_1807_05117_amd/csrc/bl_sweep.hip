@@ -27,7 +27,7 @@
 // Progress.  Owners wait for each other, so they must all be resident.  The launch has at most
 // one workgroup per compute unit, but nothing reserves the device for it: another stream's
 // kernels may hold compute units, or another sweep may hold some while waiting for the rest.  So
-// no wait is without end: a workgroup that has waited kWaitTicks abandons the sweep for all its
+// no wait is without end: a workgroup that has waited SweepRun::wait abandons the sweep for all its
 // workgroups (the abort word).  Those of an abandoned sweep take (step, block of columns) tickets
 // from one counter instead, in time order, each with a wait for all blocks of the step before.
 // The holder of a ticket waits only for earlier tickets, and those are held by workgroups that are
@@ -48,9 +48,6 @@ constexpr int kLdsBytes = 160 * 1024 - 512;
 constexpr int kTabRows = 512;       // rows of other tiles a box may hold
 constexpr int kXCDs = 8;
 typedef __attribute__((address_space(3))) void* LdsPtr;
-// 50 us of the 100 MHz realtime counter: ten steps of a sweep that has the device, and little
-// beside the tickets that follow when it has not
-constexpr uint64_t kWaitTicks = 5000;
 constexpr uint64_t kGiveUpTicks = 1000000000; // 10 s: a bound on every wait, never met
 // words of a sweep's synchronisation area (kSweepWords): all zero before the launch
 enum { SY_ABORT = 0, SY_TICKET = 16, SY_DONE = 48, SY_FLAGS = 320 };
@@ -60,6 +57,21 @@ __device__ __forceinline__ uint32_t ld_flag(const uint32_t* p) {
 }
 __device__ __forceinline__ void st_flag(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// A value that no earlier report had, to memory that the host may read meanwhile.  The address is
+// read from the kernel's arguments here, where it is rarely wanted: as a value it would be kept in
+// scalar registers, which are short, for the whole sweep (1% of a product at 128^3).
+struct KernelArgs {
+  Geo g;
+  SweepPlan p;
+  SweepArgs a;
+};
+__device__ __forceinline__ void report(int word) {
+  typedef const __attribute__((address_space(4))) KernelArgs* Ptr;
+  Ptr k = (Ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(k));
+  __hip_atomic_store(k->a.run.report + word, __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ uint32_t add_flag(uint32_t* p) {
   return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -263,16 +275,16 @@ __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, in
   const uint32_t stages = (uint32_t)g.nt + (KIND == SWEEP_STATE || KIND == SWEEP_ADJ_N ? 0u : 1u);
   for (;;) {
     __syncthreads();
-    if (threadIdx.x == 0) sh[0] = (int)add_flag(a.sync + SY_TICKET);
+    if (threadIdx.x == 0) sh[0] = (int)add_flag(a.run.sync + SY_TICKET);
     __syncthreads();
     const uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane(sh[0]);
     if (k >= stages * chunks) return;
     const uint32_t stage = k / chunks, chunk = k - stage * chunks, zb = chunk / nq;
     if (threadIdx.x == 0 && stage > 0) {
       const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      while (ld_flag(a.sync + SY_DONE + stage - 1) < chunks) {
+      while (ld_flag(a.run.sync + SY_DONE + stage - 1) < chunks) {
         if (__builtin_amdgcn_s_memrealtime() - t0 > kGiveUpTicks) {
-          *a.nonfinite = 1;
+          *a.run.nonfinite = 1;
           break;
         }
         __builtin_amdgcn_s_sleep(4);
@@ -344,7 +356,7 @@ __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, in
     }
     stores_done();
     __syncthreads();
-    if (threadIdx.x == 0) add_flag(a.sync + SY_DONE + stage);
+    if (threadIdx.x == 0) add_flag(a.run.sync + SY_DONE + stage);
   }
 }
 
@@ -355,7 +367,7 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
   uint2* const tab = reinterpret_cast<uint2*>(lds4);                  // [kTabRows] rows of other tiles
   uint32_t* const mtab = reinterpret_cast<uint32_t*>(tab + kTabRows); // [kTabRows] the stencil's rows
   float* const S = reinterpret_cast<float*>(mtab + kTabRows);         // the tile's box of rows
-  __shared__ int sh[8];                                               // 0-3 box, 4 out of time
+  __shared__ int sh[8];   // 0-3 box, 4 abandoned, 5 by this tile, 6 how long it waits
   constexpr bool kStencil = KIND != SWEEP_STATE;
   const Rows<DIM> rw(g);
   const size_t M = (size_t)g.M;
@@ -363,7 +375,7 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
   const int tile = (int)((blockIdx.x % kXCDs) * (nb / kXCDs) + blockIdx.x / kXCDs);
   const uint32_t tid = threadIdx.x, nthr = blockDim.x;
   const bool shared = p.tiles > 1;   // a single tile waits for nobody
-  uint32_t* const flags = a.sync + SY_FLAGS;
+  uint32_t* const flags = a.run.sync + SY_FLAGS;
 
   if (tile >= p.tiles) return;
   {
@@ -379,7 +391,9 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
     for (int r = 0; r < R; ++r)
       load_offsets<KIND, DIM>(g, rw, a, t, clampz(t.z0 + r, rw.rz), wx[r], wy[r], wz[r]);
     if (tid < 4) sh[tid] = (tid & 1) ? -(1 << 28) : (1 << 28);
-    if (tid == 4) sh[4] = shared && ld_flag(a.sync + SY_ABORT) != 0;   // abandoned already
+    if (tid == 4) sh[4] = shared && ld_flag(a.run.sync + SY_ABORT) != 0;   // abandoned already
+    if (tid == 5) sh[5] = 0;
+    if (tid == 6) sh[6] = (int)a.run.wait;
 
     // the state's plane around the tile, for the stencils: where its rows come from
     float* const mbuf = S + p.box_floats;
@@ -475,7 +489,10 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
     const long long nrows = (long long)(hz0 + hz1) * by + (long long)hy * sz;
     const bool fits = (long long)by * bz * pitch <= p.box_floats && nrows <= kTabRows;
     bool bail = sh[4] != 0 || !fits;
-    if (!fits && tid == 0) st_flag(a.sync + SY_ABORT, 1u);
+    if (!fits && tid == 0) {
+      st_flag(a.run.sync + SY_ABORT, 1u);
+      report(SR_LEFT);
+    }
     const int rows = bail ? 0 : (int)nrows;
     const uint32_t entries = (uint32_t)rows * n4;
     for (int i = (int)tid; i < rows; i += (int)nthr) {
@@ -603,11 +620,14 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
         for (uint32_t it = 1;; ++it) {
           const uint32_t pa = ld_flag(fa), pb = ld_flag(fb);
           if (__builtin_amdgcn_ballot_w64(min(pa, pb) < need) == 0) break;
-          if ((it & 15u) == 0) {
+          if ((it & 15u) == 0 || sh[6] == 0) {
             const uint64_t now = __builtin_amdgcn_s_memrealtime();
             if (start == 0) start = now;
-            if (now - start > kWaitTicks) st_flag(a.sync + SY_ABORT, 1u);
-            if (ld_flag(a.sync + SY_ABORT) != 0) {
+            if (now - start >= (uint32_t)sh[6]) {
+              st_flag(a.run.sync + SY_ABORT, 1u);
+              sh[5] = 1;
+            }
+            if (ld_flag(a.run.sync + SY_ABORT) != 0) {
               out_of_time = true;
               break;
             }
@@ -642,6 +662,7 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
       if (out_of_time) sh[4] = 1;
       __syncthreads();
       if (sh[4] != 0) {
+        if (tid == 0 && sh[5] != 0) report(SR_LATE);
         bail = true;
         break;
       }
@@ -802,54 +823,49 @@ SweepPlan sweep_plan(const Geo& g, int compute_units) {
   return best;
 }
 
-void sweep_state(const Geo& g, const SweepPlan& p, const float* X, float* m, uint32_t* sync,
-                 int* nonfinite, hipStream_t s) {
+void sweep_state(const Geo& g, const SweepPlan& p, const float* X, float* m, const SweepRun& r,
+                 hipStream_t s) {
   SweepArgs a{};
   a.X = X;
   a.planes = m;
-  a.sync = sync;
-  a.nonfinite = nonfinite;
+  a.run = r;
   launch_kind<SWEEP_STATE>(g, p, a, s);
 }
 void sweep_inc(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
-               float* t, uint32_t* sync, int* nonfinite, hipStream_t s) {
+               float* t, const SweepRun& r, hipStream_t s) {
   SweepArgs a{};
   a.X = X;
   a.planes = t;
   a.m = m;
   a.dv = dv;
-  a.sync = sync;
-  a.nonfinite = nonfinite;
+  a.run = r;
   launch_kind<SWEEP_INC>(g, p, a, s);
 }
 void sweep_adj(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, float* lam,
-               float* b, int keep0, uint32_t* sync, int* nonfinite, hipStream_t s) {
+               float* b, int keep0, const SweepRun& r, hipStream_t s) {
   SweepArgs a{};
   a.YA = YA;
   a.planes = lam;
   a.m = m;
   a.b = b;
   a.keep0 = keep0;
-  a.sync = sync;
-  a.nonfinite = nonfinite;
+  a.run = r;
   launch_kind<SWEEP_ADJ>(g, p, a, s);
 }
 
 void sweep_inc_n(const Geo& g, const SweepPlan& p, const float* X, const float* m, const float* dv,
-                 float* t, float* dm, uint32_t* sync, int* nonfinite, hipStream_t s) {
+                 float* t, float* dm, const SweepRun& r, hipStream_t s) {
   SweepArgs a{};
   a.X = X;
   a.planes = t;
   a.m = m;
   a.dv = dv;
   a.dm = dm;
-  a.sync = sync;
-  a.nonfinite = nonfinite;
+  a.run = r;
   launch_kind<SWEEP_INC_N>(g, p, a, s);
 }
 void sweep_adj_n(const Geo& g, const SweepPlan& p, const float4* YA, const float* m, const float* hs,
-                 const BodyStart& b2, float* acc, float* u, float* b, uint32_t* sync, int* nonfinite,
-                 hipStream_t s) {
+                 const BodyStart& b2, float* acc, float* u, float* b, const SweepRun& r, hipStream_t s) {
   SweepArgs a{};
   a.YA = YA;
   a.planes = u;
@@ -858,8 +874,7 @@ void sweep_adj_n(const Geo& g, const SweepPlan& p, const float4* YA, const float
   a.b2 = b2;
   a.acc = acc;
   a.b = b;
-  a.sync = sync;
-  a.nonfinite = nonfinite;
+  a.run = r;
   launch_kind<SWEEP_ADJ_N>(g, p, a, s);
 }
 
