@@ -311,10 +311,15 @@ int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);
  *                    wait, as far as it is known by now
  *   ctx_sweep_wait   how long a tile waits before it abandons the sweep, 0 <= microseconds <= 1e6
  *                    (default 50; 0: it never waits).  No value changes a result.
- * Errors: BL_E_INVALID for a NULL argument or a wait outside its range.
+ *   ctx_sweep_polls  how often an abandoned sweep looks for the end of its earlier parts, 0 <= polls
+ *                    <= 2^24 (the default, about ten seconds of running), before it is given up: then
+ *                    the call that waits for it, or after an enqueued product the next one that
+ *                    waits on the context, returns BL_E_DEVICE, and the velocity has to be set again
+ * Errors: BL_E_INVALID for a NULL argument or one outside its range.
  */
 int bl_lddmm_ctx_sweeps(bl_ctx* ctx, int64_t out[7]);
 int bl_lddmm_ctx_sweep_wait(bl_ctx* ctx, double microseconds);
+int bl_lddmm_ctx_sweep_polls(bl_ctx* ctx, int64_t polls);
 
 /*
  * The autotuner: besides the transports' zv, it chooses the setup kernel's form (1, 2: gathers

@@ -130,6 +130,7 @@ def load():
         "bl_lddmm_ctx_launch_shapes": (C.c_int, [_P, C.POINTER(C.c_int32)]),
         "bl_lddmm_ctx_sweeps": (C.c_int, [_P, C.POINTER(C.c_int64)]),
         "bl_lddmm_ctx_sweep_wait": (C.c_int, [_P, C.c_double]),
+        "bl_lddmm_ctx_sweep_polls": (C.c_int, [_P, C.c_int64]),
         "bl_server_create": (C.c_int, [C.c_uint64, C.c_int32, C.POINTER(C.c_void_p)]),
         "bl_server_create_batched": (C.c_int, [C.c_uint64, C.c_int32, C.POINTER(C.c_void_p)]),
         "bl_server_submit": (C.c_int, [_P, PP, C.POINTER(SolverOpts), _P, _P, _P,
@@ -419,6 +420,9 @@ class Ctx:
 
     def bl_lddmm_ctx_sweep_wait(self, microseconds):
         _check(self.lib.bl_lddmm_ctx_sweep_wait(self.h, float(microseconds)))
+
+    def bl_lddmm_ctx_sweep_polls(self, polls):
+        _check(self.lib.bl_lddmm_ctx_sweep_polls(self.h, int(polls)))
 
 
 # ----------------------------------------------------------------------------- serving

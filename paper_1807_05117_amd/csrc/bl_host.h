@@ -31,13 +31,14 @@ inline void check_launch(const char* where) {
 struct NonFinite {
   const char* what;
 };
+struct SweepGivenUp {};
 
 enum { RED_REG = 0, RED_DATA, RED_A, RED_B, RED_C, RED_SLOTS };
 // slots of the device scalars (bl_ctx::scal) and of their host-mapped mirror (bl_ctx::hscal)
 enum {
   S_REG = 0, S_DATA, S_GG, S_GINF, S_PHP, S_SLOPE, S_RR, S_RZ0, S_RZ1, S_SQD, S_FLAG, S_DONE,
   S_SWEEP,   // [direction][SR_WORDS] words: what abandoned sweeps report
-  S_SLOTS = S_SWEEP + 4
+  S_SLOTS = S_SWEEP + 6
 };
 
 int fail(int code, const std::string& msg);
@@ -128,7 +129,7 @@ struct bl_ctx {
   // where they report: [direction][SR_WORDS] at hscal[S_SWEEP], or device memory where there is no
   // host-mapped one (device address)
   uint64_t* sweep_report = nullptr;
-  uint32_t sweep_wait = bl::kSweepWait;
+  uint32_t sweep_wait = bl::kSweepWait, sweep_polls = bl::kSweepPolls;
   bool sweeps_allowed = false;      // inside an Operation that is not captured
   bool sweep_now = false;           // decided with each evaluation's or product's first launch
   // operations issued on this context and known to have ended (others are complete when the
@@ -199,6 +200,7 @@ struct CtxHolder {
 };
 // 64 doubles of pinned, coherent, device-mapped host memory for published scalars
 double* alloc_host_scalars();
+// waits for the stream; throws SweepGivenUp if a sweep on it was given up since the last call
 void sync(bl_ctx* c);
 void load_images(bl_ctx* c, const float* I0, const float* I1);
 void load_band(bl_ctx* c, const float* src, float2* dst, int ncomp);
@@ -230,6 +232,8 @@ int guarded(F&& f) {
     return fail(BL_E_DEVICE, std::string("HIP error in ") + e.where + ": " + hipGetErrorString(e.e));
   } catch (const NonFinite& e) {
     return fail(BL_E_NONFINITE, std::string("non-finite value in ") + e.what);
+  } catch (const SweepGivenUp&) {
+    return fail(BL_E_DEVICE, "a transport's workgroups waited for others without end; its fields are not valid");
   } catch (const std::bad_alloc&) {
     return fail(BL_E_NOMEM, "device working set does not fit in free memory");
   } catch (...) {

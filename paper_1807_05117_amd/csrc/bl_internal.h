@@ -324,15 +324,19 @@ struct SweepPlan {
 };
 // what the host gives a sweep beside its fields
 constexpr uint32_t kSweepWait = 5000;   // 50 us of the 100 MHz realtime counter
+// about ten seconds of running: counted in looks, since a clock also runs while a workgroup is
+// suspended for another process
+constexpr uint32_t kSweepPolls = 1u << 24;
 struct SweepRun {
   uint32_t* sync = nullptr;      // kSweepWords words, zero
-  int* nonfinite = nullptr;      // set if a wait was given up (never in a working run)
   // SR_WORDS words: a sweep that abandons itself stores the time to one of them
   uint64_t* report = nullptr;
   uint32_t wait = kSweepWait;    // realtime ticks that a tile waits for others (0: not once)
+  uint32_t polls = kSweepPolls;  // looks at an abandoned sweep's earlier blocks before it is given up
 };
-// a tile's offsets left its box; a tile waited too long
-enum { SR_LEFT = 0, SR_LATE, SR_WORDS };
+// a tile's offsets left its box; a tile waited too long; the sweep was given up, its planes are not
+// valid
+enum { SR_LEFT = 0, SR_LATE, SR_GAVE_UP, SR_WORDS };
 struct SweepArgs {
   const float* X = nullptr;      // forward offsets (state, incremental)
   const float4* YA = nullptr;    // backward offsets and reaction factor (adjoint)

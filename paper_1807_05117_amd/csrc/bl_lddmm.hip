@@ -623,7 +623,32 @@ bl_ctx* create_ctx(const bl_problem* prob, const bl::Geo& g, bool transport, boo
 inline hipMemcpyKind in_kind(const bl_ctx* c) {
   return c->devptr ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
 }
-void sync(bl_ctx* c) { HIP_TRY(hipStreamSynchronize(c->stream)); }
+// what sweeps have reported to host memory so far
+void read_sweep_reports(bl_ctx* c) {
+  if (!c->hscal) return;
+  const uint64_t* w = reinterpret_cast<const uint64_t*>(c->hscal + S_SWEEP);
+  for (int dir = 0; dir < 2; ++dir)
+    for (int k = 0; k < bl::SR_WORDS; ++k) {
+      const uint64_t t = __atomic_load_n(w + dir * bl::SR_WORDS + k, __ATOMIC_RELAXED);
+      if (t == c->sweep_seen[dir].time[k]) continue;
+      c->sweep_seen[dir].time[k] = t;
+      c->sweep_seen[dir].count[k] += 1;
+    }
+}
+
+void sync(bl_ctx* c) {
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  read_sweep_reports(c);
+  bool gave_up = false;
+  for (auto& seen : c->sweep_seen) {
+    gave_up = gave_up || seen.count[bl::SR_GAVE_UP] > 0;
+    seen.count[bl::SR_GAVE_UP] = 0;
+  }
+  if (gave_up) {   // what was computed is not valid, nor is the velocity's state
+    c->have_v = c->have_lambda = c->lamT_valid = false;
+    throw SweepGivenUp{};
+  }
+}
 
 // -------------------------------------------------------------------------------- timing
 // Timed launches record a HIP event pair at their kernel's own start and end (the dispatch
@@ -1169,24 +1194,11 @@ bl::SweepRun next_sweep(bl_ctx* c, int dir) {
   if (!c->sweep_clean[dir])
     bl::zero_band(reinterpret_cast<float2*>(r.sync), bl::kSweepWords / 2, c->stream);
   c->sweep_clean[dir] = false;
-  r.nonfinite = c->flag;
   r.report = c->sweep_report + dir * bl::SR_WORDS;
   r.wait = c->sweep_wait;
+  r.polls = c->sweep_polls;
   c->sweep_seen[dir].launched += 1;
   return r;
-}
-
-// what sweeps have reported to host memory so far
-void read_sweep_reports(bl_ctx* c) {
-  if (!c->hscal) return;
-  const uint64_t* w = reinterpret_cast<const uint64_t*>(c->hscal + S_SWEEP);
-  for (int dir = 0; dir < 2; ++dir)
-    for (int k = 0; k < bl::SR_WORDS; ++k) {
-      const uint64_t t = __atomic_load_n(w + dir * bl::SR_WORDS + k, __ATOMIC_RELAXED);
-      if (t == c->sweep_seen[dir].time[k]) continue;
-      c->sweep_seen[dir].time[k] = t;
-      c->sweep_seen[dir].count[k] += 1;
-    }
 }
 
 // band_prep of a stationary velocity or direction; zeroes the sweeps' words in the same launch
@@ -2051,6 +2063,14 @@ int bl_lddmm_ctx_sweep_wait(bl_ctx* c, double microseconds) {
   if (!(microseconds >= 0.0 && microseconds <= 1e6))
     return fail(BL_E_INVALID, "the wait must lie in [0, 1e6] microseconds");
   c->sweep_wait = (uint32_t)(microseconds * 100.0);   // ticks of 10 ns
+  return BL_OK;
+}
+
+int bl_lddmm_ctx_sweep_polls(bl_ctx* c, int64_t polls) {
+  t_err.clear();
+  if (!c) return fail(BL_E_INVALID, "NULL context");
+  if (polls < 0 || polls > bl::kSweepPolls) return fail(BL_E_INVALID, "polls must lie in [0, 2^24]");
+  c->sweep_polls = (uint32_t)polls;
   return BL_OK;
 }
 

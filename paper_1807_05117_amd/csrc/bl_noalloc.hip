@@ -76,8 +76,11 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     op_hessvec(c, c->braw, c->bout);
     store_band(c, c->bout, hv_hat, g.dim);
     int flag = 0;
+    uint64_t reports[2][bl::SR_WORDS] = {};
     HIP_TRY(hipMemcpyAsync(&flag, c->flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(reports, c->sweep_report, sizeof(reports), hipMemcpyDeviceToHost, c->stream));
     sync(c);
+    if (reports[0][bl::SR_GAVE_UP] || reports[1][bl::SR_GAVE_UP]) throw SweepGivenUp{};
     if (flag) throw NonFinite{"Hessian-vector product"};
     return BL_OK;
   });

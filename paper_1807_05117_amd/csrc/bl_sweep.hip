@@ -32,7 +32,8 @@
 // from one counter instead, in time order, each with a wait for all blocks of the step before.
 // The holder of a ticket waits only for earlier tickets, and those are held by workgroups that are
 // running, so this ends however many workgroups are resident.  It recomputes the sweep from its
-// inputs; what was finished before is stored again with the same values.
+// inputs; what was finished before is stored again with the same values.  Should a wait for earlier
+// tickets not end all the same, it is given up and reported, and the call fails.
 // A tile whose box does not fit the LDS (offsets of more than about three voxels per step at
 // 128^3) abandons the sweep in the same way.
 #include <algorithm>
@@ -48,7 +49,6 @@ constexpr int kLdsBytes = 160 * 1024 - 512;
 constexpr int kTabRows = 512;       // rows of other tiles a box may hold
 constexpr int kXCDs = 8;
 typedef __attribute__((address_space(3))) void* LdsPtr;
-constexpr uint64_t kGiveUpTicks = 1000000000; // 10 s: a bound on every wait, never met
 // words of a sweep's synchronisation area (kSweepWords): all zero before the launch
 enum { SY_ABORT = 0, SY_TICKET = 16, SY_DONE = 48, SY_FLAGS = 320 };
 
@@ -58,19 +58,22 @@ __device__ __forceinline__ uint32_t ld_flag(const uint32_t* p) {
 __device__ __forceinline__ void st_flag(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A value that no earlier report had, to memory that the host may read meanwhile.  The address is
-// read from the kernel's arguments here, where it is rarely wanted: as a value it would be kept in
-// scalar registers, which are short, for the whole sweep (1% of a product at 128^3).
+// The kernel's arguments, for those that are rarely wanted: read again there, since as values they
+// would be kept in scalar registers, which are short, for the whole sweep (1% of a product at 128^3).
 struct KernelArgs {
   Geo g;
   SweepPlan p;
   SweepArgs a;
 };
-__device__ __forceinline__ void report(int word) {
-  typedef const __attribute__((address_space(4))) KernelArgs* Ptr;
-  Ptr k = (Ptr)__builtin_amdgcn_kernarg_segment_ptr();
+typedef const __attribute__((address_space(4))) KernelArgs* KernelArgsPtr;
+__device__ __forceinline__ KernelArgsPtr kernel_args() {
+  KernelArgsPtr k = (KernelArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(k));
-  __hip_atomic_store(k->a.run.report + word, __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
+  return k;
+}
+// a value that no earlier report had, to memory that the host may read meanwhile
+__device__ __forceinline__ void report(int word) {
+  __hip_atomic_store(kernel_args()->a.run.report + word, __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ uint32_t add_flag(uint32_t* p) {
@@ -281,10 +284,10 @@ __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, in
     if (k >= stages * chunks) return;
     const uint32_t stage = k / chunks, chunk = k - stage * chunks, zb = chunk / nq;
     if (threadIdx.x == 0 && stage > 0) {
-      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      while (ld_flag(a.run.sync + SY_DONE + stage - 1) < chunks) {
-        if (__builtin_amdgcn_s_memrealtime() - t0 > kGiveUpTicks) {
-          *a.run.nonfinite = 1;
+      const uint32_t most = kernel_args()->a.run.polls;
+      for (uint32_t polls = 0; ld_flag(a.run.sync + SY_DONE + stage - 1) < chunks; ++polls) {
+        if (polls >= most) {
+          report(SR_GAVE_UP);
           break;
         }
         __builtin_amdgcn_s_sleep(4);
