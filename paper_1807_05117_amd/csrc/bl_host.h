@@ -126,6 +126,13 @@ struct bl_ctx {
     uint64_t time[bl::SR_WORDS] = {};
     int64_t count[bl::SR_WORDS] = {};
   } sweep_seen[2];
+  // offsets that leave the tiles' boxes are a matter of the velocity: no further sweep of the direction
+  // at it, and after it `rest` velocities without sweeps (twice as many each time in a row)
+  struct BoxHistory {
+    int rest = 0, back_off = 1;
+    bool resting = false, swept = false;   // the current velocity: without sweeps, had one
+    int64_t before[2] = {0, 0};            // sweep_seen[].count[SR_LEFT] when it was set
+  } box;
   // where they report: [direction][SR_WORDS] at hscal[S_SWEEP], or device memory where there is no
   // host-mapped one (device address)
   uint64_t* sweep_report = nullptr;
@@ -200,6 +207,8 @@ struct CtxHolder {
 };
 // 64 doubles of pinned, coherent, device-mapped host memory for published scalars
 double* alloc_host_scalars();
+// at the end of a velocity: what its sweeps have shown of its offsets
+void settle_box(bl_ctx* c);
 // waits for the stream; throws SweepGivenUp if a sweep on it was given up since the last call
 void sync(bl_ctx* c);
 void load_images(bl_ctx* c, const float* I0, const float* I1);

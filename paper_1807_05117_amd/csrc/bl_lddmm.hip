@@ -1184,7 +1184,35 @@ double* publish(bl_ctx* c, int slot) {
 // per-kernel timing (it times them) take the steps one by one; both give the same values.
 bool use_sweeps(const bl_ctx* c) {
   return c->sweep_now && c->sweep.run > 0 && c->g.bat.count == 1 && c->g.bat.gate == nullptr && !c->timing &&
-         !c->shapes_fixed;
+         !c->shapes_fixed && !c->box.resting;
+}
+// in one direction (0 forward, 1 backward).  What leaves the box for one sweep does so for every
+// other one of the velocity; the steps that an abandoned sweep takes through tickets last three times
+// as long as step launches (128^3, ten steps of six voxels: product 1,328 us, in step launches 390).
+bool left_box(const bl_ctx* c, int dir) { return c->sweep_seen[dir].count[bl::SR_LEFT] != c->box.before[dir]; }
+bool use_sweeps(const bl_ctx* c, int dir) { return use_sweeps(c) && !left_box(c, dir); }
+
+// The velocities of a registration or of a caller's sequence are much alike: after one that left the
+// box 1, 2, 4, ... 64 velocities rest from sweeps, until one does not leave it.
+constexpr int kMostRest = 64;
+void settle_box(bl_ctx* c) {
+  auto& b = c->box;
+  if (!b.swept) return;
+  b.swept = false;
+  if (left_box(c, 0) || left_box(c, 1)) {
+    b.rest = b.back_off;
+    b.back_off = std::min(2 * b.back_off, kMostRest);
+  } else {
+    b.back_off = 1;
+  }
+}
+void next_velocity(bl_ctx* c) {
+  read_sweep_reports(c);
+  settle_box(c);
+  auto& b = c->box;
+  for (int dir = 0; dir < 2; ++dir) b.before[dir] = c->sweep_seen[dir].count[bl::SR_LEFT];
+  b.resting = b.rest > 0;
+  if (b.resting) b.rest -= 1;
 }
 
 // the next forward (0) or backward (1) sweep, with its zeroed words
@@ -1198,6 +1226,7 @@ bl::SweepRun next_sweep(bl_ctx* c, int dir) {
   r.wait = c->sweep_wait;
   r.polls = c->sweep_polls;
   c->sweep_seen[dir].launched += 1;
+  c->box.swept = true;
   return r;
 }
 
@@ -1205,6 +1234,7 @@ bl::SweepRun next_sweep(bl_ctx* c, int dir) {
 void prep_and_clean(bl_ctx* c, const float2* raw, float2* out, int with_div, const double* Lhat64,
                     double* red_reg) {
   c->sweep_now = c->sweeps_allowed && c->sweep.run > 0 && may_sweep(c, now_ns(), thread_key());
+  read_sweep_reports(c);
   const bool z = use_sweeps(c);
   bl::band_prep(c->g, raw, out, with_div, Lhat64, red_reg, c->stream,
                 z ? c->sweep_sync : nullptr, z ? 2 * bl::kSweepWords : 0);
@@ -1218,12 +1248,13 @@ void enqueue_set_velocity(bl_ctx* c, const float2* vraw) {
   hipStream_t s = c->stream;
   double* red_reg = c->red + RED_REG * bl::kRedBlocks;
   double* red_data = c->red + RED_DATA * bl::kRedBlocks;
+  next_velocity(c);
   prep_and_clean(c, vraw, c->bv, 1, c->Lhat64, red_reg);
   bl::iota(g, c->plan, c->bv, g.dim + 1, c->V, s);
   timed(c, 6, [&] { bl::setup(g, c->V, c->X, c->YA, s); });
   if (!c->tuned) choose_launch_shapes(c);
   const size_t M = (size_t)g.M;
-  if (use_sweeps(c))
+  if (use_sweeps(c, 0))
     bl::sweep_state(g, c->sweep, c->X, c->m, next_sweep(c, 0), s);
   else
     for (int n = 0; n < g.nt; ++n)
@@ -1309,7 +1340,7 @@ void backward_and_body_force(bl_ctx* c) {
   const bl::Geo& g = c->g;
   hipStream_t s = c->stream;
   const size_t M = (size_t)g.M;
-  if (use_sweeps(c)) {
+  if (use_sweeps(c, 1)) {
     bl::sweep_adj(g, c->sweep, c->YA, c->m, c->L, c->Bf, g.newton, next_sweep(c, 1), s);
     return;
   }
@@ -1358,8 +1389,7 @@ void op_hessvec_newton(bl_ctx* c, const float2* draw, float2* hout, double* dot_
   bl::iota(g, c->plan, c->bd, g.dim, c->DV, s);
   // t^n lies in planes that the terms overwrite, or by turns in T0 and T1; then the terms hs^n (u^Nt
   // in the last plane) take DL, u^n the planes of dm^n, and b starts at b2
-  const bool sweep = use_sweeps(c);
-  if (sweep) {
+  if (use_sweeps(c, 0)) {
     bl::sweep_inc_n(g, c->sweep, c->X, c->m, c->DV, c->DL, c->DM, next_sweep(c, 0), s);
   } else {
     bl::inc_init(g, c->m, c->DV, c->T0, s);
@@ -1373,7 +1403,7 @@ void op_hessvec_newton(bl_ctx* c, const float2* draw, float2* hout, double* dot_
   }
   const bl::BodyStart b2{{c->T0, c->T1, c->U}};
   bl::newton_terms(g, c->L, c->DM, c->DV, c->DL, b2, s);
-  if (sweep) {
+  if (use_sweeps(c, 1)) {
     bl::sweep_adj_n(g, c->sweep, c->YA, c->m, c->DL, b2, c->DV, c->DM, c->Bf, next_sweep(c, 1), s);
   } else {
     const float* uin = c->DL + g.nt * M;
@@ -1410,7 +1440,7 @@ bool op_hessvec(bl_ctx* c, const float2* draw, float2* hout, double* dot_part) {
   prep_and_clean(c, draw, c->bd, 0, nullptr, nullptr);
   bl::iota_xy(g, c->plan, c->bd, g.dim, s);
   timed(c, 3, [&] { bl::iota_z(g, c->plan, g.dim, c->DV, s); });
-  if (use_sweeps(c)) {
+  if (use_sweeps(c, 0)) {
     // t^n into the planes that the backward sweep overwrites
     bl::sweep_inc(g, c->sweep, c->X, c->m, c->DV, c->L, next_sweep(c, 0), s);
   } else {

@@ -26,6 +26,26 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes + kSweepByt
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
+// each call has a context of its own: how many calls of one shape still rest from sweeps
+// (bl_ctx::box)
+struct Rest {
+  int n[3] = {0, 0, 0}, nt = 0, rest = 0, back_off = 1;
+};
+Rest g_rest[kMaxDevices];
+Rest rest_of(int device, const bl_problem& p) {
+  std::lock_guard<std::mutex> lk(g_scratch_mu);
+  const Rest& r = g_rest[device];
+  if (r.n[0] == p.n[0] && r.n[1] == p.n[1] && r.n[2] == p.n[2] && r.nt == p.nt) return r;
+  Rest fresh;
+  for (int j = 0; j < 3; ++j) fresh.n[j] = p.n[j];
+  fresh.nt = p.nt;
+  return fresh;
+}
+void keep_rest(int device, const Rest& r) {
+  std::lock_guard<std::mutex> lk(g_scratch_mu);
+  g_rest[device] = r;
+}
+
 // device address of this device's scratch array (looked up once per device, device current)
 void* scratch_address(int device) {
   std::lock_guard<std::mutex> lk(g_scratch_mu);
@@ -69,6 +89,9 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     bl_ctx* c = h.c;
     Operation op(c);
     apply_known_launch_shapes(c);
+    Rest rest = rest_of(device, *prob);
+    c->box.rest = rest.rest;
+    c->box.back_off = rest.back_off;
     load_images(c, I0, I1);
     load_band(c, v_hat, c->braw, g.dim);
     enqueue_set_velocity(c, c->braw);
@@ -80,6 +103,11 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     HIP_TRY(hipMemcpyAsync(&flag, c->flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipMemcpyAsync(reports, c->sweep_report, sizeof(reports), hipMemcpyDeviceToHost, c->stream));
     sync(c);
+    for (int dir = 0; dir < 2; ++dir) c->sweep_seen[dir].count[bl::SR_LEFT] = reports[dir][bl::SR_LEFT] != 0;
+    settle_box(c);
+    rest.rest = c->box.rest;
+    rest.back_off = c->box.back_off;
+    keep_rest(device, rest);
     if (reports[0][bl::SR_GAVE_UP] || reports[1][bl::SR_GAVE_UP]) throw SweepGivenUp{};
     if (flag) throw NonFinite{"Hessian-vector product"};
     return BL_OK;
