@@ -23,8 +23,12 @@ __device__ __forceinline__ Rsrc field_rsrc(const float* f, const Geo& g) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(f), (short)0, (int)(uint32_t)bytes,
                                            0x00020000);
 }
+// POLICY: the access's cache policy (kSC1: device scope, not served from a line that another XCD's
+// stores have left stale)
+constexpr int kSC1 = 16;
+template <int POLICY = 0>
 __device__ __forceinline__ float ld(Rsrc rs, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff, (int)soff, 0));
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff, (int)soff, POLICY));
 }
 __device__ __forceinline__ void st(Rsrc rs, uint32_t voff, uint32_t soff, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, (int)voff, (int)soff, 0);
@@ -233,7 +237,7 @@ __device__ __forceinline__ void make_taps(const Geo& g, const Col& t, const floa
 // not wrap, past the end of the buffer, where the range check returns 0 without touching memory.
 constexpr uint32_t kPastEnd = 0xFFFFFFFCu;   // >= the byte size of any field (< 2^32)
 
-template <int DIM, int ZV>
+template <int DIM, int ZV, int POLICY = 0>
 __device__ __forceinline__ void gather_zv(const Geo& g, Rsrc f, const Tap (&t)[ZV],
                                           float (&out)[ZV]) {
   constexpr int R = DIM == 3 ? 4 : 2;
@@ -244,7 +248,7 @@ __device__ __forceinline__ void gather_zv(const Geo& g, Rsrc f, const Tap (&t)[Z
     const uint32_t a[4] = {t[zz].a00, t[zz].a01, t[zz].a10, t[zz].a11};
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      v[zz][r] = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(f, (int)a[r], 0, 0));
+      v[zz][r] = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(f, (int)a[r], 0, POLICY));
     any |= __builtin_amdgcn_ballot_w64(t[zz].wrapped);
   }
   if (any != 0) {
@@ -254,7 +258,7 @@ __device__ __forceinline__ void gather_zv(const Geo& g, Rsrc f, const Tap (&t)[Z
     for (int zz = 0; zz < ZV; ++zz) {
       const uint32_t a[4] = {t[zz].a00, t[zz].a01, t[zz].a10, t[zz].a11};
 #pragma unroll
-      for (int r = 0; r < R; ++r) w[zz][r] = ld(f, t[zz].wrapped ? a[r] - back : kPastEnd, 0);
+      for (int r = 0; r < R; ++r) w[zz][r] = ld<POLICY>(f, t[zz].wrapped ? a[r] - back : kPastEnd, 0);
     }
 #pragma unroll
     for (int zz = 0; zz < ZV; ++zz)
@@ -509,8 +513,8 @@ __device__ __forceinline__ void source_f(const Geo& g, const Col& t, const float
 // together.  With YA given, lambda^0 is not read: it is formed here as the last adjoint step
 // would, a Interp(lambda^1, i + Y), with the same arithmetic (the caller then stops the
 // backward transport at lambda^1; lambda^0 is needed by nothing but this sum).  The sum starts at
-// what acc holds.
-template <int DIM, int ZV>
+// what acc holds.  POLICY: of the loads of lambda.
+template <int DIM, int ZV, int POLICY = 0>
 __device__ __forceinline__ void body_sum(const Geo& g, const Col& t, const float* lam, const float* m,
                                          const float4* YA, float (&acc)[ZV][3]) {
   const size_t M = (size_t)g.M;
@@ -530,7 +534,7 @@ __device__ __forceinline__ void body_sum(const Geo& g, const Col& t, const float
 #pragma unroll
       for (int zz = 0; zz < ZV; ++zz) {
         VOXEL(zz)
-        l[zz] = ld(rl, t.c, zo);
+        l[zz] = ld<POLICY>(rl, t.c, zo);
       }
     }
     float prev = 0.f, cur = 0.f;   // m at z - 1 and z
