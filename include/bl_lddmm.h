@@ -310,7 +310,7 @@ int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);
  *                    launched, out[3], [4] of these abandoned for their offsets and out[5], [6] for a
  *                    wait, as far as it is known by now
  *   ctx_sweep_wait   how long a tile waits before it abandons the sweep, 0 <= microseconds <= 1e6
- *                    (default 50; 0: it never waits).  No value changes a result.
+ *                    (default 100; 0: it never waits).  No value changes a result.
  *   ctx_sweep_polls  how often an abandoned sweep looks for the end of its earlier parts, 0 <= polls
  *                    <= 2^24 (the default, about ten seconds of running), before it is given up: then
  *                    the call that waits for it, or after an enqueued product the next one that

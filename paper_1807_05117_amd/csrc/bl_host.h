@@ -119,20 +119,30 @@ struct bl_ctx {
   bl::SweepPlan sweep;
   uint32_t* sweep_sync = nullptr;   // 2 * kSweepWords
   bool sweep_clean[2] = {false, false};
-  // per direction: sweeps launched, the times at which any of them abandoned itself (the last known
-  // ones) and how many did
+  // the number of the last evaluation or product with sweeps, its operation, and whether the stream
+  // has been waited for since
+  uint64_t sweep_number = 0, sweep_op = 0;
+  bool sweep_synced = false;
+  // per direction: sweeps launched; by SR_*: the number of the last one that abandoned itself, and how
+  // many did, as far as it is known
   struct SweepSeen {
     int64_t launched = 0;
-    uint64_t time[bl::SR_WORDS] = {};
+    uint64_t number[bl::SR_WORDS] = {};
     int64_t count[bl::SR_WORDS] = {};
   } sweep_seen[2];
   // offsets that leave the tiles' boxes are a matter of the velocity: no further sweep of the direction
   // at it, and after it `rest` velocities without sweeps (twice as many each time in a row)
   struct BoxHistory {
     int rest = 0, back_off = 1;
-    bool resting = false, swept = false;   // the current velocity: without sweeps, had one
-    int64_t before[2] = {0, 0};            // sweep_seen[].count[SR_LEFT] when it was set
+    bool resting = false;   // the current velocity: without sweeps
+    uint64_t before = 0;    // sweep_number when it was set
   } box;
+  // waits that ran out are a matter of what else the device does: after the second sweep in a row that
+  // was late, `rest` evaluations and products without sweeps (twice as many with each further one)
+  struct WaitHistory {
+    int rest = 0, streak = 0;
+    uint64_t late = 0;      // number of the last late one
+  } late;
   // where they report: [direction][SR_WORDS] at hscal[S_SWEEP], or device memory where there is no
   // host-mapped one (device address)
   uint64_t* sweep_report = nullptr;
@@ -207,8 +217,11 @@ struct CtxHolder {
 };
 // 64 doubles of pinned, coherent, device-mapped host memory for published scalars
 double* alloc_host_scalars();
-// at the end of a velocity: what its sweeps have shown of its offsets
+// what sweeps have reported so far ([direction][SR_WORDS] words); at the end of a velocity: what its
+// sweeps have shown of its offsets; what sweeps have shown of their waits
+void read_sweep_reports(bl_ctx* c, const uint64_t* words);
 void settle_box(bl_ctx* c);
+void settle_waits(bl_ctx* c);
 // waits for the stream; throws SweepGivenUp if a sweep on it was given up since the last call
 void sync(bl_ctx* c);
 void load_images(bl_ctx* c, const float* I0, const float* I1);

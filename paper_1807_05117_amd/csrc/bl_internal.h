@@ -323,14 +323,19 @@ struct SweepPlan {
   FastDiv div_nx, div_ty, div_ty2, div_nty, div_n4;   // by nx, ty, ty + 2, nty, 16-byte entries per row
 };
 // what the host gives a sweep beside its fields
-constexpr uint32_t kSweepWait = 5000;   // 50 us of the 100 MHz realtime counter
+// 100 us of the 100 MHz realtime counter.  A tile waits two or three microseconds for a neighbour that
+// runs; others may not be resident yet because another stream's kernel still holds compute units, and
+// short kernels are worth waiting for: products at 128^3 beside additions of 256 MB (73 us each)
+// take 687 us with a wait of 50, 429 with 100 and with 400 (696 as steps).
+constexpr uint32_t kSweepWait = 10000;
 // about ten seconds of running: counted in looks, since a clock also runs while a workgroup is
 // suspended for another process
 constexpr uint32_t kSweepPolls = 1u << 24;
 struct SweepRun {
   uint32_t* sync = nullptr;      // kSweepWords words, zero
-  // SR_WORDS words: a sweep that abandons itself stores the time to one of them
+  // SR_WORDS words: a sweep that abandons itself stores `number` to one of them
   uint64_t* report = nullptr;
+  uint64_t number = 0;
   uint32_t wait = kSweepWait;    // realtime ticks that a tile waits for others (0: not once)
   uint32_t polls = kSweepPolls;  // looks at an abandoned sweep's earlier blocks before it is given up
 };

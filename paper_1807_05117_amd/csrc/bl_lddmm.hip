@@ -623,22 +623,23 @@ bl_ctx* create_ctx(const bl_problem* prob, const bl::Geo& g, bool transport, boo
 inline hipMemcpyKind in_kind(const bl_ctx* c) {
   return c->devptr ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
 }
-// what sweeps have reported to host memory so far
-void read_sweep_reports(bl_ctx* c) {
-  if (!c->hscal) return;
-  const uint64_t* w = reinterpret_cast<const uint64_t*>(c->hscal + S_SWEEP);
+void read_sweep_reports(bl_ctx* c, const uint64_t* words) {
   for (int dir = 0; dir < 2; ++dir)
     for (int k = 0; k < bl::SR_WORDS; ++k) {
-      const uint64_t t = __atomic_load_n(w + dir * bl::SR_WORDS + k, __ATOMIC_RELAXED);
-      if (t == c->sweep_seen[dir].time[k]) continue;
-      c->sweep_seen[dir].time[k] = t;
+      const uint64_t n = __atomic_load_n(words + dir * bl::SR_WORDS + k, __ATOMIC_RELAXED);
+      if (n == c->sweep_seen[dir].number[k]) continue;
+      c->sweep_seen[dir].number[k] = n;
       c->sweep_seen[dir].count[k] += 1;
     }
+}
+void read_sweep_reports(bl_ctx* c) {
+  if (c->hscal) read_sweep_reports(c, reinterpret_cast<const uint64_t*>(c->hscal + S_SWEEP));
 }
 
 void sync(bl_ctx* c) {
   HIP_TRY(hipStreamSynchronize(c->stream));
   read_sweep_reports(c);
+  c->sweep_synced = true;
   bool gave_up = false;
   for (auto& seen : c->sweep_seen) {
     gave_up = gave_up || seen.count[bl::SR_GAVE_UP] > 0;
@@ -1189,7 +1190,7 @@ bool use_sweeps(const bl_ctx* c) {
 // in one direction (0 forward, 1 backward).  What leaves the box for one sweep does so for every
 // other one of the velocity; the steps that an abandoned sweep takes through tickets last three times
 // as long as step launches (128^3, ten steps of six voxels: product 1,328 us, in step launches 390).
-bool left_box(const bl_ctx* c, int dir) { return c->sweep_seen[dir].count[bl::SR_LEFT] != c->box.before[dir]; }
+bool left_box(const bl_ctx* c, int dir) { return c->sweep_seen[dir].number[bl::SR_LEFT] > c->box.before; }
 bool use_sweeps(const bl_ctx* c, int dir) { return use_sweeps(c) && !left_box(c, dir); }
 
 // The velocities of a registration or of a caller's sequence are much alike: after one that left the
@@ -1197,8 +1198,7 @@ bool use_sweeps(const bl_ctx* c, int dir) { return use_sweeps(c) && !left_box(c,
 constexpr int kMostRest = 64;
 void settle_box(bl_ctx* c) {
   auto& b = c->box;
-  if (!b.swept) return;
-  b.swept = false;
+  if (c->sweep_number == b.before) return;   // it had none
   if (left_box(c, 0) || left_box(c, 1)) {
     b.rest = b.back_off;
     b.back_off = std::min(2 * b.back_off, kMostRest);
@@ -1210,9 +1210,38 @@ void next_velocity(bl_ctx* c) {
   read_sweep_reports(c);
   settle_box(c);
   auto& b = c->box;
-  for (int dir = 0; dir < 2; ++dir) b.before[dir] = c->sweep_seen[dir].count[bl::SR_LEFT];
+  b.before = c->sweep_number;
   b.resting = b.rest > 0;
   if (b.resting) b.rest -= 1;
+}
+
+// the last evaluation or product with sweeps has ended, as far as it is known
+bool sweep_ended(const bl_ctx* c) { return c->sweep_synced || ops_done(c) >= c->sweep_op; }
+
+void settle_waits(bl_ctx* c) {
+  auto& l = c->late;
+  const uint64_t n = std::max(c->sweep_seen[0].number[bl::SR_LATE], c->sweep_seen[1].number[bl::SR_LATE]);
+  if (n > l.late) {
+    l.streak = n == l.late + 1 ? l.streak + 1 : 1;
+    l.late = n;
+    if (l.streak > 1) l.rest = std::min(1 << std::min(l.streak - 2, 30), kMostRest);
+  } else if (l.late != c->sweep_number && sweep_ended(c)) {
+    l.streak = 0;
+  }
+}
+// Before an evaluation or product: whether it rests from sweeps since tiles of earlier ones waited too
+// long for others: work that the library does not know of holds compute units.  Products at 128^3
+// beside another stream (us, with a sweep each time, with rests, as steps): sums of 4 M numbers by one
+// workgroup, where every sweep is late, 1,536, 379 and 386; additions of 1 GB, where many are, 1,936,
+// 759 and 729; matrix products of 2048^2, where hardly any is, 648, 647 and 1,937.  One late sweep
+// alone changes nothing; after several in a row one operation in 65 is tried, none beside one that
+// has not ended.
+bool rest_after_waits(bl_ctx* c) {
+  settle_waits(c);
+  auto& l = c->late;
+  if (l.rest == 0) return l.streak > 1 && l.late != c->sweep_number;
+  l.rest -= 1;
+  return true;
 }
 
 // the next forward (0) or backward (1) sweep, with its zeroed words
@@ -1223,19 +1252,25 @@ bl::SweepRun next_sweep(bl_ctx* c, int dir) {
     bl::zero_band(reinterpret_cast<float2*>(r.sync), bl::kSweepWords / 2, c->stream);
   c->sweep_clean[dir] = false;
   r.report = c->sweep_report + dir * bl::SR_WORDS;
+  r.number = c->sweep_number;
   r.wait = c->sweep_wait;
   r.polls = c->sweep_polls;
   c->sweep_seen[dir].launched += 1;
-  c->box.swept = true;
   return r;
 }
 
 // band_prep of a stationary velocity or direction; zeroes the sweeps' words in the same launch
 void prep_and_clean(bl_ctx* c, const float2* raw, float2* out, int with_div, const double* Lhat64,
                     double* red_reg) {
-  c->sweep_now = c->sweeps_allowed && c->sweep.run > 0 && may_sweep(c, now_ns(), thread_key());
   read_sweep_reports(c);
-  const bool z = use_sweeps(c);
+  const bool resting = rest_after_waits(c);
+  c->sweep_now = c->sweeps_allowed && c->sweep.run > 0 && !resting && may_sweep(c, now_ns(), thread_key());
+  const bool z = use_sweeps(c, 0) || use_sweeps(c, 1);
+  if (z) {
+    c->sweep_number += 1;
+    c->sweep_op = c->op_issued.load(std::memory_order_relaxed);
+    c->sweep_synced = false;
+  }
   bl::band_prep(c->g, raw, out, with_div, Lhat64, red_reg, c->stream,
                 z ? c->sweep_sync : nullptr, z ? 2 * bl::kSweepWords : 0);
   if (z) c->sweep_clean[0] = c->sweep_clean[1] = true;

@@ -26,24 +26,26 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes + kSweepByt
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
-// each call has a context of its own: how many calls of one shape still rest from sweeps
-// (bl_ctx::box)
-struct Rest {
-  int n[3] = {0, 0, 0}, nt = 0, rest = 0, back_off = 1;
+// each call has a context of its own: what the calls of one shape have learnt of sweeps
+struct History {
+  int n[3] = {0, 0, 0}, nt = 0;
+  uint64_t number = 0;
+  decltype(bl_ctx::box) box;
+  decltype(bl_ctx::late) late;
 };
-Rest g_rest[kMaxDevices];
-Rest rest_of(int device, const bl_problem& p) {
+History g_history[kMaxDevices];
+History history_of(int device, const bl_problem& p) {
   std::lock_guard<std::mutex> lk(g_scratch_mu);
-  const Rest& r = g_rest[device];
-  if (r.n[0] == p.n[0] && r.n[1] == p.n[1] && r.n[2] == p.n[2] && r.nt == p.nt) return r;
-  Rest fresh;
+  const History& h = g_history[device];
+  if (h.n[0] == p.n[0] && h.n[1] == p.n[1] && h.n[2] == p.n[2] && h.nt == p.nt) return h;
+  History fresh;
   for (int j = 0; j < 3; ++j) fresh.n[j] = p.n[j];
   fresh.nt = p.nt;
   return fresh;
 }
-void keep_rest(int device, const Rest& r) {
+void keep_history(int device, const History& h) {
   std::lock_guard<std::mutex> lk(g_scratch_mu);
-  g_rest[device] = r;
+  g_history[device] = h;
 }
 
 // device address of this device's scratch array (looked up once per device, device current)
@@ -89,9 +91,10 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     bl_ctx* c = h.c;
     Operation op(c);
     apply_known_launch_shapes(c);
-    Rest rest = rest_of(device, *prob);
-    c->box.rest = rest.rest;
-    c->box.back_off = rest.back_off;
+    History history = history_of(device, *prob);
+    c->sweep_number = history.number;
+    c->box = history.box;
+    c->late = history.late;
     load_images(c, I0, I1);
     load_band(c, v_hat, c->braw, g.dim);
     enqueue_set_velocity(c, c->braw);
@@ -103,11 +106,14 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     HIP_TRY(hipMemcpyAsync(&flag, c->flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipMemcpyAsync(reports, c->sweep_report, sizeof(reports), hipMemcpyDeviceToHost, c->stream));
     sync(c);
-    for (int dir = 0; dir < 2; ++dir) c->sweep_seen[dir].count[bl::SR_LEFT] = reports[dir][bl::SR_LEFT] != 0;
+    read_sweep_reports(c, reports[0]);
     settle_box(c);
-    rest.rest = c->box.rest;
-    rest.back_off = c->box.back_off;
-    keep_rest(device, rest);
+    settle_waits(c);
+    c->box.before = c->sweep_number;
+    history.number = c->sweep_number;
+    history.box = c->box;
+    history.late = c->late;
+    keep_history(device, history);
     if (reports[0][bl::SR_GAVE_UP] || reports[1][bl::SR_GAVE_UP]) throw SweepGivenUp{};
     if (flag) throw NonFinite{"Hessian-vector product"};
     return BL_OK;

@@ -70,10 +70,10 @@ __device__ __forceinline__ KernelArgsPtr kernel_args() {
   asm volatile("" : "+s"(k));
   return k;
 }
-// a value that no earlier report had, to memory that the host may read meanwhile
+// to memory that the host may read meanwhile
 __device__ __forceinline__ void report(int word) {
-  __hip_atomic_store(kernel_args()->a.run.report + word, __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_SYSTEM);
+  const KernelArgsPtr k = kernel_args();
+  __hip_atomic_store(k->a.run.report + word, k->a.run.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ uint32_t add_flag(uint32_t* p) {
   return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -54,7 +54,7 @@ def test_given_up_in_an_enqueued_product(gpu_lib):
     ctx.bl_lddmm_ctx_sweep_wait(0)
     ctx.bl_lddmm_ctx_sweep_polls(0)
     ctx.bl_lddmm_ctx_hessvec(ddv)
-    ctx.bl_lddmm_ctx_sweep_wait(50)
+    ctx.bl_lddmm_ctx_sweep_wait(100)
     ctx.bl_lddmm_ctx_sweep_polls(ALL)
     _device_error(lambda: ctx.bl_lddmm_ctx_set_velocity(dvs))
     E2, g2 = ctx.bl_lddmm_ctx_set_velocity(dvs)

@@ -73,7 +73,7 @@ def test_out_of_time_in_the_middle(gpu_lib, n, k, newton):
     H = ctx.bl_lddmm_ctx_hessvec(dv)
     seen = ctx.bl_lddmm_ctx_sweeps()
     assert seen[1:] == (2, 2, 0, 0, 1, 1), seen
-    ctx.bl_lddmm_ctx_sweep_wait(50)
+    ctx.bl_lddmm_ctx_sweep_wait(100)
     E0, g0, _, m0, H0, _ = _steps(ctx, prob, vs, dv)
     ctx.close()
     assert E == E0 and np.array_equal(g, g0) and np.array_equal(m, m0) and np.array_equal(H, H0)
