@@ -325,12 +325,13 @@ int bl_lddmm_ctx_sweep_polls(bl_ctx* ctx, int64_t polls);
  * The autotuner: besides the transports' zv, it chooses the setup kernel's form (1, 2: gathers
  * from global memory, one or two voxels per thread; 4, 8: neighbourhoods in LDS) and the
  * z-chunking of the FP32 iota z stage, all bitwise-invariant, by timing at the first velocity of
- * each (GPU architecture, grid, band, precision): every candidate is launched once, then all are
- * timed in turn three times over and each keeps its fastest round; another shape must beat the
- * default by 5%.  BL_TUNE_LOG=1 prints the times and choices to stderr.
+ * each (GPU architecture, grid, band, precision, stationary or not; a non-stationary setup's form
+ * goes by its number of tiles): every candidate is launched once, then all are timed in turn three
+ * times over and each keeps its fastest round; another shape must beat the default by 5%.
+ * BL_TUNE_LOG=1 prints the times and choices to stderr.
  * Choices are kept for the process and appended to a cache file read by later processes:
- * BL_TUNE_CACHE (a path, or "off"), else $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v4.txt or
- * ~/.cache/bl_lddmm/launch_shapes_v4.txt (lines with a value a class does not accept are
+ * BL_TUNE_CACHE (a path, or "off"), else $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v5.txt or
+ * ~/.cache/bl_lddmm/launch_shapes_v5.txt (lines with a value a class does not accept are
  * skipped).  BL_LAUNCH_SHAPES="s0,...,s6" fixes all classes (state, incremental, adjoint, body
  * force, setup, iota z, iota x/y); the last one (0, 16 or 32) has no effect: the x and y stages
  * of iota are one launch.

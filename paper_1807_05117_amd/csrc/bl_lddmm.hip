@@ -725,8 +725,8 @@ void t_collect(bl_ctx* c) {
 // shape (the gathers' cache behaviour depends on the real offsets); the planes they write
 // (T0, T1, Bf, DV, X, YA with the same values, the transform buffers) are work space that every
 // operation rewrites before use.  Choices are kept per (GPU architecture, grid, band,
-// precision) for the process and in a cache file -- BL_TUNE_CACHE, else
-// $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v4.txt or ~/.cache/bl_lddmm/launch_shapes_v3.txt -- read at
+// precision, stationary or not) for the process and in a cache file -- BL_TUNE_CACHE, else
+// $XDG_CACHE_HOME/bl_lddmm/launch_shapes_v5.txt or ~/.cache/bl_lddmm/launch_shapes_v5.txt -- read at
 // the first tuning and appended to after each new choice, so later processes skip the timing.
 // BL_TUNE_CACHE=off disables the file; BL_TRANSPORT_ZV = 1, 2, 4 or 8 fixes the transports'
 // and the setup's voxels per thread and skips the timing, BL_LAUNCH_SHAPES fixes every class.
@@ -738,9 +738,9 @@ std::string tune_cache_path() {
   const char* e = std::getenv("BL_TUNE_CACHE");
   if (e && *e) return std::string(e) == "off" ? std::string() : std::string(e);
   if (const char* x = std::getenv("XDG_CACHE_HOME"))
-    if (*x) return std::string(x) + "/bl_lddmm/launch_shapes_v4.txt";
+    if (*x) return std::string(x) + "/bl_lddmm/launch_shapes_v5.txt";
   if (const char* h = std::getenv("HOME"))
-    if (*h) return std::string(h) + "/.cache/bl_lddmm/launch_shapes_v4.txt";
+    if (*h) return std::string(h) + "/.cache/bl_lddmm/launch_shapes_v5.txt";
   return std::string();
 }
 
@@ -755,8 +755,8 @@ std::string shape_key(const bl_ctx* c) {
   }();
   const bl::Geo& g = c->g;
   char buf[160];
-  std::snprintf(buf, sizeof(buf), "%s %d %d %d %d %d %d %d %d", arch.c_str(), g.dim, g.nx, g.ny,
-                g.nz, g.kx, g.ky, g.kz, c->plan.mixed);
+  std::snprintf(buf, sizeof(buf), "%s %d %d %d %d %d %d %d %d%s", arch.c_str(), g.dim, g.nx, g.ny,
+                g.nz, g.kx, g.ky, g.kz, c->plan.mixed, g.nodes > 1 ? " ns" : "");
   return buf;
 }
 
@@ -769,7 +769,7 @@ bool valid_shapes(const int* v) {
   return ok && (v[bl::TR_IOTA_XY] == 0 || v[bl::TR_IOTA_XY] == 16 || v[bl::TR_IOTA_XY] == 32);
 }
 
-// the cache file's lines: "<arch> dim nx ny nz kx ky kz mixed : s0 ... s6"; malformed lines and
+// the cache file's lines: "<arch> dim nx ny nz kx ky kz mixed [ns] : s0 ... s6"; malformed lines and
 // lines with a value outside valid_shapes are skipped (caller holds g_shape_mu)
 void read_shape_file() {
   g_shapes_file_read = true;
@@ -817,7 +817,9 @@ bool lookup_shapes(bl_ctx* c) {
   if (!g_shapes_file_read) read_shape_file();
   auto it = g_shapes.find(key);
   if (it == g_shapes.end()) return false;
-  for (int k = 0; k < bl::TR_CLASSES; ++k) c->g.zv[k] = it->second[k];
+  // a non-stationary setup's form goes by the tiles of all its steps (validate), not by a time
+  for (int k = 0; k < bl::TR_CLASSES; ++k)
+    if (k != bl::TR_SETUP || c->g.nodes == 1) c->g.zv[k] = it->second[k];
   return true;
 }
 
