@@ -266,7 +266,8 @@ __global__ __launch_bounds__(kThreads) void k_def_out(Geo g, float scaleP,
                                                       const float2* __restrict__ vproj,
                                                       const float* __restrict__ Lhat,
                                                       float2* __restrict__ out,
-                                                      int* __restrict__ nonfinite, int leray_on) {
+                                                      int* __restrict__ nonfinite, int leray_on, Done done) {
+  report_begun(done);
   const int B = (int)g.B;
   const size_t ps = (size_t)g.kzh * g.ky * g.kx;
   for (int b = blockIdx.x * kThreads + threadIdx.x; b < B; b += gridDim.x * kThreads) {
@@ -481,9 +482,9 @@ void def_adj_combine(const Geo& g, float scaleP, const float2* Ph, float2* rho, 
 }
 
 void def_out(const Geo& g, float scaleP, const float2* Ph, const float2* Ksum,
-             const float2* vproj, const float* Lhat, float2* out, int* nonfinite, hipStream_t s) {
+             const float2* vproj, const float* Lhat, float2* out, int* nonfinite, hipStream_t s, Done done) {
   const int on = g.gamma ? 1 : 0;
-  DIM_DISPATCH(k_def_out, blocks_for(g.B), g, scaleP, Ph, Ksum, vproj, Lhat, out, nonfinite, on);
+  DIM_DISPATCH(k_def_out, blocks_for(g.B), g, scaleP, Ph, Ksum, vproj, Lhat, out, nonfinite, on, done);
 }
 
 void def_ig4(const Geo& g, const float* I0, float4* IG, hipStream_t s) {

@@ -349,8 +349,7 @@ __global__ __launch_bounds__(256) void k_band_finalize(Geo g,
                                                        double* __restrict__ sq_part,
                                                        double* __restrict__ max_part, Done done) {
   BL_BATCH(g.bat)
-  if (done.word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
-    __hip_atomic_store(done.word, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  report_begun(done);
   BL_AT(vproj, g.bat);
   BL_AT(Lhat, g.bat);
   BL_AT(P, g.bat);

@@ -149,13 +149,13 @@ struct bl_ctx {
   uint32_t sweep_wait = bl::kSweepWait, sweep_polls = bl::kSweepPolls;
   bool sweeps_allowed = false;      // inside an Operation that is not captured
   bool sweep_now = false;           // decided with each evaluation's or product's first launch
-  // operations issued on this context and known to have ended (others are complete when the
-  // device has stored their number to hscal[S_DONE]), when and by which thread the last one was
+  // operations issued on this context and known to have ended (others count as ended when their last
+  // kernel has begun: it stores their number to hscal[S_DONE]), when and by which thread the last one was
   // called, and its stream: read by the other contexts of the device (may_sweep)
   std::atomic<uint64_t> op_issued{0}, op_ended{0}, op_thread{0};
   std::atomic<int64_t> op_time{0};
   std::atomic<void*> op_stream{nullptr};
-  bl::Done op_done;                 // where the last kernel of an enqueued operation reports
+  bl::Done op_done;                 // where the last kernel of an enqueued operation reports that it begins
   // transport launch shapes chosen for this grid shape (Geo::zv)
   bool tuned = false;
   bool shapes_fixed = false;   // by BL_LAUNCH_SHAPES or BL_TRANSPORT_ZV: the step launches run
@@ -197,7 +197,7 @@ bl_ctx* create_ctx(const bl_problem* prob, const Geo& g, bool transport, bool so
                    double* host_scalars = nullptr, bool host_mirror = true);
 void destroy_ctx(bl_ctx* c);
 // An operation on a context from its construction to its destruction, or, where `enqueued` was
-// called, until its last kernel reports.  Sweeps are used inside operations only.
+// called, until its last kernel begins.  Sweeps are used inside operations only.
 struct Operation {
   bl_ctx* c;
   uint64_t id;
@@ -205,10 +205,9 @@ struct Operation {
   explicit Operation(bl_ctx* c);
   ~Operation();
   // the caller leaves without waiting: report() before the operation's launches lets its last
-  // kernel report its end through c->op_done; enqueued() after them (publish: by a launch of
-  // its own, where the last kernel does not)
+  // kernel report through c->op_done when it begins; enqueued() after them
   void report();
-  void enqueued(bool publish);
+  void enqueued();
 };
 // owns a context until the end of a scope
 struct CtxHolder {

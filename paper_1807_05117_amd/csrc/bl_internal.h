@@ -238,11 +238,16 @@ void band_prep_nodes(const Geo& g, const float2* raw, float2* out, int nodes, si
 // Re sum conj(dotp) out over all C components (each thread sums its band index's components in
 // order, then its block in the fixed order of block_reduce_256); with sq_part and max_part not
 // NULL likewise the partials of sum |out|^2 and of max |out|.
-// Given `done`, the launch also reports itself there (done.word = done.value, host memory).
+// Given `done`, the launch stores done.value to done.word (host memory) when it begins: everything
+// before it on the stream has then ended.
 struct Done {
   uint64_t* word = nullptr;
   uint64_t value = 0;
 };
+__device__ __forceinline__ void report_begun(const Done& d) {
+  if (d.word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    __hip_atomic_store(d.word, d.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 void band_finalize(const Geo& g, int C, const float2* vproj, const float* Lhat,
                    const float2* P, float scale, float2* out, int* nonfinite, hipStream_t s,
                    int leray = 0, const float2* dotp = nullptr, double* dot_part = nullptr,
@@ -403,7 +408,8 @@ void def_adj_combine(const Geo& g, float scaleP, const float2* Ph, float2* rho, 
                      float2* Ksum, float2* kap, int st, int more, hipStream_t s);
 // out = Lhat vproj (if vproj) + Ksum + Herm(Ph) / MP, divergence-free part when gamma = 1
 void def_out(const Geo& g, float scaleP, const float2* Ph, const float2* Ksum,
-             const float2* vproj, const float* Lhat, float2* out, int* nonfinite, hipStream_t s);
+             const float2* vproj, const float* Lhat, float2* out, int* nonfinite, hipStream_t s,
+             Done done = {});
 // image level (image grid): IG = (I0, central-difference gradient of I0)
 void def_ig4(const Geo& g, const float* I0, float4* IG, hipStream_t s);
 // m1 = I0 and GP = grad I0 interpolated at i + N_ref UG (UG: dim planes, domain units)
@@ -461,8 +467,6 @@ void reduce_final2(const double* pa, double* outa, double* hosta, const double* 
                    double* hostb, int n, hipStream_t s, bool max_b = false,
                    const int* flag = nullptr, double* host_flag = nullptr,
                    const Batch& bt = Batch{});
-// done.word = done.value (host-mapped destination)
-void publish_done(Done done, hipStream_t s);
 // y = 0; y = x (kernels, so that a captured graph holds no memset or copy node)
 void zero_band(float2* y, int64_t n, hipStream_t s, const Batch& bt = Batch{});
 void copy_band(float2* y, const float2* x, int64_t n, hipStream_t s, const Batch& bt = Batch{});

@@ -420,10 +420,9 @@ void Operation::report() {
   if (c->sweeps_allowed && c->hdev) c->op_done = {reinterpret_cast<uint64_t*>(c->hdev + S_DONE), id};
 }
 
-void Operation::enqueued(bool publish) {
-  if (!c->op_done.word) return;   // captured, or no host-mapped word: taken to have ended
-  if (publish) bl::publish_done(c->op_done, c->stream);
-  ended_by_device = true;
+void Operation::enqueued() {
+  // (captured, or no host-mapped word: taken to have ended)
+  ended_by_device = c->op_done.word != nullptr;
 }
 
 Operation::~Operation() {
@@ -997,7 +996,7 @@ void per_node_outputs(bl_ctx* c, const float2* vproj, size_t vstride, float2* ou
   bl::pi_half(g, c->plan, c->Bf, (g.nt + 1) * d, c->P, s);
   const size_t ph = (size_t)g.kzh * g.ky * g.kx;
   bl::band_finalize_nodes(g, d, vproj, vstride, c->Lhat, c->P, (size_t)d * ph,
-                          (float)(1.0 / (double)g.M), out, (size_t)d * B, g.nt + 1, c->flag, s, 1);
+                          (float)(1.0 / (double)g.M), out, (size_t)d * B, g.nt + 1, c->flag, s, 1, c->op_done);
 }
 
 void op_gradient_ns(bl_ctx* c, float2* gout) {
@@ -1108,7 +1107,7 @@ void def_sweep_backward(bl_ctx* c, const float2* vproj, float2* out) {
                          n > 0, s);
       }
     bl::pi_half(c->gP, c->planP, c->GACC, d, c->PH, s);
-    bl::def_out(g, scaleP, c->PH, c->KSUM, vproj, c->Lhat, out, c->flag, s);
+    bl::def_out(g, scaleP, c->PH, c->KSUM, vproj, c->Lhat, out, c->flag, s, c->op_done);
     return;
   }
   for (int n = g.nt - 1; n >= 0; --n)
@@ -1120,7 +1119,7 @@ void def_sweep_backward(bl_ctx* c, const float2* vproj, float2* out) {
       bl::def_adj_combine(g, scaleP, c->PH, c->RHO, c->ASUM, c->KSUM, c->KAP, st, n > 0, s);
     }
   bl::pi_half(c->gP, c->planP, c->GACC, d, c->PH, s);
-  bl::def_out(g, scaleP, c->PH, c->KSUM, vproj, c->Lhat, out, c->flag, s);
+  bl::def_out(g, scaleP, c->PH, c->KSUM, vproj, c->Lhat, out, c->flag, s, c->op_done);
 }
 
 void op_set_velocity_def(bl_ctx* c, const float2* vraw) {
@@ -1925,7 +1924,7 @@ int bl_lddmm_ctx_hessvec(bl_ctx* c, const float* dv_hat, float* hv_hat) {
     if (c->devptr) {
       op.report();
       op_hessvec(c, reinterpret_cast<const float2*>(dv_hat), reinterpret_cast<float2*>(hv_hat));
-      op.enqueued(c->g.deform || c->g.nodes > 1);
+      op.enqueued();
       return BL_OK;
     }
     load_band(c, dv_hat, c->braw, c->g.nodes * c->g.dim);

@@ -391,11 +391,6 @@ __global__ __launch_bounds__(256) void k_add_scaled_dev(float2* __restrict__ y,
   }
 }
 
-// an operation's number into host-mapped memory when it has ended
-__global__ void k_publish_done(Done done) {
-  __hip_atomic_store(done.word, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 inline int blocks_for(int64_t n) {
   (void)n;
   return kRedBlocks;
@@ -445,9 +440,6 @@ void dot_partial(const float2* a, const float2* b, int64_t n, double* partial, h
 void maxabs_partial(const float2* a, int64_t n, double* partial, hipStream_t s, const Batch& bt) {
   hipLaunchKernelGGL(k_maxabs_partial, batch_grid(dim3(kRedBlocks), bt), dim3(256), 0, s, a, n,
                      partial, bt);
-}
-void publish_done(Done done, hipStream_t s) {
-  hipLaunchKernelGGL(k_publish_done, dim3(1), dim3(1), 0, s, done);
 }
 void zero_band(float2* y, int64_t n, hipStream_t s, const Batch& bt) {
   hipLaunchKernelGGL(k_zero, batch_grid(dim3(blocks_for(n)), bt), dim3(256), 0, s, y, n, bt);
