@@ -1052,7 +1052,8 @@ const float2* def_sweep_forward(bl_ctx* c, bool incremental) {
   const int64_t MP = c->gP.M;
   const float scaleP = (float)(1.0 / (double)MP);
   const float2* src = incremental ? c->bd : c->bv;
-  HIP_TRY(hipMemsetAsync(us_slot(c, 0), 0, band_bytes(g) * d, s));
+  // (kernels, so that a captured product holds no memset nodes)
+  bl::zero_band(us_slot(c, 0), g.B * d, s);
   if (c->fused) {
     // three launches per stage; the stage state U_st is u_n (st = 1) or the state written by
     // the previous stage into DUb (used as a dim-field buffer here)
@@ -1071,7 +1072,7 @@ const float2* def_sweep_forward(bl_ctx* c, bool incremental) {
       }
     return us_slot(c, cur);
   }
-  HIP_TRY(hipMemsetAsync(c->DUb, 0, band_bytes(g) * d2, s));
+  bl::zero_band(c->DUb, g.B * d2, s);
   int cur = 0;
   for (int n = 0; n < g.nt; ++n)
     for (int st = 1; st <= 4; ++st) {
