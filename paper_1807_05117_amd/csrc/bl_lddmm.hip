@@ -837,7 +837,6 @@ void choose_launch_shapes(bl_ctx* c) {
   // BL_LAUNCH_SHAPES = "s0,...,s6" fixes every class (tests of the shapes' equivalence);
   // an invalid list keeps the defaults
   if (const char* all = std::getenv("BL_LAUNCH_SHAPES")) {
-    c->shapes_fixed = true;
     int v[bl::TR_CLASSES], n = 0, off = 0;
     const char* q = all;
     while (n < bl::TR_CLASSES && std::sscanf(q, "%d%n", &v[n], &off) == 1) {
@@ -845,16 +844,19 @@ void choose_launch_shapes(bl_ctx* c) {
       if (*q == ',') ++q;
       ++n;
     }
-    if (n == bl::TR_CLASSES && valid_shapes(v))
+    if (n == bl::TR_CLASSES && valid_shapes(v)) {
+      c->shapes_fixed = true;
       for (int k = 0; k < bl::TR_CLASSES; ++k) g.zv[k] = v[k];
+    }
     return;
   }
   const char* env = std::getenv("BL_TRANSPORT_ZV");
   if (env && *env) {
-    c->shapes_fixed = true;
     const int v = std::atoi(env);
-    if (v == 1 || v == 2 || v == 4 || v == 8)
+    if (v == 1 || v == 2 || v == 4 || v == 8) {
+      c->shapes_fixed = true;
       for (int k = 0; k <= bl::TR_SETUP; ++k) g.zv[k] = v;
+    }
     return;  // any other value keeps the defaults
   }
   if (lookup_shapes(c)) return;
