@@ -73,7 +73,7 @@ extern "C" {
  * BLHessianStateEquation: the incremental adjoint keeps its source div(lambda dv) and the
  * product keeps pi(lambda grad dm); without the flag they are Gauss-Newton (Section 3.4). The
  * Newton product may be indefinite away from a minimum; PCG then stops at the first direction
- * of non-positive curvature (the preconditioned gradient if it is the first). Needs 2 Nt + 4
+ * of non-positive curvature (the preconditioned gradient if it is the first). Needs 2 Nt + 3
  * more grid planes of device memory (bl_lddmm_footprint includes them). */
 #define BL_NEWTON      2
 /* Non-stationary velocity: one band field per time node t_n = n / nt, n = 0..nt, so every

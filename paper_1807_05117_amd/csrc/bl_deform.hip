@@ -67,23 +67,6 @@ __device__ __forceinline__ void write_deriv(const Geo& g, int b, const float* q,
 }
 
 template <int DIM>
-__global__ __launch_bounds__(kThreads) void k_def_deriv(Geo g, const float2* __restrict__ U,
-                                                        float2* __restrict__ DU) {
-  const int B = (int)g.B;
-  for (int b = blockIdx.x * kThreads + threadIdx.x; b < B; b += gridDim.x * kThreads) {
-    int jx, jy, jz;
-    bidx(g, b, jx, jy, jz);
-    float q[DIM];
-    qvec<DIM>(g, jx, jy, jz, q);
-    float2 w[DIM];
-    const bool up = unpaired_index(g, jx, jy, jz);
-#pragma unroll
-    for (int i = 0; i < DIM; ++i) w[i] = up ? make_float2(0.f, 0.f) : U[(size_t)i * B + b];
-    write_deriv<DIM>(g, b, q, w, DU);
-  }
-}
-
-template <int DIM>
 __global__ __launch_bounds__(kThreads) void k_def_stage(Geo g, float scaleP,
                                                         const float2* __restrict__ Ph,
                                                         const float2* __restrict__ src,
@@ -451,10 +434,6 @@ int blocks_for(int64_t n) {
     else                                                                                  \
       hipLaunchKernelGGL(KERNEL<2>, dim3(BLOCKS), dim3(kThreads), 0, s, __VA_ARGS__);     \
   } while (0)
-
-void def_deriv(const Geo& g, const float2* U, float2* DU, hipStream_t s) {
-  DIM_DISPATCH(k_def_deriv, blocks_for(g.B), g, U, DU);
-}
 
 void def_stage(const Geo& g, float scaleP, const float2* Ph, const float2* src, const float2* un,
                float2* acc, int st, float2* unext, float2* DU, hipStream_t s) {

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_fx_col_fwd(Geo gp, const flo
 // Backward stage, block (column chunk, component j): kg_i(z) = iota_z(F2[i]) of the cotangent;
 // GACC_j (+)= sum_i DUG_(i,j)(z) kg_i(z); G[i dim + j][h] = sum_z kg_i(z) V_j(z) conj tz[z][h]
 // for i < 3, wave w taking h = half KZH / 2 + w.
-template <int NZS, int KZH, bool UNUSED>
+template <int NZS, int KZH>
 __global__ __launch_bounds__(64 * kColWaves) void k_fx_col_bwd(Geo gp, const float2* __restrict__ F2,
                                                     const float* __restrict__ VP,
                                                     const float* __restrict__ DUG,
@@ -616,42 +616,44 @@ void fx_iota_xy(const Geo& g, const Geo& gp, const DftPlan& pl, const float2* in
   else iota_xy_mfma(gp, pl, in, g.dim, F2, s);
 }
 
-#define COL_LAUNCH(KERNEL, NZS, KZH, ...)                                                 \
-  do {                                                                                    \
-    if (flag_)                                                                            \
-      hipLaunchKernelGGL((KERNEL<NZS, KZH, true>), grid_, dim3(64 * kColWaves), 0, s,     \
-                         __VA_ARGS__);                                                    \
-    else                                                                                  \
-      hipLaunchKernelGGL((KERNEL<NZS, KZH, false>), grid_, dim3(64 * kColWaves), 0, s,    \
-                         __VA_ARGS__);                                                    \
-  } while (0)
-#define COL_KZH(KERNEL, NZS, ...)                                                         \
-  do {                                                                                    \
-    switch (kzh_of(gp.kzh)) {                                                             \
-      case 8: COL_LAUNCH(KERNEL, NZS, 8, __VA_ARGS__); break;                             \
-      default: COL_LAUNCH(KERNEL, NZS, 16, __VA_ARGS__); break;                           \
-    }                                                                                     \
-  } while (0)
-#define NZS_DISPATCH(KERNEL, ...)                                                         \
-  do {                                                                                    \
-    const dim3 grid_((gp.nx * gp.ny + kColW - 1) / kColW, 3);                             \
-    switch (nzs_of(gp.nz)) {                                                              \
-      case 2: COL_KZH(KERNEL, 2, __VA_ARGS__); break;                                     \
-      case 4: COL_KZH(KERNEL, 4, __VA_ARGS__); break;                                     \
-      default: COL_KZH(KERNEL, 6, __VA_ARGS__); break;                                    \
-    }                                                                                     \
-  } while (0)
+namespace {
+// f(planes of a wavefront, kz of a block) with the compile-time sizes that hold gp's
+template <class F>
+void with_sizes(const Geo& gp, F&& f) {
+  using std::integral_constant;
+  const auto kz = [&](auto nzs) {
+    if (kzh_of(gp.kzh) == 8) f(nzs, integral_constant<int, 8>{});
+    else f(nzs, integral_constant<int, 16>{});
+  };
+  switch (nzs_of(gp.nz)) {
+    case 2: kz(integral_constant<int, 2>{}); break;
+    case 4: kz(integral_constant<int, 4>{}); break;
+    default: kz(integral_constant<int, 6>{}); break;
+  }
+}
+dim3 col_grid(const Geo& gp) { return dim3((unsigned)((gp.nx * gp.ny + kColW - 1) / kColW), 3); }
+}  // namespace
 
 void fx_col_fwd(const Geo& gp, const DftPlan& pl, const float2* F2, const float* VP,
                 float* DUGw, const float* DUGr, const float* DVP, float2* G, hipStream_t s) {
-  const bool flag_ = DUGr != nullptr;   // products: read the stored stage derivatives
-  NZS_DISPATCH(k_fx_col_fwd, gp, F2, VP, DUGw, DUGr, DVP, pl.tw_zT, G);
+  with_sizes(gp, [&](auto nzs, auto kzh) {
+    constexpr int N = decltype(nzs)::value, K = decltype(kzh)::value;
+    if (DUGr != nullptr)   // products: read the stored stage derivatives
+      hipLaunchKernelGGL((k_fx_col_fwd<N, K, true>), col_grid(gp), dim3(64 * kColWaves), 0, s, gp, F2, VP,
+                         DUGw, DUGr, DVP, pl.tw_zT, G);
+    else
+      hipLaunchKernelGGL((k_fx_col_fwd<N, K, false>), col_grid(gp), dim3(64 * kColWaves), 0, s, gp, F2, VP,
+                         DUGw, DUGr, DVP, pl.tw_zT, G);
+  });
 }
 
 void fx_col_bwd(const Geo& gp, const DftPlan& pl, const float2* F2, const float* VP,
                 const float* DUG, float* GACC, int first, float2* G, hipStream_t s) {
-  const bool flag_ = false;
-  NZS_DISPATCH(k_fx_col_bwd, gp, F2, VP, DUG, GACC, first, pl.tw_zT, G);
+  with_sizes(gp, [&](auto nzs, auto kzh) {
+    constexpr int N = decltype(nzs)::value, K = decltype(kzh)::value;
+    hipLaunchKernelGGL((k_fx_col_bwd<N, K>), col_grid(gp), dim3(64 * kColWaves), 0, s, gp, F2, VP, DUG, GACC,
+                       first, pl.tw_zT, G);
+  });
 }
 
 void fx_pi_yx_stage(const Geo& g, const Geo& gp, const DftPlan& pl, const float2* G, float scaleP,

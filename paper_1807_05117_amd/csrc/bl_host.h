@@ -72,8 +72,8 @@ struct bl_ctx {
   float* L = nullptr;      // (nt + 1) planes: adjoint or incremental adjoint
   float* Bf = nullptr;     // dim planes: body force (per time node when non-stationary)
   // full Newton products only
-  float* DM = nullptr;     // (nt + 1) planes: dm^n (dm^0 = 0)
-  float* DL = nullptr;     // (nt + 1) planes: dlambda^n
+  float* DM = nullptr;     // (nt + 1) planes: dm^n (dm^0 = 0), then u^n
+  float* DL = nullptr;     // (nt + 1) planes: t^n (sweeps), then hs^n with u^nt, then (steps) dlambda^n
   float* U = nullptr;      // with T0 and T1, where the Newton body force starts
   float* mfinal = nullptr;  // m(1): the warped source
   // deformation state equation only (image grid)

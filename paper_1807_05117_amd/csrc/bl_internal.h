@@ -148,9 +148,9 @@ struct Geo {
   // nine grid fields an incremental step touches exceed the 256 MiB last-level cache: there
   // the hint speeds the steps up, below it the next step's reads of the output would miss.
   int stream_out;
-  // launch shapes per kernel class (TR_*): voxels per thread along z of the transports and
-  // the setup, the z-chunk multiplier of the iota z stage, the rows per block of the fused
-  // iota x/y stage.  Every choice computes bitwise the same values.
+  // launch shapes per kernel class (TR_*): voxels per thread along z of the transports, the setup's
+  // form, the z-chunk multiplier of the iota z stage, and one without effect (TR_IOTA_XY).  Every
+  // choice computes bitwise the same values.
   int zv[8];
   // several problems of this shape in one launch (default: one)
   Batch bat;
@@ -385,12 +385,10 @@ void sweep_adj_n(const Geo& g, const SweepPlan& p, const float4* YA, const float
 // Band fields are full centred bands of g (B entries per component); product-grid planes have
 // MP = px * py * pz points; Ph is a kz >= 0 half spectrum of the product grid (pi_half output,
 // kzh * ky * kx entries per component) and scaleP = 1 / MP.
-// DU[i * dim + j] = d~_j U_i (spectral derivative, lengths of the image grid)
-void def_deriv(const Geo& g, const float2* U, float2* DU, hipStream_t s);
 // one Runge-Kutta stage st = 1..4 of d_t u~ = -src - conv, conv = Herm(Ph) / MP:
 // k = -src - conv; acc = k (st 1), acc + 2k (st 2, 3), acc + k (st 4); the next state
 // un + c h k (st 1, 2, 3; c = 1/2, 1/2, 1) or un + h/6 acc (st 4, also stored to unext);
-// DU (may be null) receives its spectral derivatives
+// DU (may be null) receives its spectral derivatives DU[i * dim + j] = d~_j (lengths of the image grid)
 void def_stage(const Geo& g, float scaleP, const float2* Ph, const float2* src, const float2* un,
                float2* acc, int st, float2* unext, float2* DU, hipStream_t s);
 // out_i = sum_j DG[i dim + j] V_j (+ DG2[i dim + j] V2_j when DG2 != null), product grid
@@ -473,8 +471,6 @@ void copy_band(float2* y, const float2* x, int64_t n, hipStream_t s, const Batch
 // y = x + eps[0] d (step length in device memory)
 void add_scaled_dev(float2* y, const float2* x, const float2* d, const double* eps, int64_t n,
                     hipStream_t s, const Batch& bt = Batch{});
-// y = x + beta y
-void xpby(float2* y, const float2* x, double beta, int64_t n, hipStream_t s);
 // one PCG step: pHp = <p, Hp> from its nphp partials php_part (the same value as reduce_final
 // of them; stored to pHp[0] and, when not NULL, host-mapped pHp_host[0]),
 // alpha = rz / pHp (0 unless pHp > 0), delta += alpha p, r -= alpha Hp, z = r / Lhat,

@@ -365,14 +365,13 @@ double* alloc_host_scalars() {
 }
 
 // ------------------------------------------------------------------ operations and sweeps
-// A sweep's workgroups wait for each other and want the whole device (bl_sweep.hip): beside
-// another stream's kernels they become resident late or not at all, and what is then finished
-// through tickets is several times slower than the step launches (two threads' gradients at
-// 128^3: 1,500 per second through tickets, 3,000 as steps).  So an operation uses sweeps only if
-// no context of another stream of this process has work in flight on the device, or had some
-// called by another thread within the last millisecond (two threads that call in turn would
-// otherwise both find the device free now and then).  This is a matter of speed alone: the
-// results are the same, and sweeps that meet other work all the same end without it.
+// A sweep's workgroups wait for each other and want the whole device (bl_sweep.hip): beside another
+// sweep they become resident late or not at all, and what is then finished through tickets takes
+// twice as long as in step launches.  So an operation uses sweeps only if no context of another
+// stream of this process has work in flight on the device, or had some called by another thread
+// within the last millisecond (two threads that call in turn would otherwise both find the device
+// free now and then).  This is a matter of speed alone: the results are the same, and sweeps that
+// meet other work all the same end without it.
 std::mutex g_live_mu;
 std::vector<bl_ctx*> g_live;   // transport contexts of the process
 constexpr int64_t kQuietNs = 1000000;
@@ -716,10 +715,12 @@ void t_collect(bl_ctx* c) {
 //
 // Every class's candidates compute bitwise the same values -- they only change how work is
 // split over threads and blocks -- so tuning never changes a result:
-//   transports (state, incremental, adjoint, body force) and setup: voxels per thread along z
-//     (blocks of 256 column entries), 1, 2, 4 or 8;
+//   transports (state, incremental, adjoint, body force): voxels per thread along z (blocks of 256
+//     column entries), 1, 2, 4 or 8;
+//   setup: gathers from global memory by one or two voxels per thread (1, 2) or neighbourhoods in
+//     LDS (4, 8);
 //   iota z stage (FP32): the z-chunk multiplier of its grid, 1, 2 or 4;
-//   iota x and y stages: two kernels (0) or one fused kernel with 32 or 16 rows per block.
+//   iota x and y stages: 0, 16 or 32, all the same (one launch).
 // Candidates are timed on the context's own fields right after the first setup on a problem
 // shape (the gathers' cache behaviour depends on the real offsets); the planes they write
 // (T0, T1, Bf, DV, X, YA with the same values, the transform buffers) are work space that every
@@ -1192,8 +1193,8 @@ bool use_sweeps(const bl_ctx* c) {
          !c->shapes_fixed && !c->box.resting;
 }
 // in one direction (0 forward, 1 backward).  What leaves the box for one sweep does so for every
-// other one of the velocity; the steps that an abandoned sweep takes through tickets last three times
-// as long as step launches (128^3, ten steps of six voxels: product 1,328 us, in step launches 390).
+// other one of the velocity; through tickets the steps take twice as long as in step launches (128^3,
+// ten steps of six voxels: product 755 us, in step launches 390).
 bool left_box(const bl_ctx* c, int dir) { return c->sweep_seen[dir].number[bl::SR_LEFT] > c->box.before; }
 bool use_sweeps(const bl_ctx* c, int dir) { return use_sweeps(c) && !left_box(c, dir); }
 

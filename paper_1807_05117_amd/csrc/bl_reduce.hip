@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void k_reduce_final2(const double* __restrict_
 
 // One PCG step after the product Hp, in one launch: alpha = rz / pHp (0 unless pHp > 0),
 // delta += alpha p, r -= alpha Hp, z = r / Lhat, and the block partials of <r, r> (p0) and
-// <r, z> (p1).  Per element the arithmetic of axpy and precond_dots, in the same grid.
+// <r, z> (p1), summed as k_pcg_start sums them.
 __global__ __launch_bounds__(256) void k_pcg_step(Geo g, const float2* __restrict__ p,
                                                   const float2* __restrict__ Hp,
                                                   const double* __restrict__ rz,
@@ -267,17 +267,6 @@ __global__ __launch_bounds__(256) void k_maxabs_partial(const float2* __restrict
   block_max_store(acc, partial);
 }
 
-__global__ __launch_bounds__(256) void k_xpby(float2* __restrict__ y, const float2* __restrict__ x,
-                                              double beta, int64_t n) {
-  GRID_STRIDE(i, n) {
-    const float2 a = x[i];
-    float2 b = y[i];
-    b.x = (float)fma(beta, (double)b.x, (double)a.x);
-    b.y = (float)fma(beta, (double)b.y, (double)a.y);
-    y[i] = b;
-  }
-}
-
 __global__ __launch_bounds__(256) void k_add_scaled(float2* __restrict__ y,
                                                     const float2* __restrict__ x,
                                                     const float2* __restrict__ d, double eps,
@@ -451,9 +440,6 @@ void add_scaled_dev(float2* y, const float2* x, const float2* d, const double* e
                     hipStream_t s, const Batch& bt) {
   hipLaunchKernelGGL(k_add_scaled_dev, batch_grid(dim3(blocks_for(n)), bt), dim3(256), 0, s, y, x,
                      d, eps, n, bt);
-}
-void xpby(float2* y, const float2* x, double beta, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_xpby, dim3(blocks_for(n)), dim3(256), 0, s, y, x, beta, n);
 }
 void add_scaled(float2* y, const float2* x, const float2* d, double eps, int64_t n,
                 hipStream_t s) {

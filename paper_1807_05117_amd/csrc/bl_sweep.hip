@@ -34,8 +34,9 @@
 // running, so this ends however many workgroups are resident.  It recomputes the sweep from its
 // inputs; what was finished before is stored again with the same values.  Should a wait for earlier
 // tickets not end all the same, it is given up and reported, and the call fails.
-// A tile whose box does not fit the LDS (offsets of more than about three voxels per step at
-// 128^3) abandons the sweep in the same way.
+// A tile whose box does not fit the LDS (offsets of more than about four voxels per step at 128^3)
+// abandons the sweep in the same way.  Either reason is reported to the host, which then takes the
+// steps for a while (bl_lddmm.hip).
 #include <algorithm>
 #include <atomic>
 
