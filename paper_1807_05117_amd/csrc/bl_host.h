@@ -217,10 +217,12 @@ struct CtxHolder {
 // 64 doubles of pinned, coherent, device-mapped host memory for published scalars
 double* alloc_host_scalars();
 // what sweeps have reported so far ([direction][SR_WORDS] words); at the end of a velocity: what its
-// sweeps have shown of its offsets; what sweeps have shown of their waits
+// sweeps have shown of its offsets; what sweeps have shown of their waits, each evaluation or product
+// by itself or those with numbers past `before` as one
+constexpr uint64_t kEach = ~uint64_t(0);
 void read_sweep_reports(bl_ctx* c, const uint64_t* words);
 void settle_box(bl_ctx* c);
-void settle_waits(bl_ctx* c);
+void settle_waits(bl_ctx* c, uint64_t before = kEach);
 // waits for the stream; throws SweepGivenUp if a sweep on it was given up since the last call
 void sync(bl_ctx* c);
 void load_images(bl_ctx* c, const float* I0, const float* I1);

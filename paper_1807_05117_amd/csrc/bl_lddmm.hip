@@ -1223,12 +1223,13 @@ void next_velocity(bl_ctx* c) {
 // the last evaluation or product with sweeps has ended, as far as it is known
 bool sweep_ended(const bl_ctx* c) { return c->sweep_synced || ops_done(c) >= c->sweep_op; }
 
-void settle_waits(bl_ctx* c) {
+void settle_waits(bl_ctx* c, uint64_t before) {
   auto& l = c->late;
   const uint64_t n = std::max(c->sweep_seen[0].number[bl::SR_LATE], c->sweep_seen[1].number[bl::SR_LATE]);
   if (n > l.late) {
-    l.streak = n == l.late + 1 ? l.streak + 1 : 1;
-    l.late = n;
+    const bool call = before != kEach;
+    l.streak = l.late >= (call ? before : n - 1) ? l.streak + 1 : 1;
+    l.late = call ? c->sweep_number : n;
     if (l.streak > 1) l.rest = std::min(1 << std::min(l.streak - 2, 30), kMostRest);
   } else if (l.late != c->sweep_number && sweep_ended(c)) {
     l.streak = 0;

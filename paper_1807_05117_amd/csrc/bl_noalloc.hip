@@ -108,7 +108,8 @@ int bl_lddmm_hessvec_noalloc(const bl_problem* prob, const float* I0, const floa
     sync(c);
     read_sweep_reports(c, reports[0]);
     settle_box(c);
-    settle_waits(c);
+    // a report holds the last number alone, so the velocity and the product count as one
+    settle_waits(c, history.number);
     c->box.before = c->sweep_number;
     history.number = c->sweep_number;
     history.box = c->box;
