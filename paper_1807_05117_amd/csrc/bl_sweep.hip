@@ -58,8 +58,10 @@ __device__ __forceinline__ uint32_t ld_flag(const uint32_t* p) {
 __device__ __forceinline__ void st_flag(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The kernel's arguments, for those that are rarely wanted: read again there, since as values they
-// would be kept in scalar registers, which are short, for the whole sweep (1% of a product at 128^3).
+// The kernel's arguments, for code that is rarely run (reports, tickets): read again there, since as
+// values they would be kept in scalar registers, which are short, for the whole sweep.  With those of
+// the tickets kept, 61 (96^3) and 75 (128^3) of them were spilled to vector registers in the
+// incremental sweep, 26 and 42 without; products took 121.2 and 199.8 us, now 117.2 and 198.4.
 struct KernelArgs {
   Geo g;
   SweepPlan p;
@@ -270,7 +272,8 @@ __device__ __forceinline__ float finish(const Geo& g, int s, float v, float src,
 // workgroups of this launch have stored is read by device-scope loads (a fence in their place drops
 // every line of the XCD's L2, workgroup after workgroup), and the finished blocks are counted in kDone
 // words (256 additions to one word are made one by one).  Ten steps of six voxels at 128^3: a product
-// 755 us, 1,330 with fences and one word, 390 in step launches.
+// 755 us, 1,330 with fences and one word, 390 in step launches.  (One that is late at once, of less
+// than a voxel per step and with the host's copies: 885 us before arguments were read again, now 830.)
 constexpr uint32_t kDone = 8, kDoneStride = 16;
 template <int KIND, int DIM>
 __device__ __forceinline__ void run_tickets(const Geo& g, const SweepArgs& a, int* sh) {
@@ -742,7 +745,8 @@ __global__ __launch_bounds__(1024) void k_sweep(Geo g, SweepPlan p, SweepArgs a)
       if constexpr (is_adj(KIND)) add_node<DIM, R>(g, st, n, val, fx, fy, fz);
     }
     if (bail) {   // the same for every thread of the block
-      run_tickets<KIND, DIM>(g, a, sh);
+      const KernelArgsPtr k = kernel_args();
+      run_tickets<KIND, DIM>(*(const Geo*)&k->g, *(const SweepArgs*)&k->a, sh);
     } else if constexpr (is_adj(KIND)) {
       store_b<DIM, R>(g, rw, t, a.b, fx, fy, fz);
     }
