@@ -293,9 +293,9 @@ int bl_kernel_timing_read(bl_ctx* ctx, int32_t kclass, int64_t* launches, double
  * bitwise the same values.  The library times the candidates on the context's own fields at
  * the first velocity set on a grid shape and keeps the fastest per shape for the process; the
  * environment variable BL_TRANSPORT_ZV = 1, 2, 4 or 8 forces one shape for all classes, and 0
- * keeps the built-in defaults without timing.  While a shape is forced, here or by
+ * keeps the built-in defaults without timing.  While a shape is forced in 3D, here or by
  * BL_LAUNCH_SHAPES, every time step stays in a launch of its own.  Reads the shapes in use (all 1 in
- * 2D, and the defaults before the first velocity).  Errors: BL_E_INVALID for NULL arguments.
+ * 2D, where none is forced, and the defaults before the first velocity).  Errors: BL_E_INVALID for NULL arguments.
  */
 int bl_lddmm_ctx_launch_shapes(bl_ctx* ctx, int32_t zv_out[4]);
 

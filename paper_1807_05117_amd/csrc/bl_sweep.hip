@@ -11,8 +11,9 @@
 //     rows of other tiles, gathers from LDS (a gather from global memory occupies the address
 //     path about four times as long) and stores its voxels for the others.
 //   - A tile waits only for the tiles its box touches, through one progress word per tile.
-// Ten steps at 128^3 take 62 us for the state (121 as steps), 81 for the incremental state (162)
-// and 83 for the adjoint with the body force (154); five steps at 96^3 24 and 31 us (32 and 48).
+// Ten steps at 128^3 take 54 us for the state (121 as steps), 74 for the incremental state (162)
+// and 78 for the adjoint with the body force (154); five steps at 96^3 20 us for the state and 27 for
+// the adjoint (32 and 48).
 // What is left is the gathers' and stencils' LDS reads and the exchange, about 2 us per step for
 // a store, its progress word and the neighbours' loads.  The arithmetic per voxel is that of the
 // step launches, and the results are bitwise the same.

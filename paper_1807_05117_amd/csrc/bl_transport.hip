@@ -205,8 +205,8 @@ __global__ __launch_bounds__(kTB) void k_body_force(Geo g, const float* __restri
 // One pass over all time nodes (k_newton_terms) forms what does not depend on the adjoint: dt/2 s^n
 // and the body force's second term.  The adjoint steps then read one field more than the
 // Gauss-Newton ones, and both they and the incremental state run as sweeps where those do
-// (bl_sweep.hip).  At 128^3 with ten steps (us): incremental state 92 (184 as steps), terms 92,
-// adjoint with the body force 105.  Steps that formed s^n themselves took 182 and a body force of
+// (bl_sweep.hip).  At 128^3 with ten steps (us): incremental state 86 (184 as steps), terms 95,
+// adjoint with the body force 97.  Steps that formed s^n themselves took 182 and a body force of
 // both terms 100; as steps it is 148 + 54 now.
 
 // incremental state step that also stores dm^{n+1} = Interp(t^n, i + X) + dt/2 f^{n+1} (t_out
